@@ -6,6 +6,7 @@
 #include <math.h>
 
 #include "jv_common.h"
+#include "jv_mfma.h"
 
 namespace jv {
 
@@ -16,85 +17,247 @@ __device__ inline int slot_token(const WindowGeom &g, int wy, int wx, int slot) 
     return (r < g.H && c < g.W) ? r * g.W + c : -1;
 }
 
-__device__ inline float wave_max(float x) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x = fmaxf(x, __shfl_xor(x, off, 64));
-    return x;
-}
-__device__ inline float wave_sum(float x) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-    return x;
+// ---------------------------------------------------------------------------------------
+// fp32 path: tiles of 32 keys x 32 queries on the fp32 matrix instructions
+// (v_mfma_f32_32x32x2_f32: fp32 operands and accumulation, 64 cycles per instruction).
+// Bound by those instructions: 128 of them per tile against 16 exponentials per lane.  Scores
+// are formed transposed, S^T = K Q^T, so that a lane owns one query column: the maximum and the
+// sum are in-lane plus one exchange with lane ^ 32, and accumulator register v of the score tile
+// is, as it stands, the B operand of step v of O^T += V^T P^T (k-slot g of step v is the key that
+// lane half g holds in register v).
+// A workgroup is four wavefronts, QW = 4 / KW blocks of 32 queries times KW groups of keys: per
+// step it stages KW tiles of K and V in LDS (fetched into registers under the arithmetic of the
+// step before) and wavefront (qw, kw) takes tile kw.  With KW > 1 the KW running softmaxes of a
+// query block are merged through LDS at the end.  KW = 4 cuts a problem of few queries into four
+// times as many wavefronts; KW = 1 stages a quarter of the bytes per flop.
+// Measured: 1 369 tokens x 12 heads 103 us (516 workgroups on 256 compute units: the third
+// one some units get is a third of the time), 2 304 tokens x 64 heads 798 us = 109 of 157 TFLOP/s.
+// (The kernel before this one scored one query per wavefront with plain FMAs and read V once
+// per query: 1 675 us for the first of these.)
+// Only the first q_slots query slots of every window are computed.
+// grid (ceil(q_slots / (32 QW)), n_win, B*heads), 256 threads.
+// ---------------------------------------------------------------------------------------
+constexpr int kF32Tile = 2 * 32 * kHeadDim * 4;  // K rows, then V rows, of 32 keys: 16 KB
+
+// Workgroup -> (query block, window, batch * head) with a contiguous range of the launch per XCD
+// (the hardware deals workgroups to the eight XCDs in turn): the query blocks that read one
+// head's keys share an L2.
+__device__ inline void f32_item(int &qblock, int &win, int &bh) {
+    const long long nx = gridDim.x, ny = gridDim.y, total = nx * ny * gridDim.z;
+    const long long lin = blockIdx.x + nx * (blockIdx.y + ny * blockIdx.z);
+    const long long share = total >> 3, extra = total & 7, xcd = lin & 7;
+    const long long item = xcd * share + (xcd < extra ? xcd : extra) + (lin >> 3);
+    qblock = (int)(item % nx);
+    win = (int)((item / nx) % ny);
+    bh = (int)(item / (nx * ny));
 }
 
-// ---------------------------------------------------------------------------------------
-// fp32 path.  One wavefront per query slot; a workgroup holds four consecutive slots of one
-// window.  Key tiles of 64 slots: lane j scores key j (dot product over 64 channels), the
-// tile joins the running softmax, then lane c accumulates channel c of the output.
-// Only the first q_slots query slots of every window are computed.
-// grid (ceil(q_slots/4), n_win, B*heads), 256 threads.
-// ---------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256)
+template <int KW>
+__global__ void __launch_bounds__(256, 2)
 attn_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, int heads,
-         float scale, int q_slots) {
-    __shared__ float qs[4][kHeadDim];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int bh = blockIdx.z, b = bh / heads, h = bh % heads;
-    const int win = blockIdx.y, wy = win / g.wins_x, wx = win % g.wins_x;
-    const int qslot = blockIdx.x * 4 + wave;
-    const int qtok = qslot < q_slots ? slot_token(g, wy, wx, qslot) : -1;
-    if (qtok < 0) return;  // wave-uniform: padded query slots produce nothing
-    const float *qp = (const float *)qt.ptr + b * qt.sb + h * qt.sh + (long long)qtok * qt.sn;
+         float scale_log2, int q_slots) {
+    constexpr int QW = 4 / KW;
+    __shared__ __align__(16) unsigned char tiles[KW * kF32Tile];
+    __shared__ __align__(16) float bias[KW * 32];  // 0 for a real key, -inf for padding
+    __shared__ float ms[4][32], ls[4][32];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, li = lane & 31;
+    const int kw = wave % KW, qw = wave / KW;
+    int qblock, win, bh;
+    f32_item(qblock, win, bh);
+    const int b = bh / heads, h = bh % heads, wy = win / g.wins_x, wx = win % g.wins_x;
+    const float *qp = (const float *)qt.ptr + b * qt.sb + h * qt.sh;
     const float *kp = (const float *)kt.ptr + b * kt.sb + h * kt.sh;
     const float *vp = (const float *)vt.ptr + b * vt.sb + h * vt.sh;
-    float *op = (float *)ot.ptr + b * ot.sb + h * ot.sh + (long long)qtok * ot.sn;
-    qs[wave][lane] = qp[lane];  // read back by the same wave only
-    float m = -INFINITY, l = 0.f, acc = 0.f;
-    for (int s0 = 0; s0 < g.slots; s0 += 64) {
-        const int tok = slot_token(g, wy, wx, s0 + lane);
-        float s = -INFINITY;
-        if (tok >= 0) {
-            const float4 *krow = (const float4 *)(kp + (long long)tok * kt.sn);
-            float dot = 0.f;
+    float *op = (float *)ot.ptr + b * ot.sb + h * ot.sh;
+    const int first = wy * g.wh * g.W + wx * g.ww;  // the window's first token: always real
+    const bool padded = (wy + 1) * g.wh > g.H || (wx + 1) * g.ww > g.W;
+    const bool rows = g.ww == g.W;                  // windows of whole grid rows: slots are consecutive tokens
+    auto token = [&](int slot) {
+        if (!rows) return slot_token(g, wy, wx, slot);
+        return slot < g.slots && first + slot < g.H * g.W ? first + slot : -1;
+    };
+
+    // Queries: lane (half, li) holds channels 32 half .. +31 of query li.
+    const int q0 = qblock * (32 * QW) + qw * 32;
+    const bool live = q0 < q_slots;  // the same in the whole wavefront
+    f32x4 q[8];
+    int qtok = q0 + li < q_slots ? token(q0 + li) : -1;
+    {
+        const float *row = qp + (long long)(qtok < 0 ? first : qtok) * qt.sn + 32 * half;
 #pragma unroll
-            for (int c4 = 0; c4 < 16; ++c4) {
-                float4 kk = krow[c4];
-                dot = fmaf(qs[wave][4 * c4 + 0], kk.x, dot);
-                dot = fmaf(qs[wave][4 * c4 + 1], kk.y, dot);
-                dot = fmaf(qs[wave][4 * c4 + 2], kk.z, dot);
-                dot = fmaf(qs[wave][4 * c4 + 3], kk.w, dot);
-            }
-            s = dot * scale;
-        }
-        const float tile_max = wave_max(s);
-        if (tile_max == -INFINITY) continue;  // a tile of padding only
-        const float m_new = fmaxf(m, tile_max);
-        const float alpha = expf(m - m_new);  // exp(-inf) = 0 on the first live tile
-        const float p = (tok >= 0) ? expf(s - m_new) : 0.f;
-        l = l * alpha + wave_sum(p);
-        acc *= alpha;
-        for (int j = 0; j < 64; ++j) {
-            const int tj = __shfl(tok, j, 64);
-            if (tj < 0) continue;  // wave-uniform
-            const float pj = __shfl(p, j, 64);
-            acc = fmaf(pj, vp[(long long)tj * vt.sn + lane], acc);
-        }
-        m = m_new;
+        for (int i = 0; i < 8; ++i) q[i] = *(const f32x4 *)(row + 4 * i);
     }
-    op[lane] = acc / l;
+    f32x16 acc[2];  // channels 32 cb + 8 (v / 4) + 4 half + v % 4 of query li
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.f;
+    float m = -INFINITY, l = 0.f;
+
+    // Staging: this thread moves 16-byte chunk `chunk` of rows srow + 16 i of a step's KW tiles.
+    // K rows are read a row per lane (chunk rotated by the row), V rows 32 channels at a time by
+    // the two lane halves, four rows apart (row halves exchanged in every other group of four
+    // rows): both without bank conflicts.
+    const int chunk = tid & 15, srow = tid >> 4;
+    f32x4 kreg[2 * KW], vreg[2 * KW];
+    float breg[2 * KW];
+    auto fetch = [&](int step) {
+#pragma unroll
+        for (int i = 0; i < 2 * KW; ++i) {
+            int tok = token(step * (32 * KW) + srow + 16 * i);
+            breg[i] = tok < 0 ? -INFINITY : 0.f;
+            if (tok < 0) tok = first;
+            kreg[i] = *(const f32x4 *)(kp + (long long)tok * kt.sn + 4 * chunk);
+            vreg[i] = *(const f32x4 *)(vp + (long long)tok * vt.sn + 4 * chunk);
+        }
+    };
+    auto stage = [&]() {
+#pragma unroll
+        for (int i = 0; i < 2 * KW; ++i) {
+            const int r = (srow + 16 * i) & 31;
+            unsigned char *tile = tiles + (i >> 1) * kF32Tile + r * 256;
+            *(f32x4 *)(tile + ((chunk ^ (r & 15)) << 4)) = kreg[i];
+            *(f32x4 *)(tile + kF32Tile / 2 + ((chunk ^ ((r & 4) << 1)) << 4)) = vreg[i];
+            if (chunk == 0) bias[srow + 16 * i] = breg[i];
+        }
+    };
+    const unsigned char *ktile = tiles + kw * kF32Tile, *vtile = ktile + kF32Tile / 2;
+    const int n_step = (g.slots + 32 * KW - 1) / (32 * KW);
+    fetch(0);
+    for (int step = 0; step < n_step; ++step) {
+        if (step > 0) __syncthreads();  // the tiles before have been read
+        stage();
+        __syncthreads();
+        if (step + 1 < n_step) fetch(step + 1);
+        if (!live || (step * KW + kw) * 32 >= g.slots) continue;
+        f32x16 s;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[v] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const f32x4 kk = *(const f32x4 *)(ktile + li * 256 + (((8 * half + i) ^ (li & 15)) << 4));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kk[e], q[i][e], s, 0, 0, 0);
+        }
+        float top = -INFINITY;
+        if (padded || (step * KW + kw + 1) * 32 > g.slots) {  // (uniform) only here can a key be padding
+#pragma unroll
+            for (int v4 = 0; v4 < 4; ++v4) {
+                const f32x4 bb = *(const f32x4 *)(bias + 32 * kw + 8 * v4 + 4 * half);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s[4 * v4 + e] += bb[e];
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) top = fmaxf(top, s[v]);
+        float lo, hi;
+        pair_values(top, &lo, &hi);
+        const float m_new = fmaxf(m, fmaxf(lo, hi) * scale_log2);
+        const float ref = m_new == -INFINITY ? 0.f : m_new;  // padding only so far
+        const float alpha = __builtin_amdgcn_exp2f(m - ref);
+        m = m_new;
+        float sum = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], scale_log2, -ref));
+            sum += s[v];
+        }
+        l = fmaf(l, alpha, sum);
+        if (__any(alpha != 1.0f)) {  // some query's maximum went up: rare after the first tiles
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                acc[0][v] *= alpha;
+                acc[1][v] *= alpha;
+            }
+        }
+        const unsigned char *vrow = vtile + half * 4 * 256 + ((li * 4) ^ (half * 128));
+        const unsigned char *vrow1 = vtile + half * 4 * 256 + ((li * 4) ^ (half * 128) ^ 128);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int off = (8 * (v / 4) + v % 4) * 256;
+            acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(*(const float *)(vrow + off), s[v], acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(*(const float *)(vrow1 + off), s[v], acc[1], 0, 0, 0);
+        }
+    }
+    {
+        float lo, hi;
+        pair_values(l, &lo, &hi);
+        l = lo + hi;
+    }
+    if (KW == 1) {
+        if (qtok < 0) return;
+        const float inv = 1.0f / l;
+        float *row = op + (long long)qtok * ot.sn + 4 * half;
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+            for (int v4 = 0; v4 < 4; ++v4) {
+                f32x4 out;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) out[e] = acc[cb][4 * v4 + e] * inv;
+                *(f32x4 *)(row + 32 * cb + 8 * v4) = out;
+            }
+        return;
+    }
+    // Merge the KW softmaxes of each query block: O = sum_k 2^(m_k - M) acc_k / sum_k 2^(m_k - M) l_k.
+    __syncthreads();
+    unsigned char *mine = tiles + wave * (32 * 256);
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int v4 = 0; v4 < 4; ++v4) {
+            const f32x4 part = {acc[cb][4 * v4], acc[cb][4 * v4 + 1], acc[cb][4 * v4 + 2], acc[cb][4 * v4 + 3]};
+            *(f32x4 *)(mine + li * 256 + (((8 * cb + 2 * v4 + half) ^ (li & 15)) << 4)) = part;
+        }
+    if (half == 0) {
+        ms[wave][li] = m;
+        ls[wave][li] = l;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2 * QW; ++i) {
+        const int query = srow + 16 * i, w0 = (query >> 5) * KW, ql = query & 31;
+        const int slot = qblock * (32 * QW) + query;
+        const int tok = slot < q_slots ? token(slot) : -1;
+        if (tok < 0) continue;
+        float top = ms[w0][ql];
+#pragma unroll
+        for (int k = 1; k < KW; ++k) top = fmaxf(top, ms[w0 + k][ql]);
+        f32x4 out = {0.f, 0.f, 0.f, 0.f};
+        float den = 0.f;
+#pragma unroll
+        for (int k = 0; k < KW; ++k) {
+            const float w = __builtin_amdgcn_exp2f(ms[w0 + k][ql] - top);
+            out += w * *(const f32x4 *)(tiles + (w0 + k) * (32 * 256) + ql * 256 + ((chunk ^ (ql & 15)) << 4));
+            den = fmaf(w, ls[w0 + k][ql], den);
+        }
+        *(f32x4 *)(op + (long long)tok * ot.sn + 4 * chunk) = out * (1.0f / den);
+    }
 }
 
 // q_slots: number of leading query slots of each window to compute (all keys always take part).
 jv_status attn_bf16(const Problem &pr, const WindowGeom &g, float scale, int q_slots, hipStream_t stream);
 
+template <int KW>
+static jv_status launch_attn_f32(const Problem &pr, const WindowGeom &g, float scale, int q_slots, hipStream_t stream) {
+    constexpr int kQueries = 32 * (4 / KW);
+    const dim3 grid((unsigned)((q_slots + kQueries - 1) / kQueries), g.n_win, pr.B * pr.heads);
+    hipLaunchKernelGGL(attn_f32<KW>, grid, dim3(256), 0, stream, pr.q, pr.k, pr.v, pr.o, g, pr.heads,
+                       scale * 1.4426950408889634f, q_slots);
+    return launch_status("attn_f32");
+}
+
 static jv_status attn_dispatch(const Problem &pr, const WindowGeom &g, float scale, int q_slots,
                                hipStream_t stream) {
     if (pr.bf16) return attn_bf16(pr, g, scale, q_slots, stream);
-    const long long qblocks = (q_slots + 3) / 4;
     if (g.n_win > 65535) return fail(JV_ERR_UNSUPPORTED, "more than 65535 windows");
-    hipLaunchKernelGGL(attn_f32, dim3((unsigned)qblocks, g.n_win, pr.B * pr.heads), dim3(256), 0,
-                       stream, pr.q, pr.k, pr.v, pr.o, g, pr.heads, scale, q_slots);
-    return launch_status("attn_f32");
+    if (q_slots > g.slots) q_slots = g.slots;
+    // Key groups per query block: as long as the launch has fewer than four wavefronts per SIMD
+    // (1 024 SIMDs) with every wavefront on queries of its own, the keys of a window are cut
+    // over two or four wavefronts, if it has tiles for them.
+    const long long waves = (long long)((q_slots + 31) / 32) * g.n_win * pr.B * pr.heads;
+    const int tiles = (g.slots + 31) / 32;
+    if (waves < 2048 && tiles > 2) return launch_attn_f32<4>(pr, g, scale, q_slots, stream);
+    if (waves < 4096 && tiles > 1) return launch_attn_f32<2>(pr, g, scale, q_slots, stream);
+    return launch_attn_f32<1>(pr, g, scale, q_slots, stream);
 }
 
 // All tokens of the sequence as one window of 1 x N slots (token = slot).

@@ -47,6 +47,35 @@ def test_ragged_and_edge_shapes(B, heads, H, W, window):
     check(err_fp32(got["full"], oracle.full_attn(q, k, v)), FP32_TOL)
 
 
+@pytest.mark.parametrize("B,heads,H,W,window", [
+    (1, 1, 1, 33, (1, 32)),    # one key past a tile of 32; a window of one token
+    (1, 2, 8, 16, (8, 8)),     # four full tiles, one per key group; windows of two tiles
+    (1, 1, 3, 43, (3, 43)),    # 129 keys: the second step of the four key groups has one tile of one key
+    (2, 12, 21, 21, (7, 7)),   # 49-slot windows: a tile and a half, queries and keys
+    (2, 16, 33, 65, (8, 8)),   # enough windows for two and for one key group per query block
+])
+def test_attention_tile_edges(B, heads, H, W, window):
+    N = H * W
+    q, k, v = synth.qkv(17, B, heads, N, 64, 1.0, False)
+    dq, dk, dv = (to_device(x, False) for x in (q, k, v))
+    o = torch.empty_like(dq)
+    binding.jv_window_attn_fwd(dq, dk, dv, o, (H, W), window)
+    check(err_fp32(to_host(o), oracle.window_attn(q, k, v, H, W, *window)), FP32_TOL)
+    if N < 1000:
+        binding.jv_full_attn_fwd(dq, dk, dv, o, (H, W))
+        check(err_fp32(to_host(o), oracle.full_attn(q, k, v)), FP32_TOL)
+
+
+@pytest.mark.parametrize("N", [15, 16, 17, 63, 64, 65, 129, 513, 1100])
+def test_linear_chunk_edges(N):
+    # chunks of 64 tokens, groups of 16 in the state pass, tiles of 32 in the apply pass
+    q, k, v = synth.qkv(18, 1, 3, N, 64, 1.0, False)
+    dq, dk, dv = (to_device(x, False) for x in (q, k, v))
+    o = torch.empty_like(dq)
+    binding.jv_linear_attn_fwd(dq, dk, dv, o, (1, N), 1e-6)
+    check(err_fp32(to_host(o), oracle.linear_attn_quadratic(q, k, v, 1e-6)), FP32_TOL)
+
+
 def test_long_sequence_split_reduction_fp32():
     # N large enough that the state reduction is split over several workgroups per head
     B, heads, H, W = 1, 2, 48, 50
