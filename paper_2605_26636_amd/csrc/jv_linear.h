@@ -14,7 +14,7 @@ struct LinearPlan {
     bool combine;      // sum the partial states in a pass of their own (many chunks)
 };
 
-LinearPlan plan_linear(int B, int heads, int N);
+LinearPlan plan_linear(int B, int heads, int N, bool bf16 = true);
 size_t linear_workspace_floats(const LinearPlan &p, int B, int heads);
 
 // The depth-wise convolution branch of the block (Eq. 4) as the launchers see it.  Workspace

@@ -7,12 +7,27 @@
 //   ((p * B*heads) + b*heads + h) * kStateFloats
 // and holds S transposed, St[c2][c1] (c2 = value channel, c1 = key channel), then z[c1].
 #include "jv_linear.h"
+#include "jv_mfma.h"
 
 namespace jv {
 
-LinearPlan plan_linear(int B, int heads, int N) {
+LinearPlan plan_linear(int B, int heads, int N, bool bf16) {
     LinearPlan p;
     const long long bh = (long long)B * heads;
+    if (!bf16) {
+        // Chunks of at least 64 tokens (16 per wavefront, one round of loads in the state pass), down
+        // to which a problem is cut until it has two workgroups per compute unit; at most eight
+        // partial states, which every workgroup of the apply pass sums for itself.
+        long long want = (512 + bh - 1) / bh, most = (N + 63) / 64;
+        want = want > most ? most : want;
+        want = want > 8 ? 8 : want;
+        p.chunk = (int)((((N + want - 1) / want + 63) / 64) * 64);
+        p.n_split = (N + p.chunk - 1) / p.chunk;
+        p.apply_tokens = 1024;
+        while (p.apply_tokens > 128 && bh * ((N + p.apply_tokens - 1) / p.apply_tokens) < 512) p.apply_tokens /= 2;
+        p.combine = false;
+        return p;
+    }
     // Aim for about two workgroups per compute unit, chunks of at least 256 tokens.
     long long want = (512 + bh - 1) / bh;
     long long max_split = (N + 255) / 256;
@@ -36,140 +51,299 @@ size_t linear_workspace_floats(const LinearPlan &p, int B, int heads) {
 }
 
 // ---------------------------------------------------------------------------------------
-// fp32 path: plain FMA arithmetic, used for fp32 tensors.
+// fp32 path: both passes on the fp32 matrix instructions (v_mfma_f32_32x32x2_f32: operand lane
+// (half, i) holds row or column i at contraction index `half`; fp32 throughout), whose rate
+// would stream the tensors at 9.8 TB/s, so large problems are bound by memory and small ones by
+// the two launches.
 // ---------------------------------------------------------------------------------------
 
-// Focused feature map (Eq. 3; see focus_bf16x8 in the bf16 path) applied in place to `rows`
-// token rows of 64 already-rectified channels in shared memory; one thread per row.
-__device__ inline void focus_rows_f32(float (*rows)[kHeadDim], int n_rows, int p, int t) {
-    if (t < n_rows) {
-        float *r = rows[t];
-        float top = 0.f;
-#pragma unroll 4
-        for (int c = 0; c < kHeadDim; ++c) top = fmaxf(top, r[c]);
-        if (top > 0.f) {
-            const float inv_top = 1.0f / top;
-            float ss = 0.f, sy = 0.f;
-#pragma unroll 2
-            for (int c = 0; c < kHeadDim; ++c) {
-                const float x = r[c] * inv_top;
-                float y = x;
-                for (int i = 1; i < p; ++i) y *= x;
-                ss = fmaf(x, x, ss);
-                sy = fmaf(y, y, sy);
-                r[c] = y;
-            }
-            const float scale = top * sqrtf(ss / sy);
-#pragma unroll 4
-            for (int c = 0; c < kHeadDim; ++c) r[c] *= scale;
-        }
-    }
+// Focused feature map (Eq. 3; see focus_bf16x8 in the bf16 path) of a rectified row given the
+// largest entry `top` of the row: x <- x^p as a fraction of top; the caller scales the row by
+// top * sqrt(sum (x / top)^2 / sum (x / top)^2p).
+__device__ inline float focus_power(float x, int p, float &ss, float &sy) {
+    float y = x;
+    for (int i = 1; i < p; ++i) y *= x;
+    ss = fmaf(x, x, ss);
+    sy = fmaf(y, y, sy);
+    return y;
 }
 
-// grid (n_split, B*heads), 256 threads.  Thread t owns S[16*(t/64) .. +15][t%64].
-__global__ void __launch_bounds__(256)
+// State pass.  Wavefront w of a workgroup takes every fourth group of 16 tokens of the chunk.
+// The contraction runs over tokens and both operands are channels of one token, so a lane's
+// operand is one element of a K or V row straight from global memory (two rows of 128
+// contiguous bytes per load instruction): no staging.  St = V^T relu(K) in four 32 x 32 blocks.
+// Measured: 256 tokens x 6 heads 4.5 us (plain FMAs, one workgroup per head: 30 us).
+// grid (n_split, B*heads), 256 threads.
+__global__ void __launch_bounds__(256, 2)
 la_state_f32(TensorArg kt, TensorArg vt, float *__restrict__ ws, int heads, int N, int chunk,
              int focus_p) {
-    __shared__ float Ks[32][kHeadDim];
-    __shared__ float Vs[32][kHeadDim];
+    __shared__ __align__(16) float part[4][kHeadDim * kHeadDim];
+    __shared__ float zpart[4][kHeadDim];
     const int bh = blockIdx.y, b = bh / heads, h = bh % heads, p = blockIdx.x;
     const int BH = gridDim.y;
-    const float *kp = (const float *)kt.ptr + b * kt.sb + h * kt.sh;
-    const float *vp = (const float *)vt.ptr + b * vt.sb + h * vt.sh;
-    const int t = threadIdx.x, c2 = t & 63, rb = t >> 6;
-    float acc[16];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, li = lane & 31;
+    const float *kp = (const float *)kt.ptr + b * kt.sb + h * kt.sh + li;
+    const float *vp = (const float *)vt.ptr + b * vt.sb + h * vt.sh + li;
+    f32x16 acc[2][2];  // [value block][key block]
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    float zacc = 0.f;
+    for (int v = 0; v < 16; ++v) acc[0][0][v] = acc[0][1][v] = acc[1][0][v] = acc[1][1][v] = 0.f;
+    float z[2] = {0.f, 0.f};
     const int n0 = p * chunk, n1 = min(N, n0 + chunk);
-    for (int base = n0; base < n1; base += 32) {
-        // 32 tokens x 64 channels = 512 float4; two per thread per tensor
-        for (int e = t; e < 512; e += 256) {
-            int j = e >> 4, c4 = (e & 15) * 4, n = base + j;
-            float4 kk = make_float4(0.f, 0.f, 0.f, 0.f), vv = kk;
-            if (n < n1) {
-                kk = *(const float4 *)(kp + (long long)n * kt.sn + c4);
-                vv = *(const float4 *)(vp + (long long)n * vt.sn + c4);
-            }
-            Ks[j][c4 + 0] = fmaxf(kk.x, 0.f);
-            Ks[j][c4 + 1] = fmaxf(kk.y, 0.f);
-            Ks[j][c4 + 2] = fmaxf(kk.z, 0.f);
-            Ks[j][c4 + 3] = fmaxf(kk.w, 0.f);
-            *(float4 *)&Vs[j][c4] = vv;
-        }
-        __syncthreads();
-        if (focus_p > 1) {  // uniform
-            focus_rows_f32(Ks, 32, focus_p, t);
-            __syncthreads();
-        }
-#pragma unroll 4
-        for (int j = 0; j < 32; ++j) {
-            float vj = Vs[j][c2];
+    float k[8][2], v[8][2], knext[8][2], vnext[8][2];
+    // Rows are walked with a running pointer per lane: a 64-bit multiplication per row costs more
+    // than the products.
+    auto fetch = [&](int base) {
+        const float *kr = kp + (long long)(base + half) * kt.sn, *vr = vp + (long long)(base + half) * vt.sn;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = fmaf(Ks[j][rb * 16 + r], vj, acc[r]);
-            if (rb == 0) zacc += Ks[j][c2];
+        for (int u = 0; u < 8; ++u) {
+            knext[u][0] = kr[0]; knext[u][1] = kr[32];
+            vnext[u][0] = vr[0]; vnext[u][1] = vr[32];
+            kr += 2 * kt.sn;
+            vr += 2 * vt.sn;
         }
-        __syncthreads();
+    };
+    auto reduce = [&]() {
+        if (focus_p > 1) {  // uniform; a token's row lies in the 32 lanes of one half
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                float top = fmaxf(k[u][0], k[u][1]);
+#pragma unroll
+                for (int off = 16; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off, 64));
+                const float inv_top = top > 0.f ? 1.0f / top : 0.f;
+                float ss = 0.f, sy = 0.f;
+#pragma unroll
+                for (int c = 0; c < 2; ++c) k[u][c] = focus_power(k[u][c] * inv_top, focus_p, ss, sy);
+#pragma unroll
+                for (int off = 16; off > 0; off >>= 1) {
+                    ss += __shfl_xor(ss, off, 64);
+                    sy += __shfl_xor(sy, off, 64);
+                }
+                const float scale = top > 0.f ? top * sqrtf(ss / sy) : 0.f;
+#pragma unroll
+                for (int c = 0; c < 2; ++c) k[u][c] *= scale;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            z[0] += k[u][0];
+            z[1] += k[u][1];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[u][i], k[u][j], acc[i][j], 0, 0, 0);
+        }
+    };
+    int base = n0 + 16 * wave;
+    bool whole = base + 16 <= n1;
+    if (whole) fetch(base);
+    while (whole) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                k[u][c] = fmaxf(knext[u][c], 0.f);
+                v[u][c] = vnext[u][c];
+            }
+        base += 64;
+        whole = base + 16 <= n1;
+        if (whole) fetch(base);  // the next group's rows, in flight under this group's products
+        reduce();
     }
+    if (base < n1) {  // the last group of the chunk, with fewer than 16 tokens
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int n = base + 2 * u + half;
+            k[u][0] = k[u][1] = v[u][0] = v[u][1] = 0.f;
+            if (n < n1) {
+                const float *kr = kp + (long long)n * kt.sn, *vr = vp + (long long)n * vt.sn;
+                k[u][0] = fmaxf(kr[0], 0.f); k[u][1] = fmaxf(kr[32], 0.f);
+                v[u][0] = vr[0]; v[u][1] = vr[32];
+            }
+        }
+        reduce();
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                part[wave][(32 * i + 8 * (v / 4) + 4 * half + v % 4) * kHeadDim + 32 * j + li] = acc[i][j][v];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        z[j] += __shfl_xor(z[j], 32, 64);
+        if (half == 0) zpart[wave][32 * j + li] = z[j];
+    }
+    __syncthreads();
     float *out = ws + ((size_t)p * BH + bh) * kStateFloats;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) out[c2 * kHeadDim + rb * 16 + r] = acc[r];
-    if (rb == 0) out[kHeadDim * kHeadDim + c2] = zacc;
+    for (int i = 0; i < 4; ++i) {
+        const int e = 4 * (tid + 256 * i);
+        *(f32x4 *)(out + e) = (*(const f32x4 *)&part[0][e] + *(const f32x4 *)&part[1][e]) +
+                              (*(const f32x4 *)&part[2][e] + *(const f32x4 *)&part[3][e]);
+    }
+    if (tid < kHeadDim)
+        out[kHeadDim * kHeadDim + tid] = (zpart[0][tid] + zpart[1][tid]) + (zpart[2][tid] + zpart[3][tid]);
 }
 
-// grid (ceil(N/256), B*heads), 256 threads.
-__global__ void __launch_bounds__(256)
+// Apply pass.  The workgroup sums the partial states into LDS; every wavefront keeps all of St
+// (and z) as operands in registers and walks over tiles of 32 tokens: O^T = St relu(Q)^T with
+// lane (half, i) holding channels 32 half .. +31 of token i, so the denominator is 32 FMAs per
+// lane and one exchange.  Query and output rows pass through LDS: global memory sees whole rows.
+// Measured: 256 tokens x 6 heads 6.6 us (plain FMAs, one workgroup per head: 58 us).
+// grid (ceil(N / tokens), B*heads), 256 threads; tokens is a multiple of 128.
+__global__ void __launch_bounds__(256, 2)
 la_apply_f32(TensorArg qt, TensorArg ot, const float *__restrict__ ws, int heads, int N,
-             int n_split, float eps, int focus_p) {
-    __shared__ float S[kHeadDim][kHeadDim + 1];  // S[c1][c2]
-    __shared__ float z[kHeadDim];
-    __shared__ float Qs[64][kHeadDim];
+             int n_split, int tokens, float eps, int focus_p) {
+    // 16-byte chunks of a row are rotated by the row: row-per-lane accesses without bank conflicts
+    __shared__ __align__(16) unsigned char St[kHeadDim * 256];
+    __shared__ __align__(16) float z[kHeadDim];
+    __shared__ __align__(16) unsigned char stage[4][32 * 256];
     const int bh = blockIdx.y, b = bh / heads, h = bh % heads;
     const int BH = gridDim.y;
     const float *qp = (const float *)qt.ptr + b * qt.sb + h * qt.sh;
     float *op = (float *)ot.ptr + b * ot.sb + h * ot.sh;
-    const int t = threadIdx.x;
-    for (int e = t; e < kStateFloats; e += 256) {
-        float s = 0.f;
-        for (int p = 0; p < n_split; ++p) s += ws[((size_t)p * BH + bh) * kStateFloats + e];
-        if (e < kHeadDim * kHeadDim) S[e & 63][e >> 6] = s;  // stored transposed in the workspace
-        else z[e - kHeadDim * kHeadDim] = s;
-    }
-    const int c2 = t & 63, tg = t >> 6;
-    const int n0 = blockIdx.x * 256, n1 = min(N, n0 + 256);
-    for (int base = n0; base < n1; base += 64) {
-        __syncthreads();
-        for (int e = t; e < 1024; e += 256) {
-            int j = e >> 4, c4 = (e & 15) * 4, n = base + j;
-            float4 qq = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (n < n1) qq = *(const float4 *)(qp + (long long)n * qt.sn + c4);
-            Qs[j][c4 + 0] = fmaxf(qq.x, 0.f);
-            Qs[j][c4 + 1] = fmaxf(qq.y, 0.f);
-            Qs[j][c4 + 2] = fmaxf(qq.z, 0.f);
-            Qs[j][c4 + 3] = fmaxf(qq.w, 0.f);
-        }
-        __syncthreads();
-        if (focus_p > 1) {  // uniform
-            focus_rows_f32(Qs, 64, focus_p, t);
-            __syncthreads();
-        }
-        for (int jj = 0; jj < 16; ++jj) {
-            int j = tg * 16 + jj, n = base + j;
-            if (n >= n1) break;
-            float num = 0.f, den = 0.f;
-#pragma unroll 8
-            for (int c1 = 0; c1 < kHeadDim; ++c1) {
-                float qv = Qs[j][c1];
-                num = fmaf(qv, S[c1][c2], num);
-                den = fmaf(qv, z[c1], den);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, li = lane & 31;
+    const int n1 = min(N, (int)(blockIdx.x + 1) * tokens);
+    const int srow = lane >> 4, chunk = lane & 15;  // row layout of a tile: 4 rows per instruction
+    f32x4 q[8], next[8];
+    auto fetch = [&](int base) {
+        if (base + 32 <= n1) {
+            const float *row = qp + (long long)(base + srow) * qt.sn + 4 * chunk;
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                next[r] = *(const f32x4 *)row;
+                row += 4 * qt.sn;
             }
-            op[(long long)n * ot.sn + c2] = num / (den + eps);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+                next[r] = *(const f32x4 *)(qp + (long long)min(base + 4 * r + srow, n1 - 1) * qt.sn + 4 * chunk);
+        }
+    };
+    int base = blockIdx.x * tokens + 32 * wave;
+    fetch(base);
+    // St and z as 1040 16-byte pieces, five per thread (the fifth for the first 16 threads); the
+    // partials of four pieces and four chunks at a time, so that the sum is not a chain of round trips
+    {
+        const float *src = ws + (size_t)bh * kStateFloats;
+        f32x4 s[5];
+#pragma unroll
+        for (int i = 0; i < 5; ++i) s[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int p0 = 0; p0 < n_split; p0 += 4) {
+#pragma unroll
+            for (int dp = 0; dp < 4; ++dp) {
+                const float *part = src + (size_t)min(p0 + dp, n_split - 1) * BH * kStateFloats;
+                const float w = p0 + dp < n_split ? 1.f : 0.f;
+#pragma unroll
+                for (int i = 0; i < 5; ++i) {
+                    const f32x4 x = *(const f32x4 *)(part + 4 * min(tid + 256 * i, kStateFloats / 4 - 1));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s[i][e] = fmaf(w, x[e], s[i][e]);
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+            const int e = tid + 256 * i, row = e >> 4, c = e & 15;
+            if (row < kHeadDim) *(f32x4 *)(St + row * 256 + ((c ^ (row & 15)) << 4)) = s[i];
+            else if (row == kHeadDim) *(f32x4 *)(z + 4 * c) = s[i];
+        }
+    }
+    __syncthreads();
+    f32x4 sreg[2][8], zreg[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb)
+            sreg[cb][i] = *(const f32x4 *)(St + (32 * cb + li) * 256 + (((8 * half + i) ^ (li & 15)) << 4));
+        zreg[i] = *(const f32x4 *)(z + 32 * half + 4 * i);
+    }
+    unsigned char *mine = stage[wave];
+    for (; base < n1; base += 128) {
+        // query rows -> LDS -> 32 channels of one token per lane (the buffer is this wavefront's own)
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const int row = 4 * r + srow;
+            *(f32x4 *)(mine + row * 256 + ((chunk ^ (row & 15)) << 4)) = next[r];
+        }
+        if (base + 128 < n1) fetch(base + 128);
+        f32x4 top4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            q[i] = *(const f32x4 *)(mine + li * 256 + (((8 * half + i) ^ (li & 15)) << 4));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                q[i][e] = fmaxf(q[i][e], 0.f);
+                top4[e] = fmaxf(top4[e], q[i][e]);
+            }
+        }
+        float lo, hi;
+        if (focus_p > 1) {  // uniform; a token's row lies in lanes li and li + 32
+            pair_values(fmaxf(fmaxf(top4[0], top4[1]), fmaxf(top4[2], top4[3])), &lo, &hi);
+            const float top = fmaxf(lo, hi), inv_top = top > 0.f ? 1.0f / top : 0.f;
+            float ss = 0.f, sy = 0.f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) q[i][e] = focus_power(q[i][e] * inv_top, focus_p, ss, sy);
+            pair_values(ss, &lo, &hi);
+            ss = lo + hi;
+            pair_values(sy, &lo, &hi);
+            sy = lo + hi;
+            const float scale = top > 0.f ? top * sqrtf(ss / sy) : 0.f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) q[i] *= scale;
+        }
+        f32x4 den4 = {0.f, 0.f, 0.f, 0.f};
+        f32x16 acc[2];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                den4[e] = fmaf(q[i][e], zreg[i][e], den4[e]);
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb)
+                    acc[cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(sreg[cb][i][e], q[i][e], acc[cb], 0, 0, 0);
+            }
+        pair_values((den4[0] + den4[1]) + (den4[2] + den4[3]), &lo, &hi);
+        const float inv = 1.0f / ((lo + hi) + eps);
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+            for (int v4 = 0; v4 < 4; ++v4) {
+                f32x4 out;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) out[e] = acc[cb][4 * v4 + e] * inv;
+                *(f32x4 *)(mine + li * 256 + (((8 * cb + 2 * v4 + half) ^ (li & 15)) << 4)) = out;
+            }
+        float *orow = op + (long long)(base + srow) * ot.sn + 4 * chunk;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const int row = 4 * r + srow;
+            const f32x4 out = *(const f32x4 *)(mine + row * 256 + ((chunk ^ (row & 15)) << 4));
+            if (base + row < n1) *(f32x4 *)orow = out;
+            orow += 4 * ot.sn;
         }
     }
 }
 
-size_t linear_workspace_bytes(int B, int heads, int N) {
-    return linear_workspace_floats(plan_linear(B, heads, N), B, heads) * sizeof(float);
+size_t linear_workspace_bytes(int B, int heads, int N, bool bf16) {
+    return linear_workspace_floats(plan_linear(B, heads, N, bf16), B, heads) * sizeof(float);
+}
+
+static jv_status linear_f32(const Problem &pr, const LinearPlan &plan, float eps, float *ws, int focus_p, hipStream_t stream) {
+    const int BH = pr.B * pr.heads;
+    hipLaunchKernelGGL(la_state_f32, dim3(plan.n_split, BH), dim3(256), 0, stream, pr.k, pr.v, ws,
+                       pr.heads, pr.N, plan.chunk, focus_p);
+    jv_status st = launch_status("la_state_f32");
+    if (st != JV_OK) return st;
+    hipLaunchKernelGGL(la_apply_f32, dim3((pr.N + plan.apply_tokens - 1) / plan.apply_tokens, BH), dim3(256), 0, stream,
+                       pr.q, pr.o, ws, pr.heads, pr.N, plan.n_split, plan.apply_tokens, eps, focus_p);
+    return launch_status("la_apply_f32");
 }
 
 // The block of Eq. 4.  Order of launches: state pass (which also sums V over the tokens when
@@ -195,7 +369,7 @@ jv_status linear_block_forward(const Problem &pr, float eps, const jv_dwc_params
         if ((st = dwc_wide_filters(pr, cv, ws, stream, &arg)) != JV_OK) return st;
         return linear_wide_apply(pr, eps, ws, stream, cv.ksize, &arg);
     }
-    const LinearPlan plan = plan_linear(pr.B, pr.heads, pr.N);
+    const LinearPlan plan = plan_linear(pr.B, pr.heads, pr.N, pr.bf16);
     DwcPlan cv;
     jv_status st = plan_dwc(dwc, plan, pr.B, pr.heads, pr.N, &cv);
     if (st != JV_OK) return st;
@@ -206,14 +380,8 @@ jv_status linear_block_forward(const Problem &pr, float eps, const jv_dwc_params
     if (cv.mode == JV_DWC_TOKEN_DYNAMIC) {
         // Plain linear attention into an fp32 tensor (O itself when it is fp32), then one pass
         // that adds every token's own convolution term and rounds once.
-        if (!pr.bf16) {  // fp32 tensors: the plain two-pass attention, then the convolution added in place
-            const int BH = pr.B * pr.heads;
-            hipLaunchKernelGGL(la_state_f32, dim3(plan.n_split, BH), dim3(256), 0, stream, pr.k, pr.v, ws,
-                               pr.heads, pr.N, plan.chunk, focus_p);
-            if ((st = launch_status("la_state_f32")) != JV_OK) return st;
-            hipLaunchKernelGGL(la_apply_f32, dim3((pr.N + 255) / 256, BH), dim3(256), 0, stream, pr.q, pr.o,
-                               ws, pr.heads, pr.N, plan.n_split, eps, focus_p);
-            if ((st = launch_status("la_apply_f32")) != JV_OK) return st;
+        if (!pr.bf16) {  // fp32 tensors: the two passes, then the convolution added in place
+            if ((st = linear_f32(pr, plan, eps, ws, focus_p, stream)) != JV_OK) return st;
             return token_dwc_forward_f32(pr, cv, ws, stream);
         }
         Problem la = pr;
@@ -228,13 +396,7 @@ jv_status linear_block_forward(const Problem &pr, float eps, const jv_dwc_params
         return token_dwc_forward(pr, la.o, cv, ws, stream);
     }
     if (pr.bf16) return linear_bf16(pr, plan, eps, ws, cv, focus_p, stream);
-    const int BH = pr.B * pr.heads;
-    hipLaunchKernelGGL(la_state_f32, dim3(plan.n_split, BH), dim3(256), 0, stream, pr.k, pr.v, ws,
-                       pr.heads, pr.N, plan.chunk, focus_p);
-    if ((st = launch_status("la_state_f32")) != JV_OK) return st;
-    hipLaunchKernelGGL(la_apply_f32, dim3((pr.N + 255) / 256, BH), dim3(256), 0, stream, pr.q, pr.o,
-                       ws, pr.heads, pr.N, plan.n_split, eps, focus_p);
-    if ((st = launch_status("la_apply_f32")) != JV_OK) return st;
+    if ((st = linear_f32(pr, plan, eps, ws, focus_p, stream)) != JV_OK) return st;
     if (cv.mode == JV_DWC_NONE) return JV_OK;
     DwcArg arg = {cv.static_kernel, 0, pr.H, pr.W, pr.P};
     if (cv.mode == JV_DWC_SQUEEZE_DYNAMIC) {
@@ -244,12 +406,6 @@ jv_status linear_block_forward(const Problem &pr, float eps, const jv_dwc_params
         arg.kappa_sb = (long long)pr.heads * kHeadDim * cv.ksize * cv.ksize;
     }
     return dwc_add_f32_launch(pr, arg, cv.ksize, stream);
-}
-
-jv_status linear_forward(const Problem &pr, float eps, void *workspace, hipStream_t stream) {
-    const size_t bytes = pr.D == kHeadDimWide ? linear_wide_workspace_floats(pr.B, pr.heads, pr.N) * sizeof(float)
-                                              : linear_workspace_bytes(pr.B, pr.heads, pr.N);
-    return linear_block_forward(pr, eps, nullptr, workspace, bytes, stream);
 }
 
 }  // namespace jv
@@ -309,7 +465,7 @@ size_t jv_linear_block_workspace_bytes(const jv_attn_desc *desc, const jv_dwc_pa
             return 0;
         return cv.total_floats * sizeof(float);
     }
-    const jv::LinearPlan plan = jv::plan_linear(desc->batch, desc->heads, N);
+    const jv::LinearPlan plan = jv::plan_linear(desc->batch, desc->heads, N, desc->dtype == JV_BF16);
     if (jv::plan_dwc(dwc, plan, desc->batch, desc->heads, N, &cv) != JV_OK) return 0;
     return cv.total_floats * sizeof(float);
 }
@@ -339,7 +495,7 @@ jv_status jv_linear_attn_fwd_static(const jv_attn_desc *desc, const void *q, con
     if (st != JV_OK) return st;
     if (!(eps >= 0.0f)) return jv::fail(JV_ERR_INVALID_ARG, "eps must be >= 0");
     jv::DwcPlan plain;
-    if ((st = jv::plan_dwc(nullptr, jv::plan_linear(pr.B, pr.heads, pr.N), pr.B, pr.heads, pr.N, &plain)) != JV_OK)
+    if ((st = jv::plan_dwc(nullptr, jv::plan_linear(pr.B, pr.heads, pr.N, pr.bf16), pr.B, pr.heads, pr.N, &plain)) != JV_OK)
         return st;
     // what jv_linear_attn_workspace_bytes answers
     const size_t need = (pr.D == jv::kHeadDimWide ? jv::linear_wide_workspace_floats(pr.B, pr.heads, pr.N)
