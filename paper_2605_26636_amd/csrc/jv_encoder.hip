@@ -3,8 +3,10 @@
 // bias / GELU / residual epilogues, and the host loop that runs the blocks.
 #include <math.h>
 #include <new>
+#include <type_traits>
 
 #include "jv_common.h"
+#include "jv_gemm.h"
 #include "jv_linear.h"
 #include "jv_mfma.h"
 
@@ -15,6 +17,75 @@ namespace jv {
 // mean and variance in two register passes, fp32 statistics.
 // grid (8 * ceil(ceil(rows / 4) / 8)), 256 threads.  NV = 16-byte pieces per lane (cols <= 256 * NV).
 // ---------------------------------------------------------------------------------------
+// Piece p of a lane covers columns 4 * (lane + 64 p) .. + 3.
+template <bool BF16>
+__device__ inline f32x4 load_piece(const void *x, size_t at) {
+    if (!BF16) return *(const f32x4 *)((const float *)x + at);
+    const u32x2 raw = *(const u32x2 *)((const __bf16 *)x + at);
+    return f32x4{bf16_lo(raw[0]), bf16_hi(raw[0]), bf16_lo(raw[1]), bf16_hi(raw[1])};
+}
+template <bool BF16>
+__device__ inline void store_piece(void *y, size_t at, f32x4 v) {
+    if (BF16) *(u32x2 *)((__bf16 *)y + at) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+    else *(f32x4 *)((float *)y + at) = v;
+}
+// Scale and shift of a row, fetched by the callers before the row's own values are waited for:
+// behind the two reductions their latency would stand alone (it shows where rows are few).  Rows
+// above 2048 columns would need more registers than there are: theirs are read at the end.
+template <int NV>
+struct RowAffine {
+    static constexpr bool kHeld = NV <= 8;
+    f32x4 gamma[kHeld ? NV : 1], beta[kHeld ? NV : 1];
+    const float *g, *b;
+    __device__ void fetch(const float *g_, const float *b_, int cols, int lane) {
+        g = g_;
+        b = b_;
+        if (kHeld)
+#pragma unroll
+            for (int p = 0; p < NV; ++p) {
+                const int c = min(4 * (lane + 64 * p), cols - 4);
+                gamma[kHeld ? p : 0] = *(const f32x4 *)(g + c);
+                beta[kHeld ? p : 0] = *(const f32x4 *)(b + c);
+            }
+    }
+    __device__ f32x4 scale(int p, int c) const { return kHeld ? gamma[kHeld ? p : 0] : *(const f32x4 *)(g + c); }
+    __device__ f32x4 shift(int p, int c) const { return kHeld ? beta[kHeld ? p : 0] : *(const f32x4 *)(b + c); }
+};
+// LayerNorm of the row whose pieces are v (0 past the last column), mean and variance in two
+// register passes.
+template <bool OUT_BF16, int NV>
+__device__ inline void normalize_row(const f32x4 (&v)[NV], const RowAffine<NV> &aff, void *y, size_t row_at, int cols, int lane, float eps) {
+    float sum = 0.f;
+#pragma unroll
+    for (int p = 0; p < NV; ++p) sum += (v[p][0] + v[p][1]) + (v[p][2] + v[p][3]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    const float mean = sum / (float)cols;
+    float sq = 0.f;
+#pragma unroll
+    for (int p = 0; p < NV; ++p)
+        if (4 * (lane + 64 * p) < cols)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float dlt = v[p][e] - mean;
+                sq = fmaf(dlt, dlt, sq);
+            }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
+    const float inv = 1.0f / sqrtf(sq / (float)cols + eps);
+#pragma unroll
+    for (int p = 0; p < NV; ++p) {
+        const int c = 4 * (lane + 64 * p);
+        if (c < cols) {
+            const f32x4 gm = aff.scale(p, c), bt = aff.shift(p, c);
+            f32x4 out;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) out[e] = (v[p][e] - mean) * inv * gm[e] + bt[e];
+            store_piece<OUT_BF16>(y, row_at + c, out);
+        }
+    }
+}
+
 template <bool IN_BF16, bool OUT_BF16, int NV>
 __global__ void __launch_bounds__(256)
 layernorm_kernel(const void *__restrict__ xin, const float *__restrict__ gamma,
@@ -28,85 +99,40 @@ layernorm_kernel(const void *__restrict__ xin, const float *__restrict__ gamma,
     const long long wg = (long long)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     const long long row = wg * 4 + wave;
     if (wg >= n_wg || row >= rows) return;
-    // piece p of a lane covers columns 4 * (lane + 64 p) .. + 3
     f32x4 v[NV];
-    float sum = 0.f;
+    RowAffine<NV> aff;
 #pragma unroll
     for (int p = 0; p < NV; ++p) {
         const int c = 4 * (lane + 64 * p);
-        f32x4 x = {0.f, 0.f, 0.f, 0.f};
-        if (c < cols) {
-            if (IN_BF16) {
-                const u32x2 raw = *(const u32x2 *)((const __bf16 *)xin + row * cols + c);
-                x[0] = bf16_lo(raw[0]); x[1] = bf16_hi(raw[0]);
-                x[2] = bf16_lo(raw[1]); x[3] = bf16_hi(raw[1]);
-            } else {
-                x = *(const f32x4 *)((const float *)xin + row * cols + c);
-            }
-        }
-        v[p] = x;
-        sum += (x[0] + x[1]) + (x[2] + x[3]);
+        v[p] = c < cols ? load_piece<IN_BF16>(xin, row * cols + c) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-    const float mean = sum / (float)cols;
-    float sq = 0.f;
-#pragma unroll
-    for (int p = 0; p < NV; ++p) {
-        const int c = 4 * (lane + 64 * p);
-        if (c < cols) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float dlt = v[p][e] - mean;
-                sq = fmaf(dlt, dlt, sq);
-            }
-        }
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
-    const float inv = 1.0f / sqrtf(sq / (float)cols + eps);
-#pragma unroll
-    for (int p = 0; p < NV; ++p) {
-        const int c = 4 * (lane + 64 * p);
-        if (c < cols) {
-            const f32x4 gm = *(const f32x4 *)(gamma + c), bt = *(const f32x4 *)(beta + c);
-            f32x4 y;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) y[e] = (v[p][e] - mean) * inv * gm[e] + bt[e];
-            if (OUT_BF16) {
-                u32x2 pk = {pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
-                *(u32x2 *)((__bf16 *)yout + row * cols + c) = pk;
-            } else {
-                *(f32x4 *)((float *)yout + row * cols + c) = y;
-            }
-        }
-    }
+    aff.fetch(gamma, beta, cols, lane);
+    normalize_row<OUT_BF16, NV>(v, aff, yout, row * cols, cols, lane, eps);
 }
 
-template <bool IN_BF16, bool OUT_BF16>
-static void launch_layernorm(const void *x, const float *gamma, const float *beta, void *y,
-                             long long rows, int cols, float eps, hipStream_t stream) {
-    dim3 grid((unsigned)(8 * (((rows + 3) / 4 + 7) / 8)));
+// f(integral_constant NV) for the pieces per lane that rows of `cols` need.
+template <typename F>
+static void with_row_pieces(int cols, F f) {
     const int nv = (cols + 255) / 256;
-    if (nv <= 1)
-        hipLaunchKernelGGL((layernorm_kernel<IN_BF16, OUT_BF16, 1>), grid, dim3(256), 0, stream, x, gamma, beta, y, rows, cols, eps);
-    else if (nv <= 2)
-        hipLaunchKernelGGL((layernorm_kernel<IN_BF16, OUT_BF16, 2>), grid, dim3(256), 0, stream, x, gamma, beta, y, rows, cols, eps);
-    else if (nv <= 4)
-        hipLaunchKernelGGL((layernorm_kernel<IN_BF16, OUT_BF16, 4>), grid, dim3(256), 0, stream, x, gamma, beta, y, rows, cols, eps);
-    else if (nv <= 8)
-        hipLaunchKernelGGL((layernorm_kernel<IN_BF16, OUT_BF16, 8>), grid, dim3(256), 0, stream, x, gamma, beta, y, rows, cols, eps);
-    else
-        hipLaunchKernelGGL((layernorm_kernel<IN_BF16, OUT_BF16, 32>), grid, dim3(256), 0, stream, x, gamma, beta, y, rows, cols, eps);
+    if (nv <= 1) f(std::integral_constant<int, 1>());
+    else if (nv <= 2) f(std::integral_constant<int, 2>());
+    else if (nv <= 3) f(std::integral_constant<int, 3>());
+    else if (nv <= 4) f(std::integral_constant<int, 4>());
+    else if (nv <= 5) f(std::integral_constant<int, 5>());
+    else if (nv <= 8) f(std::integral_constant<int, 8>());
+    else f(std::integral_constant<int, 32>());
 }
 
 static jv_status layernorm_forward(const void *x, const float *gamma, const float *beta, void *y,
                                    long long rows, int cols, float eps, bool in_bf16,
                                    bool out_bf16, hipStream_t stream) {
-    if (in_bf16 && out_bf16) launch_layernorm<true, true>(x, gamma, beta, y, rows, cols, eps, stream);
-    else if (in_bf16) launch_layernorm<true, false>(x, gamma, beta, y, rows, cols, eps, stream);
-    else if (out_bf16) launch_layernorm<false, true>(x, gamma, beta, y, rows, cols, eps, stream);
-    else launch_layernorm<false, false>(x, gamma, beta, y, rows, cols, eps, stream);
+    with_row_pieces(cols, [&](auto nv_tag) {
+        constexpr int NV = decltype(nv_tag)::value;
+        const dim3 grid((unsigned)(8 * (((rows + 3) / 4 + 7) / 8)));
+        auto kernel = in_bf16 ? (out_bf16 ? layernorm_kernel<true, true, NV> : layernorm_kernel<true, false, NV>)
+                              : (out_bf16 ? layernorm_kernel<false, true, NV> : layernorm_kernel<false, false, NV>);
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, x, gamma, beta, y, rows, cols, eps);
+    });
     return launch_status("layernorm_kernel");
 }
 
@@ -142,24 +168,6 @@ constexpr int kGemmPart = kBM * kBK * 2;               // one operand part: 32 K
 constexpr int kGemmSlots = 5;
 constexpr int kGemmLds = kGemmSlots * kGemmPart;       // 160 KB
 
-typedef __attribute__((address_space(1))) const void global_cvoid;
-typedef __attribute__((address_space(3))) void lds_void;
-
-// gelu(x) = x Phi(x), Phi the standard normal distribution function.  The GEMM epilogue reads
-// Phi from a table in LDS (kPhiSteps intervals on [-6, 6], linear interpolation: absolute error
-// below 5e-6; outside the range Phi is 0 or 1 to 1e-9) that every workgroup builds for itself
-// from  Phi(x) = 1 - erfc(x / sqrt 2) / 2,  erfc(z) = (a1 t + ... + a5 t^5) exp(-z^2),
-// t = 1 / (1 + p z), z >= 0  (Abramowitz-Stegun 7.1.26, absolute error 1.5e-7).
-constexpr int kPhiSteps = 1024;
-constexpr float kPhiLo = -6.0f, kPhiStep = 12.0f / kPhiSteps;
-__device__ inline float normal_cdf(float x) {
-    const float z = fabsf(x) * 0.70710678118654752f;
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, z, 1.0f));
-    const float poly = t * fmaf(t, fmaf(t, fmaf(t, fmaf(t, 1.061405429f, -1.453152027f), 1.421413741f),
-                                        -0.284496736f), 0.254829592f);
-    const float half_erfc = 0.5f * poly * __builtin_amdgcn_exp2f(-1.4426950408889634f * z * z);
-    return x < 0.f ? half_erfc : 1.0f - half_erfc;
-}
 // table[2 i] = Phi(x_i), table[2 i + 1] = Phi(x_i+1) - Phi(x_i), x_i = kPhiLo + i kPhiStep.
 __device__ inline float gelu_from_table(float x, const float *table) {
     const float t = __builtin_amdgcn_fmed3f(fmaf(x, 1.0f / kPhiStep, -kPhiLo / kPhiStep), 0.0f,
@@ -167,11 +175,6 @@ __device__ inline float gelu_from_table(float x, const float *table) {
     const unsigned i = (unsigned)t;
     const float2 pd = *(const float2 *)(table + 2 * i);
     return x * fmaf(t - (float)i, pd.y, pd.x);
-}
-
-// Byte offset of 16-byte chunk `chunk` (0..7) of row `row` in a [rows][64] bf16 LDS part.
-__device__ inline unsigned gemm_part_off(int row, int chunk) {
-    return (unsigned)(row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4));
 }
 
 // Wait until at most `pending` of this wavefront's vector-memory loads are outstanding, then
@@ -194,7 +197,7 @@ __device__ inline void wait_loads_and_barrier(int pending) {
 // that bf16 stream, w is (w gamma) rounded to bf16, `bias` is c2; every workgroup first merges
 // the group statistics of its 256 rows into mean and 1/sigma (pairwise update of mean and
 // squared deviations), and the epilogue applies the formula above.
-enum { kLnNone = 0, kLnConsume = 1, kLnProduce = 2, kGemmExtras = 3 };  // kGemmExtras: w_rows / k_split below are read
+enum { kLnNone = 0, kLnConsume = 1, kLnProduce = 2, kGemmExtras = 3 };  // kGemmExtras: w_rows below is read
 struct GemmLn {
     const float *c1;        // consume: [N]
     const float *stats_in;  // consume: [groups][M][2] (mean, sum of squared deviations) of 64 features each
@@ -207,11 +210,6 @@ struct GemmLn {
     // w_rows is a multiple of the tile height, so a tile never straddles two matrices.
     int w_rows;
     long long w_stride;     // elements
-    // K split over k_split workgroups per tile (0 or 1: none): workgroup (part, tile) multiplies
-    // columns part * K / k_split .. of a and w and writes its tile of partial part, y_split
-    // elements after the one before (plain epilogue, fp32 output; gemm_split_combine adds them up).
-    int k_split;
-    long long y_split;      // elements
 };
 
 // Sum over the 16 lanes of a DPP row (the lanes that hold one token row of the fp32 tile).
@@ -234,19 +232,9 @@ gemm_bf16_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W,
                  int K, int lda, int tiles_n, int n_tiles, GemmLn ln) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, li = lane & 31;
-    // (the per-image weights and the K split exist only in the kGemmExtras instances: the
-    // other instances pay nothing for them)
-    const int k_split = (LN == kGemmExtras && ln.k_split > 1) ? ln.k_split : 1;
-    const int per_xcd = (n_tiles * k_split + 7) / 8;
-    int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (tile >= n_tiles * k_split) return;  // whole workgroup
-    int k_part = 0, k_len = K;          // which part of K, and the columns this workgroup multiplies
-    if (LN == kGemmExtras) {
-        k_part = tile / n_tiles;
-        tile -= k_part * n_tiles;
-        k_len = K / k_split;
-        Y = (void *)((char *)Y + (size_t)k_part * (size_t)ln.y_split * (OUT_BF16 ? 2 : 4));
-    }
+    const int per_xcd = (n_tiles + 7) / 8;
+    const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (tile >= n_tiles) return;  // whole workgroup
     const int m0 = (tile / tiles_n) * kBM, n0 = (tile % tiles_n) * kBN;
     const int wm = wave >> 2, wn = wave & 3;  // 128-token half, 64-feature quarter
     constexpr int kPartLoads = 4;             // load instructions per part and wavefront
@@ -257,9 +245,9 @@ gemm_bf16_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W,
     const int lrow = lane >> 3;
     // The tile's first rows are 64-bit bases (the same in every lane); the offsets inside the
     // tile, 255 rows at most, fit 32 bits (the launcher bounds lda and K).
-    const char *a_tile = (const char *)(A + (size_t)m0 * lda + (size_t)k_part * k_len);
-    const char *w_tile = (const char *)(W + (size_t)n0 * K + (size_t)k_part * k_len +
-                                        ((LN == kGemmExtras && ln.w_rows) ? (size_t)(m0 / ln.w_rows) * (size_t)ln.w_stride : (size_t)0));
+    // (the per-image weights exist only in the kGemmExtras instances)
+    const char *a_tile = (const char *)(A + (size_t)m0 * lda);
+    const char *w_tile = (const char *)(W + (size_t)n0 * K + ((LN == kGemmExtras && ln.w_rows) ? (size_t)(m0 / ln.w_rows) * (size_t)ln.w_stride : (size_t)0));
     unsigned a_off[kPartLoads], w_off[kPartLoads];  // byte offsets of this lane's 16 bytes, k = 0
 #pragma unroll
     for (int j = 0; j < kPartLoads; ++j) {
@@ -269,7 +257,7 @@ gemm_bf16_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W,
         a_off[j] = 2u * ((unsigned)ar * (unsigned)lda + gchunk * 8);  // rows of a are lda elements apart
         w_off[j] = 2u * ((unsigned)wr * (unsigned)K + gchunk * 8);
     }
-    const int n_b = k_len / kBK, n_parts = 2 * n_b;
+    const int n_b = K / kBK, n_parts = 2 * n_b;
     // part = 2 * block + (0: a, 1: w); it lives in slot part % 5.  Loads j0 .. j1-1 of a part:
     auto issue_loads = [&](int part, int slot, int j0, int j1) __attribute__((always_inline)) {
         unsigned char *base = smem + slot * kGemmPart + wave * 32 * 128;
@@ -589,66 +577,109 @@ static jv_status launch_gemm(const void *a, const void *w, const float *bias, co
     if (st != JV_OK) return st;
     const int tiles_m = (int)((M + kBM - 1) / kBM), tiles_n = (N + kBN - 1) / kBN;
     const int n_tiles = tiles_m * tiles_n;
-    dim3 grid(8 * ((n_tiles * ((LN == kGemmExtras && ln.k_split > 1) ? ln.k_split : 1) + 7) / 8));
+    dim3 grid(8 * ((n_tiles + 7) / 8));
     hipLaunchKernelGGL((gemm_bf16_kernel<EPI, OUT_BF16, LN>), grid, dim3(512), kGemmLds, stream,
                        (const __bf16 *)a, (const __bf16 *)w, bias, residual, y, (int)M, N, K, lda,
                        tiles_n, n_tiles, ln);
     return launch_status("gemm_bf16_kernel");
 }
 
-// Residual product with K split over several workgroups per tile, for launches that would leave
-// most compute units without a tile (fc2 of a ViT-L block on 8 192 tokens: 128 tiles of
-// 256 x 256 for 256 units, each with a K loop of 4096): k_split workgroups per tile multiply a
-// part of K each and write fp32 partial tiles; gemm_split_combine then forms
-//     y = sum of the partials + bias + residual
-// in a fixed order (no atomics: the same bits on every run).
-constexpr int kComputeUnits = 256;  // MI355X
-// k_split for a residual product of M x N x K, or 1: as many parts as fill the chip, at most 4,
-// each a multiple of the K block and at least 1024 long.
-static int gemm_k_split(long long M, int N, int K) {
-    const long long tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
-    int split = 1;
-    while (split < 4 && tiles * split * 2 <= kComputeUnits && K % (2 * split * kBK) == 0 && K / (2 * split) >= 1024) split *= 2;
-    return split;
-}
-// grid (ceil(M * N / 4 / 256)), 256 threads; N % 4 == 0; y may be the residual itself.
-template <bool OUT_BF16>
-__global__ void __launch_bounds__(256)
-gemm_split_combine(const float *__restrict__ parts, long long part_stride, int n_parts,
-                   const float *__restrict__ bias, const void *residual, void *y, long long total4, int N) {
-    const long long i4 = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i4 >= total4) return;
-    const int col = (int)((i4 * 4) % N);
-    f32x4 sum = *(const f32x4 *)(parts + i4 * 4);
-    for (int p = 1; p < n_parts; ++p) sum += *(const f32x4 *)(parts + (size_t)p * part_stride + i4 * 4);
-    if (bias) sum += *(const f32x4 *)(bias + col);
-    if (OUT_BF16) {
-        const u32x2 rr = *(const u32x2 *)((const __bf16 *)residual + i4 * 4);
-        sum[0] += bf16_lo(rr[0]); sum[1] += bf16_hi(rr[0]);
-        sum[2] += bf16_lo(rr[1]); sum[3] += bf16_hi(rr[1]);
-        u32x2 pk = {pack_bf16x2(sum[0], sum[1]), pack_bf16x2(sum[2], sum[3])};
-        *(u32x2 *)((__bf16 *)y + i4 * 4) = pk;
-    } else {
-        sum += *(const f32x4 *)((const float *)residual + i4 * 4);
-        *(f32x4 *)((float *)y + i4 * 4) = sum;
+// Choice of the tile shape and of the K split for one product.  What a launch takes is modelled as
+//     sum over its rounds of (K blocks of 64 * a + e),
+// a round being what fits the chip at once, a between `lo` (one workgroup) and `hi` (every slot
+// taken); a split further pays for the way of its parts through memory.  The figures (microseconds)
+// are fitted so that the choice loses least against the best of all shapes and splits over 1 400
+// measured launches (200 to 16 384 rows, widths 768, 1024, 1280 and the four products of a block,
+// operands not in the L2; the choice is 0.5 % off the best on average), so a row says when to take
+// a shape rather than what it takes.  The tendency behind them: a 64-deep block costs about 0.22,
+// 0.33, 0.35, 0.56 and 1.15 us on 64 x 64, 64 x 128, 128 x 128, 256 x 128 and 256 x 256 tiles when
+// a workgroup is alone, i.e. the larger the tile the nearer to the matrix rate; with the chip full
+// the clock falls and all of them meet at about 1.1 PFLOP/s.  So: the largest tile that fills the
+// chip, below that the smallest that leaves no unit with two tiles while others have one.
+struct TileModel {
+    int bm, bn, slots;    // slots: workgroups that fit the chip
+    float lo, hi, e;
+};
+constexpr TileModel kTileModels[kGemmTileShapes] = {
+    {256, 256, 256, 0.611f, 1.182f, 0.44f},   // kTile256x256
+    {256, 128, 256, 0.367f, 0.670f, 1.35f},   // kTile256x128
+    {128, 128, 256, 0.444f, 0.455f, 0.37f},   // kTile128x128Deep
+    {128, 128, 512, 0.554f, 0.702f, 0.40f},   // kTile128x128
+    {64, 128, 512, 0.283f, 0.620f, 0.21f},    // kTile64x128
+    {64, 64, 512, 0.212f, 0.518f, 0.24f},     // kTile64x64
+};
+struct GemmPlan {
+    GemmTile tile;
+    int k_split;
+};
+// max_split: most workgroups that may share a tile's K loop.  parts > 1: K has to be summed in that
+// many parts, by a split or (gemm_residual_parts) inside one workgroup.
+static GemmPlan plan_gemm(long long M, int N, int K, int max_split, int parts = 1) {
+    GemmPlan best = {kTile256x256, 1};
+    float best_t = 1e30f;
+    for (int c = 0; c < kGemmTileShapes; ++c) {
+        const TileModel &m = kTileModels[c];
+        const long long tiles = ((M + m.bm - 1) / m.bm) * ((N + m.bn - 1) / m.bn);
+        for (int split = 1; split <= max_split; split *= 2) {
+            if (split > 1 && (c == kTile256x256 || K / 64 < 2 * split)) break;
+            if (parts > 1 && split != parts && !(split == 1 && (c == kTile256x128 || c == kTile128x128Deep || c == kTile64x128))) continue;
+            const long long n = tiles * split, rounds = n / m.slots, rest = n % m.slots;
+            const float blocks = (float)((K / 64 + split - 1) / split);
+            float t = (float)rounds * (blocks * m.hi + m.e);
+            if (rest) t += blocks * (m.lo + (m.hi - m.lo) * (float)rest / (float)m.slots) + m.e;
+            if (split > 1) t += 0.1f + (float)M * (float)N * 1.0e-6f * (0.107f + 1.133f * (float)split);
+            if (t < best_t) {
+                best_t = t;
+                best = {(GemmTile)c, split};
+            }
+        }
     }
+    return best;
 }
-// y = a w^T + bias + residual with K split k_split ways; parts: k_split * M * N floats of scratch.
-static jv_status gemm_residual_split(const void *a, const void *w, const float *bias, const void *residual,
-                                     void *y, long long M, int N, int K, bool out_bf16, int k_split,
-                                     float *parts, hipStream_t stream) {
-    GemmLn ex{};
-    ex.k_split = k_split;
-    ex.y_split = M * N;
-    jv_status st = launch_gemm<JV_EPI_NONE, false, kGemmExtras>(a, w, nullptr, nullptr, parts, M, N, K, K, stream, ex);
-    if (st != JV_OK) return st;
-    const long long total4 = M * N / 4;
-    const dim3 grid((unsigned)((total4 + 255) / 256));
-    if (out_bf16)
-        hipLaunchKernelGGL(gemm_split_combine<true>, grid, dim3(256), 0, stream, parts, M * N, k_split, bias, residual, y, total4, N);
-    else
-        hipLaunchKernelGGL(gemm_split_combine<false>, grid, dim3(256), 0, stream, parts, M * N, k_split, bias, residual, y, total4, N);
-    return launch_status("gemm_split_combine");
+
+// Residual product with K split over several workgroups per tile, for launches that would leave
+// most compute units without a tile: the parts are fp32 sums, and this pass forms
+//     y = sum of the parts + bias + residual
+// in a fixed order (no atomics: the same bits on every run).  The LayerNorm that follows in the
+// block (`narrow` != null) is taken from the row while it is in registers: a pass over the stream
+// and a launch less.  One wavefront per row, grid (ceil(rows / 4)), 256 threads; y may be the
+// residual itself.
+template <bool BF16, int NV>  // BF16: element type of the residual and of y
+__global__ void __launch_bounds__(256)
+split_combine_kernel(const float *__restrict__ parts, long long part_stride, int n_parts, const float *__restrict__ bias,
+                     const void *residual, void *y, const float *gamma, const float *beta, __bf16 *narrow,
+                     long long rows, int cols, float eps) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const long long row = (long long)blockIdx.x * 4 + wave;
+    if (row >= rows) return;
+    const size_t at = (size_t)row * cols;
+    f32x4 v[NV], res[NV];
+    RowAffine<NV> aff;
+#pragma unroll
+    for (int p = 0; p < NV; ++p) {
+        const int c = min(4 * (lane + 64 * p), cols - 4);  // (lanes past the row re-read its end; dropped below)
+        v[p] = *(const f32x4 *)(parts + at + c);
+        res[p] = load_piece<BF16>(residual, at + c);
+    }
+    for (int q = 1; q < n_parts; ++q)
+#pragma unroll
+        for (int p = 0; p < NV; ++p) v[p] += *(const f32x4 *)(parts + (size_t)q * part_stride + at + min(4 * (lane + 64 * p), cols - 4));
+    if (narrow) aff.fetch(gamma, beta, cols, lane);
+#pragma unroll
+    for (int p = 0; p < NV; ++p) {
+        const int c = 4 * (lane + 64 * p);
+        if (c < cols) {
+            if (bias) v[p] += *(const f32x4 *)(bias + c);
+            v[p] += res[p];
+            store_piece<BF16>(y, at + c, v[p]);
+            if (BF16)  // the LayerNorm reads the stream as stored
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[p][e] = (float)(__bf16)v[p][e];
+        } else {
+            v[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    if (narrow) normalize_row<true, NV>(v, aff, narrow, at, cols, lane, eps);
 }
 
 // Shape limits of the GEMM (no pointers): what jv_gemm_bias_act documents.  The kernel addresses
@@ -678,6 +709,9 @@ jv_status gemm_forward(const void *a, const void *w, const float *bias, const vo
         return fail(JV_ERR_INVALID_ARG, "pointers must be 16-byte aligned");
     if (epi == JV_EPI_RESIDUAL && !residual)
         return fail(JV_ERR_INVALID_ARG, "residual epilogue needs a residual tensor");
+    const GemmPlan plan = plan_gemm(M, N, K, 1);
+    if (plan.tile != kTile256x256)
+        return gemm_tiles_forward(plan.tile, 1, 0, a, w, bias, residual, y, (int)M, N, K, lda, epi, out_bf16, stream);
     switch (epi) {
         case JV_EPI_NONE:
             return out_bf16 ? launch_gemm<JV_EPI_NONE, true>(a, w, bias, residual, y, M, N, K, lda, stream)
@@ -693,6 +727,40 @@ jv_status gemm_forward(const void *a, const void *w, const float *bias, const vo
                             : launch_gemm<JV_EPI_SILU, false>(a, w, bias, residual, y, M, N, K, lda, stream);
     }
     return fail(JV_ERR_INVALID_ARG, "unknown epilogue");
+}
+
+// Parts that K of fc2 is summed in: as many as give every compute unit a 256 x 256 tile, at most
+// 4, each a multiple of the K block and at least 1024 long.  The scratch of the split residual
+// products is sized by it.
+static int split_parts_room(long long M, int N, int K) {
+    const long long tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
+    int split = 1;
+    while (split < 4 && tiles * split * 2 <= kComputeUnits && K % (2 * split * kBK) == 0 && K / (2 * split) >= 1024) split *= 2;
+    return split;
+}
+// y = a w^T + bias + residual and, where gamma is given, narrow = bf16(LayerNorm(y)).  parts:
+// room * M * N floats of scratch (room 1: none).  `ordered`: K is summed in `room` parts, no more
+// and no fewer.
+static jv_status gemm_residual_layernorm(const void *a, const void *w, const float *bias, const void *residual, void *y,
+                                         long long M, int N, int K, bool stream_bf16, const float *gamma, const float *beta,
+                                         __bf16 *narrow, float eps, int room, bool ordered, float *parts, hipStream_t stream) {
+    jv_status st;
+    const GemmPlan plan = plan_gemm(M, N, K, room, ordered ? room : 1);
+    if (plan.k_split == 1) {
+        if (ordered && room > 1) st = gemm_residual_parts(plan.tile, room, a, w, bias, residual, y, (int)M, N, K, stream_bf16, stream);
+        else st = gemm_forward(a, w, bias, residual, y, M, N, K, JV_EPI_RESIDUAL, stream_bf16, stream);
+        if (st != JV_OK) return st;
+        return gamma ? layernorm_forward(y, gamma, beta, narrow, M, N, eps, stream_bf16, true, stream) : JV_OK;
+    }
+    st = gemm_tiles_forward(plan.tile, plan.k_split, M * N, a, w, nullptr, nullptr, parts, (int)M, N, K, K, JV_EPI_NONE, false, stream);
+    if (st != JV_OK) return st;
+    with_row_pieces(N, [&](auto nv_tag) {
+        constexpr int NV = decltype(nv_tag)::value;
+        auto kernel = stream_bf16 ? split_combine_kernel<true, NV> : split_combine_kernel<false, NV>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, stream, parts, M * N, plan.k_split, bias, residual, y,
+                           gamma, beta, gamma ? narrow : nullptr, M, N, eps);
+    });
+    return launch_status("split_combine_kernel");
 }
 
 // The two GEMM forms of the folded LayerNorm (encoder only; shapes checked by the caller).
@@ -1015,8 +1083,8 @@ jv_status jv_encoder_fold_layernorm(jv_encoder *enc, void *buffer, size_t buffer
 // folded LayerNorms also a second [T, width] bf16 buffer and the row statistics
 // [T, width / 64, 2] fp32; with fused linear-attention projections the summed states
 // [batch * heads][64 * 64 + 64] fp32 and the per-image weights [batch][width][width] bf16; for
-// small token counts (fc2 with fewer than 128 output tiles) the fp32 partial results of its
-// K split, [parts][T, width].
+// small token counts (fc2 with fewer than 128 output tiles of 256 x 256) the fp32 partial results
+// of a K split, [parts][T, width].
 size_t jv_encoder_workspace_bytes(const jv_encoder *enc, int32_t batch, int32_t grid_h,
                                   int32_t grid_w) {
     jv::clear_error();
@@ -1028,8 +1096,8 @@ size_t jv_encoder_workspace_bytes(const jv_encoder *enc, int32_t batch, int32_t 
     const size_t fuse = jv::encoder_any_block_fuses(enc, N)
                             ? jv::align256((size_t)batch * enc->cfg.heads * jv::kStateFloats * 4) + jv::align256((size_t)batch * C * C * 2)
                             : 0;
-    const int k_split = enc->folded ? 1 : jv::gemm_k_split((long long)T, (int)C, enc->cfg.mlp_hidden);
-    const size_t split = k_split > 1 ? jv::align256((size_t)k_split * T * C * 4) : 0;
+    const int room = enc->folded || C > 8192 ? 1 : jv::split_parts_room((long long)T, (int)C, enc->cfg.mlp_hidden);
+    const size_t split = room > 1 ? jv::align256((size_t)room * T * C * 4) : 0;
     return jv::align256(T * C * 2) + jv::align256(T * wide * 2) +
            jv::align256(jv::encoder_linear_workspace(enc, batch, N)) + fold + fuse + split;
 }
@@ -1088,11 +1156,12 @@ jv_status jv_encoder_forward_taps(const jv_encoder *enc, const void *x, void *y,
                                (fold ? jv::align256(T * C * 2) + jv::align256(T * (C / 64) * 8) : 0);
     float *la_states = (float *)fuse_base;
     __bf16 *w_fold = (__bf16 *)(fuse_base + jv::align256((size_t)batch * c.heads * jv::kStateFloats * 4));
-    // K split of fc2 when its tiles would leave most compute units idle (gemm_residual_split)
-    const int fc2_split = fold ? 1 : jv::gemm_k_split(T, C, c.mlp_hidden);
-    float *fc2_parts = (float *)(fuse_base + (jv::encoder_any_block_fuses(enc, N)
+    // scratch for the K split of the residual products (gemm_residual_layernorm)
+    const int room = fold || C > 8192 ? 1 : jv::split_parts_room(T, C, c.mlp_hidden);
+    float *parts = (float *)(fuse_base + (jv::encoder_any_block_fuses(enc, N)
                                                   ? jv::align256((size_t)batch * c.heads * jv::kStateFloats * 4) + jv::align256((size_t)batch * C * C * 2)
                                                   : 0));
+    bool ln1_done = false;    // the previous block's last product has left this block's LayerNorm 1 in `narrow`
     bool ln1_folded = false;  // the previous block's last product has left rows and statistics for LayerNorm 1
 
     // Q, K, V as strided views of the [B, N, 3, heads, 64] projection output; O as [B, N, heads, 64].
@@ -1108,6 +1177,9 @@ jv_status jv_encoder_forward_taps(const jv_encoder *enc, const void *x, void *y,
 
     jv_status st;
     const bool s16 = c.stream_dtype == JV_BF16;  // element type of the residual stream
+    // A bf16 stream is rounded 48 times in 24 blocks, and whatever moves a sum's last bit moves
+    // some of those roundings: its products keep one order of summation, K of fc2 in `room` parts
+    // and K of the projection in one, whatever tiles the plan takes.
     const void *resid = x;  // the first residual add reads the input and writes y
     int next_tap = 0;
     for (int l = 0; l < c.n_blocks; ++l) {
@@ -1118,7 +1190,7 @@ jv_status jv_encoder_forward_taps(const jv_encoder *enc, const void *x, void *y,
                                      (const float *)(fw + fl.c2qkv), row_stats, c.ln_eps, widebuf, T, 3 * C, C, false, stream);
             if (st != JV_OK) return st;
         } else {
-            if ((st = jv::layernorm_forward(resid, b.ln1_g, b.ln1_b, narrow, T, C, c.ln_eps, s16, true, stream)) != JV_OK) return st;
+            if (!ln1_done && (st = jv::layernorm_forward(resid, b.ln1_g, b.ln1_b, narrow, T, C, c.ln_eps, s16, true, stream)) != JV_OK) return st;
             if ((st = jv::gemm_forward(narrow, b.w_qkv, b.b_qkv, nullptr, widebuf, T, 3 * C, C, JV_EPI_NONE, true, stream)) != JV_OK) return st;
         }
         const bool fused = jv::encoder_block_fuses(enc, l, N);
@@ -1146,11 +1218,11 @@ jv_status jv_encoder_forward_taps(const jv_encoder *enc, const void *x, void *y,
                 per_image.w_stride = (long long)C * C;
                 st = s16 ? jv::launch_gemm<JV_EPI_RESIDUAL, true, jv::kGemmExtras>(narrow, w_fold, b.b_o, resid, y, T, C, C, C, stream, per_image)
                          : jv::launch_gemm<JV_EPI_RESIDUAL, false, jv::kGemmExtras>(narrow, w_fold, b.b_o, resid, y, T, C, C, C, stream, per_image);
-            } else {
-                st = jv::gemm_forward(narrow, b.w_o, b.b_o, resid, y, T, C, C, JV_EPI_RESIDUAL, s16, stream);
+                if (st == JV_OK) st = jv::layernorm_forward(y, b.ln2_g, b.ln2_b, narrow, T, C, c.ln_eps, s16, true, stream);
+            } else {  // (its input rows become its LayerNorm's output rows: the product has read them all by then)
+                st = jv::gemm_residual_layernorm(narrow, b.w_o, b.b_o, resid, y, T, C, C, s16, b.ln2_g, b.ln2_b, narrow, c.ln_eps, s16 ? 1 : room, s16, parts, stream);
             }
             if (st != JV_OK) return st;
-            if ((st = jv::layernorm_forward(y, b.ln2_g, b.ln2_b, narrow, T, C, c.ln_eps, s16, true, stream)) != JV_OK) return st;
             if ((st = jv::gemm_forward(narrow, b.w_fc1, b.b_fc1, nullptr, widebuf, T, c.mlp_hidden, C, JV_EPI_GELU, true, stream)) != JV_OK) return st;
         }
         // A tapped block leaves its result in the tap buffer and the next block picks the stream
@@ -1160,10 +1232,12 @@ jv_status jv_encoder_forward_taps(const jv_encoder *enc, const void *x, void *y,
         ln1_folded = fold && l + 1 < c.n_blocks;
         if (ln1_folded) {  // (the bf16 rows go where the next block's LayerNorm 1 would have written)
             if ((st = jv::gemm_ln_produce(widebuf, b.w_fc2, b.b_fc2, y, out, T, C, c.mlp_hidden, s16, narrow, row_stats, stream)) != JV_OK) return st;
-        } else if (fc2_split > 1) {
-            if ((st = jv::gemm_residual_split(widebuf, b.w_fc2, b.b_fc2, y, out, T, C, c.mlp_hidden, s16, fc2_split, fc2_parts, stream)) != JV_OK) return st;
         } else {
-            if ((st = jv::gemm_forward(widebuf, b.w_fc2, b.b_fc2, y, out, T, C, c.mlp_hidden, JV_EPI_RESIDUAL, s16, stream)) != JV_OK) return st;
+            const bool more = !fold && l + 1 < c.n_blocks;
+            const float *g1 = more ? enc->blocks[l + 1].ln1_g : nullptr, *b1 = more ? enc->blocks[l + 1].ln1_b : nullptr;
+            st = jv::gemm_residual_layernorm(widebuf, b.w_fc2, b.b_fc2, y, out, T, C, c.mlp_hidden, s16, g1, b1, narrow, c.ln_eps, room, s16, parts, stream);
+            if (st != JV_OK) return st;
+            ln1_done = more;
         }
         if (tapped && out == y) {
             hipError_t e = hipMemcpyAsync(tap_out[next_tap], y, (size_t)T * C * (s16 ? 2 : 4), hipMemcpyDeviceToDevice, stream);

@@ -72,6 +72,41 @@ def test_gemm_epilogues(M, N, K):
     check(err_bf16(to_host(y32), plain / (1.0 + np.exp(-plain))), 1e-4)
 
 
+@pytest.mark.parametrize("M,N,K", [
+    (37, 72, 64),        # 64 x 64 tiles, fewer blocks of K than the operand ring holds
+    (600, 1032, 192),    # 64 x 64, a last tile of eight features
+    (1230, 1032, 192),   # 64 x 128
+    (2390, 1000, 1024),  # 128 x 128, deep ring
+    (3000, 2056, 64),    # 128 x 128, two workgroups per compute unit, one block of K
+    (1700, 4104, 1024),  # the same with sixteen
+    (980, 4104, 1024),   # 256 x 128
+])
+def test_gemm_tile_shapes(M, N, K):
+    """One ragged product per tile shape, against fp32 products of the same bf16 values; the order of
+    summation is that of the largest tiles, so a batch of the same rows gives the same bits."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    a = torch.randn(M, K, generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn(N, K, generator=g, device="cuda") / K ** 0.5).to(torch.bfloat16)
+    bias = torch.randn(N, generator=g, device="cuda")
+    plain = a.float() @ w.float().t() + bias
+    y = torch.full((M + 2, N), 768.0, device="cuda")    # guard rows around the result
+    binding.jv_gemm_bias_act(a, w, bias, None, y[1:M + 1], binding.JV_EPI_NONE)
+    check(err_bf16(to_host(y[1:M + 1]), to_host(plain)), 1e-4)   # fp32 sums of up to 1 024 terms
+    assert float(y[0].min()) == 768.0 and float(y[M + 1].max()) == 768.0
+    h = torch.full((M, N), float("nan"), device="cuda", dtype=torch.bfloat16)
+    binding.jv_gemm_bias_act(a, w, bias, None, h, binding.JV_EPI_GELU)
+    check(err_bf16_stored(to_host(h.float()), to_host(torch.nn.functional.gelu(plain))), 2e-4)
+    rep = -(-20000 // M)
+    big = torch.empty(rep * M, N, device="cuda")
+    binding.jv_gemm_bias_act(a.repeat(rep, 1), w, bias, None, big, binding.JV_EPI_NONE)
+    assert torch.equal(big[:M], y[1:M + 1])
+    res = torch.randn(M, N, generator=g, device="cuda")
+    z = torch.empty_like(res)
+    binding.jv_gemm_bias_act(a, w, bias, res, z, binding.JV_EPI_RESIDUAL)
+    assert torch.equal(z, y[1:M + 1] + res)
+
+
 def test_gemm_rows_beyond_32_bit_offsets_and_rerun_bits():
     """A above 2^30 elements (270 336 rows of 4096: the fc2 shape of a 256 x 256 grid at batch 4):
     row tiles are addressed from 64-bit bases.  A is one 4096-row block repeated, so every block
