@@ -2,7 +2,9 @@
 // descriptor and calls the C entry points of libjetvit.so.  What binding.py did through ctypes
 // structures took 7 to 10 us of host time per call, as long as the kernels of a small problem
 // (256 tokens x 6 heads: 13.2 us a call, host-bound, against 11 us of kernels); here it is below 1 us.
-// Every function returns the entry point's status; binding.py turns it into an exception.
+// Every function returns the entry point's status; binding.py turns it into an exception.  The
+// interpreter lock is released around the entry points, as ctypes does, so that a launch that waits
+// for room in the queue holds up no other thread.
 #include <Python.h>
 
 #include <ATen/hip/impl/HIPStreamMasqueradingAsCUDA.h>
@@ -122,6 +124,16 @@ bool mixer_args(PyObject *const *args, PyObject *stream, Call *c) {
     return stream_arg(stream, &c->stream);
 }
 
+// f() without the interpreter lock.
+template <typename F>
+jv_status unlocked(F f) {
+    jv_status st;
+    Py_BEGIN_ALLOW_THREADS
+    st = f();
+    Py_END_ALLOW_THREADS
+    return st;
+}
+
 bool arg_count(Py_ssize_t n, Py_ssize_t want) {
     if (n == want) return true;
     PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
@@ -144,7 +156,7 @@ PyObject *linear_attn_fwd(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (!arg_count(n, 8) || !mixer_args(a, a[7], &c)) return nullptr;
     const double eps = PyFloat_AsDouble(a[5]);
     if ((eps == -1.0 && PyErr_Occurred()) || !workspace_arg(a[6], &ws, &bytes)) return nullptr;
-    return PyLong_FromLong(jv_linear_attn_fwd(&c.desc, c.q, c.k, c.v, c.o, (float)eps, ws, bytes, c.stream));
+    return PyLong_FromLong(unlocked([&] { return jv_linear_attn_fwd(&c.desc, c.q, c.k, c.v, c.o, (float)eps, ws, bytes, c.stream); }));
 }
 
 // One fp32 device tensor of the convolution's parameters.
@@ -183,7 +195,12 @@ bool dwc_args(PyObject *kernel, PyObject *squeeze, PyObject *ksize, PyObject *to
     if (!ok) PyErr_SetString(PyExc_ValueError, "generator weights must be (w1, b1, w2, b2)");
     const float **dst[4] = {&p->w1, &p->b1, &p->w2, &p->b2};
     int64_t hidden = 0;
-    for (int i = 0; ok && i < 4; ++i) ok = param_arg(PySequence_Fast_GET_ITEM(fast, i), dst[i], i == 0 ? &hidden : nullptr);
+    try {
+        for (int i = 0; ok && i < 4; ++i) ok = param_arg(PySequence_Fast_GET_ITEM(fast, i), dst[i], i == 0 ? &hidden : nullptr);
+    } catch (...) {
+        Py_DECREF(fast);
+        throw;
+    }
     p->hidden = (int32_t)hidden;
     Py_DECREF(fast);
     return ok;
@@ -200,9 +217,10 @@ PyObject *linear_block_fwd(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (eps == -1.0 && PyErr_Occurred()) return nullptr;
     const long focus = PyLong_AsLong(a[10]);
     if ((focus == -1 && PyErr_Occurred()) || !workspace_arg(a[11], &ws, &bytes)) return nullptr;
-    const jv_status st = focus == 0 ? jv_linear_block_fwd(&c.desc, c.q, c.k, c.v, c.o, (float)eps, &dwc, ws, bytes, c.stream)
-                                    : jv_linear_block_focused_fwd(&c.desc, c.q, c.k, c.v, c.o, (float)eps, (int32_t)focus, &dwc, ws, bytes, c.stream);
-    return PyLong_FromLong(st);
+    return PyLong_FromLong(unlocked([&] {
+        return focus == 0 ? jv_linear_block_fwd(&c.desc, c.q, c.k, c.v, c.o, (float)eps, &dwc, ws, bytes, c.stream)
+                          : jv_linear_block_focused_fwd(&c.desc, c.q, c.k, c.v, c.o, (float)eps, (int32_t)focus, &dwc, ws, bytes, c.stream);
+    }));
 }
 
 // (q, k, v, o, grid, window, scale, stream)
@@ -212,7 +230,7 @@ PyObject *window_attn_fwd(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (!arg_count(n, 8) || !mixer_args(a, a[7], &c) || !pair_arg(a[5], &wh, &ww)) return nullptr;
     const double scale = PyFloat_AsDouble(a[6]);
     if (scale == -1.0 && PyErr_Occurred()) return nullptr;
-    return PyLong_FromLong(jv_window_attn_fwd(&c.desc, c.q, c.k, c.v, c.o, wh, ww, (float)scale, c.stream));
+    return PyLong_FromLong(unlocked([&] { return jv_window_attn_fwd(&c.desc, c.q, c.k, c.v, c.o, wh, ww, (float)scale, c.stream); }));
 }
 
 // (q, k, v, o, grid, scale, stream)
@@ -221,14 +239,28 @@ PyObject *full_attn_fwd(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (!arg_count(n, 7) || !mixer_args(a, a[6], &c)) return nullptr;
     const double scale = PyFloat_AsDouble(a[5]);
     if (scale == -1.0 && PyErr_Occurred()) return nullptr;
-    return PyLong_FromLong(jv_full_attn_fwd(&c.desc, c.q, c.k, c.v, c.o, (float)scale, c.stream));
+    return PyLong_FromLong(unlocked([&] { return jv_full_attn_fwd(&c.desc, c.q, c.k, c.v, c.o, (float)scale, c.stream); }));
+}
+
+// Tensors without memory of their own (under tracing or vmap) throw where their pointer or strides
+// are asked for: a Python exception, not the end of the process.
+template <PyObject *(*F)(PyObject *, PyObject *const *, Py_ssize_t)>
+PyObject *guarded(PyObject *self, PyObject *const *a, Py_ssize_t n) {
+    try {
+        return F(self, a, n);
+    } catch (const c10::Error &e) {
+        if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
+    } catch (const std::exception &e) {
+        if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what());
+    }
+    return nullptr;
 }
 
 PyMethodDef methods[] = {
-    {"linear_attn_fwd", (PyCFunction)(void *)linear_attn_fwd, METH_FASTCALL, nullptr},
-    {"linear_block_fwd", (PyCFunction)(void *)linear_block_fwd, METH_FASTCALL, nullptr},
-    {"window_attn_fwd", (PyCFunction)(void *)window_attn_fwd, METH_FASTCALL, nullptr},
-    {"full_attn_fwd", (PyCFunction)(void *)full_attn_fwd, METH_FASTCALL, nullptr},
+    {"linear_attn_fwd", (PyCFunction)(void *)guarded<linear_attn_fwd>, METH_FASTCALL, nullptr},
+    {"linear_block_fwd", (PyCFunction)(void *)guarded<linear_block_fwd>, METH_FASTCALL, nullptr},
+    {"window_attn_fwd", (PyCFunction)(void *)guarded<window_attn_fwd>, METH_FASTCALL, nullptr},
+    {"full_attn_fwd", (PyCFunction)(void *)guarded<full_attn_fwd>, METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -207,3 +207,16 @@ def test_encoder_workspace_query_follows_the_options():
     enc.fuse_linear_projection(False)
     assert enc.workspace_bytes(4, (18, 18)) == with_option
     enc.close()
+
+
+def test_native_marshalling_turns_c_plus_plus_exceptions_into_python_ones():
+    """A traced tensor has no memory, and without a device torch throws where the current stream is
+    asked for: both must reach Python as an error of the call."""
+    import torch
+    from torch._subclasses.fake_tensor import FakeTensorMode
+    with FakeTensorMode():
+        t = [torch.empty(1, 2, 16, 64, device="cuda") for _ in range(4)]
+    with pytest.raises(RuntimeError):
+        binding.jv_full_attn_fwd(*t, (4, 4))
+    with pytest.raises(RuntimeError):
+        binding.jv_window_attn_fwd(*t, (4, 4), (2, 2))
