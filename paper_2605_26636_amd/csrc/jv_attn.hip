@@ -114,6 +114,7 @@ attn_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, i
         for (int i = 0; i < 2 * KW; ++i) {
             const int r = (srow + 16 * i) & 31;
             unsigned char *tile = tiles + (i >> 1) * kF32Tile + r * 256;
+            if (breg[i] != 0.f) kreg[i] = vreg[i] = f32x4{0.f, 0.f, 0.f, 0.f};  // 0 x inf of a padded key's row would be NaN
             *(f32x4 *)(tile + ((chunk ^ (r & 15)) << 4)) = kreg[i];
             *(f32x4 *)(tile + kF32Tile / 2 + ((chunk ^ ((r & 4) << 1)) << 4)) = vreg[i];
             if (chunk == 0) bias[srow + 16 * i] = breg[i];

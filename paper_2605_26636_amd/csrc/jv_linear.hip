@@ -235,12 +235,12 @@ la_apply_f32(TensorArg qt, TensorArg ot, const float *__restrict__ ws, int heads
 #pragma unroll
             for (int dp = 0; dp < 4; ++dp) {
                 const float *part = src + (size_t)min(p0 + dp, n_split - 1) * BH * kStateFloats;
-                const float w = p0 + dp < n_split ? 1.f : 0.f;
+                const bool live = p0 + dp < n_split;
 #pragma unroll
                 for (int i = 0; i < 5; ++i) {
                     const f32x4 x = *(const f32x4 *)(part + 4 * min(tid + 256 * i, kStateFloats / 4 - 1));
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) s[i][e] = fmaf(w, x[e], s[i][e]);
+                    for (int e = 0; e < 4; ++e) s[i][e] += live ? x[e] : 0.f;
                 }
             }
         }

@@ -149,3 +149,26 @@ def test_padding_never_reaches_the_output():
     o = torch.empty(B, heads, N, 64, device="cuda")
     binding.jv_window_attn_fwd(*views, o, (H, W), (4, 4))
     check(err_fp32(to_host(o), oracle.window_attn(q, k, v, H, W, 4, 4)), FP32_TOL)
+
+def test_padding_takes_no_part_where_values_are_infinite():
+    # padded keys stand in for the window's first token, absent partial states for the last one:
+    # an infinity there stays what the sums make of it (0 x inf would turn it into NaN)
+    H = W = 6
+    q, k, v = (torch.rand(1, 1, H * W, 64, device="cuda") + 0.1 for _ in range(3))
+    v[..., 0, 5] = v[..., 4, 7] = float("inf")       # first tokens of the windows at (0, 0) and (0, 4)
+    o = torch.empty_like(q)
+    binding.jv_window_attn_fwd(q, k, v, o, (H, W), (4, 4))
+    first = torch.zeros(H, W, dtype=torch.bool, device="cuda")
+    second = first.clone()
+    first[:4, :4] = True
+    second[:4, 4:] = True
+    assert torch.equal(torch.isinf(o[0, 0, :, 5]), first.flatten())
+    assert torch.equal(torch.isinf(o[0, 0, :, 7]), second.flatten())
+    assert not torch.isnan(o).any()
+    N = 190                                            # three partial states, summed four at a time
+    q, k, v = (torch.rand(1, 1, N, 64, device="cuda") + 0.1 for _ in range(3))
+    v[..., N - 1, 5] = float("inf")
+    o = torch.empty_like(q)
+    binding.jv_linear_attn_fwd(q, k, v, o, (1, N))
+    assert torch.isinf(o[..., 5]).all() and not torch.isnan(o).any()
+    assert torch.isfinite(o[..., 6:]).all()
