@@ -23,20 +23,21 @@ namespace jv {
 // that many gives, without the parts' way through memory (and the idle units of an unsplit launch).
 // grid (8 * ceil(tiles * k_split / 8)), 64 WM WN threads.
 // ---------------------------------------------------------------------------------------
-template <int WM, int WN, int MT, int BK, int STAGES, int EPI>
+constexpr int kBlockK = 64;
+
+template <int WM, int WN, int MT, int STAGES, int EPI>
 struct TileShape {
     static constexpr int kWaves = WM * WN, kThreads = 64 * kWaves;
     static constexpr int kBM = 32 * MT * WM, kBN = 64 * WN;
-    static constexpr int kRow = 2 * BK, kRowsPerLoad = 1024 / kRow;  // bytes of a row in LDS; rows of a 1 KB load instruction
+    static constexpr int kRow = 2 * kBlockK, kRowsPerLoad = 1024 / kRow;  // bytes of a row in LDS; rows of a 1 KB load instruction
     static constexpr int kPartA = kBM * kRow, kPartW = kBN * kRow, kStage = kPartA + kPartW;
     static constexpr int kLoadsA = kBM / kRowsPerLoad / kWaves, kLoadsW = kBN / kRowsPerLoad / kWaves;  // per wavefront
     static constexpr int kTable = EPI == JV_EPI_GELU ? (kPhiSteps + 2) * 4 : 0;
     static constexpr int kRing = STAGES * kStage > kWaves * 8192 ? STAGES * kStage : kWaves * 8192;
     static constexpr int kLds = kRing + kTable;
-    static_assert(BK == 64 || BK == 32, "rows of 128 or 64 bytes");
     static_assert(kBM % (kRowsPerLoad * kWaves) == 0 && kBN % (kRowsPerLoad * kWaves) == 0, "whole load instructions per wavefront");
     // Rotation of a row's 16-byte chunks: 16 consecutive rows spread over all 64 banks.
-    static __device__ int rotation(int row) { return BK == 64 ? (row >> 1) & 7 : (row >> 2) & 3; }
+    static __device__ int rotation(int row) { return (row >> 1) & 7; }
     static __device__ unsigned offset(int row, int chunk) { return (unsigned)(row * kRow + ((chunk ^ rotation(row)) << 4)); }
 };
 
@@ -45,13 +46,13 @@ __device__ inline void wait_vm_and_barrier() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-template <int WM, int WN, int MT, int BK, int STAGES, int EPI, bool OUT_BF16, bool PARTS>
+template <int WM, int WN, int MT, int STAGES, int EPI, bool OUT_BF16, bool PARTS>
 __global__ void __launch_bounds__(64 * WM * WN)
 gemm_tile_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W, const float *__restrict__ bias,
                  const void *residual, void *Y, int M, int N, int K, int lda, int tiles_m, int tiles_n,
                  int tokens_fast, int k_split, long long y_split, int parts) {
 #ifdef __HIP_DEVICE_COMPILE__  // (the host pass does not know the buffer-resource builtins)
-    using S = TileShape<WM, WN, MT, BK, STAGES, EPI>;
+    using S = TileShape<WM, WN, MT, STAGES, EPI>;
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 5, li = lane & 31;
     const int wm = wave / WN, wn = wave % WN;
@@ -65,8 +66,7 @@ gemm_tile_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W, con
     const int tm = tokens_fast ? item % tiles_m : item / tiles_n;
     const int tn = tokens_fast ? item / tiles_m : item % tiles_n;
     const int m0 = tm * S::kBM, n0 = tn * S::kBN;
-    const int all_b = K / 64;  // (parts of K are whole multiples of 64, so that n_b is even for BK 32)
-    const int b0 = all_b * k_part / k_split * (64 / BK), n_b = all_b * (k_part + 1) / k_split * (64 / BK) - b0;
+    const int all_b = K / kBlockK, b0 = all_b * k_part / k_split, n_b = all_b * (k_part + 1) / k_split - b0;
 
     // Global -> LDS: lane = 8 * (row in group of 8) + LDS chunk slot, and it fetches the global
     // chunk that belongs in that slot under the row rotation.  Buffer loads: the tile's first row
@@ -120,7 +120,7 @@ gemm_tile_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W, con
             for (int mt = 0; mt < MT; ++mt) total[nt][PARTS ? mt : 0] = acc[nt][mt];
     // Operands of a step (16 in K), each read two steps before it is used.  The reads are in
     // assembly with counted waits: left to itself the compiler waits for all of them.
-    constexpr int kSteps = BK / 16, kSets = 4, kReads = MT + 2;
+    constexpr int kSteps = kBlockK / 16, kSets = kSteps, kReads = MT + 2;
     static_assert(MT <= 2, "operand reads are written out for one or two token blocks");
     u32x4 aop[kSets][MT], wop[kSets][2];
     unsigned a_addr[kSteps], w_addr[kSteps];  // LDS byte address of this lane's row in slot 0, per step
@@ -167,7 +167,7 @@ gemm_tile_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W, con
     constexpr int kBarStep = kSteps - 2;
     constexpr int kSpread = STAGES > 2 ? kSteps : 2, kPerStep = (kLoads + kSpread - 1) / kSpread;
     int slot = 0;
-    auto block = [&](int p, int set0, auto tail_tag, auto refill_tag, auto next_tag) __attribute__((always_inline)) {
+    auto block = [&](int p, auto tail_tag, auto refill_tag, auto next_tag) __attribute__((always_inline)) {
         constexpr bool tail = decltype(tail_tag)::value, refill = decltype(refill_tag)::value, next = decltype(next_tag)::value;
         if (PARTS && p == part_end) {
             ++part;
@@ -184,7 +184,7 @@ gemm_tile_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W, con
         const int nslot = slot + 1 == STAGES ? 0 : slot + 1, pslot = slot == 0 ? STAGES - 1 : slot - 1;
 #pragma unroll
         for (int s = 0; s < kSteps; ++s) {
-            const int set = (set0 + s) % kSets, rset = (set0 + s + 2) % kSets;
+            const int set = s, rset = (s + 2) % kSets;
             if (s == kBarStep && next) {
                 if (refill) wait_vm_and_barrier<(STAGES - 2) * kLoads>();
                 else landed(min(STAGES - 2, n_b - 2 - p));
@@ -214,31 +214,13 @@ gemm_tile_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W, con
     };
     using T = std::true_type; using F = std::false_type;
     int p = 0;
-    if (BK == 64) {
-        if (n_b > STAGES) {
-            block(0, 0, F(), T(), T());
-            for (p = 1; p + STAGES < n_b; ++p) block(p, 0, T(), T(), T());
-            block(p++, 0, T(), F(), T());
-        }
-        for (; p + 1 < n_b; ++p) block(p, 0, F(), F(), T());
-        block(p, 0, F(), F(), F());
-    } else {  // an even number of blocks; the operand sets take turns
-        for (; p + 1 + STAGES < n_b; p += 2) {
-            block(p, 0, F(), T(), T());
-            block(p + 1, 2, F(), T(), T());
-        }
-        if (STAGES % 2 && p + STAGES < n_b) {
-            block(p, 0, F(), T(), T());
-            block(p + 1, 2, F(), F(), T());
-            p += 2;
-        }
-        for (; p + 2 < n_b; p += 2) {
-            block(p, 0, F(), F(), T());
-            block(p + 1, 2, F(), F(), T());
-        }
-        block(p, 0, F(), F(), T());
-        block(p + 1, 2, F(), F(), F());
+    if (n_b > STAGES) {
+        block(0, F(), T(), T());
+        for (p = 1; p + STAGES < n_b; ++p) block(p, T(), T(), T());
+        block(p++, T(), F(), T());
     }
+    for (; p + 1 < n_b; ++p) block(p, F(), F(), T());
+    block(p, F(), F(), F());
 
     if (PARTS)
 #pragma unroll
@@ -339,11 +321,11 @@ gemm_tile_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W, con
 #endif
 }
 
-template <int WM, int WN, int MT, int BK, int STAGES, int EPI, bool OUT_BF16, bool PARTS = false>
+template <int WM, int WN, int MT, int STAGES, int EPI, bool OUT_BF16, bool PARTS = false>
 static jv_status launch_tiles(int k_split, long long y_split, const void *a, const void *w, const float *bias,
                               const void *residual, void *y, int M, int N, int K, int lda, hipStream_t stream, int parts = 1) {
-    using S = TileShape<WM, WN, MT, BK, STAGES, EPI>;
-    auto kernel = gemm_tile_kernel<WM, WN, MT, BK, STAGES, EPI, OUT_BF16, PARTS>;
+    using S = TileShape<WM, WN, MT, STAGES, EPI>;
+    auto kernel = gemm_tile_kernel<WM, WN, MT, STAGES, EPI, OUT_BF16, PARTS>;
     static LdsLimit lds_limit;
     jv_status st = ensure_lds_limit(lds_limit, (const void *)kernel, S::kLds);
     if (st != JV_OK) return st;
@@ -354,13 +336,13 @@ static jv_status launch_tiles(int k_split, long long y_split, const void *a, con
     return launch_status("gemm_tile_kernel");
 }
 
-template <int WM, int WN, int MT, int BK, int STAGES, typename... Args>
+template <int WM, int WN, int MT, int STAGES, typename... Args>
 static jv_status launch_epilogue(int epi, bool out_bf16, Args... args) {
     switch (epi) {
-        case JV_EPI_NONE: return out_bf16 ? launch_tiles<WM, WN, MT, BK, STAGES, JV_EPI_NONE, true>(args...) : launch_tiles<WM, WN, MT, BK, STAGES, JV_EPI_NONE, false>(args...);
-        case JV_EPI_GELU: return out_bf16 ? launch_tiles<WM, WN, MT, BK, STAGES, JV_EPI_GELU, true>(args...) : launch_tiles<WM, WN, MT, BK, STAGES, JV_EPI_GELU, false>(args...);
-        case JV_EPI_RESIDUAL: return out_bf16 ? launch_tiles<WM, WN, MT, BK, STAGES, JV_EPI_RESIDUAL, true>(args...) : launch_tiles<WM, WN, MT, BK, STAGES, JV_EPI_RESIDUAL, false>(args...);
-        case JV_EPI_SILU: return out_bf16 ? launch_tiles<WM, WN, MT, BK, STAGES, JV_EPI_SILU, true>(args...) : launch_tiles<WM, WN, MT, BK, STAGES, JV_EPI_SILU, false>(args...);
+        case JV_EPI_NONE: return out_bf16 ? launch_tiles<WM, WN, MT, STAGES, JV_EPI_NONE, true>(args...) : launch_tiles<WM, WN, MT, STAGES, JV_EPI_NONE, false>(args...);
+        case JV_EPI_GELU: return out_bf16 ? launch_tiles<WM, WN, MT, STAGES, JV_EPI_GELU, true>(args...) : launch_tiles<WM, WN, MT, STAGES, JV_EPI_GELU, false>(args...);
+        case JV_EPI_RESIDUAL: return out_bf16 ? launch_tiles<WM, WN, MT, STAGES, JV_EPI_RESIDUAL, true>(args...) : launch_tiles<WM, WN, MT, STAGES, JV_EPI_RESIDUAL, false>(args...);
+        case JV_EPI_SILU: return out_bf16 ? launch_tiles<WM, WN, MT, STAGES, JV_EPI_SILU, true>(args...) : launch_tiles<WM, WN, MT, STAGES, JV_EPI_SILU, false>(args...);
     }
     return fail(JV_ERR_INVALID_ARG, "unknown epilogue");
 }
@@ -369,25 +351,25 @@ jv_status gemm_tiles_forward(GemmTile tile, int k_split, long long y_split, cons
                              const float *bias, const void *residual, void *y, int M, int N, int K, int lda,
                              int epi, bool out_bf16, hipStream_t stream) {
     switch (tile) {
-        case kTile256x128: return launch_epilogue<4, 2, 2, 64, 3>(epi, out_bf16, k_split, y_split, a, w, bias, residual, y, M, N, K, lda, stream);
-        case kTile128x128Deep: return launch_epilogue<2, 2, 2, 64, 4>(epi, out_bf16, k_split, y_split, a, w, bias, residual, y, M, N, K, lda, stream);
-        case kTile128x128: return launch_epilogue<2, 2, 2, 64, 2>(epi, out_bf16, k_split, y_split, a, w, bias, residual, y, M, N, K, lda, stream);
-        case kTile64x128: return launch_epilogue<2, 2, 1, 64, 3>(epi, out_bf16, k_split, y_split, a, w, bias, residual, y, M, N, K, lda, stream);
-        case kTile64x64: return launch_epilogue<2, 1, 1, 64, 4>(epi, out_bf16, k_split, y_split, a, w, bias, residual, y, M, N, K, lda, stream);
+        case kTile256x128: return launch_epilogue<4, 2, 2, 3>(epi, out_bf16, k_split, y_split, a, w, bias, residual, y, M, N, K, lda, stream);
+        case kTile128x128Deep: return launch_epilogue<2, 2, 2, 4>(epi, out_bf16, k_split, y_split, a, w, bias, residual, y, M, N, K, lda, stream);
+        case kTile128x128: return launch_epilogue<2, 2, 2, 2>(epi, out_bf16, k_split, y_split, a, w, bias, residual, y, M, N, K, lda, stream);
+        case kTile64x128: return launch_epilogue<2, 2, 1, 3>(epi, out_bf16, k_split, y_split, a, w, bias, residual, y, M, N, K, lda, stream);
+        case kTile64x64: return launch_epilogue<2, 1, 1, 4>(epi, out_bf16, k_split, y_split, a, w, bias, residual, y, M, N, K, lda, stream);
         default: return fail(JV_ERR_INVALID_ARG, "no kernel for this tile shape");
     }
 }
 
-template <int WM, int WN, int MT, int BK, int STAGES, typename... Args>
+template <int WM, int WN, int MT, int STAGES, typename... Args>
 static jv_status launch_parts(bool out_bf16, Args... args) {
-    return out_bf16 ? launch_tiles<WM, WN, MT, BK, STAGES, JV_EPI_RESIDUAL, true, true>(args...) : launch_tiles<WM, WN, MT, BK, STAGES, JV_EPI_RESIDUAL, false, true>(args...);
+    return out_bf16 ? launch_tiles<WM, WN, MT, STAGES, JV_EPI_RESIDUAL, true, true>(args...) : launch_tiles<WM, WN, MT, STAGES, JV_EPI_RESIDUAL, false, true>(args...);
 }
 jv_status gemm_residual_parts(GemmTile tile, int parts, const void *a, const void *w, const float *bias, const void *residual, void *y,
                               int M, int N, int K, bool out_bf16, hipStream_t stream) {
     switch (tile) {
-        case kTile256x128: return launch_parts<4, 2, 2, 64, 3>(out_bf16, 1, 0, a, w, bias, residual, y, M, N, K, K, stream, parts);
-        case kTile128x128Deep: return launch_parts<2, 2, 2, 64, 4>(out_bf16, 1, 0, a, w, bias, residual, y, M, N, K, K, stream, parts);
-        case kTile64x128: return launch_parts<2, 2, 1, 64, 3>(out_bf16, 1, 0, a, w, bias, residual, y, M, N, K, K, stream, parts);
+        case kTile256x128: return launch_parts<4, 2, 2, 3>(out_bf16, 1, 0, a, w, bias, residual, y, M, N, K, K, stream, parts);
+        case kTile128x128Deep: return launch_parts<2, 2, 2, 4>(out_bf16, 1, 0, a, w, bias, residual, y, M, N, K, K, stream, parts);
+        case kTile64x128: return launch_parts<2, 2, 1, 3>(out_bf16, 1, 0, a, w, bias, residual, y, M, N, K, K, stream, parts);
         default: return fail(JV_ERR_INVALID_ARG, "no kernel for this tile shape");
     }
 }
