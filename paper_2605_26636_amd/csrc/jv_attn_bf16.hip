@@ -1751,6 +1751,17 @@ jv_status attn_bf16(const Problem &pr, const WindowGeom &g, float scale, int q_s
     if (fast && !all_queries && a.q_slots <= 64 && g.n_win == 1)
         return pr.o_bf16 ? launch_prefix<true>(a, pr.B * pr.heads, stream)
                          : launch_prefix<false>(a, pr.B * pr.heads, stream);
+    // At most half the compute units with a block of 256 queries: blocks of 128 on the streaming kernel, which are twice
+    // as many (same tiles of 32 keys in the same order: the same bits).  A lone wavefront per SIMD waits for itself
+    // either way, but with half the arithmetic between its waits.  Blocks of 256 / of 128, us: 12 blocks (200 tokens) 9.6 / 8.1,
+    // 48 (784 tokens) 21.2 / 18.8, 96 (1 374 tokens) 33.0 / 30.2, 128 (2 048 tokens) 45.6 / 42.6, but 192 (1 374 tokens)
+    // 33.0 / 38.7: some units get two of the small blocks there and one of the large.
+    const long long blocks = (long long)((a.q_slots + 255) / 256) * g.n_win * a.n_bh;
+    if (fast && NT == 2 && blocks <= 128) {
+        if (pr.o_bf16) hipLaunchKernelGGL((attn_stream_bf16<true, 1>), ring_grid(a, 128), dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((attn_stream_bf16<false, 1>), ring_grid(a, 128), dim3(256), 0, stream, a);
+        return launch_status("attn_stream_bf16");
+    }
     if (fast && NT == 2) {
         if (pr.o_bf16) hipLaunchKernelGGL((attn_ring_bf16<true>), ring_grid(a, 256), dim3(256), 0, stream, a);
         else hipLaunchKernelGGL((attn_ring_bf16<false>), ring_grid(a, 256), dim3(256), 0, stream, a);

@@ -187,3 +187,18 @@ def test_window_attention_token_sweep_sampled_rows(B, H, W):
     ref = oracle.window_attn_rows(q, k, v, H, W, 16, 16, rows)
     check_bf16_pair(_window(q, k, v, H, W, (16, 16), torch.float32), o, ref, rows)
     assert torch.isfinite(o.float()).all()
+
+
+@pytest.mark.parametrize("N", [1, 35, 128, 129, 960, 1080, 1089, 1369])
+def test_blocks_of_128_and_of_256_queries_give_the_same_bits(N):
+    # one image is few enough blocks for the small ones; repeated past 128 blocks of 256 queries it
+    # takes the large ones, and both add the same key tiles in the same order
+    q, k, v = (to_device(x, True) for x in synth.qkv(31, 1, 2, N, 64, 1.0, True))
+    reps = 129 // (2 * ((N + 255) // 256)) + 1
+    for dtype in (torch.float32, torch.bfloat16):
+        small = torch.full(q.shape, float("nan"), dtype=dtype, device="cuda")
+        binding.jv_full_attn_fwd(q, k, v, small, (1, N))
+        Q, K, V = (t.repeat(reps, 1, 1, 1) for t in (q, k, v))
+        large = torch.full(Q.shape, float("nan"), dtype=dtype, device="cuda")
+        binding.jv_full_attn_fwd(Q, K, V, large, (1, N))
+        assert torch.equal(large, small.expand_as(large))
