@@ -310,14 +310,20 @@ la_apply_f32(TensorArg qt, TensorArg ot, const float *__restrict__ ws, int heads
                     acc[cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(sreg[cb][i][e], q[i][e], acc[cb], 0, 0, 0);
             }
         pair_values((den4[0] + den4[1]) + (den4[2] + den4[3]), &lo, &hi);
-        const float inv = 1.0f / ((lo + hi) + eps);
+        // Below 2^-128 (eps 0, small queries and keys) 1 / den overflows where the quotient need not:
+        // small denominators and their numerators first take a factor 2^60.  (32 divisions instead,
+        // 256 tokens x 6 heads: 10.8 against 10.2 us a call.)
+        float den = (lo + hi) + eps;
+        const float up = den < 0x1p-100f ? 0x1p60f : 1.0f;
+        den *= up;
+        const float inv = 1.0f / den;
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
             for (int v4 = 0; v4 < 4; ++v4) {
                 f32x4 out;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) out[e] = acc[cb][4 * v4 + e] * inv;
+                for (int e = 0; e < 4; ++e) out[e] = acc[cb][4 * v4 + e] * up * inv;
                 *(f32x4 *)(mine + li * 256 + (((8 * cb + 2 * v4 + half) ^ (li & 15)) << 4)) = out;
             }
         float *orow = op + (long long)(base + srow) * ot.sn + 4 * chunk;

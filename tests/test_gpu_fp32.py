@@ -172,3 +172,17 @@ def test_padding_takes_no_part_where_values_are_infinite():
     binding.jv_linear_attn_fwd(q, k, v, o, (1, N))
     assert torch.isinf(o[..., 5]).all() and not torch.isnan(o).any()
     assert torch.isfinite(o[..., 6:]).all()
+
+
+def test_linear_denominators_without_a_finite_reciprocal():
+    # eps = 0 and a denominator of 64 * 2^-67 * 2^-67 = 2^-128, whose reciprocal is 2^128 = inf in
+    # fp32; the result is the one live value row, up to the roundings of its sum over 64 equal
+    # channels (63 additions, each within 2^-24 of the sum so far)
+    N = 5
+    q = torch.full((1, 2, N, 64), 2.0 ** -67, device="cuda")
+    k = torch.full_like(q, -1.0)
+    k[:, :, 0] = 2.0 ** -67
+    v = torch.from_numpy(synth.normal((1, 2, N, 64), 19)).cuda() * 2.0 ** 40
+    o = torch.empty_like(q)
+    binding.jv_linear_attn_fwd(q, k, v, o, (1, N), 0.0)
+    check(err_fp32(to_host(o), to_host(v[:, :, :1].expand_as(o))), 64 * 2.0 ** -24)
