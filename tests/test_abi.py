@@ -127,6 +127,20 @@ def test_block_workspace_query_by_convolution_mode():
     assert binding.jv_linear_block_workspace_bytes(d, params(4)) == 0
 
 
+def test_token_wise_workspace_is_the_same_for_both_element_types():
+    def query(dtype, B, heads, H, W, ksize):
+        N = H * W
+        s = binding.JvStrides(heads * N * 64, N * 64, 64)
+        d = binding.JvAttnDesc(B, heads, H, W, 64, dtype, dtype, s, s, s, s, 0)
+        dwc = binding.JvDwcParams(binding.JV_DWC_TOKEN_DYNAMIC, ksize, 64, None, 16, 16, 16, 16)
+        return binding.jv_linear_block_workspace_bytes(d, dwc), binding.jv_linear_attn_workspace_bytes(d)
+    for shape in ((1, 6, 16, 16), (1, 1, 1, 1), (1, 2, 8, 16), (2, 6, 32, 32), (1, 1, 128, 128), (64, 12, 14, 14)):
+        for ksize in (3, 5):
+            both = [query(dtype, *shape, ksize) for dtype in (binding.JV_F32, binding.JV_BF16)]
+            assert both[0][0] == both[1][0] > 0
+            assert both[0][0] >= both[0][1]     # (the fp32 states fit)
+
+
 def test_block_workspace_query_for_wide_heads():
     """The same query for heads of 128 channels (host only): four 64 x 64 quadrant states per head
     and chunk plus their sums; static filters need nothing more, squeeze-dynamic filters the
