@@ -3,7 +3,8 @@
 Argument marshalling only: every computation runs inside the library's HIP
 kernels.  The token-mixer calls are marshalled by the extension module _native
 (csrc/jv_native.cpp: a small problem's kernels are shorter than a ctypes call
-with its descriptor), everything else through ctypes.  Tensors are torch tensors on the GPU (torch is used for device memory
+with its descriptor) where their arguments have the ordinary forms, everything else
+goes through ctypes.  Tensors are torch tensors on the GPU (torch is used for device memory
 and streams); the functions carry the names of the C entry points.  There is no
 CPU fallback: a missing library or a non-OK status raises.
 """
@@ -198,9 +199,15 @@ def jv_linear_attn_workspace_bytes(desc):
 def jv_linear_attn_fwd(q, k, v, o, grid, eps=1e-6, workspace=None, stream=None):
     """o <- ReLU linear attention of (q, k, v); returns the workspace tensor used."""
     if workspace is None:
+        grid = tuple(grid)
         need = jv_linear_attn_workspace_bytes(make_desc(q, k, v, o, grid))
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
-    _check((_native or _load_native()).linear_attn_fwd(q, k, v, o, grid, eps, workspace, stream))
+    st = (_native or _load_native()).linear_attn_fwd(q, k, v, o, grid, eps, workspace, stream)
+    if st is None:
+        desc = make_desc(q, k, v, o, grid)
+        st = lib().jv_linear_attn_fwd(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), eps,
+                                      workspace.data_ptr(), workspace.numel() * workspace.element_size(), _stream(stream))
+    _check(st)
     return workspace
 
 
@@ -241,12 +248,20 @@ def jv_linear_block_workspace_bytes(desc, dwc):
     return int(lib().jv_linear_block_workspace_bytes(ctypes.byref(desc), ctypes.byref(dwc)))
 
 
-def _linear_block(q, k, v, o, grid, eps, static_kernel, squeeze, ksize, token, focus_p, workspace, stream):
+def _linear_block(q, k, v, o, grid, eps, static_kernel, squeeze, ksize, token, focused, focus_p, workspace, stream):
     if workspace is None:
+        grid = tuple(grid)
         need = jv_linear_block_workspace_bytes(make_desc(q, k, v, o, grid), make_dwc_params(static_kernel, squeeze, ksize, token))
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
-    _check((_native or _load_native()).linear_block_fwd(q, k, v, o, grid, eps, static_kernel, squeeze, ksize, token,
-                                                        focus_p, workspace, stream))
+    st = (_native or _load_native()).linear_block_fwd(q, k, v, o, grid, eps, static_kernel, squeeze, ksize, token,
+                                                      focus_p, workspace, stream)
+    if st is None:
+        desc, dwc = make_desc(q, k, v, o, grid), make_dwc_params(static_kernel, squeeze, ksize, token)
+        tail = (ctypes.byref(dwc), workspace.data_ptr(), workspace.numel() * workspace.element_size(), _stream(stream))
+        head = (ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), eps)
+        st = (lib().jv_linear_block_focused_fwd(*head, focus_p, *tail) if focused else
+              lib().jv_linear_block_fwd(*head, *tail))
+    _check(st)
     return workspace
 
 
@@ -254,24 +269,34 @@ def jv_linear_block_fwd(q, k, v, o, grid, eps=1e-6, static_kernel=None, squeeze=
                         workspace=None, stream=None, token=None):
     """o <- linear attention + depth-wise convolution of v (the paper's linear-attention block);
     returns the workspace tensor used."""
-    return _linear_block(q, k, v, o, grid, eps, static_kernel, squeeze, ksize, token, 0, workspace, stream)
+    return _linear_block(q, k, v, o, grid, eps, static_kernel, squeeze, ksize, token, False, 0, workspace, stream)
 
 
 def jv_linear_block_focused_fwd(q, k, v, o, grid, focus_p, eps=1e-6, static_kernel=None, squeeze=None,
                                 ksize=3, workspace=None, stream=None, token=None):
     """The linear-attention block with the focused feature map of power focus_p in place of
     ReLU; returns the workspace tensor used."""
-    if focus_p == 0:   # (0 stands for the ReLU map below; here it is an error of the entry point)
+    if focus_p == 0:   # (0 stands for the ReLU map in _native; here it is an error of the entry point)
         focus_p = -1
-    return _linear_block(q, k, v, o, grid, eps, static_kernel, squeeze, ksize, token, focus_p, workspace, stream)
+    return _linear_block(q, k, v, o, grid, eps, static_kernel, squeeze, ksize, token, True, focus_p, workspace, stream)
 
 
 def jv_window_attn_fwd(q, k, v, o, grid, window, scale=0.0, stream=None):
-    _check((_native or _load_native()).window_attn_fwd(q, k, v, o, grid, window, scale, stream))
+    st = (_native or _load_native()).window_attn_fwd(q, k, v, o, grid, window, scale, stream)
+    if st is None:
+        desc = make_desc(q, k, v, o, grid)
+        st = lib().jv_window_attn_fwd(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
+                                      window[0], window[1], scale, _stream(stream))
+    _check(st)
 
 
 def jv_full_attn_fwd(q, k, v, o, grid, scale=0.0, stream=None):
-    _check((_native or _load_native()).full_attn_fwd(q, k, v, o, grid, scale, stream))
+    st = (_native or _load_native()).full_attn_fwd(q, k, v, o, grid, scale, stream)
+    if st is None:
+        desc = make_desc(q, k, v, o, grid)
+        st = lib().jv_full_attn_fwd(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
+                                    scale, _stream(stream))
+    _check(st)
 
 
 def jv_window_geometry(grid_h, grid_w, win_h, win_w):

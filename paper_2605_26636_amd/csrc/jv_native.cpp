@@ -1,10 +1,12 @@
 // Argument marshalling of the token-mixer calls for Python: checks the tensors, fills the
-// descriptor and calls the C entry points of libjetvit.so.  What binding.py did through ctypes
-// structures took 7 to 10 us of host time per call, as long as the kernels of a small problem
-// (256 tokens x 6 heads: 13.2 us a call, host-bound, against 11 us of kernels); here it is below 1 us.
-// Every function returns the entry point's status; binding.py turns it into an exception.  The
-// interpreter lock is released around the entry points, as ctypes does, so that a launch that waits
-// for room in the queue holds up no other thread.
+// descriptor and calls the C entry points of libjetvit.so.  Host time of a call, launches included,
+// through ctypes structures / here: window or full attention 10.3 / 3.9 us, linear attention
+// 13.7 / 7.4 us, the block with generated filters 25.4 / 20.3 us, where the kernels of a small problem take about 10.
+// Only the ordinary forms are marshalled here: torch tensors with memory, pairs as tuples or lists.
+// Every function returns the entry point's status, or None for arguments of any other form, valid
+// or not, which binding.py then takes through ctypes: what is accepted, and the exceptions of what
+// is not, are those of that path.  The interpreter lock is released around the entry points, as
+// ctypes does, so that a launch that waits for room in the queue holds up no other thread.
 #include <Python.h>
 
 #include <ATen/hip/impl/HIPStreamMasqueradingAsCUDA.h>
@@ -14,41 +16,38 @@
 
 namespace {
 
-const at::Tensor *tensor_arg(PyObject *obj) {
-    if (!THPVariable_Check(obj)) {
-        PyErr_SetString(PyExc_TypeError, "q, k, v, o must be torch tensors");
-        return nullptr;
-    }
-    return &THPVariable_Unpack(obj);
-}
+// The readers below return false (or null) for a form that is left to binding.py; a Python error
+// they leave set is cleared by `guarded`.
+const at::Tensor *tensor_arg(PyObject *obj) { return THPVariable_Check(obj) ? &THPVariable_Unpack(obj) : nullptr; }
 
 bool dtype_code(const at::Tensor &t, jv_dtype *out) {
     if (t.scalar_type() == at::kFloat) *out = JV_F32;
     else if (t.scalar_type() == at::kBFloat16) *out = JV_BF16;
-    else {
-        PyErr_SetString(PyExc_TypeError, "unsupported dtype");
-        return false;
-    }
+    else return false;
     return true;
 }
 
+bool int_arg(PyObject *obj, int32_t *out) {
+    const long x = PyLong_AsLong(obj);
+    *out = (int32_t)x;
+    return x == *out && !(x == -1 && PyErr_Occurred());
+}
+
+bool float_arg(PyObject *obj, float *out) {
+    const double x = PyFloat_AsDouble(obj);
+    *out = (float)x;
+    return !(x == -1.0 && PyErr_Occurred());
+}
+
+// Items of a tuple or list of exactly n (borrowed references), or null.
+PyObject **items_arg(PyObject *seq, Py_ssize_t n) {
+    if (!PyTuple_Check(seq) && !PyList_Check(seq)) return nullptr;
+    return PySequence_Fast_GET_SIZE(seq) == n ? PySequence_Fast_ITEMS(seq) : nullptr;
+}
+
 bool pair_arg(PyObject *seq, int32_t *a, int32_t *b) {
-    PyObject *fast = PySequence_Fast(seq, "expected a pair of integers");
-    if (!fast) return false;
-    bool ok = PySequence_Fast_GET_SIZE(fast) == 2;
-    if (!ok) PyErr_SetString(PyExc_ValueError, "expected a pair of integers");
-    if (ok) {
-        const long x = PyLong_AsLong(PySequence_Fast_GET_ITEM(fast, 0)), y = PyLong_AsLong(PySequence_Fast_GET_ITEM(fast, 1));
-        ok = !PyErr_Occurred();
-        if (ok && (x != (int32_t)x || y != (int32_t)y)) {
-            PyErr_SetString(PyExc_OverflowError, "grid or window side does not fit 32 bits");
-            ok = false;
-        }
-        *a = (int32_t)x;
-        *b = (int32_t)y;
-    }
-    Py_DECREF(fast);
-    return ok;
+    PyObject **items = items_arg(seq, 2);
+    return items && int_arg(items[0], a) && int_arg(items[1], b);
 }
 
 struct Call {
@@ -75,48 +74,24 @@ bool mixer_args(PyObject *const *args, PyObject *stream, Call *c) {
     for (int i = 0; i < 4; ++i)
         if (!(t[i] = tensor_arg(args[i]))) return false;
     jv_attn_desc &d = c->desc;
-    if (!pair_arg(args[4], &d.grid_h, &d.grid_w)) return false;
-    if (t[0]->dim() != 4) {
-        PyErr_SetString(PyExc_ValueError, "tensors must be [batch, heads, N, head_dim] views with a contiguous last axis");
-        return false;
-    }
+    if (!pair_arg(args[4], &d.grid_h, &d.grid_w) || t[0]->dim() != 4) return false;
     const auto shape = t[0]->sizes();
-    if (shape[2] < (int64_t)d.grid_h * d.grid_w) {
-        PyErr_SetString(PyExc_ValueError, "fewer tokens than grid cells");
-        return false;
-    }
+    const int64_t prefix = shape[2] - (int64_t)d.grid_h * d.grid_w;
+    if (prefix < 0 || prefix != (int32_t)prefix) return false;
     jv_strides *strides[4] = {&d.q, &d.k, &d.v, &d.o};
     for (int i = 0; i < 4; ++i) {
-        if (t[i]->sizes() != shape) {
-            PyErr_SetString(PyExc_ValueError, "q, k, v, o must share one shape");
-            return false;
-        }
-        if (i < 3 && t[i]->scalar_type() != t[0]->scalar_type()) {
-            PyErr_SetString(PyExc_TypeError, "q, k, v must share one dtype");
-            return false;
-        }
-        if (!t[i]->is_cuda()) {
-            PyErr_SetString(PyExc_ValueError, "tensors must live on the GPU");
-            return false;
-        }
+        if (t[i]->sizes() != shape || !t[i]->is_cuda() || (i < 3 && t[i]->scalar_type() != t[0]->scalar_type())) return false;
         const auto s = t[i]->strides();
-        if (s[3] != 1) {
-            PyErr_SetString(PyExc_ValueError, "tensors must be [batch, heads, N, head_dim] views with a contiguous last axis");
-            return false;
-        }
+        if (s[3] != 1) return false;
         *strides[i] = {s[0], s[1], s[2]};
     }
     if (!dtype_code(*t[0], &d.dtype) || !dtype_code(*t[3], &d.o_dtype)) return false;
     for (int i : {0, 1, 3})
-        if (shape[i] != (int32_t)shape[i]) {
-            PyErr_SetString(PyExc_OverflowError, "tensor axis does not fit 32 bits");
-            return false;
-        }
+        if (shape[i] != (int32_t)shape[i]) return false;
     d.batch = (int32_t)shape[0];
     d.heads = (int32_t)shape[1];
     d.head_dim = (int32_t)shape[3];
-    const int64_t prefix = shape[2] - (int64_t)d.grid_h * d.grid_w;
-    d.n_prefix = prefix > 1 << 30 ? 1 << 30 : (int32_t)prefix;  // (the entry point refuses more than 64)
+    d.n_prefix = (int32_t)prefix;
     c->q = t[0]->data_ptr();
     c->k = t[1]->data_ptr();
     c->v = t[2]->data_ptr();
@@ -126,18 +101,12 @@ bool mixer_args(PyObject *const *args, PyObject *stream, Call *c) {
 
 // f() without the interpreter lock.
 template <typename F>
-jv_status unlocked(F f) {
+PyObject *status_of(F f) {
     jv_status st;
     Py_BEGIN_ALLOW_THREADS
     st = f();
     Py_END_ALLOW_THREADS
-    return st;
-}
-
-bool arg_count(Py_ssize_t n, Py_ssize_t want) {
-    if (n == want) return true;
-    PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
-    return false;
+    return PyLong_FromLong(st);
 }
 
 bool workspace_arg(PyObject *obj, void **ptr, size_t *bytes) {
@@ -149,118 +118,97 @@ bool workspace_arg(PyObject *obj, void **ptr, size_t *bytes) {
 }
 
 // (q, k, v, o, grid, eps, workspace, stream)
-PyObject *linear_attn_fwd(PyObject *, PyObject *const *a, Py_ssize_t n) {
+PyObject *linear_attn_fwd(PyObject *const *a) {
     Call c;
+    float eps;
     void *ws;
     size_t bytes;
-    if (!arg_count(n, 8) || !mixer_args(a, a[7], &c)) return nullptr;
-    const double eps = PyFloat_AsDouble(a[5]);
-    if ((eps == -1.0 && PyErr_Occurred()) || !workspace_arg(a[6], &ws, &bytes)) return nullptr;
-    return PyLong_FromLong(unlocked([&] { return jv_linear_attn_fwd(&c.desc, c.q, c.k, c.v, c.o, (float)eps, ws, bytes, c.stream); }));
+    if (!mixer_args(a, a[7], &c) || !float_arg(a[5], &eps) || !workspace_arg(a[6], &ws, &bytes)) return nullptr;
+    return status_of([&] { return jv_linear_attn_fwd(&c.desc, c.q, c.k, c.v, c.o, eps, ws, bytes, c.stream); });
 }
 
-// One fp32 device tensor of the convolution's parameters.
-bool param_arg(PyObject *obj, const float **out, int64_t *rows) {
+// One fp32 device tensor of the convolution's parameters; rows: the length of its first axis, if asked for.
+bool param_arg(PyObject *obj, const float **out, int32_t *rows = nullptr) {
     const at::Tensor *t = tensor_arg(obj);
-    if (!t) return false;
-    if (t->scalar_type() != at::kFloat || !t->is_cuda() || !t->is_contiguous()) {
-        PyErr_SetString(PyExc_ValueError, "convolution parameters must be contiguous fp32 device tensors");
-        return false;
-    }
+    if (!t || t->scalar_type() != at::kFloat || !t->is_cuda() || !t->is_contiguous()) return false;
     *out = (const float *)t->data_ptr();
-    if (rows) *rows = t->dim() > 0 ? t->size(0) : 0;
+    if (!rows) return true;
+    if (t->dim() == 0 || t->size(0) != (int32_t)t->size(0)) return false;
+    *rows = (int32_t)t->size(0);
     return true;
 }
 
 // static_kernel, squeeze, ksize, token as make_dwc_params of binding.py takes them
 bool dwc_args(PyObject *kernel, PyObject *squeeze, PyObject *ksize, PyObject *token, jv_dwc_params *p) {
     *p = {JV_DWC_NONE, 3, 0, nullptr, nullptr, nullptr, nullptr, nullptr};
-    if ((kernel != Py_None) + (squeeze != Py_None) + (token != Py_None) > 1) {
-        PyErr_SetString(PyExc_ValueError, "give a static kernel or one set of generator weights, not several");
-        return false;
-    }
-    const long k = PyLong_AsLong(ksize);
-    if (k == -1 && PyErr_Occurred()) return false;
-    p->ksize = k == (int32_t)k ? (int32_t)k : -1;
+    if ((kernel != Py_None) + (squeeze != Py_None) + (token != Py_None) > 1 || !int_arg(ksize, &p->ksize)) return false;
     if (kernel != Py_None) {
         p->mode = JV_DWC_STATIC;
-        return param_arg(kernel, &p->static_kernel, nullptr);
+        return param_arg(kernel, &p->static_kernel);
     }
     PyObject *weights = squeeze != Py_None ? squeeze : token;
     if (weights == Py_None) return true;
     p->mode = squeeze != Py_None ? JV_DWC_SQUEEZE_DYNAMIC : JV_DWC_TOKEN_DYNAMIC;
-    PyObject *fast = PySequence_Fast(weights, "generator weights must be (w1, b1, w2, b2)");
-    if (!fast) return false;
-    bool ok = PySequence_Fast_GET_SIZE(fast) == 4;
-    if (!ok) PyErr_SetString(PyExc_ValueError, "generator weights must be (w1, b1, w2, b2)");
-    const float **dst[4] = {&p->w1, &p->b1, &p->w2, &p->b2};
-    int64_t hidden = 0;
-    try {
-        for (int i = 0; ok && i < 4; ++i) ok = param_arg(PySequence_Fast_GET_ITEM(fast, i), dst[i], i == 0 ? &hidden : nullptr);
-    } catch (...) {
-        Py_DECREF(fast);
-        throw;
-    }
-    p->hidden = (int32_t)hidden;
-    Py_DECREF(fast);
-    return ok;
+    PyObject **w = items_arg(weights, 4);
+    return w && param_arg(w[0], &p->w1, &p->hidden) && param_arg(w[1], &p->b1) && param_arg(w[2], &p->w2) && param_arg(w[3], &p->b2);
 }
 
 // (q, k, v, o, grid, eps, static_kernel, squeeze, ksize, token, focus_p, workspace, stream); focus_p 0: the ReLU map
-PyObject *linear_block_fwd(PyObject *, PyObject *const *a, Py_ssize_t n) {
+PyObject *linear_block_fwd(PyObject *const *a) {
     Call c;
     jv_dwc_params dwc;
+    float eps;
+    int32_t focus;
     void *ws;
     size_t bytes;
-    if (!arg_count(n, 13) || !mixer_args(a, a[12], &c) || !dwc_args(a[6], a[7], a[8], a[9], &dwc)) return nullptr;
-    const double eps = PyFloat_AsDouble(a[5]);
-    if (eps == -1.0 && PyErr_Occurred()) return nullptr;
-    const long focus = PyLong_AsLong(a[10]);
-    if ((focus == -1 && PyErr_Occurred()) || !workspace_arg(a[11], &ws, &bytes)) return nullptr;
-    return PyLong_FromLong(unlocked([&] {
-        return focus == 0 ? jv_linear_block_fwd(&c.desc, c.q, c.k, c.v, c.o, (float)eps, &dwc, ws, bytes, c.stream)
-                          : jv_linear_block_focused_fwd(&c.desc, c.q, c.k, c.v, c.o, (float)eps, (int32_t)focus, &dwc, ws, bytes, c.stream);
-    }));
+    if (!mixer_args(a, a[12], &c) || !dwc_args(a[6], a[7], a[8], a[9], &dwc) || !float_arg(a[5], &eps) ||
+        !int_arg(a[10], &focus) || !workspace_arg(a[11], &ws, &bytes))
+        return nullptr;
+    return status_of([&] {
+        return focus == 0 ? jv_linear_block_fwd(&c.desc, c.q, c.k, c.v, c.o, eps, &dwc, ws, bytes, c.stream)
+                          : jv_linear_block_focused_fwd(&c.desc, c.q, c.k, c.v, c.o, eps, focus, &dwc, ws, bytes, c.stream);
+    });
 }
 
 // (q, k, v, o, grid, window, scale, stream)
-PyObject *window_attn_fwd(PyObject *, PyObject *const *a, Py_ssize_t n) {
+PyObject *window_attn_fwd(PyObject *const *a) {
     Call c;
     int32_t wh, ww;
-    if (!arg_count(n, 8) || !mixer_args(a, a[7], &c) || !pair_arg(a[5], &wh, &ww)) return nullptr;
-    const double scale = PyFloat_AsDouble(a[6]);
-    if (scale == -1.0 && PyErr_Occurred()) return nullptr;
-    return PyLong_FromLong(unlocked([&] { return jv_window_attn_fwd(&c.desc, c.q, c.k, c.v, c.o, wh, ww, (float)scale, c.stream); }));
+    float scale;
+    if (!mixer_args(a, a[7], &c) || !pair_arg(a[5], &wh, &ww) || !float_arg(a[6], &scale)) return nullptr;
+    return status_of([&] { return jv_window_attn_fwd(&c.desc, c.q, c.k, c.v, c.o, wh, ww, scale, c.stream); });
 }
 
 // (q, k, v, o, grid, scale, stream)
-PyObject *full_attn_fwd(PyObject *, PyObject *const *a, Py_ssize_t n) {
+PyObject *full_attn_fwd(PyObject *const *a) {
     Call c;
-    if (!arg_count(n, 7) || !mixer_args(a, a[6], &c)) return nullptr;
-    const double scale = PyFloat_AsDouble(a[5]);
-    if (scale == -1.0 && PyErr_Occurred()) return nullptr;
-    return PyLong_FromLong(unlocked([&] { return jv_full_attn_fwd(&c.desc, c.q, c.k, c.v, c.o, (float)scale, c.stream); }));
+    float scale;
+    if (!mixer_args(a, a[6], &c) || !float_arg(a[5], &scale)) return nullptr;
+    return status_of([&] { return jv_full_attn_fwd(&c.desc, c.q, c.k, c.v, c.o, scale, c.stream); });
 }
 
 // Tensors without memory of their own (under tracing or vmap) throw where their pointer or strides
-// are asked for: a Python exception, not the end of the process.
-template <PyObject *(*F)(PyObject *, PyObject *const *, Py_ssize_t)>
-PyObject *guarded(PyObject *self, PyObject *const *a, Py_ssize_t n) {
-    try {
-        return F(self, a, n);
-    } catch (const c10::Error &e) {
-        if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
-    } catch (const std::exception &e) {
-        if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what());
+// are asked for, and torch where it has no device for the current stream: left to binding.py too.
+// Nothing throws behind an entry point, so no call is made twice.
+template <PyObject *(*F)(PyObject *const *), Py_ssize_t ARGS>
+PyObject *guarded(PyObject *, PyObject *const *a, Py_ssize_t n) {
+    if (n != ARGS) {
+        PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
+        return nullptr;
     }
-    return nullptr;
+    try {
+        if (PyObject *status = F(a)) return status;
+    } catch (const std::exception &) {
+    }
+    PyErr_Clear();
+    Py_RETURN_NONE;
 }
 
 PyMethodDef methods[] = {
-    {"linear_attn_fwd", (PyCFunction)(void *)guarded<linear_attn_fwd>, METH_FASTCALL, nullptr},
-    {"linear_block_fwd", (PyCFunction)(void *)guarded<linear_block_fwd>, METH_FASTCALL, nullptr},
-    {"window_attn_fwd", (PyCFunction)(void *)guarded<window_attn_fwd>, METH_FASTCALL, nullptr},
-    {"full_attn_fwd", (PyCFunction)(void *)guarded<full_attn_fwd>, METH_FASTCALL, nullptr},
+    {"linear_attn_fwd", (PyCFunction)(void *)guarded<linear_attn_fwd, 8>, METH_FASTCALL, nullptr},
+    {"linear_block_fwd", (PyCFunction)(void *)guarded<linear_block_fwd, 13>, METH_FASTCALL, nullptr},
+    {"window_attn_fwd", (PyCFunction)(void *)guarded<window_attn_fwd, 8>, METH_FASTCALL, nullptr},
+    {"full_attn_fwd", (PyCFunction)(void *)guarded<full_attn_fwd, 7>, METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

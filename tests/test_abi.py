@@ -234,3 +234,24 @@ def test_native_marshalling_turns_c_plus_plus_exceptions_into_python_ones():
         binding.jv_full_attn_fwd(*t, (4, 4))
     with pytest.raises(RuntimeError):
         binding.jv_window_attn_fwd(*t, (4, 4), (2, 2))
+
+
+def test_what_the_marshalling_module_does_not_take_raises_as_through_ctypes():
+    import ctypes
+    import torch
+    t = [torch.empty(1, 2, 16, 64) for _ in range(4)]
+    ws = torch.empty(1 << 16, dtype=torch.uint8)
+    with pytest.raises(ValueError, match="live on the GPU"):
+        binding.jv_full_attn_fwd(*t, (4, 4))
+    with pytest.raises(ValueError, match="fewer tokens"):
+        binding.jv_full_attn_fwd(*t, (4, 5))
+    with pytest.raises(ValueError, match="share one shape"):
+        binding.jv_window_attn_fwd(t[0], t[1][:, :1], t[2], t[3], (4, 4), (2, 2))
+    with pytest.raises(TypeError, match="share one dtype"):
+        binding.jv_linear_attn_fwd(t[0], t[1].double(), t[2], t[3], (4, 4), workspace=ws)
+    with pytest.raises(ValueError):
+        binding.jv_full_attn_fwd(*t, (4, 4, 1))
+    with pytest.raises(AttributeError):
+        binding.jv_full_attn_fwd(None, *t[1:], (4, 4))
+    with pytest.raises(ValueError, match="not several"):
+        binding.make_dwc_params(static_kernel=t[0], squeeze=t)

@@ -186,3 +186,46 @@ def test_linear_denominators_without_a_finite_reciprocal():
     o = torch.empty_like(q)
     binding.jv_linear_attn_fwd(q, k, v, o, (1, N), 0.0)
     check(err_fp32(to_host(o), to_host(v[:, :, :1].expand_as(o))), 64 * 2.0 ** -24)
+
+
+class _LikeATensor:
+    """Has what the binding asks of a tensor, without being one."""
+    def __init__(self, t):
+        self.t = t
+
+    def __getattr__(self, name):
+        return getattr(self.t, name)
+
+
+def test_calls_take_every_form_of_their_arguments():
+    # the compiled marshalling takes tensors and pairs in tuples or lists; the rest goes through ctypes
+    H, W, N = 8, 6, 48
+    dq, dk, dv = (to_device(x, False) for x in synth.qkv(20, 1, 2, N, 64, 1.0, False))
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    sq = tuple(torch.from_numpy(a).cuda() for a in synth.squeeze_weights(128, 16, 3, 21))
+
+    def result(call, *args, **kwargs):
+        o = torch.full_like(dq, float("nan"))
+        call(dq, dk, dv, o, *args, **kwargs)
+        assert torch.isfinite(o).all()
+        return o
+    want = result(binding.jv_window_attn_fwd, (H, W), (4, 4))
+    for window in ([4, 4], (4, 4, 1), torch.tensor([4, 4]), np.array([4, 4]), {0: 4, 1: 4}):
+        assert torch.equal(result(binding.jv_window_attn_fwd, (H, W), window), want)
+    for grid in ([H, W], torch.Size((H, W)), np.array([H, W]), (n for n in (H, W))):
+        assert torch.equal(result(binding.jv_window_attn_fwd, grid, (4, 4)), want)
+    o = torch.full_like(dq, float("nan"))
+    binding.jv_window_attn_fwd(*(_LikeATensor(t) for t in (dq, dk, dv, o)), (H, W), (4, 4))
+    assert torch.equal(o, want)
+    for call, kwargs in ((binding.jv_linear_attn_fwd, {}), (binding.jv_linear_block_fwd, {"squeeze": sq}),
+                         (binding.jv_linear_block_focused_fwd, {"focus_p": 3, "squeeze": sq})):
+        want = result(call, (H, W), workspace=ws, **kwargs)
+        assert torch.equal(result(call, (H, W), workspace=_LikeATensor(ws), **kwargs), want)
+        if kwargs:
+            kwargs["squeeze"] = [_LikeATensor(t) for t in sq]
+            assert torch.equal(result(call, (H, W), workspace=ws, **kwargs), want)
+    for focus_p in (0, 17, np.int64(0)):
+        with pytest.raises(binding.JvError):
+            result(binding.jv_linear_block_focused_fwd, (H, W), focus_p, workspace=ws)
+    for call in (binding.jv_full_attn_fwd, binding.jv_linear_attn_fwd, binding.jv_linear_block_fwd):
+        assert torch.equal(result(call, (n for n in (H, W)), stream=torch.cuda.current_stream()), result(call, (H, W)))
