@@ -29,12 +29,11 @@ __device__ inline void store_piece(void *y, size_t at, f32x4 v) {
     if (BF16) *(u32x2 *)((__bf16 *)y + at) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
     else *(f32x4 *)((float *)y + at) = v;
 }
-// Scale and shift of a row, fetched by the callers before the row's own values are waited for:
-// behind the two reductions their latency would stand alone (it shows where rows are few).  Rows
-// above 2048 columns would need more registers than there are: theirs are read at the end.
-template <int NV>
+// Scale and shift of a row, `HELD` in registers: fetched by the callers before the row's own values
+// are waited for (behind the two reductions their latency would stand alone), or read at the end.
+template <int NV, bool HELD>
 struct RowAffine {
-    static constexpr bool kHeld = NV <= 8;
+    static constexpr bool kHeld = HELD;
     f32x4 gamma[kHeld ? NV : 1], beta[kHeld ? NV : 1];
     const float *g, *b;
     __device__ void fetch(const float *g_, const float *b_, int cols, int lane) {
@@ -53,8 +52,8 @@ struct RowAffine {
 };
 // LayerNorm of the row whose pieces are v (0 past the last column), mean and variance in two
 // register passes.
-template <bool OUT_BF16, int NV>
-__device__ inline void normalize_row(const f32x4 (&v)[NV], const RowAffine<NV> &aff, void *y, size_t row_at, int cols, int lane, float eps) {
+template <bool OUT_BF16, int NV, bool HELD>
+__device__ inline void normalize_row(const f32x4 (&v)[NV], const RowAffine<NV, HELD> &aff, void *y, size_t row_at, int cols, int lane, float eps) {
     float sum = 0.f;
 #pragma unroll
     for (int p = 0; p < NV; ++p) sum += (v[p][0] + v[p][1]) + (v[p][2] + v[p][3]);
@@ -86,7 +85,7 @@ __device__ inline void normalize_row(const f32x4 (&v)[NV], const RowAffine<NV> &
     }
 }
 
-template <bool IN_BF16, bool OUT_BF16, int NV>
+template <bool IN_BF16, bool OUT_BF16, int NV, bool HELD>
 __global__ void __launch_bounds__(256)
 layernorm_kernel(const void *__restrict__ xin, const float *__restrict__ gamma,
                  const float *__restrict__ beta, void *__restrict__ yout, long long rows, int cols,
@@ -100,14 +99,14 @@ layernorm_kernel(const void *__restrict__ xin, const float *__restrict__ gamma,
     const long long row = wg * 4 + wave;
     if (wg >= n_wg || row >= rows) return;
     f32x4 v[NV];
-    RowAffine<NV> aff;
+    RowAffine<NV, HELD> aff;
 #pragma unroll
     for (int p = 0; p < NV; ++p) {
         const int c = 4 * (lane + 64 * p);
         v[p] = c < cols ? load_piece<IN_BF16>(xin, row * cols + c) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
     aff.fetch(gamma, beta, cols, lane);
-    normalize_row<OUT_BF16, NV>(v, aff, yout, row * cols, cols, lane, eps);
+    normalize_row<OUT_BF16, NV, HELD>(v, aff, yout, row * cols, cols, lane, eps);
 }
 
 // f(integral_constant NV) for the pieces per lane that rows of `cols` need.
@@ -123,14 +122,37 @@ static void with_row_pieces(int cols, F f) {
     else f(std::integral_constant<int, 32>());
 }
 
+// Are scale and shift held in registers?  Rows of up to 768 columns: always; above 2048: never (more
+// registers than there are).  Between, they take wavefronts: seven fit a SIMD up to 1024 columns, six
+// up to 1280 and four up to 2048, where eight fit without.  fp32 rows: held (65 536 x 1280 to bf16 91 us,
+// read at the end 95; 4 096 x 1024 6.6 / 6.8).  bf16 rows need the rows in flight: held only where that
+// costs no further round of the chip (or, up to 1024 columns, where it is one of many), with 4 096 rows
+// a round above 1024 columns (six wavefronts lose to eight on 6 144 rows already).  Held / read at the end, us: 1 374 x 1280 5.2 / 5.4, 4 096 x 1280 7.3 / 7.5,
+// 8 192 x 1280 16.0 / 13.4, 65 536 x 1280 102 / 87, 8 192 x 2048 23 / 17; 6 144 x 1024 7.7 / 8.0,
+// 8 192 x 1024 10.4 / 9.9, 10 000 x 1024 14.1 / 14.9, 16 384 x 1024 19.8 / 18.6, 32 768 x 1024 35.9 / 37.0.
+static bool layernorm_holds_affine(int pieces, bool in_bf16, long long rows) {
+    if (pieces <= 3) return true;
+    if (pieces > 8) return false;
+    if (!in_bf16) return true;
+    if (pieces == 4 && rows > 3 * 8192) return true;
+    const long long round = pieces == 4 ? 7168 : 4096;
+    return (rows + round - 1) / round == (rows + 8191) / 8192;
+}
+
+template <bool IN_BF16, int NV, bool HELD>
+static auto layernorm_instance(bool out_bf16) {
+    return out_bf16 ? layernorm_kernel<IN_BF16, true, NV, HELD> : layernorm_kernel<IN_BF16, false, NV, HELD>;
+}
+
 static jv_status layernorm_forward(const void *x, const float *gamma, const float *beta, void *y,
                                    long long rows, int cols, float eps, bool in_bf16,
                                    bool out_bf16, hipStream_t stream) {
     with_row_pieces(cols, [&](auto nv_tag) {
         constexpr int NV = decltype(nv_tag)::value;
         const dim3 grid((unsigned)(8 * (((rows + 3) / 4 + 7) / 8)));
-        auto kernel = in_bf16 ? (out_bf16 ? layernorm_kernel<true, true, NV> : layernorm_kernel<true, false, NV>)
-                              : (out_bf16 ? layernorm_kernel<false, true, NV> : layernorm_kernel<false, false, NV>);
+        auto kernel = !in_bf16 ? layernorm_instance<false, NV, (NV <= 8)>(out_bf16)
+                      : layernorm_holds_affine(NV, in_bf16, rows) ? layernorm_instance<true, NV, (NV <= 8)>(out_bf16)
+                                                                  : layernorm_instance<true, NV, (NV <= 3)>(out_bf16);
         hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, x, gamma, beta, y, rows, cols, eps);
     });
     return launch_status("layernorm_kernel");
@@ -654,7 +676,7 @@ split_combine_kernel(const float *__restrict__ parts, long long part_stride, int
     if (row >= rows) return;
     const size_t at = (size_t)row * cols;
     f32x4 v[NV], res[NV];
-    RowAffine<NV> aff;
+    RowAffine<NV, (NV <= 8)> aff;  // (rows above 2048 columns would need more registers than there are)
 #pragma unroll
     for (int p = 0; p < NV; ++p) {
         const int c = min(4 * (lane + 64 * p), cols - 4);  // (lanes past the row re-read its end; dropped below)
@@ -679,7 +701,7 @@ split_combine_kernel(const float *__restrict__ parts, long long part_stride, int
             v[p] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
     }
-    if (narrow) normalize_row<true, NV>(v, aff, narrow, at, cols, lane, eps);
+    if (narrow) normalize_row<true, NV, (NV <= 8)>(v, aff, narrow, at, cols, lane, eps);
 }
 
 // Shape limits of the GEMM (no pointers): what jv_gemm_bias_act documents.  The kernel addresses

@@ -28,6 +28,25 @@ def test_layernorm(rows, cols):
     check(err_fp32(to_host(y32), oracle.layernorm(xb.astype(np.float64), g, b, 1e-6)), 1e-4)
 
 
+@pytest.mark.parametrize("rows,cols", [(7168, 1024), (7169, 1000), (8193, 1024), (4096, 1280), (4097, 1032), (4097, 2048)])
+def test_layernorm_bits_do_not_depend_on_the_number_of_rows(rows, cols):
+    """Scale and shift are held in registers or read at the end, by the number of rows."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows)
+    x = (torch.randn(rows, cols, generator=g, device="cuda") * 2 + 0.5).to(torch.bfloat16)
+    gamma, beta = (torch.randn(cols, generator=g, device="cuda") for _ in range(2))
+    for dtype in (torch.float32, torch.bfloat16):
+        y = torch.full((rows, cols), float("nan"), device="cuda", dtype=dtype)
+        binding.jv_layernorm_fwd(x, gamma, beta, y, 1e-6)
+        for first in (0, rows - 37):
+            few = torch.full((37, cols), float("nan"), device="cuda", dtype=dtype)
+            binding.jv_layernorm_fwd(x[first:first + 37], gamma, beta, few, 1e-6)
+            assert torch.equal(few, y[first:first + 37])
+    x64 = x.double()
+    ref = (x64 - x64.mean(1, True)) / (x64.var(1, unbiased=False, keepdim=True) + 1e-6).sqrt() * gamma.double() + beta.double()
+    check(err_bf16_stored(to_host(y), ref.cpu().numpy()), 1e-4)
+
+
 @pytest.mark.parametrize("M,N,K", [
     (256, 256, 64),      # one tile, one K step
     (300, 520, 192),     # ragged M and N, three K steps
