@@ -66,6 +66,34 @@ def test_attention_tile_edges(B, heads, H, W, window):
         check(err_fp32(to_host(o), oracle.full_attn(q, k, v)), FP32_TOL)
 
 
+@pytest.mark.parametrize("H,W,window,P", [
+    (5, 7, (1, 1), 0),         # every token alone: the result is its value row
+    (5, 7, (1, 2), 0), (7, 5, (3, 1), 3), (9, 11, (2, 2), 5), (6, 6, (2, 4), 0), (3, 5, (4, 2), 0),
+    (9, 11, (3, 3), 0),        # one slot more: the tiles
+    (2, 4, (2, 4), 0),         # one window that spans the grid
+])
+def test_windows_of_a_few_slots(H, W, window, P):
+    N = P + H * W
+    q, k, v = synth.qkv(22, 2, 3, N, 64, 1.0, False)
+    dq, dk, dv = (to_device(x, False) for x in (q, k, v))
+    o = torch.full_like(dq, float("nan"))
+    binding.jv_window_attn_fwd(dq, dk, dv, o, (H, W), window)
+    grid = to_host(o)[:, :, P:]
+    check(err_fp32(grid, oracle.window_attn(q[:, :, P:], k[:, :, P:], v[:, :, P:], H, W, *window)), FP32_TOL)
+    assert torch.isfinite(o).all()
+    if window == (1, 1):
+        assert torch.equal(o, dv)
+    # a score of -inf takes no part, and a value no window holds stays out of it
+    if window == (2, 2):
+        dk[..., P, :] = -3e38
+        dv[..., P, :] = 5.0
+        dv[..., P + 2, 7] = float("inf")
+        binding.jv_window_attn_fwd(dq.abs() + 1, dk, dv, o, (H, W), window)
+        c = torch.arange(H * W, device="cuda")
+        assert torch.equal(torch.isinf(o[0, 0, P:, 7]), (c // W < 2) & (c % W // 2 == 1))
+        assert not torch.isnan(o[:, :, P:]).any()
+
+
 @pytest.mark.parametrize("N", [15, 16, 17, 63, 64, 65, 129, 513, 1100])
 def test_linear_chunk_edges(N):
     # chunks of 64 tokens, groups of 16 in the state pass, tiles of 32 in the apply pass
