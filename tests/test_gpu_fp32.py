@@ -94,6 +94,20 @@ def test_windows_of_a_few_slots(H, W, window, P):
         assert not torch.isnan(o[:, :, P:]).any()
 
 
+@pytest.mark.parametrize("H,W,window,P", [
+    (8, 8, (64, 64), 0), (5, 9, (6, 10), 2), (1, 70, (40, 16), 0), (70, 1, (16, 40), 0), (9, 11, (4, 200), 3), (3, 5, (128, 128), 0),
+])
+def test_windows_beyond_the_grid_are_those_that_end_with_it(H, W, window, P):
+    N = P + H * W
+    q, k, v = synth.qkv(23, 2, 3, N, 64, 1.0, False)
+    dq, dk, dv = (to_device(x, False) for x in (q, k, v))
+    o, inside = torch.full_like(dq, float("nan")), torch.full_like(dq, float("nan"))
+    binding.jv_window_attn_fwd(dq, dk, dv, o, (H, W), window)
+    binding.jv_window_attn_fwd(dq, dk, dv, inside, (H, W), (min(window[0], H), min(window[1], W)))
+    assert torch.equal(o, inside)    # the same launch
+    check(err_fp32(to_host(o)[:, :, P:], oracle.window_attn(q[:, :, P:], k[:, :, P:], v[:, :, P:], H, W, *window)), FP32_TOL)
+
+
 @pytest.mark.parametrize("N", [15, 16, 17, 63, 64, 65, 129, 513, 1100])
 def test_linear_chunk_edges(N):
     # chunks of 64 tokens, groups of 16 in the state pass, tiles of 32 in the apply pass
