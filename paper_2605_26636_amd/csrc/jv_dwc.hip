@@ -17,8 +17,8 @@ static size_t align64f(size_t floats) { return (floats + 63) & ~(size_t)63; }  /
 jv_status plan_dwc(const jv_dwc_params *dwc, const LinearPlan &lp, int B, int heads, int N, DwcPlan *out) {
     DwcPlan p;
     // Token-wise filters: one size for both element types.  The regions are those of the bf16 plan; the
-    // states of the fp32 plan (at most 65 floats a token and head beyond the first state) reach from
-    // the start of the workspace into regions that are written only after the apply pass has read them.
+    // states of the fp32 plan (at most 65 floats a token and head and two states) reach from the
+    // start of the workspace into regions that are written only after the apply pass has read them.
     const bool token = dwc && dwc->mode == JV_DWC_TOKEN_DYNAMIC;
     const size_t base = align64f(linear_workspace_floats(token ? plan_linear(B, heads, N) : lp, B, heads));
     p.total_floats = base;

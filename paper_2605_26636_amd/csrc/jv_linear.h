@@ -9,13 +9,16 @@ constexpr int kStateFloats = kHeadDim * kHeadDim + kHeadDim;  // St[c2][c1] then
 
 struct LinearPlan {
     int n_split;       // token chunks per (batch, head) in the state pass
-    int chunk;         // tokens per chunk (multiple of 256 unless it covers all of N)
+    int chunk;         // tokens per chunk (a multiple of 256, fp32 tensors: of 64)
     int apply_tokens;  // tokens per workgroup in the apply pass
     bool combine;      // sum the partial states in a pass of their own (many chunks)
 };
 
 LinearPlan plan_linear(int B, int heads, int N, bool bf16 = true);
 size_t linear_workspace_floats(const LinearPlan &p, int B, int heads);
+
+// dst[bh] = sum over the n_split partial states of ws; with vsum, the partial token sums of V into the first.
+jv_status combine_states(const float *ws, float *dst, float *vsum, int n_split, int BH, hipStream_t stream);
 
 // The depth-wise convolution branch of the block (Eq. 4) as the launchers see it.  Workspace
 // regions (float offsets from the workspace base) follow the linear-attention states.

@@ -16,16 +16,20 @@ LinearPlan plan_linear(int B, int heads, int N, bool bf16) {
     const long long bh = (long long)B * heads;
     if (!bf16) {
         // Chunks of at least 64 tokens (16 per wavefront, one round of loads in the state pass), down
-        // to which a problem is cut until it has two workgroups per compute unit; at most eight
-        // partial states, which every workgroup of the apply pass sums for itself.
+        // to which a problem is cut until it has two workgroups per compute unit.  Up to eight
+        // partial states are summed by every workgroup of the apply pass for itself, up to 64 in a
+        // pass of their own: that pays where eight chunks of up to 16 heads leave half of the chip idle for
+        // long.  Eight states / up to 64, us: 6 heads of 4 096 tokens 22.7 / 24.5, of 6 144 32.5 / 28.7, of
+        // 16 384 66 / 46, of 262 144 783 / 388; 16 heads of 8 192 48.3 / 46.9, 24 of 8 192 62 / 70.
         long long want = (512 + bh - 1) / bh, most = (N + 63) / 64;
         want = want > most ? most : want;
-        want = want > 8 ? 8 : want;
+        want = want > 64 ? 64 : want;
+        if (want > 8 && (N <= 4096 || bh > 16)) want = 8;
         p.chunk = (int)((((N + want - 1) / want + 63) / 64) * 64);
         p.n_split = (N + p.chunk - 1) / p.chunk;
         p.apply_tokens = 1024;
         while (p.apply_tokens > 128 && bh * ((N + p.apply_tokens - 1) / p.apply_tokens) < 512) p.apply_tokens /= 2;
-        p.combine = false;
+        p.combine = p.n_split > 8;
         return p;
     }
     // Aim for about two workgroups per compute unit, chunks of at least 256 tokens.
@@ -53,7 +57,7 @@ size_t linear_workspace_floats(const LinearPlan &p, int B, int heads) {
 // ---------------------------------------------------------------------------------------
 // fp32 path: both passes on the fp32 matrix instructions (v_mfma_f32_32x32x2_f32: operand lane
 // (half, i) holds row or column i at contraction index `half`; fp32 throughout), whose rate
-// would stream the tensors at 9.8 TB/s, so large problems are bound by memory and small ones by
+// would stream the tensors at 9.8 TB/s, so problems that fill the chip are bound by memory and small ones by
 // the two launches.
 // ---------------------------------------------------------------------------------------
 
@@ -347,8 +351,14 @@ static jv_status linear_f32(const Problem &pr, const LinearPlan &plan, float eps
                        pr.heads, pr.N, plan.chunk, focus_p);
     jv_status st = launch_status("la_state_f32");
     if (st != JV_OK) return st;
+    const float *states = ws;
+    if (plan.combine) {
+        float *sum = ws + (size_t)plan.n_split * BH * kStateFloats;
+        if ((st = combine_states(ws, sum, nullptr, plan.n_split, BH, stream)) != JV_OK) return st;
+        states = sum;
+    }
     hipLaunchKernelGGL(la_apply_f32, dim3((pr.N + plan.apply_tokens - 1) / plan.apply_tokens, BH), dim3(256), 0, stream,
-                       pr.q, pr.o, ws, pr.heads, pr.N, plan.n_split, plan.apply_tokens, eps, focus_p);
+                       pr.q, pr.o, states, pr.heads, pr.N, plan.combine ? 1 : plan.n_split, plan.apply_tokens, eps, focus_p);
     return launch_status("la_apply_f32");
 }
 

@@ -244,6 +244,12 @@ la_combine(const float *__restrict__ ws, float *__restrict__ dst, float *vsum, i
     else ((f32x4 *)vsum)[(size_t)bh * kSumVec + (e4 - kStateVec)] = sum;
 }
 
+jv_status combine_states(const float *ws, float *dst, float *vsum, int n_split, int BH, hipStream_t stream) {
+    hipLaunchKernelGGL(la_combine, dim3(8 * ((BH + 7) / 8), ((kStateFloats + kHeadDim) / 4 + 255) / 256), dim3(256), 0,
+                       stream, ws, dst, vsum, n_split, BH, 1);
+    return launch_status("la_combine");
+}
+
 // grid (8 * ceil(n_chunks * B*heads / 8)), 256 threads.  Workgroups are dealt to the eight XCDs
 // in turn; the index is remapped so that the workgroups one XCD receives walk (batch, head)
 // pairs chunk by chunk: the token chunks of a pair then share that XCD's L2 copy of the state.
@@ -538,9 +544,7 @@ jv_status linear_bf16(const Problem &pr, const LinearPlan &plan, float eps, floa
     long long part_stride = (long long)BH * kStateFloats;
     if (plan.combine) {
         float *dst = ws + (size_t)plan.n_split * BH * kStateFloats;
-        hipLaunchKernelGGL(la_combine, dim3(8 * ((BH + 7) / 8), ((kStateFloats + kHeadDim) / 4 + 255) / 256), dim3(256), 0,
-                           stream, ws, dst, dynamic ? ws + dwc.vsum_off : (float *)nullptr, plan.n_split, BH, 1);
-        if ((st = launch_status("la_combine")) != JV_OK) return st;
+        if ((st = combine_states(ws, dst, dynamic ? ws + dwc.vsum_off : (float *)nullptr, plan.n_split, BH, stream)) != JV_OK) return st;
         states = dst;
         n_part = 1;
     }
