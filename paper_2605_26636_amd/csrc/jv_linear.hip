@@ -318,8 +318,12 @@ la_apply_f32(TensorArg qt, TensorArg ot, const float *__restrict__ ws, int heads
         // small denominators and their numerators first take a factor 2^60.  (32 divisions instead,
         // 256 tokens x 6 heads: 10.8 against 10.2 us a call.)
         float den = (lo + hi) + eps;
-        const float up = den < 0x1p-100f ? 0x1p60f : 1.0f;
-        den *= up;
+        if (__any(den < 0x1p-100f)) {
+            const float up = den < 0x1p-100f ? 0x1p60f : 1.0f;
+            den *= up;
+            acc[0] *= up;
+            acc[1] *= up;
+        }
         const float inv = 1.0f / den;
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb)
@@ -327,7 +331,7 @@ la_apply_f32(TensorArg qt, TensorArg ot, const float *__restrict__ ws, int heads
             for (int v4 = 0; v4 < 4; ++v4) {
                 f32x4 out;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) out[e] = acc[cb][4 * v4 + e] * up * inv;
+                for (int e = 0; e < 4; ++e) out[e] = acc[cb][4 * v4 + e] * inv;
                 *(f32x4 *)(mine + li * 256 + (((8 * cb + 2 * v4 + half) ^ (li & 15)) << 4)) = out;
             }
         float *orow = op + (long long)(base + srow) * ot.sn + 4 * chunk;
