@@ -36,12 +36,14 @@ def _run(what, cmd, verbose):
 
 
 def build(verbose: bool = False) -> str:
+    import torch
     from torch.utils import cpp_extension
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     _run("hipcc", [hipcc] + FLAGS + sources() + ["-o", OUT], verbose)
     includes = cpp_extension.include_paths("cuda") + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
     libs = cpp_extension.library_paths("cuda")
-    _run("g++", ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM"]
+    _run("g++", ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+                 f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}"]
          + [f for i in includes for f in ("-isystem", i)] + [os.path.join(CSRC, "jv_native.cpp"), "-o", NATIVE]
          + ["-L" + d for d in libs] + ["-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10", "-lc10_hip",
                                        "-L" + HERE, "-l:libjetvit.so", "-Wl,-rpath,$ORIGIN"], verbose)

@@ -255,3 +255,17 @@ def test_what_the_marshalling_module_does_not_take_raises_as_through_ctypes():
         binding.jv_full_attn_fwd(None, *t[1:], (4, 4))
     with pytest.raises(ValueError, match="not several"):
         binding.make_dwc_params(static_kernel=t[0], squeeze=t)
+
+
+def test_build_fails_where_a_built_module_does_not_load(monkeypatch):
+    import sys
+    import __graft_entry__
+    from oracle import build as oracle_build
+    from paper_2605_26636_amd import build as hip_build
+    monkeypatch.setattr(hip_build, "build", lambda verbose=False: None)
+    monkeypatch.setattr(oracle_build, "build", lambda force=False: None)
+    __graft_entry__.build()
+    monkeypatch.setitem(sys.modules, "paper_2605_26636_amd._native", None)   # import raises ImportError
+    monkeypatch.delattr("paper_2605_26636_amd._native", raising=False)
+    with pytest.raises(RuntimeError, match="_native"):
+        __graft_entry__.build()
