@@ -11,7 +11,8 @@ from parity import BF16_TOL, check, err_bf16, err_bf16_stored, err_fp32, to_host
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rows,cols", [(37, 1024), (5, 64), (300, 4096), (3, 8), (64, 1000)])
+@pytest.mark.parametrize("rows,cols", [(37, 1024), (5, 64), (300, 4096), (3, 8), (64, 1000),
+                                       (6, 520), (37, 768), (5, 1032), (33, 1280), (7, 2048)])
 def test_layernorm(rows, cols):
     x = synth.normal((rows, cols), 500 + cols) * 2.0 + 0.5
     g, b = 1.0 + 0.1 * synth.normal((cols,), 501), 0.1 * synth.normal((cols,), 502)
@@ -124,6 +125,27 @@ def test_gemm_tile_shapes(M, N, K):
     z = torch.empty_like(res)
     binding.jv_gemm_bias_act(a, w, bias, res, z, binding.JV_EPI_RESIDUAL)
     assert torch.equal(z, y[1:M + 1] + res)
+
+
+def test_gemm_capture_at_sizes_of_every_tile_shape():
+    """The tile follows from the sizes, so a captured product may be the first of its kernel; replays
+    with eager products and synchronisations between them give the eager bits."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    a = torch.randn(4096, 256, generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn(1024, 256, generator=g, device="cuda") / 16).to(torch.bfloat16)
+    for M in (37, 600, 1230, 980, 2390, 3000, 4096):
+        got = torch.full((M, 1024), float("nan"), device="cuda")
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            binding.jv_gemm_bias_act(a[:M], w, None, None, got, binding.JV_EPI_SILU)
+        want = torch.empty_like(got)
+        for _ in range(3):
+            got.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            binding.jv_gemm_bias_act(a[:M], w, None, None, want, binding.JV_EPI_SILU)
+            assert torch.equal(got, want)
 
 
 def test_gemm_rows_beyond_32_bit_offsets_and_rerun_bits():
@@ -303,17 +325,17 @@ def test_vit_l_blocks_teacher_forced():
 
 
 def test_vit_l_block_fc2_with_split_k():
-    """Few tokens leave fc2 (K = 4096, 1024 output features) with fewer output tiles than half
-    the compute units; the encoder then splits its K loop over two or four workgroups per tile
-    and adds the partial results in a second pass.  6 144 tokens (96 tiles: two parts) and 2 304
-    tokens (36 tiles: four parts), a linear-attention block at ViT-L width, both stream types;
-    a second run gives the same bits (the partial results are added in a fixed order)."""
+    """Few tokens leave fc2 (K = 4096, 1024 output features) with few output tiles; its K is then
+    summed in parts, by workgroups of their own whose results a second pass adds (1 024 tokens: four parts
+    for both stream types; 2 304, fp32 stream: two) or inside one workgroup (bf16 stream: 2 304 tokens in four
+    parts, 6 144 in two).  A linear-attention block at ViT-L width; a second run gives the same bits (the
+    parts are added in a fixed order)."""
     heads, hidden = 16, 4096
     C = heads * 64
     wts = synth.block_weights(C, hidden, 830)
     wts["b_fc2"] = synth.normal(wts["b_fc2"].shape, 831) * 0.1
     dev = _device_blocks([wts])
-    for H, W in ((64, 96), (48, 48)):
+    for H, W in ((64, 96), (48, 48), (32, 32)):
         x = synth.round_to_bf16(synth.normal((1, H * W, C), 832 + H))
         ref = oracle.encoder_block(x.astype(np.float64), wts, 0, H, W, heads, (16, 16))
         for sd in (torch.float32, torch.bfloat16):
@@ -326,6 +348,56 @@ def test_vit_l_block_fc2_with_split_k():
             enc.forward(z, z, (H, W))     # in place: the residual is the output
             assert torch.equal(z, y)
             enc.close()
+
+
+@pytest.mark.parametrize("heads,hidden,side,batches", [
+    # bf16 stream: K of fc2 in two parts, split on 64 x 64, 64 x 128, 128 x 128 and 256 x 128 tiles, then inside
+    # one workgroup on 128 x 128 and 256 x 128; fp32 stream: the projection split too (one image)
+    (12, 3072, 16, (1, 3, 6, 11, 15, 24)),
+    # in four parts: split on 64 x 64, 64 x 128, 128 x 128 (deep and short ring) and 256 x 128 tiles, inside one workgroup
+    # on 128 x 128; fp32 stream: the projection in four and in two parts
+    (16, 4096, 16, (1, 2, 3, 5, 7, 9, 16)),
+    # five pieces a row in the pass that adds the parts and takes the LayerNorm
+    (20, 5120, 16, (1, 2, 4, 6, 8)),
+    # inside one workgroup on 64 x 128 (65 images), 128 x 128 and 256 x 128 tiles
+    (8, 2048, 8, (1, 17, 40, 65, 70, 130)),
+])
+def test_blocks_whose_products_sum_k_in_parts(heads, hidden, side, batches):
+    """Three blocks, so that the pass that adds the parts also takes the next block's LayerNorm 1 (and, where
+    the projection of an fp32 stream is split, LayerNorm 2), against its blocks run one by one, where a
+    pass of its own takes LayerNorm 1: the same bits.  Every block of one image against the oracle on the
+    block's own input.  For a bf16 stream the image also in batches of other sizes, which take other tiles
+    and sum in the same order: the same bits."""
+    C, N, pattern = heads * 64, side * side, [1, 2, 1]
+    blocks = [synth.block_weights(C, hidden, 1200 + l) for l in range(3)]
+    dev = _device_blocks(blocks)
+    x = synth.round_to_bf16(synth.normal((max(batches), N, C), 1210))
+    for sd in (torch.float32, torch.bfloat16):
+        err = err_bf16 if sd == torch.float32 else err_bf16_stored
+        enc = binding.Encoder(dev, pattern, heads, hidden, window=(8, 8), stream_dtype=sd)
+        single = [binding.Encoder(dev[l:l + 1], pattern[l:l + 1], heads, hidden, window=(8, 8), stream_dtype=sd) for l in range(3)]
+        dx = torch.from_numpy(x).cuda().to(sd)
+        first = None
+        for B in batches:
+            y, tap, tapped = (torch.empty_like(dx[:B]) for _ in range(3))
+            enc.forward(dx[:B], y, (side, side))
+            enc.forward(dx[:B], tapped, (side, side), taps={0: tap})
+            assert torch.equal(tapped, y)
+            if first is not None and sd == torch.bfloat16:
+                assert torch.equal(y[0], first)
+            step = dx[:B]
+            for l in range(3):
+                out = torch.empty_like(y)
+                single[l].forward(step, out, (side, side))
+                if first is None or sd == torch.float32:
+                    ref = oracle.encoder_block(to_host(step[:1]), blocks[l], pattern[l], side, side, heads, (8, 8))
+                    check(err(to_host(out[:1]), ref), BF16_TOL)
+                step = out
+                assert l > 0 or torch.equal(out, tap)
+            assert torch.equal(step, y)
+            first = y[0].clone() if first is None else first
+        for e in [enc] + single:
+            e.close()
 
 
 @pytest.mark.parametrize("fold", [False, True], ids=["layernorm passes", "layernorm folded"])
