@@ -44,8 +44,10 @@
  *  - Thread safety: concurrent calls are safe as long as their output and
  *    workspace buffers do not overlap.  The only process-wide state is, per kernel
  *    that needs more than 64 KB of LDS, an atomic record of the devices on which
- *    that limit has been raised (done on the first call on each device, with that
- *    device current: make the first call on a device outside stream capture).
+ *    that limit has been raised (done on the first call that takes the kernel on each
+ *    device, with that device current: make the first call on a device outside stream
+ *    capture.  Later calls may be captured at sizes that take other kernels: raising a
+ *    limit is no stream operation).
  */
 #ifndef JETVIT_H
 #define JETVIT_H
@@ -308,10 +310,12 @@ jv_status jv_gemm_bias_act(const void *a, const void *w, const float *bias, cons
  * aligned.  About 8 launches per block, all on hip_stream, no synchronisation.  Every shape the
  * pass would launch (its four matrix products, the window partition, the token counts) is
  * checked before the first launch; jv_encoder_workspace_bytes returns 0 for a (batch, grid) that
- * jv_encoder_forward would refuse.  With few tokens (the output of the second MLP product has
- * fewer than 128 tiles of 256 x 256) that product's K loop is split over two or four workgroups
- * per tile, whose fp32 partial results are added, with bias and residual, in a pass of their
- * own and in a fixed order; the workspace query accounts for the partial results.
+ * jv_encoder_forward would refuse.  With few tokens (the output of the second MLP product has at most
+ * 128 tiles of 256 x 256) the K loop of a residual product may be split over two or four workgroups
+ * per tile, whose fp32 partial results are added, with bias and residual, in a pass of their own and in
+ * a fixed order; the workspace query always accounts for the partial results then.  With a bf16 stream
+ * the second MLP product sums K in two or four parts at these sizes, split or not, so its bits
+ * do not depend on the tiles taken; they do depend on the number of tokens through the number of parts.
  *
  * jv_encoder_forward_taps: the same forward pass that also hands out the residual stream after
  * chosen blocks, which is what a dense-prediction head attached to the encoder reads (the

@@ -30,8 +30,8 @@ __device__ inline int slot_token(const WindowGeom &g, int wy, int wx, int slot) 
 // step before) and wavefront (qw, kw) takes tile kw.  With KW > 1 the KW running softmaxes of a
 // query block are merged through LDS at the end.  KW = 4 cuts a problem of few queries into four
 // times as many wavefronts; KW = 1 stages a quarter of the bytes per flop.
-// Measured: 1 369 tokens x 12 heads 103 us (516 workgroups on 256 compute units: the third
-// one some units get is a third of the time), 2 304 tokens x 64 heads 798 us = 109 of 157 TFLOP/s.
+// Measured: 1 369 tokens x 12 heads 104 us (two workgroups fit a compute unit, and the last four of
+// 516 run alone for a third of the time), 2 304 tokens x 64 heads 798 us = 109 of 157 TFLOP/s.
 // (The kernel before this one scored one query per wavefront with plain FMAs and read V once
 // per query: 1 675 us for the first of these.)
 // Only the first q_slots query slots of every window are computed.

@@ -1755,7 +1755,8 @@ jv_status attn_bf16(const Problem &pr, const WindowGeom &g, float scale, int q_s
     // as many (same tiles of 32 keys in the same order: the same bits).  A lone wavefront per SIMD waits for itself
     // either way, but with half the arithmetic between its waits.  Blocks of 256 / of 128, us: 12 blocks (200 tokens) 9.6 / 8.1,
     // 48 (784 tokens) 21.2 / 18.8, 96 (1 374 tokens) 33.0 / 30.2, 128 (2 048 tokens) 45.6 / 42.6, but 192 (1 374 tokens)
-    // 33.0 / 38.7: some units get two of the small blocks there and one of the large.
+    // 33.0 / 38.7: some units get two of the small blocks there and one of the large.  However many the keys: one head
+    // of 4 096 tokens 84 / 76, of 32 768 641 / 585; windows of 512 of 4 096 tokens x 6 heads 15.4 / 12.8.
     const long long blocks = (long long)((a.q_slots + 255) / 256) * g.n_win * a.n_bh;
     if (fast && NT == 2 && blocks <= 128) {
         if (pr.o_bf16) hipLaunchKernelGGL((attn_stream_bf16<true, 1>), ring_grid(a, 128), dim3(256), 0, stream, a);

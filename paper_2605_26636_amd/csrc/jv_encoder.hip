@@ -190,6 +190,8 @@ constexpr int kGemmPart = kBM * kBK * 2;               // one operand part: 32 K
 constexpr int kGemmSlots = 5;
 constexpr int kGemmLds = kGemmSlots * kGemmPart;       // 160 KB
 
+typedef __attribute__((address_space(1))) const void global_cvoid;
+
 // table[2 i] = Phi(x_i), table[2 i + 1] = Phi(x_i+1) - Phi(x_i), x_i = kPhiLo + i kPhiStep.
 __device__ inline float gelu_from_table(float x, const float *table) {
     const float t = __builtin_amdgcn_fmed3f(fmaf(x, 1.0f / kPhiStep, -kPhiLo / kPhiStep), 0.0f,
@@ -197,6 +199,11 @@ __device__ inline float gelu_from_table(float x, const float *table) {
     const unsigned i = (unsigned)t;
     const float2 pd = *(const float2 *)(table + 2 * i);
     return x * fmaf(t - (float)i, pd.y, pd.x);
+}
+
+// Byte offset of 16-byte chunk `chunk` (0..7) of row `row` in a [rows][64] bf16 LDS part.
+__device__ inline unsigned gemm_part_off(int row, int chunk) {
+    return (unsigned)(row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4));
 }
 
 // Wait until at most `pending` of this wavefront's vector-memory loads are outstanding, then
@@ -606,18 +613,22 @@ static jv_status launch_gemm(const void *a, const void *w, const float *bias, co
     return launch_status("gemm_bf16_kernel");
 }
 
-// Choice of the tile shape and of the K split for one product.  What a launch takes is modelled as
-//     sum over its rounds of (K blocks of 64 * a + e),
+// Choice of the tile shape and of the K split for one product.  Shapes are ranked by
+//     sum over the launch's rounds of (K blocks of 64 * a + e),
 // a round being what fits the chip at once, a between `lo` (one workgroup) and `hi` (every slot
-// taken); a split further pays for the way of its parts through memory.  The figures (microseconds)
-// are fitted so that the choice loses least against the best of all shapes and splits over 1 400
-// measured launches (200 to 16 384 rows, widths 768, 1024, 1280 and the four products of a block,
-// operands not in the L2; the choice is 0.5 % off the best on average), so a row says when to take
-// a shape rather than what it takes.  The tendency behind them: a 64-deep block costs about 0.22,
-// 0.33, 0.35, 0.56 and 1.15 us on 64 x 64, 64 x 128, 128 x 128, 256 x 128 and 256 x 256 tiles when
-// a workgroup is alone, i.e. the larger the tile the nearer to the matrix rate; with the chip full
-// the clock falls and all of them meet at about 1.1 PFLOP/s.  So: the largest tile that fills the
-// chip, below that the smallest that leaves no unit with two tiles while others have one.
+// taken); a split further pays for the way of its parts through memory.  The figures are weights, no
+// times: they were fitted so that the choice loses least against the best of all shapes and splits over
+// 1 400 measured launches (200 to 16 384 rows, widths 768, 1024, 1280 and the four products of a block,
+// operands not in the L2; the choice is 0.5 % off the best on average).  What they express: a lone
+// 64-deep block costs about 0.22, 0.33, 0.35, 0.56 and 1.15 us on 64 x 64, 64 x 128, 128 x 128, 256 x 128 and
+// 256 x 256 tiles, i.e. the larger the tile the nearer to the matrix rate.  So: the largest tile that
+// fills the chip, below that the smallest that leaves no unit with two tiles while others have one.
+// Products of a block of width 1024 on the tiles chosen, us (PFLOP/s), operands not in the L2:
+//     rows      QKV          projection   fc1          fc2 (not split)
+//     1 374     18.8 (0.46)  10.3 (0.28)  22.5 (0.51)  31.5 (0.37)
+//     4 096     32.0 (0.81)  16.9 (0.51)  38.7 (0.89)  42.4 (0.81)
+//     8 192     61.2 (0.84)  26.9 (0.64)  75.5 (0.91)  66.8 (1.03)
+//     16 384    100 (1.03)   43.2 (0.80)  148 (0.93)   119 (1.16)
 struct TileModel {
     int bm, bn, slots;    // slots: workgroups that fit the chip
     float lo, hi, e;
@@ -751,9 +762,10 @@ jv_status gemm_forward(const void *a, const void *w, const float *bias, const vo
     return fail(JV_ERR_INVALID_ARG, "unknown epilogue");
 }
 
-// Parts that K of fc2 is summed in: as many as give every compute unit a 256 x 256 tile, at most
-// 4, each a multiple of the K block and at least 1024 long.  The scratch of the split residual
-// products is sized by it.
+// Parts that K of fc2 may be summed in at this number of rows: as many as give every compute unit
+// a 256 x 256 tile, at most 4, each a multiple of the K block and at least 1024 long.  The scratch
+// of the split residual products is sized by it, whether or not the plan then splits one.
+constexpr int kComputeUnits = 256;  // MI355X
 static int split_parts_room(long long M, int N, int K) {
     const long long tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
     int split = 1;
@@ -1200,8 +1212,9 @@ jv_status jv_encoder_forward_taps(const jv_encoder *enc, const void *x, void *y,
     jv_status st;
     const bool s16 = c.stream_dtype == JV_BF16;  // element type of the residual stream
     // A bf16 stream is rounded 48 times in 24 blocks, and whatever moves a sum's last bit moves
-    // some of those roundings: its products keep one order of summation, K of fc2 in `room` parts
-    // and K of the projection in one, whatever tiles the plan takes.
+    // some of those roundings.  So its order of summation depends on nothing but the shapes of the
+    // product: K of fc2 in `room` parts (1, 2 or 4 by the number of tokens) and K of the projection
+    // in one, whatever tiles the plan takes.
     const void *resid = x;  // the first residual add reads the input and writes y
     int next_tap = 0;
     for (int l = 0; l < c.n_blocks; ++l) {

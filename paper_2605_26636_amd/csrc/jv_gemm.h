@@ -1,5 +1,5 @@
-// Device helpers shared by the two bf16 matrix-product kernels (the 256 x 256 tiles of
-// jv_encoder.hip and the smaller tiles of jv_gemm_tiles.hip), and the launcher of the latter.
+// What the two bf16 matrix-product kernels share (the 256 x 256 tiles of jv_encoder.hip and the
+// smaller tiles of jv_gemm_tiles.hip): the function behind GELU, the tile shapes, and the launchers of the latter.
 #pragma once
 
 #include "jv_common.h"
@@ -7,7 +7,6 @@
 
 namespace jv {
 
-typedef __attribute__((address_space(1))) const void global_cvoid;
 typedef __attribute__((address_space(3))) void lds_void;
 
 // gelu(x) = x Phi(x), Phi the standard normal distribution function.  The epilogues read
@@ -25,13 +24,6 @@ __device__ inline float normal_cdf(float x) {
     const float half_erfc = 0.5f * poly * __builtin_amdgcn_exp2f(-1.4426950408889634f * z * z);
     return x < 0.f ? half_erfc : 1.0f - half_erfc;
 }
-
-// Byte offset of 16-byte chunk `chunk` (0..7) of row `row` in a [rows][64] bf16 LDS part.
-__device__ inline unsigned gemm_part_off(int row, int chunk) {
-    return (unsigned)(row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4));
-}
-
-constexpr int kComputeUnits = 256;  // MI355X
 
 // Tile shapes (tokens x features): the kernel of jv_encoder.hip, then those of jv_gemm_tiles.hip
 // (128 x 128 in two forms: a deep operand ring with one workgroup per compute unit, a short one

@@ -11,11 +11,11 @@ namespace jv {
 // WM x WN wavefronts owns a tile of 32 MT WM tokens x 64 WN features, a wavefront 32 MT tokens x
 // 64 features of it (MT x 2 blocks of 32 x 32).  K is walked in blocks of 64; the rows of a and w
 // go straight into LDS through a ring of STAGES blocks (row layout and rotation of the 256 x 256
-// kernel).  A block is four steps of 16 in K.  The barrier of a block sits before its last step,
-// when every operand of the block has been read: behind it the first operands of the next block
-// are read and the block STAGES ahead is fetched into the slot just left, under the matrix
-// instructions of the last step, so that neither starts with an LDS round trip and
-// STAGES - 1 blocks are in flight.
+// kernel).  A block is four steps of 16 in K, and a step's operands are read two steps ahead.  So the barrier
+// of a block sits before its last two steps, when every operand of the block has been read: behind it
+// the first operands of the next block are read and the block STAGES ahead is fetched into the
+// slot just left, under the matrix instructions of those two steps, so that neither starts with an
+// LDS round trip and STAGES - 1 blocks are in flight.
 // The launch deals contiguous ranges of tiles to the XCDs.  Which of the two tile indices runs
 // fastest decides what an XCD's L2 holds: with `tokens_fast` a range is a band of features over
 // all tokens (each row of w is fetched by one XCD, a by all eight), else a band of tokens.
@@ -60,7 +60,7 @@ gemm_tile_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W, con
     const int per_xcd = (n_work + 7) / 8;
     int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if ((int)(blockIdx.x >> 3) >= per_xcd || item >= n_work) return;  // whole workgroup
-    // parts of one tile are neighbours: they share nothing, but their tiles' neighbours do
+    // the tiles of one part of K follow one another: neighbouring tiles share rows of a or w, the parts of a tile nothing
     const int k_part = item / n_tiles;
     item -= k_part * n_tiles;
     const int tm = tokens_fast ? item % tiles_m : item / tiles_n;
