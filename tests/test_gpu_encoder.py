@@ -29,7 +29,7 @@ def test_layernorm(rows, cols):
     check(err_fp32(to_host(y32), oracle.layernorm(xb.astype(np.float64), g, b, 1e-6)), 1e-4)
 
 
-@pytest.mark.parametrize("rows,cols", [(7168, 1024), (7169, 1000), (8193, 1024), (4096, 1280), (4097, 1032), (4097, 2048)])
+@pytest.mark.parametrize("rows,cols", [(7168, 1024), (7169, 1000), (8193, 1024), (24577, 1024), (5120, 1280), (5121, 1032), (4096, 1288), (4097, 2048)])
 def test_layernorm_bits_do_not_depend_on_the_number_of_rows(rows, cols):
     """Scale and shift are held in registers or read at the end, by the number of rows."""
     g = torch.Generator(device="cuda")
