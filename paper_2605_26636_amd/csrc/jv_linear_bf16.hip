@@ -250,6 +250,39 @@ jv_status combine_states(const float *ws, float *dst, float *vsum, int n_split, 
     return launch_status("la_combine");
 }
 
+// The partial states of one (batch, head) summed into LDS by 256 threads: St[c2][c1] with the
+// 8-float group index rotated by the row, then z.  16-byte loads, all of them issued before the first use.
+__device__ inline void sum_states(const float *states, int n_part, long long part_stride, float *St, float *zs, int tid) {
+    const f32x4 *src = (const f32x4 *)states;
+    const long long stride4 = part_stride / 4;
+    constexpr int kVec = kStateFloats / 4, kIter = (kVec + 255) / 256;
+    f32x4 part[kIter][4];
+#pragma unroll
+    for (int it = 0; it < kIter; ++it)
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const int e4 = it * 256 + tid;
+            f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+            part[it][p] = (e4 < kVec && p < n_part) ? src[p * stride4 + e4] : zero;
+        }
+#pragma unroll
+    for (int it = 0; it < kIter; ++it) {
+        const int e4 = it * 256 + tid;
+        if (e4 >= kVec) break;
+        f32x4 sum = part[it][0];
+        for (int p = 4; p < n_part; ++p) sum += src[p * stride4 + e4];  // more than 4: rare
+#pragma unroll
+        for (int p = 1; p < 4; ++p) sum += part[it][p];
+        const int e = 4 * e4;
+        if (e < kHeadDim * kHeadDim) {
+            const int c2 = e >> 6, c1 = e & 63;  // 4 consecutive c1 stay inside one group
+            *(f32x4 *)(St + c2 * 64 + ((((c1 >> 3) ^ (c2 & 7)) << 3) | (c1 & 7))) = sum;
+        } else {
+            *(f32x4 *)(zs + e - kHeadDim * kHeadDim) = sum;
+        }
+    }
+}
+
 // grid (8 * ceil(n_chunks * B*heads / 8)), 256 threads.  Workgroups are dealt to the eight XCDs
 // in turn; the index is remapped so that the workgroups one XCD receives walk (batch, head)
 // pairs chunk by chunk: the token chunks of a pair then share that XCD's L2 copy of the state.
@@ -299,37 +332,7 @@ la_apply_bf16(TensorArg qt, TensorArg ot, const float *__restrict__ states, int 
         for (int e = tid; e < kHeadDim * KS * KS; e += 256) kap[(e % (KS * KS)) * kHeadDim + e / (KS * KS)] = kbase[e];
     }
 
-    // Sum the partial states: 16-byte loads, all of them issued before the first use.
-    {
-        const f32x4 *src = (const f32x4 *)(states + (size_t)bh * kStateFloats);
-        const long long stride4 = part_stride / 4;
-        constexpr int kVec = kStateFloats / 4, kIter = (kVec + 255) / 256;
-        f32x4 part[kIter][4];
-#pragma unroll
-        for (int it = 0; it < kIter; ++it)
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const int e4 = it * 256 + tid;
-                f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-                part[it][p] = (e4 < kVec && p < n_part) ? src[p * stride4 + e4] : zero;
-            }
-#pragma unroll
-        for (int it = 0; it < kIter; ++it) {
-            const int e4 = it * 256 + tid;
-            if (e4 >= kVec) break;
-            f32x4 sum = part[it][0];
-            for (int p = 4; p < n_part; ++p) sum += src[p * stride4 + e4];  // more than 4: rare
-#pragma unroll
-            for (int p = 1; p < 4; ++p) sum += part[it][p];
-            const int e = 4 * e4;
-            if (e < kHeadDim * kHeadDim) {
-                const int c2 = e >> 6, c1 = e & 63;  // 4 consecutive c1 stay inside one group
-                *(f32x4 *)(St + c2 * 64 + ((((c1 >> 3) ^ (c2 & 7)) << 3) | (c1 & 7))) = sum;
-            } else {
-                *(f32x4 *)(zs + e - kHeadDim * kHeadDim) = sum;
-            }
-        }
-    }
+    sum_states(states + (size_t)bh * kStateFloats, n_part, part_stride, St, zs, tid);
     __syncthreads();
 
     // A operands: S^T rows c2 = 32*mi + li, k-slots c1 = 16*ks + 8g + (0..7), as bf16 hi + lo.
@@ -510,14 +513,320 @@ la_apply_bf16(TensorArg qt, TensorArg ot, const float *__restrict__ states, int 
     }
 }
 
+// ---------------------------------------------------------------------------------------
+// The apply pass with the convolution branch on a window of V that moves through LDS.  What bounds
+// la_apply_bf16<., KS> is its V loads (every V row comes through the vector memory path 4.5 times
+// for KS = 3: 30 of 85 us at 32 images of 37 x 37, 16 heads) and the vector instructions of the taps
+// and their masks; here every row is fetched once per workgroup.  That shape: 97 -> 63 us for 270 MB
+// (4.3 TB/s), vector instructions now 45 % of the time; 8 images of 64 x 64 44 -> 36 us.
+// The workgroup walks its chunk in steps of 128 tokens, 32 per wavefront.  Its ring in LDS holds the
+// grid cells whose taps a step needs, 128 + 2 pad (W + 1) rows (pad = KS / 2, cells outside the grid as
+// zeros), and the 128 cells the next step adds are in flight in registers meanwhile.  The 32
+// rows behind the ring's end repeat its first, so that a wavefront's sources in a tap row are consecutive.
+// The product is formed as relu(Q) S with the columns of S dealt so that lane (g, li) holds channels
+// 2 li and 2 li + 1 of the tokens 8 q4 + 4 g .. + 3 (q4 = 0 .. 3): the filters of two channels
+// stay in registers for the whole pass, a V row is one dword per lane, nothing is staged, and
+// an output row leaves as 128 contiguous bytes.  Taps outside the grid's width are skipped under the execution mask.
+// Grid and XCD mapping as la_apply_bf16, 256 threads, conv_ring_lds bytes of dynamic LDS.
+// ---------------------------------------------------------------------------------------
+constexpr int kRingStep = 128, kRingRepeat = 32;
+constexpr int kRingFixedLds = kStateFloats * 4 + 4 * 32 * 4;  // the state, afterwards four query tiles; 1 / denominators
+static int conv_ring_rows(int ksize, int W) { return kRingStep + 2 * (ksize / 2) * (W + 1); }
+static int conv_ring_lds(int ksize, int W) { return kRingFixedLds + (conv_ring_rows(ksize, W) + kRingRepeat) * 128; }
+
+// The 3 x 3 taps of one token and two channels, row by row (the order in which la_apply_bf16 adds them):
+// s0 += k[di][dj][0] x[di][dj][0], s1 likewise, column dj in the lanes of use[dj] only.  For wavefronts whose lanes are all active.
+__device__ inline void masked_taps3(const unsigned long long (&use)[3], const float (&k)[9][2], const float (*x0)[2], const float (*x1)[2],
+                                    const float (*x2)[2], float &s0, float &s1) {
+    unsigned long long saved;
+    asm("s_mov_b64 %2, exec\n\t"
+        "s_mov_b64 exec, %3\n\tv_fmac_f32 %0, %6, %24\n\tv_fmac_f32 %1, %7, %25\n\t"
+        "s_mov_b64 exec, %4\n\tv_fmac_f32 %0, %8, %26\n\tv_fmac_f32 %1, %9, %27\n\t"
+        "s_mov_b64 exec, %5\n\tv_fmac_f32 %0, %10, %28\n\tv_fmac_f32 %1, %11, %29\n\t"
+        "s_mov_b64 exec, %3\n\tv_fmac_f32 %0, %12, %30\n\tv_fmac_f32 %1, %13, %31\n\t"
+        "s_mov_b64 exec, %4\n\tv_fmac_f32 %0, %14, %32\n\tv_fmac_f32 %1, %15, %33\n\t"
+        "s_mov_b64 exec, %5\n\tv_fmac_f32 %0, %16, %34\n\tv_fmac_f32 %1, %17, %35\n\t"
+        "s_mov_b64 exec, %3\n\tv_fmac_f32 %0, %18, %36\n\tv_fmac_f32 %1, %19, %37\n\t"
+        "s_mov_b64 exec, %4\n\tv_fmac_f32 %0, %20, %38\n\tv_fmac_f32 %1, %21, %39\n\t"
+        "s_mov_b64 exec, %5\n\tv_fmac_f32 %0, %22, %40\n\tv_fmac_f32 %1, %23, %41\n\t"
+        "s_mov_b64 exec, %2"
+        : "+v"(s0), "+v"(s1), "=&s"(saved)
+        : "s"(use[0]), "s"(use[1]), "s"(use[2]), "v"(k[0][0]), "v"(k[0][1]), "v"(k[1][0]), "v"(k[1][1]), "v"(k[2][0]), "v"(k[2][1]),
+          "v"(k[3][0]), "v"(k[3][1]), "v"(k[4][0]), "v"(k[4][1]), "v"(k[5][0]), "v"(k[5][1]), "v"(k[6][0]), "v"(k[6][1]),
+          "v"(k[7][0]), "v"(k[7][1]), "v"(k[8][0]), "v"(k[8][1]), "v"(x0[0][0]), "v"(x0[0][1]), "v"(x0[1][0]), "v"(x0[1][1]),
+          "v"(x0[2][0]), "v"(x0[2][1]), "v"(x1[0][0]), "v"(x1[0][1]), "v"(x1[1][0]), "v"(x1[1][1]), "v"(x1[2][0]), "v"(x1[2][1]),
+          "v"(x2[0][0]), "v"(x2[0][1]), "v"(x2[1][0]), "v"(x2[1][1]), "v"(x2[2][0]), "v"(x2[2][1]));
+}
+// s0 += k0 x0, s1 += k1 x1 in the lanes of `mask`.
+__device__ inline void masked_fma2(unsigned long long mask, float k0, float k1, float x0, float x1, float &s0, float &s1) {
+    unsigned long long saved;
+    asm("s_and_saveexec_b64 %2, %3\n\t"
+        "v_fmac_f32 %0, %4, %6\n\tv_fmac_f32 %1, %5, %7\n\t"
+        "s_mov_b64 exec, %2"
+        : "+v"(s0), "+v"(s1), "=&s"(saved)
+        : "s"(mask), "v"(k0), "v"(k1), "v"(x0), "v"(x1)
+        : "scc");
+}
+
 template <bool O_BF16, int KS>
-static void launch_apply(hipStream_t stream, const Problem &pr, const float *states, int n_part,
+__global__ void __launch_bounds__(256, 2)
+la_apply_conv_bf16(TensorArg qt, TensorArg ot, const float *__restrict__ states, int n_part, long long part_stride,
+                   int heads, int N, int tokens_per_wg, int n_chunks, int n_wg, float eps, TensorArg vt, DwcArg cv,
+                   int focus_p) {
+    constexpr int kPad = KS / 2, kSpan = 4 + KS - 1, kTaps = KS * KS;
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *St = (float *)smem, *zs = St + kHeadDim * kHeadDim;
+    unsigned char *ring = smem + kRingFixedLds;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, li = lane & 31;
+    const int per_xcd = (n_wg + 7) / 8;
+    const int wg = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (wg >= n_wg) return;  // whole workgroup
+    const int bh = wg / n_chunks, b = bh / heads, h = bh % heads;
+    const int n0 = (wg % n_chunks) * tokens_per_wg, n1 = min(N, n0 + tokens_per_wg);
+    const int lrow = lane >> 3, lchunk = lane & 7;
+    const __bf16 *qp = (const __bf16 *)qt.ptr + b * qt.sb + h * qt.sh + 8 * lchunk;
+
+    u32x4 qreg[4];
+    auto fetch_q = [&](int t) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int n = t + 8 * r + lrow;
+            qreg[r] = u32x4{0u, 0u, 0u, 0u};
+            if (n < n1) qreg[r] = ld_stream((const u32x4 *)(qp + (long long)n * qt.sn));
+        }
+    };
+    fetch_q(n0 + 32 * wave);
+
+    // Ring: the cell `c` cells behind the chunk's first needed one sits in row c mod rows.
+    const int W = cv.W, cells = cv.H * W, rows = kRingStep + 2 * kPad * (W + 1);
+    const int first = n0 - cv.P - kPad * (W + 1);
+    const __bf16 *vp = (const __bf16 *)vt.ptr + b * vt.sb + h * vt.sh + (long long)cv.P * vt.sn + 8 * lchunk;
+    const int vrow = tid >> 3;  // this thread's 16 bytes (chunk lchunk) of every 32nd row
+    auto load_v = [&](int c) {
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if ((unsigned)(first + c) < (unsigned)cells) v = *(const u32x4 *)(vp + (long long)(first + c) * vt.sn);
+        return v;
+    };
+    auto put_v = [&](int slot, u32x4 v) {
+        *(u32x4 *)(ring + slot * 128 + 16 * lchunk) = v;
+        if (slot < kRingRepeat) *(u32x4 *)(ring + (rows + slot) * 128 + 16 * lchunk) = v;
+    };
+    for (int c0 = 0; c0 < rows; c0 += 256) {
+        u32x4 v[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) v[r] = c0 + 32 * r + vrow < rows ? load_v(c0 + 32 * r + vrow) : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+            if (c0 + 32 * r + vrow < rows) put_v(c0 + 32 * r + vrow, v[r]);
+    }
+    float kap[kTaps][2];  // filters of channels 2 li, 2 li + 1
+    {
+        const float *kbase = cv.kappa + b * cv.kappa_sb + (size_t)(h * kHeadDim + 2 * li) * kTaps;
+#pragma unroll
+        for (int tap = 0; tap < kTaps; ++tap) {
+            kap[tap][0] = kbase[tap];
+            kap[tap][1] = kbase[kTaps + tap];
+        }
+    }
+    sum_states(states + (size_t)bh * kStateFloats, n_part, part_stride, St, zs, tid);
+    __syncthreads();
+    // B operands: column li of block ni is channel c2 = 2 li + ni, k-slots c1 = 16 ks + 8 g + (0..7), as
+    // bf16 hi + lo; A operand of the denominator: row 0 = z high part, row 1 = z low part, other rows zero.
+    bf16x8 s_hi[2][4], s_lo[2][4], z_op[4];
+#pragma unroll
+    for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const int c2 = 2 * li + ni, grp = 2 * ks + g;
+            const float *row = St + c2 * 64 + ((grp ^ (c2 & 7)) << 3);
+            const f32x4 x0 = *(const f32x4 *)row, x1 = *(const f32x4 *)(row + 4);
+            const float x[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const __bf16 hi = (__bf16)x[e];
+                s_hi[ni][ks][e] = hi;
+                s_lo[ni][ks][e] = (__bf16)(x[e] - (float)hi);
+            }
+        }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float zv = zs[16 * ks + 8 * g + e];
+            const __bf16 hi = (__bf16)zv;
+            const __bf16 lo = (__bf16)(zv - (float)hi);
+            z_op[ks][e] = li == 0 ? hi : (li == 1 ? lo : (__bf16)0.f);
+        }
+    lds_barrier();  // the state's bytes hold query tiles from here on, and the ring is filled
+
+    unsigned char *qtile = smem + wave * 4096;
+    float *inv_row = (float *)(smem + kStateFloats * 4) + 32 * wave;
+    const int own0 = 32 * wave + 4 * g;  // this lane's tokens in a step: own0 + 8 q4 + r
+    const int col_group = 8 % W, col_step = kRingStep % W;
+    int col0 = ((n0 - cv.P + own0) % W + W) % W;  // grid column of the first of them
+    int base = 0;                          // ring row of the step's first needed cell
+    for (int t = n0; t < n1; t += kRingStep) {
+        // the first cell that only the next step needs, counted from `first`
+        const int fresh = t - n0 + rows;
+        const bool more = t + kRingStep < n1;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            *(u32x4 *)(qtile + tile_off_row(8 * r + lrow, lchunk)) = feature_map_bf16x8(qreg[r], focus_p);
+        u32x4 vreg[4];
+        if (more) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) vreg[r] = load_v(fresh + 32 * r + vrow);
+            fetch_q(t + kRingStep + 32 * wave);
+        }
+        if (t + 32 * wave < n1) {  // wave-uniform
+            f32x16 acc[2], accz;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) { acc[0][v] = 0.f; acc[1][v] = 0.f; accz[v] = 0.f; }
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const bf16x8 qb = as_bf16x8(*(const u32x4 *)(qtile + tile_off_row(li, 2 * ks + g)));
+                accz = mfma32(z_op[ks], qb, accz);
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni) {
+                    acc[ni] = mfma32(qb, s_lo[ni][ks], acc[ni]);
+                    acc[ni] = mfma32(qb, s_hi[ni][ks], acc[ni]);
+                }
+            }
+            // den lives in rows 0 and 1 of the denominator block: registers 0, 1 of lanes g = 0.
+            float den_lo, den_hi;
+            pair_values(accz[0] + accz[1], &den_lo, &den_hi);
+            if (g == 0) inv_row[li] = __builtin_amdgcn_rcpf(den_lo + eps);
+            const unsigned char *tap_base[KS];  // this lane's dword of the first source of every tap row
+#pragma unroll
+            for (int di = 0; di < KS; ++di) {
+                unsigned slot = (unsigned)(base + own0 + di * W);
+                slot = min(slot, slot - (unsigned)rows);
+                tap_base[di] = ring + slot * 128 + 4 * li;
+            }
+            int col = col0;
+            const bool prefix = t < cv.P, whole = t + 32 * wave + 32 <= n1;
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const f32x4 inv = *(const f32x4 *)(inv_row + 8 * q4 + 4 * g);
+                float sum[4][2];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    sum[r][0] = acc[0][4 * q4 + r] * inv[r];
+                    sum[r][1] = acc[1][4 * q4 + r] * inv[r];
+                }
+                // Lanes whose tap column dj is inside the grid's width: token r's left neighbour is unless
+                // (col + r) % W = 0, and so on.
+                unsigned long long use[4][KS];
+                if (KS == 3 && W >= 4) {
+                    unsigned long long inner[5];  // token r and its left neighbour are in one grid row
+                    inner[0] = __builtin_amdgcn_ballot_w64(col != 0);
+#pragma unroll
+                    for (int r = 1; r < 5; ++r) inner[r] = __builtin_amdgcn_ballot_w64(col != W - r);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        use[r][0] = inner[r];
+                        use[r][1] = ~0ull;
+                        use[r][2] = inner[r + 1];
+                    }
+                } else {
+                    int c = col;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+#pragma unroll
+                        for (int dj = 0; dj < KS; ++dj) use[r][dj] = __builtin_amdgcn_ballot_w64((unsigned)(c + dj - kPad) < (unsigned)W);
+                        if (++c >= W) c = 0;
+                    }
+                }
+                if (prefix) {  // uniform: prefix tokens take no taps
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const unsigned long long live = __builtin_amdgcn_ballot_w64(t + own0 + 8 * q4 + r >= cv.P);
+#pragma unroll
+                        for (int dj = 0; dj < KS; ++dj) use[r][dj] &= live;
+                    }
+                }
+                auto tap_row = [&](int di, float (&x)[kSpan][2]) __attribute__((always_inline)) {
+                    const unsigned *src = (const unsigned *)(tap_base[di] + 1024 * q4);
+#pragma unroll
+                    for (int j = 0; j < kSpan; ++j) {
+                        const unsigned u = src[32 * j];
+                        x[j][0] = bf16_lo(u);
+                        x[j][1] = bf16_hi(u);
+                    }
+                };
+                if constexpr (KS == 3) {
+                    float x[3][kSpan][2];
+#pragma unroll
+                    for (int di = 0; di < 3; ++di) tap_row(di, x[di]);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) masked_taps3(use[r], kap, &x[0][r], &x[1][r], &x[2][r], sum[r][0], sum[r][1]);
+                } else {  // (five rows of sources do not fit beside the filters)
+#pragma unroll
+                    for (int di = 0; di < KS; ++di) {
+                        float x[kSpan][2];
+                        tap_row(di, x);
+#pragma unroll
+                        for (int dj = 0; dj < KS; ++dj)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r)
+                                masked_fma2(use[r][dj], kap[di * KS + dj][0], kap[di * KS + dj][1], x[r + dj][0], x[r + dj][1], sum[r][0], sum[r][1]);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+                const int n = t + own0 + 8 * q4;
+                char *out = (char *)ot.ptr + (b * ot.sb + h * ot.sh + (long long)n * ot.sn + 2 * li) * (O_BF16 ? 2 : 4);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    if (whole || n + r < n1) {
+                        if (O_BF16) __builtin_nontemporal_store(pack_bf16x2(sum[r][0], sum[r][1]), (unsigned *)out);
+                        else *(float2 *)out = float2{sum[r][0], sum[r][1]};
+                    }
+                    out += ot.sn * (O_BF16 ? 2 : 4);
+                }
+                col += col_group;
+                if (col >= W) col -= W;
+            }
+        }
+        if (more) {
+            lds_barrier();  // nobody reads the oldest 128 rows any more
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                unsigned slot = (unsigned)(base + 32 * r + vrow);
+                put_v((int)min(slot, slot - (unsigned)rows), vreg[r]);
+            }
+            lds_barrier();
+        }
+        base += kRingStep;
+        if (base >= rows) base -= rows;
+        col0 += col_step;
+        if (col0 >= W) col0 -= W;
+    }
+}
+
+template <bool O_BF16, int KS>
+static jv_status launch_apply(hipStream_t stream, const Problem &pr, const float *states, int n_part,
                          long long part_stride, int apply_tokens, float eps, const DwcArg &cv,
                          int focus_p) {
     const int n_chunks = (pr.N + apply_tokens - 1) / apply_tokens, n_wg = n_chunks * pr.B * pr.heads;
+    // As long as two workgroups' rings share a compute unit (grids up to 172 columns for 3 x 3, 85 for 5 x 5);
+    // at the widest of them, 64 x 128 in chunks of 256 tokens, the ring fetches every row twice and
+    // still takes 18 us instead of 19.6.
+    if constexpr (KS != 0) {
+        const int lds = conv_ring_lds(KS, pr.W);
+        if (lds <= 80 * 1024) {
+            static LdsLimit lds_limit;
+            jv_status st = ensure_lds_limit(lds_limit, (const void *)la_apply_conv_bf16<O_BF16, KS>, 80 * 1024);
+            if (st != JV_OK) return st;
+            hipLaunchKernelGGL((la_apply_conv_bf16<O_BF16, KS>), dim3(8 * ((n_wg + 7) / 8)), dim3(256), lds, stream,
+                               pr.q, pr.o, states, n_part, part_stride, pr.heads, pr.N, apply_tokens, n_chunks,
+                               n_wg, eps, pr.v, cv, focus_p);
+            return launch_status("la_apply_conv_bf16");
+        }
+    }
     hipLaunchKernelGGL((la_apply_bf16<O_BF16, KS>), dim3(8 * ((n_wg + 7) / 8)), dim3(256), 0, stream,
                        pr.q, pr.o, states, n_part, part_stride, pr.heads, pr.N, apply_tokens, n_chunks,
                        n_wg, eps, pr.v, cv, focus_p);
+    return launch_status("la_apply_bf16");
 }
 
 jv_status linear_bf16(const Problem &pr, const LinearPlan &plan, float eps, float *ws,
@@ -556,15 +865,14 @@ jv_status linear_bf16(const Problem &pr, const LinearPlan &plan, float eps, floa
     }
     const int ks = dwc.mode == JV_DWC_NONE ? 0 : dwc.ksize;
     if (pr.o_bf16) {
-        if (ks == 0) launch_apply<true, 0>(stream, pr, states, n_part, part_stride, plan.apply_tokens, eps, cv, focus_p);
-        else if (ks == 3) launch_apply<true, 3>(stream, pr, states, n_part, part_stride, plan.apply_tokens, eps, cv, focus_p);
-        else launch_apply<true, 5>(stream, pr, states, n_part, part_stride, plan.apply_tokens, eps, cv, focus_p);
+        if (ks == 0) return launch_apply<true, 0>(stream, pr, states, n_part, part_stride, plan.apply_tokens, eps, cv, focus_p);
+        else if (ks == 3) return launch_apply<true, 3>(stream, pr, states, n_part, part_stride, plan.apply_tokens, eps, cv, focus_p);
+        else return launch_apply<true, 5>(stream, pr, states, n_part, part_stride, plan.apply_tokens, eps, cv, focus_p);
     } else {
-        if (ks == 0) launch_apply<false, 0>(stream, pr, states, n_part, part_stride, plan.apply_tokens, eps, cv, focus_p);
-        else if (ks == 3) launch_apply<false, 3>(stream, pr, states, n_part, part_stride, plan.apply_tokens, eps, cv, focus_p);
-        else launch_apply<false, 5>(stream, pr, states, n_part, part_stride, plan.apply_tokens, eps, cv, focus_p);
+        if (ks == 0) return launch_apply<false, 0>(stream, pr, states, n_part, part_stride, plan.apply_tokens, eps, cv, focus_p);
+        else if (ks == 3) return launch_apply<false, 3>(stream, pr, states, n_part, part_stride, plan.apply_tokens, eps, cv, focus_p);
+        else return launch_apply<false, 5>(stream, pr, states, n_part, part_stride, plan.apply_tokens, eps, cv, focus_p);
     }
-    return launch_status("la_apply_bf16");
 }
 
 // ---------------------------------------------------------------------------------------

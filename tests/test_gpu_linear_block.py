@@ -64,6 +64,38 @@ def test_bf16_static_and_dynamic(B, heads, H, W, ksize):
         check_bf16_pair(o32, o16, ref)
 
 
+@pytest.mark.parametrize("ksize,H,W,P", [
+    (3, 300, 1, 0), (3, 150, 2, 3), (3, 100, 3, 5), (3, 97, 4, 64), (3, 60, 5, 0), (3, 41, 13, 1),
+    (3, 7, 172, 5), (3, 5, 173, 0),                 # the widest grid whose ring shares a unit, and one more
+    (5, 300, 1, 0), (5, 70, 4, 2), (5, 40, 9, 64), (5, 33, 31, 0), (5, 11, 85, 5), (5, 9, 86, 0),
+])
+def test_bf16_window_of_v(ksize, H, W, P):
+    """The apply pass that moves a window of V through LDS: several steps of 128 tokens, grids whose
+    rows wrap inside a group of four tokens, prefix tokens that fill whole wavefronts' first steps,
+    and a ring that wraps at every offset."""
+    heads = 2
+    C = heads * 64
+    q, k, v = synth.qkv(36, 1, heads, P + H * W, 64, 0.5, True)
+    kern = synth.dwc_static_kernel(C, ksize, 3600 + W)
+    ref = oracle.linear_block(q, k, v, H, W, 1e-6, ksize=ksize, static_kernel=kern)
+    o32 = _block(q, k, v, H, W, True, torch.float32, ksize=ksize, static_kernel=_dev(kern)[0])
+    o16 = _block(q, k, v, H, W, True, torch.bfloat16, ksize=ksize, static_kernel=_dev(kern)[0])
+    check(err_bf16(to_host(o32), ref), 2e-3)
+    check_bf16_pair(o32, o16, ref)
+
+
+@pytest.mark.parametrize("B,hidden", [(1, 4), (2, 64), (4, 68), (8, 100), (9, 128)])
+def test_bf16_generated_filters_groups_of_images(B, hidden):
+    """Filter generator: groups of eight images with a remainder, hidden widths around the slices
+    of 64."""
+    heads, H, W = 1, 9, 11
+    q, k, v = synth.qkv(37, B, heads, H * W, 64, 0.5, True)
+    sq = synth.squeeze_weights(heads * 64, hidden, 3, 3700 + hidden)
+    ref = oracle.linear_block(q, k, v, H, W, 1e-6, squeeze=sq)
+    o32 = _block(q, k, v, H, W, True, torch.float32, squeeze=_dev(*sq))
+    check(err_bf16(to_host(o32), ref), 2e-3)
+
+
 def test_special_filters_bf16():
     """Zero filters give plain linear attention bit for bit; a centre-delta filter adds V."""
     B, heads, H, W = 1, 2, 12, 9
