@@ -30,10 +30,8 @@ __device__ inline int slot_token(const WindowGeom &g, int wy, int wx, int slot) 
 // step before) and wavefront (qw, kw) takes tile kw.  With KW > 1 the KW running softmaxes of a
 // query block are merged through LDS at the end.  KW = 4 cuts a problem of few queries into four
 // times as many wavefronts; KW = 1 stages a quarter of the bytes per flop.
-// Measured: 1 369 tokens x 12 heads 104 us (two workgroups fit a compute unit, and the last four of
-// 516 run alone for a third of the time), 2 304 tokens x 64 heads 798 us = 109 of 157 TFLOP/s.
-// (The kernel before this one scored one query per wavefront with plain FMAs and read V once
-// per query: 1 675 us for the first of these.)
+// Measured: 2 304 tokens x 64 heads 798 us = 109 TFLOP/s (a loop of these instructions alone reaches 138, at
+// the 2.1 GHz the chip holds under them).
 // Only the first q_slots query slots of every window are computed.
 // grid (ceil(q_slots / (32 QW)), n_win, B*heads), 256 threads.
 // ---------------------------------------------------------------------------------------
@@ -50,6 +48,55 @@ __device__ inline void f32_item(int &qblock, int &win, int &bh) {
     qblock = (int)(item % nx);
     win = (int)((item / nx) % ny);
     bh = (int)(item / (nx * ny));
+}
+
+// Tail of the fp32 kernels.  A wavefront without partners stores its rows ...
+__device__ inline void f32_store_row(const f32x16 (&acc)[2], float inv, float *row) {
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int v4 = 0; v4 < 4; ++v4) {
+            f32x4 out;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) out[e] = acc[cb][4 * v4 + e] * inv;
+            *(f32x4 *)(row + 32 * cb + 8 * v4) = out;
+        }
+}
+// ... and one with partners leaves its sums as [query][channel] rows of 256 bytes (chunks rotated by the row) for
+__device__ inline void f32_park(const f32x16 (&acc)[2], unsigned char *mine, int li, int half) {
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int v4 = 0; v4 < 4; ++v4) {
+            const f32x4 part = {acc[cb][4 * v4], acc[cb][4 * v4 + 1], acc[cb][4 * v4 + 2], acc[cb][4 * v4 + 3]};
+            *(f32x4 *)(mine + li * 256 + (((8 * cb + 2 * v4 + half) ^ (li & 15)) << 4)) = part;
+        }
+}
+// the merge of the KW softmaxes of each query block: O = sum_k 2^(m_k - M) acc_k / sum_k 2^(m_k - M) l_k.
+template <int KW, class Token>
+__device__ inline void f32_merge(const unsigned char *parts, const float (&ms)[4][32], const float (&ls)[4][32], int qblock, int q_slots,
+                                 Token token, float *op, long long sn, int tid) {
+    constexpr int QW = 4 / KW;
+    const int chunk = tid & 15, srow = tid >> 4;
+#pragma unroll
+    for (int i = 0; i < 2 * QW; ++i) {
+        const int query = srow + 16 * i, w0 = (query >> 5) * KW, ql = query & 31;
+        const int slot = qblock * (32 * QW) + query;
+        const int tok = slot < q_slots ? token(slot) : -1;
+        if (tok < 0) continue;
+        float top = ms[w0][ql];
+#pragma unroll
+        for (int k = 1; k < KW; ++k) top = fmaxf(top, ms[w0 + k][ql]);
+        f32x4 out = {0.f, 0.f, 0.f, 0.f};
+        float den = 0.f;
+#pragma unroll
+        for (int k = 0; k < KW; ++k) {
+            const float w = __builtin_amdgcn_exp2f(ms[w0 + k][ql] - top);
+            out += w * *(const f32x4 *)(parts + (w0 + k) * (32 * 256) + ql * 256 + ((chunk ^ (ql & 15)) << 4));
+            den = fmaf(w, ls[w0 + k][ql], den);
+        }
+        *(f32x4 *)(op + (long long)tok * sn + 4 * chunk) = out * (1.0f / den);
+    }
 }
 
 template <int KW>
@@ -184,54 +231,200 @@ attn_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, i
         l = lo + hi;
     }
     if (KW == 1) {
-        if (qtok < 0) return;
-        const float inv = 1.0f / l;
-        float *row = op + (long long)qtok * ot.sn + 4 * half;
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-            for (int v4 = 0; v4 < 4; ++v4) {
-                f32x4 out;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) out[e] = acc[cb][4 * v4 + e] * inv;
-                *(f32x4 *)(row + 32 * cb + 8 * v4) = out;
-            }
+        if (qtok >= 0) f32_store_row(acc, 1.0f / l, op + (long long)qtok * ot.sn + 4 * half);
         return;
     }
-    // Merge the KW softmaxes of each query block: O = sum_k 2^(m_k - M) acc_k / sum_k 2^(m_k - M) l_k.
     __syncthreads();
-    unsigned char *mine = tiles + wave * (32 * 256);
-#pragma unroll
-    for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4) {
-            const f32x4 part = {acc[cb][4 * v4], acc[cb][4 * v4 + 1], acc[cb][4 * v4 + 2], acc[cb][4 * v4 + 3]};
-            *(f32x4 *)(mine + li * 256 + (((8 * cb + 2 * v4 + half) ^ (li & 15)) << 4)) = part;
-        }
+    f32_park(acc, tiles + wave * (32 * 256), li, half);
     if (half == 0) {
         ms[wave][li] = m;
         ls[wave][li] = l;
     }
     __syncthreads();
+    f32_merge<KW>(tiles, ms, ls, qblock, q_slots, token, op, ot.sn, tid);
+}
+
+// attn_f32<4> with K and V fetched straight into operand registers: its wavefronts share queries and
+// no keys, so nothing is staged and the key loop has no barrier.  A contraction step takes channels
+// 8 i + 4 half + e (i = 0 .. 7, e = 0 .. 3): a lane's K and Q operands are 16-byte pieces of one row and an
+// instruction reads 32 bytes of every row; a V operand is one dword of a row, an instruction
+// two runs of 128 bytes.  Half tiles of K and V rotate through three sets of sixteen registers, each
+// fetched while the matrix instructions of two others run (1 024 cycles each); with no LDS but the merge's
+// and 168 registers three workgroups fit a compute unit.  Against attn_f32<4>, us: 1 369 tokens x 12 heads
+// 104.6 -> 89.9 (516 workgroups: four units have three and the others two; x 11 68.7 -> 60.9), 256 x 6 10.6 -> 9.7,
+// 1 025 + 5 x 36 139 -> 114, windows of 14 x 14 on 40 x 40 x 24 49.4 -> 39.4.  The matrix instructions are 44 us of the 61.
+// (Two chains of score products instead of one: the same; two workgroups per unit and more registers: the same.)
+// grid (ceil(q_slots / 32), n_win, B*heads), 256 threads.  Byte offsets inside a (batch, head) slice of K
+// and V below 2^32.
+__global__ void __launch_bounds__(256, 3)
+attn_direct_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, int heads,
+                float scale_log2, int q_slots) {
+    constexpr int KW = 4;
+    __shared__ __align__(16) unsigned char parts[4 * 32 * 256];
+    __shared__ float ms[4][32], ls[4][32];
+    const int tid = threadIdx.x, kw = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, li = lane & 31;
+    int qblock, win, bh;
+    f32_item(qblock, win, bh);
+    const int b = bh / heads, h = bh % heads, wy = win / g.wins_x, wx = win % g.wins_x;
+    const float *qp = (const float *)qt.ptr + b * qt.sb + h * qt.sh;
+    const char *kp = (const char *)((const float *)kt.ptr + b * kt.sb + h * kt.sh);  // (uniform)
+    const char *vp = (const char *)((const float *)vt.ptr + b * vt.sb + h * vt.sh);
+    const unsigned ksn = 4u * (unsigned)kt.sn, vsn = 4u * (unsigned)vt.sn;
+    const unsigned vlane = 4u * half * vsn + 4u * li;
+    const int first = wy * g.wh * g.W + wx * g.ww;  // the window's first token: always real
+    const bool rows = g.ww == g.W;                  // windows of whole grid rows: slots are consecutive tokens
+    auto token = [&](int slot) {
+        if (!rows) return slot_token(g, wy, wx, slot);
+        return slot < g.slots && first + slot < g.H * g.W ? first + slot : -1;
+    };
+    f32x4 q[8];
+    {
+        const int slot = qblock * 32 + li, qtok = slot < q_slots ? token(slot) : -1;
+        const float *row = qp + (long long)(qtok < 0 ? first : qtok) * qt.sn + 4 * half;
 #pragma unroll
-    for (int i = 0; i < 2 * QW; ++i) {
-        const int query = srow + 16 * i, w0 = (query >> 5) * KW, ql = query & 31;
-        const int slot = qblock * (32 * QW) + query;
-        const int tok = slot < q_slots ? token(slot) : -1;
-        if (tok < 0) continue;
-        float top = ms[w0][ql];
-#pragma unroll
-        for (int k = 1; k < KW; ++k) top = fmaxf(top, ms[w0 + k][ql]);
-        f32x4 out = {0.f, 0.f, 0.f, 0.f};
-        float den = 0.f;
-#pragma unroll
-        for (int k = 0; k < KW; ++k) {
-            const float w = __builtin_amdgcn_exp2f(ms[w0 + k][ql] - top);
-            out += w * *(const f32x4 *)(tiles + (w0 + k) * (32 * 256) + ql * 256 + ((chunk ^ (ql & 15)) << 4));
-            den = fmaf(w, ls[w0 + k][ql], den);
-        }
-        *(f32x4 *)(op + (long long)tok * ot.sn + 4 * chunk) = out * (1.0f / den);
+        for (int i = 0; i < 8; ++i) q[i] = *(const f32x4 *)(row + 8 * i);
     }
+    f32x16 acc[2];  // channels 32 cb + 8 (v / 4) + 4 half + v % 4 of query li
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[0][i] = acc[1][i] = 0.f;
+    float m = -1.0e30f, l = 0.f;  // (finite stand-in for "no maximum yet")
+    const int n_tile = (g.slots + 31) / 32;
+    float set[3][16];
+    // K operands of steps 4 hf .. + 3 of the tile whose key li is token `tok` (negative: padding)
+    auto fetch_k = [&](float (&r)[16], int tok, int hf) __attribute__((always_inline)) {
+        const unsigned at = (unsigned)(tok < 0 ? first : tok) * ksn + 16u * half;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const f32x4 x = *(const f32x4 *)(kp + at + 32 * (4 * hf + i));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r[4 * i + e] = x[e];
+        }
+    };
+    // r[2 j + cb]: channel 32 cb + li of key 16 hf + 8 (j / 4) + 4 half + j % 4
+    auto fetch_v = [&](float (&r)[16], int tok, unsigned pad, int hf) __attribute__((always_inline)) {
+        if (rows && pad == 0u) {
+            const char *row = vp + (unsigned)(__builtin_amdgcn_readfirstlane(tok) + 16 * hf) * (size_t)vsn;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                r[2 * j] = *(const float *)(row + vlane);
+                r[2 * j + 1] = *(const float *)(row + vlane + 128);
+                row += (j == 3 ? 5 : 1) * (size_t)vsn;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int t = __shfl(tok, 16 * hf + 8 * (j / 4) + 4 * half + j % 4, 64);
+                const unsigned at = (unsigned)(t < 0 ? first : t) * vsn + 4u * li;
+                r[2 * j] = *(const float *)(vp + at);
+                r[2 * j + 1] = *(const float *)(vp + at + 128);
+            }
+            // (keeps the two branches' loads apart: merged into one set they would take every address
+            // in a vector register of its own)
+            asm volatile("");
+        }
+    };
+    auto real_token = [&](int tile, int &tok, unsigned &pad) __attribute__((always_inline)) {
+        tok = token(32 * tile + li);
+        pad = (unsigned)__builtin_amdgcn_ballot_w64(tok < 0);  // bit j: key j of the tile is padding
+    };
+    int tok = 0;
+    unsigned pad = 0u;
+    // A tile whose K operands are in (or on their way to) ka and kb; leaves those of tile + KW in kb and vc.
+    auto run_tile = [&](int tile, float (&ka)[16], float (&kb)[16], float (&vc)[16]) __attribute__((always_inline)) {
+        const int cur = tok;
+        const unsigned cur_pad = pad, pads = half ? pad >> 4 : pad;
+        const bool more = tile + KW < n_tile;
+        fetch_v(vc, cur, cur_pad, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        f32x16 s;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[i], q[i / 4][i % 4], s, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch_v(ka, cur, cur_pad, 1);
+        if (more) real_token(tile + KW, tok, pad);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kb[i], q[4 + i / 4][i % 4], s, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) fetch_k(kb, tok, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (cur_pad != 0u) {  // (uniform) padded keys have no weight ...
+#pragma unroll
+            for (int j = 0; j < 16; ++j) s[j] = (pads >> (8 * (j / 4) + j % 4)) & 1u ? -INFINITY : s[j];
+        }
+        // The reference stays while no logit is more than 8 binary orders above it (numerator and
+        // denominator share it, so the result is the same), and goes up to the maximum otherwise.
+        float top = s[0];
+#pragma unroll
+        for (int j = 1; j < 16; ++j) top = fmaxf(top, s[j]);
+        if (__any(top * scale_log2 > m + 8.0f)) {
+            float lo, hi;
+            pair_values(top, &lo, &hi);
+            const float m_new = fmaxf(m, fmaxf(lo, hi) * scale_log2), alpha = __builtin_amdgcn_exp2f(m - m_new);
+            m = m_new;
+            l *= alpha;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                acc[0][j] *= alpha;
+                acc[1][j] *= alpha;
+            }
+        }
+        float sum = 0.f;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            s[j] = __builtin_amdgcn_exp2f(fmaf(s[j], scale_log2, -m));
+            sum += s[j];
+        }
+        l += sum;
+        auto product = [&](float (&r)[16], int hf) __attribute__((always_inline)) {
+            if (cur_pad != 0u) {  // ... and zeros for the values they meet (0 x inf would be NaN)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const bool p = (pads >> (16 * hf + 8 * (j / 4) + j % 4)) & 1u;
+                    r[2 * j] = p ? 0.f : r[2 * j];
+                    r[2 * j + 1] = p ? 0.f : r[2 * j + 1];
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(r[2 * j], s[8 * hf + j], acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(r[2 * j + 1], s[8 * hf + j], acc[1], 0, 0, 0);
+            }
+        };
+        product(vc, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) fetch_k(vc, tok, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        product(ka, 1);
+    };
+    if (kw < n_tile) {
+        real_token(kw, tok, pad);
+        fetch_k(set[0], tok, 0);
+        fetch_k(set[1], tok, 1);
+        for (int tile = kw;;) {
+            run_tile(tile, set[0], set[1], set[2]);
+            if ((tile += KW) >= n_tile) break;
+            run_tile(tile, set[1], set[2], set[0]);
+            if ((tile += KW) >= n_tile) break;
+            run_tile(tile, set[2], set[0], set[1]);
+            if ((tile += KW) >= n_tile) break;
+        }
+    }
+    {
+        float lo, hi;
+        pair_values(l, &lo, &hi);
+        l = lo + hi;
+    }
+    f32_park(acc, parts + kw * (32 * 256), li, half);
+    if (half == 0) {
+        ms[kw][li] = m;
+        ls[kw][li] = l;
+    }
+    __syncthreads();
+    float *op = (float *)ot.ptr + b * ot.sb + h * ot.sh;
+    f32_merge<KW>(parts, ms, ls, qblock, q_slots, token, op, ot.sn, tid);
 }
 
 // Windows of a few slots, of which a 32 x 32 tile would be padding but for a corner: sixteen lanes per
@@ -297,7 +490,14 @@ static jv_status attn_dispatch(const Problem &pr, const WindowGeom &g, float sca
     // over two or four wavefronts, if it has tiles for them.
     const long long waves = (long long)((q_slots + 31) / 32) * g.n_win * pr.B * pr.heads;
     const int tiles = (g.slots + 31) / 32;
-    if (waves < 2048 && tiles > 2) return launch_attn_f32<4>(pr, g, scale, q_slots, stream);
+    if (waves < 2048 && tiles > 2) {
+        const long long max_sn = pr.k.sn > pr.v.sn ? pr.k.sn : pr.v.sn;
+        if (((long long)g.H * g.W + 64) * max_sn * 4 >= (1ll << 32))  // attn_direct_f32 counts bytes in 32 bits
+            return launch_attn_f32<4>(pr, g, scale, q_slots, stream);
+        hipLaunchKernelGGL(attn_direct_f32, dim3((unsigned)((q_slots + 31) / 32), g.n_win, pr.B * pr.heads), dim3(256), 0, stream,
+                           pr.q, pr.k, pr.v, pr.o, g, pr.heads, scale * 1.4426950408889634f, q_slots);
+        return launch_status("attn_direct_f32");
+    }
     if (waves < 4096 && tiles > 1) return launch_attn_f32<2>(pr, g, scale, q_slots, stream);
     return launch_attn_f32<1>(pr, g, scale, q_slots, stream);
 }

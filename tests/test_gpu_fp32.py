@@ -67,6 +67,28 @@ def test_attention_tile_edges(B, heads, H, W, window):
 
 
 @pytest.mark.parametrize("H,W,window,P", [
+    (1, 65, None, 0), (1, 96, None, 0), (1, 97, None, 0), (1, 128, None, 0), (1, 129, None, 0),  # 3 to 5 tiles on 4 wavefronts
+    (1, 383, None, 1), (20, 21, None, 5),    # prefix tokens: key counts 384, 425
+    (20, 30, (9, 11), 0), (20, 30, (12, 30), 2), (11, 13, (11, 8), 64),  # windows: ragged, of whole rows, with prefix queries
+])
+def test_keys_split_over_wavefronts(H, W, window, P):
+    """Launches of few queries (the keys split over the wavefronts of a workgroup), with logits that
+    climb along the sequence so that the softmax reference goes up in late tiles too."""
+    N = P + H * W
+    q, k, v = synth.qkv(44, 1, 2, N, 64, 1.0, False)
+    k = (k * np.linspace(0.2, 6.0, N, dtype=np.float32)[None, None, :, None]).astype(np.float32)
+    dq, dk, dv = (to_device(x, False) for x in (q, k, v))
+    o = torch.full(dq.shape, float("nan"), device="cuda")
+    if window is None:
+        binding.jv_full_attn_fwd(dq, dk, dv, o, (H, W))
+        ref = oracle.full_attn(q, k, v)
+    else:
+        binding.jv_window_attn_fwd(dq, dk, dv, o, (H, W), window)
+        ref = oracle.window_attn_prefix(q, k, v, P, H, W, *window)
+    check(err_fp32(to_host(o), ref), FP32_TOL)
+
+
+@pytest.mark.parametrize("H,W,window,P", [
     (5, 7, (1, 1), 0),         # every token alone: the result is its value row
     (5, 7, (1, 2), 0), (7, 5, (3, 1), 3), (9, 11, (2, 2), 5), (6, 6, (2, 4), 0), (3, 5, (4, 2), 0),
     (9, 11, (3, 3), 0),        # one slot more: the tiles
