@@ -799,20 +799,20 @@ constexpr int kRing = 3;
 // are at vaddr + VOFF, and if KNEXT >= 0 the K operands at kaddr + KNEXT are read into `ka`
 // under the exponentials.  MASKED: the tile's keys are keys krow0 .. +31 of their stage, and
 // keys with index (inside the stage) >= key_limit are padding.
-template <int KNEXT, bool MASKED, int VOFF>
-__device__ __forceinline__ void ring_tile32(WaveState<2> &w, const u32x4 (&qreg)[2][4], u32x4 (&ka)[4],
+template <int NT, int KNEXT, bool MASKED, int VOFF>
+__device__ __forceinline__ void ring_tile32(WaveState<NT> &w, const u32x4 (&qreg)[NT][4], u32x4 (&ka)[4],
                                    const unsigned (&kaddr)[4], const unsigned (&vaddr)[2],
                                    int krow0, int key_limit, float c, int lane) {
     const int g = lane >> 5;
-    f32x16 s[2];
+    f32x16 s[NT];
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int v = 0; v < 16; ++v) s[nt][v] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) s[nt] = mfma32(as_bf16x8(ka[ks]), as_bf16x8(qreg[nt][ks]), s[nt]);
+        for (int nt = 0; nt < NT; ++nt) s[nt] = mfma32(as_bf16x8(ka[ks]), as_bf16x8(qreg[nt][ks]), s[nt]);
     __builtin_amdgcn_sched_barrier(0);  // the score products are issued before the reads below
     u32x4 va[2][2];
     load_vt_operands<VOFF>(va, vaddr);
@@ -823,25 +823,28 @@ __device__ __forceinline__ void ring_tile32(WaveState<2> &w, const u32x4 (&qreg)
         for (int v = 0; v < 16; ++v) {
             const bool pad = krow0 + 8 * (v / 4) + 4 * g + (v % 4) >= key_limit;
 #pragma unroll
-            for (int nt = 0; nt < 2; ++nt) s[nt][v] = pad ? -INFINITY : s[nt][v];
+            for (int nt = 0; nt < NT; ++nt) s[nt][v] = pad ? -INFINITY : s[nt][v];
         }
     }
     // Lazy softmax reference, as in attn_tile32, with one test for both query blocks.
-    unsigned pk[2][8];
-    float sum0 = exp_block(s[0], pk[0], c, -w.m[0]);
-    float sum1 = exp_block(s[1], pk[1], c, -w.m[1]);
-    if (__builtin_amdgcn_ballot_w64(!(sum0 <= kLazySum) || !(sum1 <= kLazySum)) != 0) {  // NaN too
-        if (__builtin_amdgcn_ballot_w64(!(sum0 <= kLazySum)) != 0) {
-            raise_reference<2>(w, 0, s[0], c);
-            sum0 = exp_block(s[0], pk[0], c, -w.m[0]);
-        }
-        if (__builtin_amdgcn_ballot_w64(!(sum1 <= kLazySum)) != 0) {
-            raise_reference<2>(w, 1, s[1], c);
-            sum1 = exp_block(s[1], pk[1], c, -w.m[1]);
-        }
+    unsigned pk[NT][8];
+    float sum[NT];
+    bool large = false;  // NaN too
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        sum[nt] = exp_block(s[nt], pk[nt], c, -w.m[nt]);
+        large = large || !(sum[nt] <= kLazySum);
     }
-    w.l[0] += sum0;
-    w.l[1] += sum1;
+    if (__builtin_amdgcn_ballot_w64(large) != 0) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            if (NT == 1 || __builtin_amdgcn_ballot_w64(!(sum[nt] <= kLazySum)) != 0) {
+                raise_reference<NT>(w, nt, s[nt], c);
+                sum[nt] = exp_block(s[nt], pk[nt], c, -w.m[nt]);
+            }
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) w.l[nt] += sum[nt];
     if (KNEXT >= 0) lds_reads_landed(va[0], va[1], ka);
     else lds_reads_landed(va[0][0], va[0][1], va[1][0], va[1][1]);
 #pragma unroll
@@ -849,14 +852,14 @@ __device__ __forceinline__ void ring_tile32(WaveState<2> &w, const u32x4 (&qreg)
 #pragma unroll
         for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
+            for (int nt = 0; nt < NT; ++nt) {
                 u32x4 pb = {pk[nt][4 * kk], pk[nt][4 * kk + 1], pk[nt][4 * kk + 2], pk[nt][4 * kk + 3]};
                 w.acc[mi][nt] = mfma32(as_bf16x8(va[kk][mi]), as_bf16x8(pb), w.acc[mi][nt]);
             }
 }
 
-template <bool O_BF16>
-__global__ void __launch_bounds__(256, 2) attn_ring_bf16(AttnArgs a) {
+template <bool O_BF16, int NT>
+__global__ void __launch_bounds__(256, NT == 1 ? 3 : 2) attn_ring_bf16(AttnArgs a) {
     // the logit scale, fetched (a kernel argument) and waited for here, not inside the key loop
     float c_log2 = a.c;
     asm volatile("" : "+s"(c_log2));
@@ -866,17 +869,17 @@ __global__ void __launch_bounds__(256, 2) attn_ring_bf16(AttnArgs a) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     RingItem it;
-    if (!ring_item(a, 64 * WAVES, it)) return;  // whole workgroup
+    if (!ring_item(a, 32 * NT * WAVES, it)) return;  // whole workgroup
     const int bh = it.bh, b = bh / a.heads, h = bh % a.heads;
     const int win = it.win, wy = win / a.g.wins_x, wx = win % a.g.wins_x;
-    const int q0 = it.qblock * (64 * WAVES) + wave * 64;
+    const int q0 = it.qblock * (32 * NT * WAVES) + wave * (32 * NT);
     const long long qbase = b * a.q.sb + h * a.q.sh, obase = b * a.o.sb + h * a.o.sh;
     const bool wave_live = q0 < a.q_slots;
 
-    u32x4 qreg[2][4];
-    load_queries<2>(qreg, a, wy, wx, q0, qbase, lane);
-    WaveState<2> w;
-    wave_state_init<2>(w);
+    u32x4 qreg[NT][4];
+    load_queries<NT>(qreg, a, wy, wx, q0, qbase, lane);
+    WaveState<NT> w;
+    wave_state_init<NT>(w);
 
     // Key slots of the window that hold tokens: slot s is token tok_first + s.
     const int tok_first = wy * a.g.wh * a.g.W;
@@ -949,10 +952,10 @@ __global__ void __launch_bounds__(256, 2) attn_ring_bf16(AttnArgs a) {
     auto full_stage = [&](int st, auto slot_tag) {
         constexpr int slot = decltype(slot_tag)::value, after = (slot + 1) % kRing;
         if (wave_live)
-            ring_tile32<slot * kStageBytes + 32 * 128, false, slot * kStageBytes>(w, qreg, ka, kaddr, vaddr, 0, 0, c_log2, lane);
+            ring_tile32<NT, slot * kStageBytes + 32 * 128, false, slot * kStageBytes>(w, qreg, ka, kaddr, vaddr, 0, 0, c_log2, lane);
         next_stage_ready(st);
         if (wave_live)  // (after the window's last stage the K operands read here are not used)
-            ring_tile32<after * kStageBytes, false, slot * kStageBytes + 32 * 128>(w, qreg, ka, kaddr, vaddr, 32, 0, c_log2, lane);
+            ring_tile32<NT, after * kStageBytes, false, slot * kStageBytes + 32 * 128>(w, qreg, ka, kaddr, vaddr, 32, 0, c_log2, lane);
     };
 
     if (n_stage > 0) issue(0);
@@ -962,7 +965,7 @@ __global__ void __launch_bounds__(256, 2) attn_ring_bf16(AttnArgs a) {
     else if (n_stage > 1) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();  // stage 0 has landed
-    queries_landed<2>(qreg);  // (older than the loads of stage 0)
+    queries_landed<NT>(qreg);  // (older than the loads of stage 0)
     load_k_operands<0>(ka, kaddr);
     k_operands_landed(ka);
     int st = 0;
@@ -990,17 +993,17 @@ __global__ void __launch_bounds__(256, 2) attn_ring_bf16(AttnArgs a) {
         const unsigned klast[4] = {kaddr[0] + at, kaddr[1] + at, kaddr[2] + at, kaddr[3] + at};
         const int key_limit = tok_limit - st * kStage;  // 1 .. 63
         if (key_limit > 32) {
-            ring_tile32<32 * 128, true, 0>(w, qreg, ka, klast, vlast, 0, key_limit, c_log2, lane);
-            ring_tile32<-1, true, 32 * 128>(w, qreg, ka, klast, vlast, 32, key_limit, c_log2, lane);
+            ring_tile32<NT, 32 * 128, true, 0>(w, qreg, ka, klast, vlast, 0, key_limit, c_log2, lane);
+            ring_tile32<NT, -1, true, 32 * 128>(w, qreg, ka, klast, vlast, 32, key_limit, c_log2, lane);
         } else {
-            ring_tile32<-1, true, 0>(w, qreg, ka, klast, vlast, 0, key_limit, c_log2, lane);
+            ring_tile32<NT, -1, true, 0>(w, qreg, ka, klast, vlast, 0, key_limit, c_log2, lane);
         }
     }
     __syncthreads();  // every wavefront is done with the ring: reuse it as staging
     if (wave_live) {
         AttnArgs st = a;
         st.g.slots = a.q_slots;  // query slots past the limit are not stored
-        wave_store<O_BF16, 2>(w, st, wy, wx, q0, obase, smem + wave * 4096, lane);
+        wave_store<O_BF16, NT>(w, st, wy, wx, q0, obase, smem + wave * 4096, lane);
     }
 }
 
@@ -1075,8 +1078,8 @@ __global__ void __launch_bounds__(512, 1) attn_prefix_bf16(AttnArgs a) {
         k_operands_landed(ka);
         // (one masked tile code for whole and partial stages: this kernel waits for its loads,
         // not for its arithmetic)
-        ring_tile32<32 * 128, true, 0>(w, qreg, ka, kaddr, vaddr, 0, key_limit, c_log2, ln);
-        if (key_limit > 32) ring_tile32<-1, true, 32 * 128>(w, qreg, ka, kaddr, vaddr, 32, key_limit, c_log2, ln);
+        ring_tile32<2, 32 * 128, true, 0>(w, qreg, ka, kaddr, vaddr, 0, key_limit, c_log2, ln);
+        if (key_limit > 32) ring_tile32<2, -1, true, 32 * 128>(w, qreg, ka, kaddr, vaddr, 32, key_limit, c_log2, ln);
     }
 
     // Partial results into LDS: the accumulators as [query][channel] fp32 in the wavefront's own
@@ -1751,21 +1754,27 @@ jv_status attn_bf16(const Problem &pr, const WindowGeom &g, float scale, int q_s
     if (fast && !all_queries && a.q_slots <= 64 && g.n_win == 1)
         return pr.o_bf16 ? launch_prefix<true>(a, pr.B * pr.heads, stream)
                          : launch_prefix<false>(a, pr.B * pr.heads, stream);
-    // At most half the compute units with a block of 256 queries: blocks of 128 on the streaming kernel, which are twice
-    // as many (same tiles of 32 keys in the same order: the same bits).  A lone wavefront per SIMD waits for itself
-    // either way, but with half the arithmetic between its waits.  Blocks of 256 / of 128, us: 12 blocks (200 tokens) 9.6 / 8.1,
-    // 48 (784 tokens) 21.2 / 18.8, 96 (1 374 tokens) 33.0 / 30.2, 128 (2 048 tokens) 45.6 / 42.6, but 192 (1 374 tokens)
-    // 33.0 / 38.7: some units get two of the small blocks there and one of the large.  However many the keys: one head
-    // of 4 096 tokens 84 / 76, of 32 768 641 / 585; windows of 512 of 4 096 tokens x 6 heads 15.4 / 12.8.
-    const long long blocks = (long long)((a.q_slots + 255) / 256) * g.n_win * a.n_bh;
-    if (fast && NT == 2 && blocks <= 128) {
-        if (pr.o_bf16) hipLaunchKernelGGL((attn_stream_bf16<true, 1>), ring_grid(a, 128), dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((attn_stream_bf16<false, 1>), ring_grid(a, 128), dim3(256), 0, stream, a);
-        return launch_status("attn_stream_bf16");
+    // The ring kernel with two blocks of 32 queries per wavefront or with one (the same bits): two workgroups of
+    // 256 queries on a compute unit do the most per second, but three of 128 come close, and the smaller
+    // blocks leave fewer units with less than their share.  Time of a launch's last round by the workgroups
+    // a unit has in it, and of a full round, as measured at 1 374 keys, us: 256 queries 32.6 (one), 45.4 (two);
+    // 128 queries 21.6, 28.4, 38.5 (three).  Two blocks / one, us: 1 374 tokens x 16 heads 20.2 / 14.3, x 32 32.6 / 28.4,
+    // x 48 45.2 / 36.2, 5 184 x 16 151 / 130, 8 192 x 16 257 / 291, 4 096 x 64 260 / 281, x 128 515 / 550.
+    const long long lanes = (long long)g.n_win * a.n_bh;
+    const long long blocks2 = (a.q_slots + 255) / 256 * lanes, blocks1 = (a.q_slots + 127) / 128 * lanes;
+    const auto last = [](long long rest, float one, float two, float three) {
+        return rest == 0 ? 0.f : rest <= 256 ? one : rest <= 512 ? two : three;
+    };
+    const float t2 = (float)(blocks2 / 512) * 45.4f + last(blocks2 % 512, 32.6f, 45.4f, 0.f);
+    const float t1 = (float)(blocks1 / 768) * 38.5f + last(blocks1 % 768, 21.6f, 28.4f, 38.5f);
+    if (fast && NT == 2 && 1.08f * t1 < t2) {  // (rounds overlap, to the large blocks' advantage)
+        if (pr.o_bf16) hipLaunchKernelGGL((attn_ring_bf16<true, 1>), ring_grid(a, 128), dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((attn_ring_bf16<false, 1>), ring_grid(a, 128), dim3(256), 0, stream, a);
+        return launch_status("attn_ring_bf16");
     }
     if (fast && NT == 2) {
-        if (pr.o_bf16) hipLaunchKernelGGL((attn_ring_bf16<true>), ring_grid(a, 256), dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((attn_ring_bf16<false>), ring_grid(a, 256), dim3(256), 0, stream, a);
+        if (pr.o_bf16) hipLaunchKernelGGL((attn_ring_bf16<true, 2>), ring_grid(a, 256), dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((attn_ring_bf16<false, 2>), ring_grid(a, 256), dim3(256), 0, stream, a);
         return launch_status("attn_ring_bf16");
     }
     if (pr.o_bf16)

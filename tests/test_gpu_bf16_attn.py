@@ -45,6 +45,22 @@ def test_full_attention_small_shapes(B, heads, H, W, vscale):
     check_bf16_pair(_full(q, k, v, H, W, torch.float32), _full(q, k, v, H, W), ref)
 
 
+@pytest.mark.parametrize("N", [31, 32, 33, 64, 65, 127, 128, 129, 160, 191, 193, 257])
+def test_query_blocks_of_either_size_give_the_same_bits(N):
+    """One image takes workgroups of 128 queries, 512 copies of it those of 256: the same bits, and
+    the oracle's values (logits that climb along the sequence, so that the reference goes up in late tiles)."""
+    q, k, v = synth.qkv(38, 1, 1, N, 64, 0.5, True)
+    k = synth.round_to_bf16((k * np.linspace(0.2, 8.0, N, dtype=np.float32)[None, None, :, None]).astype(np.float32))
+    one = _full(q, k, v, 1, N, torch.float32)
+    # A probability rounded to bf16 is off by at most 2^-9 of itself, the sum of probabilities is not
+    # rounded: an element is off by at most 2^-9 max |V| (and fp32 sums).  With one key in charge of
+    # most rows that bound is reached, where the general bar of 2e-2 RMS assumes many.
+    ref = oracle.full_attn(q, k, v)
+    check(err_bf16(to_host(one), ref), 2.0 ** -9 * float(np.abs(v).max()) / float(np.sqrt(np.mean(ref * ref))) + 1e-4)
+    many = _full(*(np.repeat(x, 512, axis=0) for x in (q, k, v)), 1, N, torch.float32)
+    assert torch.equal(many, one.expand_as(many))
+
+
 @pytest.mark.parametrize("B,heads,H,W,window,vscale", [
     (2, 2, 16, 16, (8, 8), 1.0),      # config-1 geometry in bf16
     (1, 2, 37, 37, (8, 8), 0.125),    # padded 40 x 40, windows of 64 / 40 / 25 real tokens
