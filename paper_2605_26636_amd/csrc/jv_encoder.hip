@@ -622,11 +622,14 @@ static jv_status launch_gemm(const void *a, const void *w, const float *bias, co
 // 64-deep block costs about 0.22, 0.33, 0.35, 0.56 and 1.15 us on 64 x 64, 64 x 128, 128 x 128, 256 x 128 and
 // 256 x 256 tiles, i.e. the larger the tile the nearer to the matrix rate.  So: the largest tile that
 // fills the chip, below that the smallest that leaves no unit with two tiles while others have one.
+// 256 x 192 tiles (fitted afterwards on 180 products of 1 374 to 20 000 rows: without them the choice was 2.8 % off the
+// best, with them 0.4 %) take launches that the large tiles would end with a round of few: QKV of width 1024
+// on 2 750 rows 26.6 -> 23.2 us, on 5 476 48.2 -> 44.2, on 8 192 58.6 -> 54.5, on 10 952 84.1 -> 76.2; fc2 on 20 000 187 -> 178.
 // Products of a block of width 1024 on the tiles chosen, us (PFLOP/s), operands not in the L2:
 //     rows      QKV          projection   fc1          fc2 (not split)
 //     1 374     18.8 (0.46)  10.3 (0.28)  22.5 (0.51)  31.5 (0.37)
-//     4 096     32.0 (0.81)  16.9 (0.51)  38.7 (0.89)  42.4 (0.81)
-//     8 192     61.2 (0.84)  26.9 (0.64)  75.5 (0.91)  66.8 (1.03)
+//     4 096     27.9 (0.92)  16.9 (0.51)  38.7 (0.89)  42.4 (0.81)
+//     8 192     54.5 (0.95)  26.9 (0.64)  75.5 (0.91)  66.8 (1.03)
 //     16 384    100 (1.03)   43.2 (0.80)  148 (0.93)   119 (1.16)
 struct TileModel {
     int bm, bn, slots;    // slots: workgroups that fit the chip
@@ -639,6 +642,7 @@ constexpr TileModel kTileModels[kGemmTileShapes] = {
     {128, 128, 512, 0.554f, 0.702f, 0.40f},   // kTile128x128
     {64, 128, 512, 0.283f, 0.620f, 0.21f},    // kTile64x128
     {64, 64, 512, 0.212f, 0.518f, 0.24f},     // kTile64x64
+    {256, 192, 256, 0.453f, 0.897f, 0.90f},   // kTile256x192
 };
 struct GemmPlan {
     GemmTile tile;
@@ -653,7 +657,7 @@ static GemmPlan plan_gemm(long long M, int N, int K, int max_split, int parts = 
         const TileModel &m = kTileModels[c];
         const long long tiles = ((M + m.bm - 1) / m.bm) * ((N + m.bn - 1) / m.bn);
         for (int split = 1; split <= max_split; split *= 2) {
-            if (split > 1 && (c == kTile256x256 || K / 64 < 2 * split)) break;
+            if (split > 1 && (c == kTile256x256 || c == kTile256x192 || K / 64 < 2 * split)) break;
             if (parts > 1 && split != parts && !(split == 1 && (c == kTile256x128 || c == kTile128x128Deep || c == kTile64x128))) continue;
             const long long n = tiles * split, rounds = n / m.slots, rest = n % m.slots;
             const float blocks = (float)((K / 64 + split - 1) / split);

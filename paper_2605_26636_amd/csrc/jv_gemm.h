@@ -28,7 +28,7 @@ __device__ inline float normal_cdf(float x) {
 // Tile shapes (tokens x features): the kernel of jv_encoder.hip, then those of jv_gemm_tiles.hip
 // (128 x 128 in two forms: a deep operand ring with one workgroup per compute unit, a short one
 // with two).
-enum GemmTile { kTile256x256 = 0, kTile256x128, kTile128x128Deep, kTile128x128, kTile64x128, kTile64x64, kGemmTileShapes };
+enum GemmTile { kTile256x256 = 0, kTile256x128, kTile128x128Deep, kTile128x128, kTile64x128, kTile64x64, kTile256x192, kGemmTileShapes };
 
 // y = epilogue(a w^T + bias) on tiles of shape `tile`, K split over k_split workgroups per tile
 // (1: none; above 1 only with the plain epilogue and fp32 output: part p writes its sums

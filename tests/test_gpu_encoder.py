@@ -127,6 +127,35 @@ def test_gemm_tile_shapes(M, N, K):
     assert torch.equal(z, y[1:M + 1] + res)
 
 
+@pytest.mark.parametrize("M,N,K", [
+    (2310, 3336, 192),   # three blocks of K, ragged rows, a last tile of 72 features
+    (4612, 1672, 320),   # five blocks, tiles of features over all tokens (M > N)
+    (2750, 3072, 1024),  # sixteen, whole tiles of features
+])
+def test_gemm_tiles_of_192_features(M, N, K):
+    """Tiles of 256 x 192: every epilogue and output type against fp32 products of the same bf16 values;
+    few rows of the same product (on smaller tiles) have the same bits."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    a = torch.randn(M, K, generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn(N, K, generator=g, device="cuda") / K ** 0.5).to(torch.bfloat16)
+    bias = torch.randn(N, generator=g, device="cuda")
+    plain = a.float() @ w.float().t() + bias
+    for dtype in (torch.float32, torch.bfloat16):
+        res = torch.randn(M, N, generator=g, device="cuda").to(dtype)
+        for epi, want in ((binding.JV_EPI_NONE, plain), (binding.JV_EPI_GELU, torch.nn.functional.gelu(plain)),
+                          (binding.JV_EPI_RESIDUAL, plain + res.float()), (binding.JV_EPI_SILU, torch.nn.functional.silu(plain))):
+            r = res if epi == binding.JV_EPI_RESIDUAL else None
+            y = torch.full((M + 2, N), 768.0, device="cuda", dtype=dtype)  # guard rows around the result
+            binding.jv_gemm_bias_act(a, w, bias, r, y[1:M + 1], epi)
+            assert float(y[0].min()) == 768.0 and float(y[M + 1].max()) == 768.0
+            got, ref = to_host(y[1:M + 1].float()), to_host(want)
+            check((err_bf16 if dtype == torch.float32 else err_bf16_stored)(got, ref), 2e-4)
+            few = torch.empty((37, N), device="cuda", dtype=dtype)
+            binding.jv_gemm_bias_act(a[-37:], w, bias, None if r is None else r[-37:], few, epi)
+            assert torch.equal(few, y[M - 36:M + 1])
+
+
 def test_gemm_capture_at_sizes_of_every_tile_shape():
     """The tile follows from the sizes, so a captured product may be the first of its kernel; replays
     with eager products and synchronisations between them give the eager bits."""
