@@ -191,15 +191,6 @@ constexpr int kGemmLds = kGemmSlots * kGemmPart;       // 160 KB
 
 typedef __attribute__((address_space(1))) const void global_cvoid;
 
-// table[2 i] = Phi(x_i), table[2 i + 1] = Phi(x_i+1) - Phi(x_i), x_i = kPhiLo + i kPhiStep.
-__device__ inline float gelu_from_table(float x, const float *table) {
-    const float t = __builtin_amdgcn_fmed3f(fmaf(x, 1.0f / kPhiStep, -kPhiLo / kPhiStep), 0.0f,
-                                            (float)kPhiSteps - 0.004f);
-    const unsigned i = (unsigned)t;
-    const float2 pd = *(const float2 *)(table + 2 * i);
-    return x * fmaf(t - (float)i, pd.y, pd.x);
-}
-
 // Byte offset of 16-byte chunk `chunk` (0..7) of row `row` in a [rows][64] bf16 LDS part.
 __device__ inline unsigned gemm_part_off(int row, int chunk) {
     return (unsigned)(row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4));
@@ -459,13 +450,8 @@ gemm_bf16_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W,
     // go to the lanes that hold the rows' tokens through LDS.
     float2 *row_stats = (float2 *)(smem + a_slot * kGemmPart + 16384);  // behind the table, [256]
     if (LN == kLnConsume && tid < kBM) row_stats[tid] = float2{row_mean, row_rstd};
-    if (EPI == JV_EPI_GELU) {
-        for (int i = tid; i <= kPhiSteps; i += 512) {
-            const float p0 = normal_cdf(kPhiLo + (float)i * kPhiStep);
-            phi_table[2 * i] = p0;
-            phi_table[2 * i + 1] = normal_cdf(kPhiLo + (float)(i + 1) * kPhiStep) - p0;
-        }
-    }
+    if (EPI == JV_EPI_GELU)
+        phi_table_fill(phi_table, tid, 512);
     if (EPI == JV_EPI_GELU || LN == kLnConsume) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     f32x4 c1_reg[2][4];
     if (LN == kLnConsume) {

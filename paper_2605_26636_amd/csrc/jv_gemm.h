@@ -25,6 +25,24 @@ __device__ inline float normal_cdf(float x) {
     return x < 0.f ? half_erfc : 1.0f - half_erfc;
 }
 
+// table[2 i] = Phi(x_i), table[2 i + 1] = Phi(x_i+1) - Phi(x_i), x_i = kPhiLo + i kPhiStep, i < kPhiSteps; filled by
+// `threads` threads, kPhiSteps / threads consecutive entries each.
+__device__ inline void phi_table_fill(float *table, int tid, int threads) {
+    const int n = kPhiSteps / threads;
+    float p0 = normal_cdf(kPhiLo + (float)(tid * n) * kPhiStep);
+    for (int i = tid * n; i < (tid + 1) * n; ++i) {
+        const float p1 = normal_cdf(kPhiLo + (float)(i + 1) * kPhiStep);
+        *(float2 *)(table + 2 * i) = float2{p0, p1 - p0};
+        p0 = p1;
+    }
+}
+__device__ inline float gelu_from_table(float x, const float *table) {
+    const float t = __builtin_amdgcn_fmed3f(fmaf(x, 1.0f / kPhiStep, -kPhiLo / kPhiStep), 0.0f,
+                                            (float)kPhiSteps - 0.004f);
+    const float2 pd = *(const float2 *)(table + 2 * (unsigned)t);
+    return x * fmaf(__builtin_amdgcn_fractf(t), pd.y, pd.x);
+}
+
 // Tile shapes (tokens x features): the kernel of jv_encoder.hip, then those of jv_gemm_tiles.hip
 // (128 x 128 in two forms: a deep operand ring with one workgroup per compute unit, a short one
 // with two).

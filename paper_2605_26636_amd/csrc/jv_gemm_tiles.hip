@@ -32,7 +32,7 @@ struct TileShape {
     static constexpr int kRow = 2 * kBlockK, kRowsPerLoad = 1024 / kRow;  // bytes of a row in LDS; rows of a 1 KB load instruction
     static constexpr int kPartA = kBM * kRow, kPartW = kBN * kRow, kStage = kPartA + kPartW;
     static constexpr int kLoadsA = kBM / kRowsPerLoad / kWaves, kLoadsW = kBN / kRowsPerLoad / kWaves;  // per wavefront
-    static constexpr int kTable = EPI == JV_EPI_GELU ? (kPhiSteps + 2) * 4 : 0;
+    static constexpr int kTable = EPI == JV_EPI_GELU ? kPhiSteps * 8 : 0;
     static constexpr int kRing = STAGES * kStage > kWaves * 8192 ? STAGES * kStage : kWaves * 8192;
     static constexpr int kLds = kRing + kTable;
     static_assert(kBM % (kRowsPerLoad * kWaves) == 0 && kBN % (kRowsPerLoad * kWaves) == 0, "whole load instructions per wavefront");
@@ -51,12 +51,7 @@ template <int EPI>
 __device__ inline void tile_activation(f32x4 &val, const float *phi_table) {
     if (EPI == JV_EPI_GELU) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float t = __builtin_amdgcn_fmed3f(fmaf(val[e], 1.0f / kPhiStep, -kPhiLo / kPhiStep), 0.0f, (float)kPhiSteps - 0.004f);
-            const unsigned i = (unsigned)t;
-            const float p0 = phi_table[i], p1 = phi_table[i + 1];
-            val[e] = val[e] * fmaf(t - (float)i, p1 - p0, p0);
-        }
+        for (int e = 0; e < 4; ++e) val[e] = gelu_from_table(val[e], phi_table);
     }
     if (EPI == JV_EPI_SILU) {
 #pragma unroll
@@ -170,7 +165,7 @@ gemm_tile_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W, con
     // GELU's table behind the ring, built while the first blocks are in flight
     float *phi_table = (float *)(smem + S::kRing);
     if (EPI == JV_EPI_GELU)
-        for (int i = tid; i <= kPhiSteps + 1; i += S::kThreads) phi_table[i] = normal_cdf(kPhiLo + (float)i * kPhiStep);
+        phi_table_fill(phi_table, tid, S::kThreads);
     landed(min(STAGES, n_b) - 1);
 #pragma unroll
     for (int s = 0; s < 2; ++s)
@@ -337,7 +332,7 @@ gemm_tile_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W, con
 // grid (8 * ceil(tiles / 8)), 512 threads, kTile192Lds bytes of dynamic LDS.
 // ---------------------------------------------------------------------------------------
 constexpr int kT192N = 192, kT192PartA = 256 * 128, kT192PartW = kT192N * 128, kT192Ring = 3 * kT192PartA + 2 * kT192PartW;
-constexpr int kTile192Lds = kT192Ring + (kPhiSteps + 2) * 4;
+constexpr int kTile192Lds = kT192Ring + kPhiSteps * 8;
 
 template <int EPI, bool OUT_BF16>
 __global__ void __launch_bounds__(512)
@@ -419,7 +414,7 @@ gemm_tile192_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W, 
     // GELU's table behind the ring, built while the first blocks are in flight
     float *phi_table = (float *)(smem + kT192Ring);
     if (EPI == JV_EPI_GELU)
-        for (int i = tid; i <= kPhiSteps + 1; i += 512) phi_table[i] = normal_cdf(kPhiLo + (float)i * kPhiStep);
+        phi_table_fill(phi_table, tid, 512);
     if (n_b > 1) wait_vm_and_barrier<kLoadsA + kLoadsW>();
     else wait_vm_and_barrier<0>();
 #pragma unroll
