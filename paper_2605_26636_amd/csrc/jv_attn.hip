@@ -461,7 +461,9 @@ attn_small_window_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, Wi
     *(f32x4 *)((float *)ot.ptr + b * ot.sb + h * ot.sh + (long long)tok * ot.sn + c4) = acc * (1.0f / l);
 }
 
-// q_slots: number of leading query slots of each window to compute (all keys always take part).
+// q_slots: number of leading query slots of each window to compute (all keys always take part).  With
+// fewer than all of them the rows of O behind them are scratch.
+jv_status attn_bf16_check(const Problem &pr, const WindowGeom &g, int q_slots);
 jv_status attn_bf16(const Problem &pr, const WindowGeom &g, float scale, int q_slots, hipStream_t stream);
 
 template <int KW>
@@ -543,8 +545,11 @@ jv_status window_forward(const Problem &pr, int wh, int ww, float scale, hipStre
     grid.k = from_token(pr.k, pr.P, pr.bf16);
     grid.v = from_token(pr.v, pr.P, pr.bf16);
     grid.o = from_token(pr.o, pr.P, pr.o_bf16);
-    if ((st = attn_dispatch(grid, g, resolve_scale(scale, pr.D), g.slots, stream)) != JV_OK) return st;
-    return attn_dispatch(pr, sequence_geom(pr.N), resolve_scale(scale, pr.D), pr.P, stream);
+    // The prefix tokens go first: their partial sums lie in the grid rows of O until the windows
+    // overwrite them.  Nothing is launched for a grid that the window kernels refuse.
+    if (pr.bf16 && (st = attn_bf16_check(grid, g, g.slots)) != JV_OK) return st;
+    if ((st = attn_dispatch(pr, sequence_geom(pr.N), resolve_scale(scale, pr.D), pr.P, stream)) != JV_OK) return st;
+    return attn_dispatch(grid, g, resolve_scale(scale, pr.D), g.slots, stream);
 }
 
 jv_status full_forward(const Problem &pr, float scale, hipStream_t stream) {

@@ -1010,32 +1010,49 @@ __global__ void __launch_bounds__(256, NT == 1 ? 3 : 2) attn_ring_bf16(AttnArgs 
 // ---------------------------------------------------------------------------------------
 // A few queries against a whole sequence: the prefix tokens (at most 64, the first query slots
 // of a one-window geometry whose slot s is token s) attend to all N tokens.  With so few
-// queries the parallelism has to come from the keys: one workgroup of eight wavefronts per
-// (batch, head); every wavefront holds all the queries, takes every eighth stage of 64 keys
-// into a tile of its own (loads straight into LDS, no barriers in the loop) and keeps its own
-// running softmax; at the end the eight partial results are merged through LDS,
+// queries the parallelism has to come from the keys: eight chains per (batch, head), chain w taking
+// every eighth stage of 64 keys from stage w on, one wavefront each with all the queries (NT blocks of 32)
+// and a running softmax of its own; the partial results are merged in the order of the chains,
 //     O = sum_w acc_w 2^(m_w - M) / sum_w l_w 2^(m_w - M),   M = max_w m_w.
-// grid (B*heads), 512 threads, kPrefixLds bytes of dynamic LDS.  Requirements as attn_ring_bf16.
+//
+// SPLIT: every chain is a workgroup of its own (grid (chains, B*heads), 64 threads) with two tiles,
+// the next stage in flight under the present one, and leaves (acc, m, l) in the rows of O behind the queries,
+// which the window kernels overwrite afterwards (the caller launches them behind this one on the same
+// stream): three rows of 64 elements, 128 bytes of each, for a query of a chain: channels 0 - 31,
+// channels 32 - 63, (m, l).  prefix_combine_bf16 merges them.  Otherwise (launch_prefix) the chains are the
+// wavefronts of one workgroup (grid (1, B*heads), 512 threads) and meet in LDS.  The same bits either way.
+// The one workgroup is bound by what its compute unit takes in and by the round trips of a stage, one
+// after the other; the chains by those of an eighth of the stages, half of them hidden.
+// Dynamic LDS: prefix_lds(SPLIT).  Requirements as attn_ring_bf16.
 // ---------------------------------------------------------------------------------------
-constexpr int kPrefixWaves = 8;
-constexpr int kPrefixLds = kPrefixWaves * kStageBytes + 2 * kPrefixWaves * 64 * 4;
+constexpr int kPrefixChains = 8;
+constexpr int kPrefixRows = 3;  // rows of O a query of a chain takes
+constexpr int prefix_lds(bool split) {
+    return split ? 2 * kStageBytes : kPrefixChains * kStageBytes + 2 * kPrefixChains * 64 * 4;
+}
 
+// Byte address of row `row` of the scratch in O of one (batch, head); obase in elements.
 template <bool O_BF16>
-__global__ void __launch_bounds__(512, 1) attn_prefix_bf16(AttnArgs a) {
+__device__ inline char *prefix_scratch(const AttnArgs &a, long long obase, int row) {
+    return (char *)a.o.ptr + (O_BF16 ? 2 : 4) * (obase + (long long)(a.q_slots + row) * a.o.sn);
+}
+
+template <bool O_BF16, int NT, bool SPLIT>
+__global__ void __launch_bounds__(SPLIT ? 64 : 512, 1) attn_prefix_bf16(AttnArgs a) {
     // the logit scale, fetched (a kernel argument) and waited for here, not inside the key loop
     float c_log2 = a.c;
     asm volatile("" : "+s"(c_log2));
     extern __shared__ __align__(16) unsigned char psm[];
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, li = lane & 31;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int bh = blockIdx.x, b = bh / a.heads, h = bh % a.heads;
-    const long long qbase = b * a.q.sb + h * a.q.sh;
+    const int chain = SPLIT ? (int)blockIdx.x : __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bh = blockIdx.y, b = bh / a.heads, h = bh % a.heads;
+    const long long qbase = b * a.q.sb + h * a.q.sh, obase = b * a.o.sb + h * a.o.sh;
     const int N = a.g.slots;
 
-    u32x4 qreg[2][4];
-    load_queries<2>(qreg, a, 0, 0, 0, qbase, lane);
-    WaveState<2> w;
-    wave_state_init<2>(w);
+    u32x4 qreg[NT][4];
+    load_queries<NT>(qreg, a, 0, 0, 0, qbase, lane);
+    WaveState<NT> w;
+    wave_state_init<NT>(w);
 
     auto uniform = [](const char *ptr) {
         const unsigned long long u = (unsigned long long)ptr;
@@ -1045,12 +1062,11 @@ __global__ void __launch_bounds__(512, 1) attn_prefix_bf16(AttnArgs a) {
     };
     const char *kbytes = uniform((const char *)((const __bf16 *)a.k.ptr + b * a.k.sb + h * a.k.sh));
     const char *vbytes = uniform((const char *)((const __bf16 *)a.v.ptr + b * a.v.sb + h * a.v.sh));
-    unsigned char *kt = psm + wave * kStageBytes, *vt = kt + kStage * 128;
+    unsigned char *own = psm + (SPLIT ? 0 : chain * kStageBytes);  // this chain's tile, or its two
     const int lrow = lane >> 3, lslot = lane & 7;
     const int n_stage = (N + kStage - 1) / kStage;
-    for (int st = wave; st < n_stage; st += kPrefixWaves) {
-        // (the LDS reads of the previous stage have been waited for before the matrix
-        // instructions that used them, so the tile may be overwritten)
+    auto issue = [&](int st, int at) {  // sixteen loads
+        unsigned char *kt = own + at, *vt = kt + kStage * 128;
 #pragma unroll 1
         for (int i = 0; i < 8; ++i) {
             const int row = 8 * i + lrow;
@@ -1062,14 +1078,27 @@ __global__ void __launch_bounds__(512, 1) attn_prefix_bf16(AttnArgs a) {
             __builtin_amdgcn_global_load_lds((attn_global_cvoid *)(vbytes + vo),
                                              (attn_lds_void *)(vt + 8 * i * 128), 16, 0, 0);
         }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        queries_landed<2>(qreg);
+    };
+    int at = 0;  // byte offset of the present stage's tile
+    if (SPLIT) issue(chain, 0);  // (a split launch has more stages than chains)
+    for (int st = chain; st < n_stage; st += kPrefixChains) {
+        // (the LDS reads of the previous stage have been waited for before the matrix
+        // instructions that used them, so its tile may be overwritten)
+        if (!SPLIT) issue(st, 0);
+        if (SPLIT && st + kPrefixChains < n_stage) {
+            issue(st + kPrefixChains, kStageBytes - at);
+            asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+        } else {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+        queries_landed<NT>(qreg);
         const int key_limit = N - st * kStage;
         // The operand addresses depend on the lane only; `ln` is the lane, but opaque to the
         // compiler, which would otherwise keep every address of every tile variant in a
         // register of its own across the loop (and spill them).
         int ln = lane;
         asm volatile("" : "+v"(ln));
+        const unsigned char *kt = own + at, *vt = kt + kStage * 128;
         const unsigned vaddr[2] = {vt_lane_address(vt, 0, ln), vt_lane_address(vt, 1, ln)};
         unsigned kaddr[4];
         k_lane_addresses(kaddr, kt, ln);
@@ -1078,17 +1107,47 @@ __global__ void __launch_bounds__(512, 1) attn_prefix_bf16(AttnArgs a) {
         k_operands_landed(ka);
         // (one masked tile code for whole and partial stages: this kernel waits for its loads,
         // not for its arithmetic)
-        ring_tile32<2, 32 * 128, true, 0>(w, qreg, ka, kaddr, vaddr, 0, key_limit, c_log2, ln);
-        if (key_limit > 32) ring_tile32<2, -1, true, 32 * 128>(w, qreg, ka, kaddr, vaddr, 32, key_limit, c_log2, ln);
+        ring_tile32<NT, 32 * 128, true, 0>(w, qreg, ka, kaddr, vaddr, 0, key_limit, c_log2, ln);
+        if (key_limit > 32) ring_tile32<NT, -1, true, 32 * 128>(w, qreg, ka, kaddr, vaddr, 32, key_limit, c_log2, ln);
+        if (SPLIT) at = kStageBytes - at;
+    }
+    // A wavefront without a stage still has its queries in flight: their registers are not free before this.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    queries_landed<NT>(qreg);
+
+    if (SPLIT) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int qcol = 32 * nt + li, row = (chain * a.q_slots + qcol) * kPrefixRows;
+            float lo, hi;
+            pair_values(w.l[nt], &lo, &hi);
+            if (qcol >= a.q_slots) continue;
+#pragma unroll
+            for (int mi = 0; mi < 2; ++mi) {
+                float *acc = (float *)prefix_scratch<O_BF16>(a, obase, row + mi);
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    const f32x16 &x = w.acc[mi][nt];
+                    f32x4 val = {x[4 * q4], x[4 * q4 + 1], x[4 * q4 + 2], x[4 * q4 + 3]};
+                    *(f32x4 *)(acc + 8 * q4 + 4 * g) = val;
+                }
+            }
+            if (g == 0) {
+                float *ml = (float *)prefix_scratch<O_BF16>(a, obase, row + 2);
+                ml[0] = w.m[nt];
+                ml[1] = lo + hi;
+            }
+        }
+        return;
     }
 
     // Partial results into LDS: the accumulators as [query][channel] fp32 in the wavefront's own
     // tile bytes (16-byte pieces rotated by the query to spread the banks), references and sums
     // behind the tiles.
-    float *mine = (float *)(psm + wave * kStageBytes);
-    float *mbuf = (float *)(psm + kPrefixWaves * kStageBytes), *lbuf = mbuf + kPrefixWaves * 64;
+    float *mine = (float *)own;
+    float *mbuf = (float *)(psm + kPrefixChains * kStageBytes), *lbuf = mbuf + kPrefixChains * 64;
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
+    for (int nt = 0; nt < NT; ++nt) {
         const int qcol = 32 * nt + li;
 #pragma unroll
         for (int mi = 0; mi < 2; ++mi)
@@ -1101,8 +1160,8 @@ __global__ void __launch_bounds__(512, 1) attn_prefix_bf16(AttnArgs a) {
         float lo, hi;
         pair_values(w.l[nt], &lo, &hi);
         if (g == 0) {
-            mbuf[wave * 64 + qcol] = w.m[nt];
-            lbuf[wave * 64 + qcol] = lo + hi;
+            mbuf[chain * 64 + qcol] = w.m[nt];
+            lbuf[chain * 64 + qcol] = lo + hi;
         }
     }
     __syncthreads();
@@ -1111,11 +1170,11 @@ __global__ void __launch_bounds__(512, 1) attn_prefix_bf16(AttnArgs a) {
     if (qcol < a.q_slots && qcol < N) {
         float top = kMinusHuge;
 #pragma unroll
-        for (int wv = 0; wv < kPrefixWaves; ++wv) top = fmaxf(top, mbuf[wv * 64 + qcol]);
+        for (int wv = 0; wv < kPrefixChains; ++wv) top = fmaxf(top, mbuf[wv * 64 + qcol]);
         float den = 0.f;
         f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
 #pragma unroll
-        for (int wv = 0; wv < kPrefixWaves; ++wv) {
+        for (int wv = 0; wv < kPrefixChains; ++wv) {
             const float scale = __builtin_amdgcn_exp2f(mbuf[wv * 64 + qcol] - top);
             den = fmaf(lbuf[wv * 64 + qcol], scale, den);
             const float *row = (const float *)(psm + wv * kStageBytes) + qcol * 64;
@@ -1127,25 +1186,70 @@ __global__ void __launch_bounds__(512, 1) attn_prefix_bf16(AttnArgs a) {
         const float inv = 1.0f / den;
         s0 *= inv;
         s1 *= inv;
-        const long long at = b * a.o.sb + h * a.o.sh + (long long)qcol * a.o.sn + 8 * piece;
+        const long long out = obase + (long long)qcol * a.o.sn + 8 * piece;
         if (O_BF16) {
             u32x4 pk = {pack_bf16x2(s0[0], s0[1]), pack_bf16x2(s0[2], s0[3]), pack_bf16x2(s1[0], s1[1]),
                         pack_bf16x2(s1[2], s1[3])};
-            *(u32x4 *)((__bf16 *)a.o.ptr + at) = pk;
+            *(u32x4 *)((__bf16 *)a.o.ptr + out) = pk;
         } else {
-            *(f32x4 *)((float *)a.o.ptr + at) = s0;
-            *(f32x4 *)((float *)a.o.ptr + at + 4) = s1;
+            *(f32x4 *)((float *)a.o.ptr + out) = s0;
+            *(f32x4 *)((float *)a.o.ptr + out + 4) = s1;
         }
     }
 }
 
+// The chains of attn_prefix_bf16<.., SPLIT> merged: one wavefront per (query, batch * head), a lane per
+// channel, all rows in flight together.  grid (queries, B*heads).
 template <bool O_BF16>
+__global__ void __launch_bounds__(64) prefix_combine_bf16(AttnArgs a) {
+    const int lane = threadIdx.x, qcol = blockIdx.x, bh = blockIdx.y, b = bh / a.heads, h = bh % a.heads;
+    const long long obase = b * a.o.sb + h * a.o.sh;
+    float m[kPrefixChains], l[kPrefixChains], x[kPrefixChains];
+#pragma unroll
+    for (int wv = 0; wv < kPrefixChains; ++wv) {
+        const int row = (wv * a.q_slots + qcol) * kPrefixRows;
+        const float *ml = (const float *)prefix_scratch<O_BF16>(a, obase, row + 2);
+        m[wv] = ml[0];
+        l[wv] = ml[1];
+        x[wv] = *((const float *)prefix_scratch<O_BF16>(a, obase, row + (lane >> 5)) + (lane & 31));
+    }
+    float top = kMinusHuge;
+#pragma unroll
+    for (int wv = 0; wv < kPrefixChains; ++wv) top = fmaxf(top, m[wv]);
+    float den = 0.f, sum = 0.f;
+#pragma unroll
+    for (int wv = 0; wv < kPrefixChains; ++wv) {
+        const float scale = __builtin_amdgcn_exp2f(m[wv] - top);
+        den = fmaf(l[wv], scale, den);
+        sum = fmaf(x[wv], scale, sum);
+    }
+    const float out = sum * (1.0f / den);
+    const long long at = obase + (long long)qcol * a.o.sn + lane;
+    if (O_BF16) ((__bf16 *)a.o.ptr)[at] = (__bf16)out;
+    else ((float *)a.o.ptr)[at] = out;
+}
+
+// Split where a chain has more than one stage, the (batch, head)s alone leave units without a workgroup and
+// the rows behind the queries hold the chains (24 rows a query).  What five prefix tokens add to window
+// attention, us, one workgroup with two blocks of queries whatever their number / as chosen here: split
+// 1 369 tokens x 12 heads 14.4 / 8.8, 4 096 x 16 31.8 / 16.6, x 128 37 / 28, 8 192 x 16 54 / 24, 16 384 x 32
+// 101 / 46; not split 1 369 x 512 42.7 / 33.3 (split 44), 400 x 80 9.0 / 6.5 (split 8.9), 196 x 256 7.8 / 5.3 (8.9).
+template <bool O_BF16, int NT>
 static jv_status launch_prefix(const AttnArgs &a, int BH, hipStream_t stream) {
-    static LdsLimit lds_limit;
-    jv_status st = ensure_lds_limit(lds_limit, (const void *)attn_prefix_bf16<O_BF16>, kPrefixLds);
+    const bool split = a.g.slots > kPrefixChains * kStage && BH <= 256 &&
+                       kPrefixRows * kPrefixChains * a.q_slots <= a.g.slots - a.q_slots;
+    if (!split) {
+        static LdsLimit lds_limit;
+        jv_status st = ensure_lds_limit(lds_limit, (const void *)attn_prefix_bf16<O_BF16, NT, false>, prefix_lds(false));
+        if (st != JV_OK) return st;
+        hipLaunchKernelGGL((attn_prefix_bf16<O_BF16, NT, false>), dim3(1, BH), dim3(512), prefix_lds(false), stream, a);
+        return launch_status("attn_prefix_bf16");
+    }
+    hipLaunchKernelGGL((attn_prefix_bf16<O_BF16, NT, true>), dim3(kPrefixChains, BH), dim3(64), prefix_lds(true), stream, a);
+    jv_status st = launch_status("attn_prefix_bf16");
     if (st != JV_OK) return st;
-    hipLaunchKernelGGL((attn_prefix_bf16<O_BF16>), dim3(BH), dim3(512), kPrefixLds, stream, a);
-    return launch_status("attn_prefix_bf16");
+    hipLaunchKernelGGL((prefix_combine_bf16<O_BF16>), dim3(a.q_slots, BH), dim3(64), 0, stream, a);
+    return launch_status("prefix_combine_bf16");
 }
 
 template <bool O_BF16, int WPW>
@@ -1702,7 +1806,17 @@ __global__ void __launch_bounds__(256, 2) attn_ring_wide_bf16(AttnArgs a) {
     }
 }
 
+jv_status attn_bf16_check(const Problem &pr, const WindowGeom &g, int q_slots) {
+    if (g.n_win > 65535) return fail(JV_ERR_UNSUPPORTED, "more than 65535 windows");
+    // the streaming and ring kernels number their work items (query block, window, batch * head) in 32 bits
+    if (((long long)(q_slots < g.slots ? q_slots : g.slots) + 127) / 128 * g.n_win * pr.B * pr.heads >= (1ll << 28))
+        return fail(JV_ERR_UNSUPPORTED, "more than 2^28 blocks of 128 queries");
+    return JV_OK;
+}
+
 jv_status attn_bf16(const Problem &pr, const WindowGeom &g, float scale, int q_slots, hipStream_t stream) {
+    const jv_status checked = attn_bf16_check(pr, g, q_slots);
+    if (checked != JV_OK) return checked;
     AttnArgs a;
     a.q = pr.q; a.k = pr.k; a.v = pr.v; a.o = pr.o;
     a.g = g;
@@ -1711,10 +1825,6 @@ jv_status attn_bf16(const Problem &pr, const WindowGeom &g, float scale, int q_s
     a.q_slots = q_slots < g.slots ? q_slots : g.slots;
     a.c = scale * kLog2e;
     a.n_bh = pr.B * pr.heads;
-    if (g.n_win > 65535) return fail(JV_ERR_UNSUPPORTED, "more than 65535 windows");
-    // the streaming and ring kernels number their work items (query block, window, batch * head) in 32 bits
-    if ((long long)((a.q_slots + 127) / 128) * g.n_win * a.n_bh >= (1ll << 28))
-        return fail(JV_ERR_UNSUPPORTED, "more than 2^28 blocks of 128 queries");
     if (pr.D == kHeadDimWide) {
         // windows of whole grid rows, and unpadded windows whose width divides a key stage, with 32-bit
         // byte offsets inside a (batch, head) slice: the ring kernel
@@ -1751,9 +1861,13 @@ jv_status attn_bf16(const Problem &pr, const WindowGeom &g, float scale, int q_s
     const long long max_sn = pr.k.sn > pr.v.sn ? pr.k.sn : pr.v.sn;
     const bool fast = a.contig && ((long long)pr.N + 2 * kStage) * max_sn * 2 + 256 < (1ll << 31);
     // a handful of queries against the whole sequence (prefix tokens): split the keys instead
-    if (fast && !all_queries && a.q_slots <= 64 && g.n_win == 1)
-        return pr.o_bf16 ? launch_prefix<true>(a, pr.B * pr.heads, stream)
-                         : launch_prefix<false>(a, pr.B * pr.heads, stream);
+    if (fast && !all_queries && a.q_slots <= 64 && g.n_win == 1) {
+        if (a.q_slots <= 32)
+            return pr.o_bf16 ? launch_prefix<true, 1>(a, pr.B * pr.heads, stream)
+                             : launch_prefix<false, 1>(a, pr.B * pr.heads, stream);
+        return pr.o_bf16 ? launch_prefix<true, 2>(a, pr.B * pr.heads, stream)
+                         : launch_prefix<false, 2>(a, pr.B * pr.heads, stream);
+    }
     // The ring kernel with two blocks of 32 queries per wavefront or with one (the same bits): two workgroups of
     // 256 queries on a compute unit do the most per second, but three of 128 come close, and the smaller
     // blocks leave fewer units with less than their share.  Time of a launch's last round by the workgroups
