@@ -1198,35 +1198,45 @@ __global__ void __launch_bounds__(SPLIT ? 64 : 512, 1) attn_prefix_bf16(AttnArgs
     }
 }
 
-// The chains of attn_prefix_bf16<.., SPLIT> merged: one wavefront per (query, batch * head), a lane per
-// channel, all rows in flight together.  grid (queries, B*heads).
-template <bool O_BF16>
+// The chains of attn_prefix_bf16<.., SPLIT> or attn_prefix_wide_bf16 merged in their order: one wavefront per
+// (query, batch * head), a lane per channel, or per channel of either half of a wide head; all rows in
+// flight together.  grid (queries, B*heads).
+template <bool O_BF16, int D, int CHAINS>
 __global__ void __launch_bounds__(64) prefix_combine_bf16(AttnArgs a) {
     const int lane = threadIdx.x, qcol = blockIdx.x, bh = blockIdx.y, b = bh / a.heads, h = bh % a.heads;
     const long long obase = b * a.o.sb + h * a.o.sh;
-    float m[kPrefixChains], l[kPrefixChains], x[kPrefixChains];
+    constexpr int kHalf = D / 2;  // channels in a row of the scratch
+    float m[CHAINS], l[CHAINS], x[D / 64][CHAINS];
 #pragma unroll
-    for (int wv = 0; wv < kPrefixChains; ++wv) {
+    for (int wv = 0; wv < CHAINS; ++wv) {
         const int row = (wv * a.q_slots + qcol) * kPrefixRows;
         const float *ml = (const float *)prefix_scratch<O_BF16>(a, obase, row + 2);
         m[wv] = ml[0];
         l[wv] = ml[1];
-        x[wv] = *((const float *)prefix_scratch<O_BF16>(a, obase, row + (lane >> 5)) + (lane & 31));
+#pragma unroll
+        for (int i = 0; i < D / 64; ++i) {
+            const int c = 64 * i + lane;
+            x[i][wv] = *((const float *)prefix_scratch<O_BF16>(a, obase, row + c / kHalf) + c % kHalf);
+        }
     }
     float top = kMinusHuge;
 #pragma unroll
-    for (int wv = 0; wv < kPrefixChains; ++wv) top = fmaxf(top, m[wv]);
-    float den = 0.f, sum = 0.f;
+    for (int wv = 0; wv < CHAINS; ++wv) top = fmaxf(top, m[wv]);
+    float den = 0.f, sum[D / 64] = {};
 #pragma unroll
-    for (int wv = 0; wv < kPrefixChains; ++wv) {
+    for (int wv = 0; wv < CHAINS; ++wv) {
         const float scale = __builtin_amdgcn_exp2f(m[wv] - top);
         den = fmaf(l[wv], scale, den);
-        sum = fmaf(x[wv], scale, sum);
+#pragma unroll
+        for (int i = 0; i < D / 64; ++i) sum[i] = fmaf(x[i][wv], scale, sum[i]);
     }
-    const float out = sum * (1.0f / den);
+    const float inv = 1.0f / den;
     const long long at = obase + (long long)qcol * a.o.sn + lane;
-    if (O_BF16) ((__bf16 *)a.o.ptr)[at] = (__bf16)out;
-    else ((float *)a.o.ptr)[at] = out;
+#pragma unroll
+    for (int i = 0; i < D / 64; ++i) {
+        if (O_BF16) ((__bf16 *)a.o.ptr)[at + 64 * i] = (__bf16)(sum[i] * inv);
+        else ((float *)a.o.ptr)[at + 64 * i] = sum[i] * inv;
+    }
 }
 
 // Split where a chain has more than one stage, the (batch, head)s alone leave units without a workgroup and
@@ -1248,7 +1258,7 @@ static jv_status launch_prefix(const AttnArgs &a, int BH, hipStream_t stream) {
     hipLaunchKernelGGL((attn_prefix_bf16<O_BF16, NT, true>), dim3(kPrefixChains, BH), dim3(64), prefix_lds(true), stream, a);
     jv_status st = launch_status("attn_prefix_bf16");
     if (st != JV_OK) return st;
-    hipLaunchKernelGGL((prefix_combine_bf16<O_BF16>), dim3(a.q_slots, BH), dim3(64), 0, stream, a);
+    hipLaunchKernelGGL((prefix_combine_bf16<O_BF16, kHeadDim, kPrefixChains>), dim3(a.q_slots, BH), dim3(64), 0, stream, a);
     return launch_status("prefix_combine_bf16");
 }
 
@@ -1806,6 +1816,105 @@ __global__ void __launch_bounds__(256, 2) attn_ring_wide_bf16(AttnArgs a) {
     }
 }
 
+// Prefix queries of wide heads, as attn_prefix_bf16<.., SPLIT>: sixteen chains per (batch, head), chain w
+// taking every sixteenth stage of 32 keys from stage w on, one wavefront and two stages of LDS each, for one block
+// of 32 queries; the rows of the scratch hold 64 channels.
+// grid (kPrefixChainsWide, B*heads, blocks of 32 queries), 64 threads.  Requirements as attn_ring_wide_bf16.
+constexpr int kPrefixChainsWide = 16;
+
+template <bool O_BF16>
+__global__ void __launch_bounds__(64, 2) attn_prefix_wide_bf16(AttnArgs a) {
+    float c_log2 = a.c;
+    asm volatile("" : "+s"(c_log2));  // fetched and waited for here, not inside the key loop
+    __shared__ __align__(16) unsigned char smem[2 * kStageWideBytes];
+    const int lane = threadIdx.x, g = lane >> 5, li = lane & 31;
+    const int chain = blockIdx.x, bh = blockIdx.y, b = bh / a.heads, h = bh % a.heads;
+    const int qcol = 32 * blockIdx.z + li, N = a.g.slots;
+    const long long obase = b * a.o.sb + h * a.o.sh;
+
+    u32x4 qreg[1][8];  // in assembly (the wavefront's oldest loads; see load_queries)
+    {
+        const __bf16 *row = (const __bf16 *)a.q.ptr + b * a.q.sb + h * a.q.sh + (long long)min(qcol, N - 1) * a.q.sn + g * 8;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks)
+            asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(qreg[0][ks]) : "v"(row), "n"(32 * ks));
+    }
+    WideState<1> w;
+#pragma unroll
+    for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) w.acc[mi][0][v] = 0.f;
+    w.m[0] = kMinusHuge;
+    w.l[0] = 0.f;
+
+    const char *kbytes = (const char *)((const __bf16 *)a.k.ptr + b * a.k.sb + h * a.k.sh);
+    const char *vbytes = (const char *)((const __bf16 *)a.v.ptr + b * a.v.sb + h * a.v.sh);
+    const int lrow = lane >> 4, lslot = lane & 15;
+    const int n_stage = (N + kStageWide - 1) / kStageWide;
+    auto issue = [&](int st, int at) {  // sixteen loads of four rows
+        unsigned char *kt = smem + at, *vt = kt + kTileWideBytes;
+#pragma unroll 1
+        for (int i = 0; i < 8; ++i) {
+            const int row = 4 * i + lrow;
+            const int tok = st * kStageWide + row < N ? st * kStageWide + row : 0;  // past the end: any valid row
+            const unsigned ko = 2u * (unsigned)tok * (unsigned)a.k.sn + 16u * (unsigned)(lslot ^ (row & 15));
+            const unsigned vo = 2u * (unsigned)tok * (unsigned)a.v.sn + 16u * (unsigned)((((lslot >> 2) ^ (row & 3)) << 2) | (lslot & 3));
+            __builtin_amdgcn_global_load_lds((attn_global_cvoid *)(kbytes + ko), (attn_lds_void *)(kt + 4 * i * 256), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((attn_global_cvoid *)(vbytes + vo), (attn_lds_void *)(vt + 4 * i * 256), 16, 0, 0);
+        }
+    };
+    int at = 0;  // byte offset of the present stage
+    issue(chain, 0);  // (more stages than chains: launch_prefix_wide)
+    for (int st = chain; st < n_stage; st += kPrefixChainsWide) {
+        if (st + kPrefixChainsWide < n_stage) {
+            issue(st + kPrefixChainsWide, kStageWideBytes - at);
+            asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+        } else {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+v"(qreg[0][ks]));  // older than the stage: landed too
+        int ln = lane;
+        asm volatile("" : "+v"(ln));  // (addresses formed anew, not kept; see attn_prefix_bf16)
+        unsigned kaddr[8], vaddr[4];
+        wide_lane_addresses(kaddr, vaddr, smem + at, ln);
+        u32x4 ka[8];
+        wide_load_k<0>(ka, kaddr);
+        asm volatile("s_waitcnt lgkmcnt(0)"
+                     : "+v"(ka[0]), "+v"(ka[1]), "+v"(ka[2]), "+v"(ka[3]), "+v"(ka[4]), "+v"(ka[5]), "+v"(ka[6]), "+v"(ka[7]));
+        wide_ring_tile<1, -1, true, 0>(w, qreg, ka, kaddr, vaddr, N - st * kStageWide, c_log2, ln, [] {});
+        at = kStageWideBytes - at;
+    }
+    float lo, hi;
+    pair_values(w.l[0], &lo, &hi);
+    if (qcol >= a.q_slots) return;
+    const int row = (chain * a.q_slots + qcol) * kPrefixRows;
+#pragma unroll
+    for (int mi = 0; mi < 4; ++mi) {
+        float *acc = (float *)prefix_scratch<O_BF16>(a, obase, row + mi / 2) + 32 * (mi & 1) + 4 * g;
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const f32x16 &x = w.acc[mi][0];
+            f32x4 val = {x[4 * q4], x[4 * q4 + 1], x[4 * q4 + 2], x[4 * q4 + 3]};
+            *(f32x4 *)(acc + 8 * q4) = val;
+        }
+    }
+    if (g == 0) {
+        float *ml = (float *)prefix_scratch<O_BF16>(a, obase, row + 2);
+        ml[0] = w.m[0];
+        ml[1] = lo + hi;
+    }
+}
+
+template <bool O_BF16>
+static jv_status launch_prefix_wide(const AttnArgs &a, int BH, hipStream_t stream) {
+    hipLaunchKernelGGL((attn_prefix_wide_bf16<O_BF16>), dim3(kPrefixChainsWide, BH, (a.q_slots + 31) / 32), dim3(64), 0, stream, a);
+    jv_status st = launch_status("attn_prefix_wide_bf16");
+    if (st != JV_OK) return st;
+    hipLaunchKernelGGL((prefix_combine_bf16<O_BF16, kHeadDimWide, kPrefixChainsWide>), dim3(a.q_slots, BH), dim3(64), 0, stream, a);
+    return launch_status("prefix_combine_bf16");
+}
+
 jv_status attn_bf16_check(const Problem &pr, const WindowGeom &g, int q_slots) {
     if (g.n_win > 65535) return fail(JV_ERR_UNSUPPORTED, "more than 65535 windows");
     // the streaming and ring kernels number their work items (query block, window, batch * head) in 32 bits
@@ -1832,6 +1941,15 @@ jv_status attn_bf16(const Problem &pr, const WindowGeom &g, float scale, int q_s
         const bool whole_windows = g.H % g.wh == 0 && g.W % g.ww == 0 && kStageWide % g.ww == 0;
         if ((a.contig || whole_windows) &&
             ((long long)pr.N + 2ll * kStageWide * g.W) * wide_sn * 2 + 512 < (1ll << 31)) {
+            // a few queries against the whole sequence (prefix tokens): the keys cut into chains, if there are
+            // stages and, behind the queries in O, rows for them.  What five prefix tokens add to window attention,
+            // us, ring kernel / chains: 1 369 tokens x 8 heads 30 / 8.6, 4 096 x 8 82 / 14.6, x 64 90 / 30,
+            // 16 384 x 8 324 / 36.
+            if (a.contig && a.q_slots < g.slots && a.q_slots <= 64 && g.n_win == 1 &&
+                g.slots > kPrefixChainsWide * kStageWide &&
+                kPrefixRows * kPrefixChainsWide * a.q_slots <= g.slots - a.q_slots)
+                return pr.o_bf16 ? launch_prefix_wide<true>(a, a.n_bh, stream)
+                                 : launch_prefix_wide<false>(a, a.n_bh, stream);
             if (pr.o_bf16) hipLaunchKernelGGL((attn_ring_wide_bf16<true, 1>), ring_grid(a, 128), dim3(256), 0, stream, a);
             else hipLaunchKernelGGL((attn_ring_wide_bf16<false, 1>), ring_grid(a, 128), dim3(256), 0, stream, a);
             return launch_status("attn_ring_wide_bf16");

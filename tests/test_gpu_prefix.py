@@ -71,36 +71,43 @@ def test_fp32_mixers_with_prefix(P, B, heads, H, W, window):
     check(err_fp32(to_host(got), oracle.linear_block(q, k, v, H, W, 1e-6, static_kernel=kern)), FP32_TOL)
 
 
-@pytest.mark.parametrize("P,H,W,fused", [
-    (1, 5, 5, True),       # one workgroup, one stage
-    (1, 7, 73, False),     # one workgroup: eight stages
-    (1, 16, 32, True),     # split: nine stages, the last of a single key
-    (5, 37, 37, True),     # 22 stages: chains of two and of three
-    (32, 29, 29, True),    # one block of queries at its largest
-    (33, 28, 29, True),    # two blocks; 812 grid tokens are rows for eight chains of 33
-    (33, 27, 29, True),    # 783 are not: one workgroup
-    (64, 32, 48, False),   # just the rows of eight chains of 64
-    (1, 128, 130, False),  # 261 stages
+@pytest.mark.parametrize("P,H,W,fused,D", [
+    (1, 5, 5, True, 64),       # one workgroup, one stage
+    (1, 7, 73, False, 64),     # one workgroup: eight stages
+    (1, 16, 32, True, 64),     # split: nine stages, the last of a single key
+    (5, 37, 37, True, 64),     # 22 stages: chains of two and of three
+    (32, 29, 29, True, 64),    # one block of queries at its largest
+    (33, 28, 29, True, 64),    # two blocks; 812 grid tokens are rows for eight chains of 33
+    (33, 27, 29, True, 64),    # 783 are not: one workgroup
+    (64, 32, 48, False, 64),   # just the rows of eight chains of 64
+    (1, 128, 130, False, 64),  # 261 stages
+    (1, 7, 73, False, 128),    # sixteen stages: not split
+    (1, 16, 32, True, 128),    # seventeen, the last of a single key
+    (5, 37, 37, True, 128),    # 43 stages: chains of two and of three
+    (32, 32, 48, True, 128),   # just the rows of sixteen chains of 32
+    (32, 31, 49, True, 128),   # a row too few
+    (33, 40, 40, True, 128),   # two blocks of queries
+    (64, 50, 62, False, 128),  # the largest prefix
 ])
-def test_prefix_rows_of_split_chains(P, H, W, fused):
+def test_prefix_rows_of_split_chains(P, H, W, fused, D):
     """The rows of the prefix tokens against the oracle's full attention, with inputs that raise the
     softmax reference along the keys; grid rows, where the chains' sums lie meanwhile, as without prefix."""
     B, heads, N = 2, 2, P + H * W
-    q, k, v = synth.qkv(66, B, heads, N, 64, 0.5, True)
+    q, k, v = synth.qkv(66, B, heads, N, D, 0.5, True)
     k = to_host(to_device(k * np.linspace(0.2, 3.0, N, dtype=np.float32)[:, None], True)).astype(np.float32)
     rows = [(b, h, i) for b in range(B) for h in range(heads) for i in range(P)]
-    ref = oracle.full_attn_rows(q, k, v, rows).reshape(B, heads, P, 64)
+    ref = oracle.full_attn_rows(q, k, v, rows).reshape(B, heads, P, D)
     outs = []
     for dt in (torch.float32, torch.bfloat16):
         dq, dk, dv = (to_device(x, True) for x in (q, k, v))
         if fused:
             qkv = torch.stack([t.permute(0, 2, 1, 3) for t in (dq, dk, dv)], 2).contiguous()
             dq, dk, dv = (qkv[:, :, i].permute(0, 2, 1, 3) for i in range(3))
-            o = torch.full((B, N, heads, 64), float("nan"), dtype=dt, device="cuda").permute(0, 2, 1, 3)
+            o = torch.full((B, N, heads, D), float("nan"), dtype=dt, device="cuda").permute(0, 2, 1, 3)
         else:
-            o = torch.full((B, heads, N, 64), float("nan"), dtype=dt, device="cuda")
+            o = torch.full((B, heads, N, D), float("nan"), dtype=dt, device="cuda")
         binding.jv_window_attn_fwd(dq, dk, dv, o, (H, W), (8, 8))
-        grid = torch.empty((B, heads, H * W, 64), dtype=dt, device="cuda")
+        grid = torch.empty((B, heads, H * W, D), dtype=dt, device="cuda")
         binding.jv_window_attn_fwd(*(t[:, :, P:].contiguous() for t in (dq, dk, dv)), grid, (H, W), (8, 8))
         assert torch.equal(o[:, :, P:], grid)
         outs.append(o[:, :, :P].contiguous())
