@@ -15,6 +15,7 @@
 
 #include "jv_linear.h"
 #include "jv_mfma.h"
+#include "jv_plan.h"
 
 namespace jv {
 
@@ -529,10 +530,7 @@ la_apply_bf16(TensorArg qt, TensorArg ot, const float *__restrict__ states, int 
 // an output row leaves as 128 contiguous bytes.  Taps outside the grid's width are skipped under the execution mask.
 // Grid and XCD mapping as la_apply_bf16, 256 threads, conv_ring_lds bytes of dynamic LDS.
 // ---------------------------------------------------------------------------------------
-constexpr int kRingStep = 128, kRingRepeat = 32;
-constexpr int kRingFixedLds = kStateFloats * 4 + 4 * 32 * 4;  // the state, afterwards four query tiles; 1 / denominators
-static int conv_ring_rows(int ksize, int W) { return kRingStep + 2 * (ksize / 2) * (W + 1); }
-static int conv_ring_lds(int ksize, int W) { return kRingFixedLds + (conv_ring_rows(ksize, W) + kRingRepeat) * 128; }
+static_assert(kRingFixedLds == kStateFloats * 4 + 4 * 32 * 4, "the ring follows the state");
 
 // The 3 x 3 taps of one token and two channels, row by row (the order in which la_apply_bf16 adds them):
 // s0 += k[di][dj][0] x[di][dj][0], s1 likewise, column dj in the lanes of use[dj] only.  For wavefronts whose lanes are all active.
@@ -812,12 +810,12 @@ static jv_status launch_apply(hipStream_t stream, const Problem &pr, const float
     // at the widest of them, 64 x 128 in chunks of 256 tokens, the ring fetches every row twice and
     // still takes 18 us instead of 19.6.
     if constexpr (KS != 0) {
-        const int lds = conv_ring_lds(KS, pr.W);
-        if (lds <= 80 * 1024) {
+        const long long lds = conv_ring_lds(KS, pr.W);
+        if (lds <= kRingMostLds) {
             static LdsLimit lds_limit;
-            jv_status st = ensure_lds_limit(lds_limit, (const void *)la_apply_conv_bf16<O_BF16, KS>, 80 * 1024);
+            jv_status st = ensure_lds_limit(lds_limit, (const void *)la_apply_conv_bf16<O_BF16, KS>, kRingMostLds);
             if (st != JV_OK) return st;
-            hipLaunchKernelGGL((la_apply_conv_bf16<O_BF16, KS>), dim3(8 * ((n_wg + 7) / 8)), dim3(256), lds, stream,
+            hipLaunchKernelGGL((la_apply_conv_bf16<O_BF16, KS>), dim3(8 * ((n_wg + 7) / 8)), dim3(256), (unsigned)lds, stream,
                                pr.q, pr.o, states, n_part, part_stride, pr.heads, pr.N, apply_tokens, n_chunks,
                                n_wg, eps, pr.v, cv, focus_p);
             return launch_status("la_apply_conv_bf16");

@@ -1,0 +1,43 @@
+"""The rules that choose kernels by sizes (csrc/jv_plan.h), on the host: a small program compiled
+against the header answers what the launchers would choose."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2605_26636_amd", "csrc")
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    """rule(expressions): the values of C++ integer expressions over namespace jv."""
+    def ask(expressions):
+        d = tmp_path_factory.mktemp("rules")
+        lines = "".join(f'    std::printf("%lld\\n", (long long)({e}));\n' for e in expressions)
+        (d / "main.cpp").write_text('#include <cstdio>\n#include "jv_plan.h"\nusing namespace jv;\nint main() {\n' + lines + "}\n")
+        exe = str(d / "rules")
+        # (signed overflow in a rule ends the program)
+        cmd = ["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=undefined", "-static-libubsan",
+               "-Wall", "-I", CSRC, str(d / "main.cpp"), "-o", exe]
+        built = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        assert built.returncode == 0, built.stdout
+        ran = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=60)
+        assert ran.returncode == 0, ran.stdout
+        return [int(x) for x in ran.stdout.split()]
+    return ask
+
+
+def test_ring_of_v_rows_at_every_width(rule):
+    """The ring's bytes are counted without wrapping, so grids of up to 2^24 columns never pass for small ones."""
+    sizes = [(k, w) for k in (3, 5) for w in (1, 3, 64, 85, 86, 128, 172, 173, 1 << 10, 1 << 20, 1 << 22, 1 << 23, (1 << 24) - 1, 1 << 24)]
+    got = rule([f"conv_ring_lds({k}, {w})" for k, w in sizes])
+    for (k, w), lds in zip(sizes, got):
+        rows = 128 + 2 * (k // 2) * (w + 1) + 32
+        assert lds == 65 * 64 * 4 + 512 + rows * 128
+    most, = rule(["kRingMostLds"])
+    assert {(k, w) for (k, w), lds in zip(sizes, got) if lds <= most} == {
+        (k, w) for k, w in sizes if w <= (172 if k == 3 else 85)}

@@ -117,6 +117,23 @@ def test_special_filters_bf16():
     assert torch.equal(got, plain + dv.float())
 
 
+@pytest.mark.parametrize("ksize,W", [(3, 1 << 24), (5, 1 << 23), (5, 1 << 22)])
+def test_bf16_grid_of_one_very_long_row(ksize, W):
+    """Up to 2^24 columns, where the bytes of a ring of V rows pass 2^32: a filter of one tap beside the
+    centre adds the next token's V."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(W)
+    q, k, v = (torch.randn((1, 1, W, 64), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    want = torch.empty(q.shape, dtype=torch.float32, device="cuda")
+    binding.jv_linear_attn_fwd(q, k, v, want, (1, W))
+    want[:, :, :-1] += v[:, :, 1:]
+    kern = torch.zeros(64, ksize, ksize, device="cuda")
+    kern[:, ksize // 2, ksize // 2 + 1] = 1.0
+    got = torch.empty_like(want)
+    binding.jv_linear_block_fwd(q, k, v, got, (1, W), static_kernel=kern, ksize=ksize)
+    assert torch.equal(got, want)
+
+
 def test_config2_block_sampled_rows():
     """The block at the benchmark workload's size (batch 8, 64 x 64 grid, 16 heads), squeeze-
     dynamic 3 x 3 filters with hidden width C / 16; sampled rows against the oracle."""
