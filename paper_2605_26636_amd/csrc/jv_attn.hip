@@ -251,8 +251,8 @@ attn_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, i
 // two runs of 128 bytes.  Half tiles of K and V rotate through three sets of sixteen registers, each
 // fetched while the matrix instructions of two others run (1 024 cycles each); with no LDS but the merge's
 // and 168 registers three workgroups fit a compute unit.  Against attn_f32<4>, us: 1 369 tokens x 12 heads
-// 104.6 -> 89.9 (516 workgroups: four units have three and the others two; x 11 68.7 -> 60.9), 256 x 6 10.6 -> 9.7,
-// 1 025 + 5 x 36 139 -> 114, windows of 14 x 14 on 40 x 40 x 24 49.4 -> 39.4.  The matrix instructions are 44 us of the 61.
+// 104.6 -> 87.2 (516 workgroups: four units have three and the others two; x 11 68.7 -> 60.0), 256 x 6 10.6 -> 9.7,
+// 1 025 + 5 x 36 139 -> 112, windows of 14 x 14 on 40 x 40 x 24 49.4 -> 39.7.  The matrix instructions are 44 us of the 61.
 // (Two chains of score products instead of one: the same; two workgroups per unit and more registers: the same.)
 // grid (ceil(q_slots / 32), n_win, B*heads), 256 threads.  Byte offsets inside a (batch, head) slice of K
 // and V below 2^32.
@@ -355,7 +355,11 @@ attn_direct_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGe
             for (int j = 0; j < 16; ++j) s[j] = (pads >> (8 * (j / 4) + j % 4)) & 1u ? -INFINITY : s[j];
         }
         // The reference stays while no logit is more than 8 binary orders above it (numerator and
-        // denominator share it, so the result is the same), and goes up to the maximum otherwise.
+        // denominator share it, so the result is the same), and goes up to the maximum otherwise.  The weights
+        // take a factor of 2^-8, exactly: none is above 1, and values up to the largest floats pass through the
+        // sums as under the maximum itself.  (The sixteen products: 1.5 % of a launch that leaves units with one
+        // workgroup.  A reference 8 orders up instead costs none, but rounds the exponents of the largest weights
+        // more coarsely: 4.7e-7 against 4.5e-7 from 64 bits at 1 369 tokens.)
         float top = s[0];
 #pragma unroll
         for (int j = 1; j < 16; ++j) top = fmaxf(top, s[j]);
@@ -374,7 +378,7 @@ attn_direct_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGe
         float sum = 0.f;
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-            s[j] = __builtin_amdgcn_exp2f(fmaf(s[j], scale_log2, -m));
+            s[j] = __builtin_amdgcn_exp2f(fmaf(s[j], scale_log2, -m)) * 0x1p-8f;
             sum += s[j];
         }
         l += sum;

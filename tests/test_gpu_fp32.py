@@ -88,6 +88,22 @@ def test_keys_split_over_wavefronts(H, W, window, P):
     check(err_fp32(to_host(o), ref), FP32_TOL)
 
 
+@pytest.mark.parametrize("N", [160, 256, 1030])
+def test_values_near_the_largest_floats(N):
+    """Weights of at most 1, also where a late key is some binary orders above the early ones: values of 1e37
+    pass through the sums without overflow (the oracle's maximum-subtracted softmax in 64 bits)."""
+    g = np.random.default_rng(45)
+    q, k, v = np.zeros((1, 2, N, 64), np.float32), np.zeros((1, 2, N, 64), np.float32), None
+    q[..., 0] = 8.0  # logits are k[..., 0]
+    k[..., 0] = 0.1 * g.standard_normal((1, 2, N))
+    k[:, :, 128 + 5::32, 0] = np.linspace(4.5, 5.4, k[:, :, 128 + 5::32].shape[2])  # one key of every later tile: 2^6.5 .. 2^7.8
+    v = (1e37 * g.uniform(0.5, 1.0, (1, 2, N, 64))).astype(np.float32)
+    dq, dk, dv = (to_device(x, False) for x in (q, k, v))
+    o = torch.full(dq.shape, float("nan"), device="cuda")
+    binding.jv_full_attn_fwd(dq, dk, dv, o, (1, N))
+    check(err_fp32(to_host(o), oracle.full_attn(q, k, v)), FP32_TOL)
+
+
 @pytest.mark.parametrize("H,W,window,P", [
     (5, 7, (1, 1), 0),         # every token alone: the result is its value row
     (5, 7, (1, 2), 0), (7, 5, (3, 1), 3), (9, 11, (2, 2), 5), (6, 6, (2, 4), 0), (3, 5, (4, 2), 0),
