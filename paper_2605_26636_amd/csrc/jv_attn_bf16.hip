@@ -17,6 +17,7 @@
 
 #include "jv_common.h"
 #include "jv_mfma.h"
+#include "jv_plan.h"
 
 #ifndef JV_ATTN_NT
 #define JV_ATTN_NT 2   // blocks of 32 query columns per wavefront
@@ -342,7 +343,6 @@ __device__ inline void queries_landed(u32x4 (&qreg)[NT][4]) {
 // the window's keys through LDS in double-buffered stages of 64.
 // grid ring_grid(a, 128 * NT): one workgroup per (block of 128 * NT query slots, window, batch * head); 256 threads.
 // ---------------------------------------------------------------------------------------
-constexpr int kStage = 64;
 constexpr int kStageBytes = 2 * kStage * 128;  // K rows then V rows
 
 template <bool O_BF16, int NT>
@@ -1025,8 +1025,6 @@ __global__ void __launch_bounds__(256, NT == 1 ? 3 : 2) attn_ring_bf16(AttnArgs 
 // after the other; the chains by those of an eighth of the stages, half of them hidden.
 // Dynamic LDS: prefix_lds(SPLIT).  Requirements as attn_ring_bf16.
 // ---------------------------------------------------------------------------------------
-constexpr int kPrefixChains = 8;
-constexpr int kPrefixRows = 3;  // rows of O a query of a chain takes
 constexpr int prefix_lds(bool split) {
     return split ? 2 * kStageBytes : kPrefixChains * kStageBytes + 2 * kPrefixChains * 64 * 4;
 }
@@ -1239,16 +1237,12 @@ __global__ void __launch_bounds__(64) prefix_combine_bf16(AttnArgs a) {
     }
 }
 
-// Split where a chain has more than one stage, the (batch, head)s alone leave units without a workgroup and
-// the rows behind the queries hold the chains (24 rows a query).  What five prefix tokens add to window
-// attention, us, one workgroup with two blocks of queries whatever their number / as chosen here: split
-// 1 369 tokens x 12 heads 14.4 / 8.8, 4 096 x 16 31.8 / 16.6, x 128 37 / 28, 8 192 x 16 54 / 24, 16 384 x 32
-// 101 / 46; not split 1 369 x 512 42.7 / 33.3 (split 44), 400 x 80 9.0 / 6.5 (split 8.9), 196 x 256 7.8 / 5.3 (8.9).
+// What five prefix tokens add to window attention, us, one workgroup with two blocks of queries whatever their number / as
+// chosen (prefix_in_chains): in chains 1 369 tokens x 12 heads 14.4 / 8.8, 4 096 x 16 31.8 / 16.6, x 128 37 / 28, 8 192 x 16 54 / 24,
+// 16 384 x 32 101 / 46; in one 1 369 x 512 42.7 / 33.3 (chains 44), 400 x 80 9.0 / 6.5 (8.9), 196 x 256 7.8 / 5.3 (8.9).
 template <bool O_BF16, int NT>
 static jv_status launch_prefix(const AttnArgs &a, int BH, hipStream_t stream) {
-    const bool split = a.g.slots > kPrefixChains * kStage && BH <= 256 &&
-                       kPrefixRows * kPrefixChains * a.q_slots <= a.g.slots - a.q_slots;
-    if (!split) {
+    if (!prefix_in_chains(a.g.slots, a.q_slots, BH)) {
         static LdsLimit lds_limit;
         jv_status st = ensure_lds_limit(lds_limit, (const void *)attn_prefix_bf16<O_BF16, NT, false>, prefix_lds(false));
         if (st != JV_OK) return st;

@@ -41,3 +41,13 @@ def test_ring_of_v_rows_at_every_width(rule):
     most, = rule(["kRingMostLds"])
     assert {(k, w) for (k, w), lds in zip(sizes, got) if lds <= most} == {
         (k, w) for k, w in sizes if w <= (172 if k == 3 else 85)}
+
+
+def test_prefix_chains_of_64_channel_heads(rule):
+    """(prefix tokens, grid tokens, batch x heads) on either side of every line of the rule, as measured."""
+    one = [(5, 576, 12), (1, 784, 16), (5, 784, 64), (5, 1369, 144), (16, 1369, 192), (5, 2304, 160), (5, 4096, 256), (33, 1000, 64),
+           (33, 1369, 96), (33, 1369, 144), (64, 2304, 128), (64, 4096, 144), (64, 1500, 4), (5, 100, 4)]
+    chains = [(1, 896, 4), (5, 1000, 64), (5, 1369, 12), (5, 1369, 128), (16, 1369, 96), (5, 4096, 192), (1, 16384, 128),
+              (33, 1369, 64), (33, 2304, 96), (64, 4096, 128), (64, 1536, 4)]
+    got = rule([f"prefix_in_chains({p + n}, {p}, {bh})" for p, n, bh in one + chains])
+    assert got == [0] * len(one) + [1] * len(chains)

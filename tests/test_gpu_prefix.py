@@ -74,11 +74,16 @@ def test_fp32_mixers_with_prefix(P, B, heads, H, W, window):
 @pytest.mark.parametrize("P,H,W,fused,D", [
     (1, 5, 5, True, 64),       # one workgroup, one stage
     (1, 7, 73, False, 64),     # one workgroup: eight stages
-    (1, 16, 32, True, 64),     # split: nine stages, the last of a single key
+    (1, 16, 32, True, 64),     # one workgroup: nine stages, the last of a single key
+    (32, 29, 29, True, 64),    # one workgroup: 14 stages, one block of queries at its largest
+    (33, 28, 29, True, 64),    # one workgroup, two blocks
+    (33, 27, 29, True, 64),
+    (1, 28, 32, True, 64),     # chains: 15 stages, the last of a single key
     (5, 37, 37, True, 64),     # 22 stages: chains of two and of three
-    (32, 29, 29, True, 64),    # one block of queries at its largest
-    (33, 28, 29, True, 64),    # two blocks; 812 grid tokens are rows for eight chains of 33
-    (33, 27, 29, True, 64),    # 783 are not: one workgroup
+    (32, 29, 30, True, 64),    # one block of queries at its largest
+    (33, 29, 31, True, 64),    # two blocks
+    (37, 24, 37, True, 64),    # 888 grid tokens are just the rows of eight chains of 37
+    (37, 1, 887, True, 64),    # a row too few: one workgroup
     (64, 32, 48, False, 64),   # just the rows of eight chains of 64
     (1, 128, 130, False, 64),  # 261 stages
     (1, 7, 73, False, 128),    # sixteen stages: not split
