@@ -1293,7 +1293,6 @@ static jv_status launch_window8(const AttnArgs &a, int BH, hipStream_t stream) {
 // vector work per matrix instruction is half that of the 64-channel kernels.
 // grid ring_grid(a, 128): one workgroup per (block of 128 query slots, window, batch * head); 256 threads.
 // ---------------------------------------------------------------------------------------
-constexpr int kStageWide = 32;
 constexpr int kTileWideBytes = kStageWide * 256;    // the K rows or the V rows of a stage
 constexpr int kStageWideBytes = 2 * kTileWideBytes;
 
@@ -1814,8 +1813,6 @@ __global__ void __launch_bounds__(256, 2) attn_ring_wide_bf16(AttnArgs a) {
 // taking every sixteenth stage of 32 keys from stage w on, one wavefront and two stages of LDS each, for one block
 // of 32 queries; the rows of the scratch hold 64 channels.
 // grid (kPrefixChainsWide, B*heads, blocks of 32 queries), 64 threads.  Requirements as attn_ring_wide_bf16.
-constexpr int kPrefixChainsWide = 16;
-
 template <bool O_BF16>
 __global__ void __launch_bounds__(64, 2) attn_prefix_wide_bf16(AttnArgs a) {
     float c_log2 = a.c;
@@ -1935,13 +1932,11 @@ jv_status attn_bf16(const Problem &pr, const WindowGeom &g, float scale, int q_s
         const bool whole_windows = g.H % g.wh == 0 && g.W % g.ww == 0 && kStageWide % g.ww == 0;
         if ((a.contig || whole_windows) &&
             ((long long)pr.N + 2ll * kStageWide * g.W) * wide_sn * 2 + 512 < (1ll << 31)) {
-            // a few queries against the whole sequence (prefix tokens): the keys cut into chains, if there are
-            // stages and, behind the queries in O, rows for them.  What five prefix tokens add to window attention,
-            // us, ring kernel / chains: 1 369 tokens x 8 heads 30 / 8.6, 4 096 x 8 82 / 14.6, x 64 90 / 30,
-            // 16 384 x 8 324 / 36.
+            // a few queries against the whole sequence (prefix tokens): the keys cut into chains.  What five prefix
+            // tokens add to window attention, us, ring kernel / chains: 1 369 tokens x 8 heads 30 / 8.6, 4 096 x 8
+            // 82 / 14.6, x 64 90 / 30, 16 384 x 8 324 / 36.
             if (a.contig && a.q_slots < g.slots && a.q_slots <= 64 && g.n_win == 1 &&
-                g.slots > kPrefixChainsWide * kStageWide &&
-                kPrefixRows * kPrefixChainsWide * a.q_slots <= g.slots - a.q_slots)
+                prefix_in_chains_wide(g.slots, a.q_slots, a.n_bh))
                 return pr.o_bf16 ? launch_prefix_wide<true>(a, a.n_bh, stream)
                                  : launch_prefix_wide<false>(a, a.n_bh, stream);
             if (pr.o_bf16) hipLaunchKernelGGL((attn_ring_wide_bf16<true, 1>), ring_grid(a, 128), dim3(256), 0, stream, a);

@@ -17,8 +17,8 @@ constexpr long long conv_ring_lds(int ksize, long long W) {
 // Prefix tokens: `queries` <= 64 queries against the `keys` tokens of a whole sequence, per (batch, head) (jv_attn_bf16.hip).
 // Keys come in stages; chains of stages run as workgroups of their own whose sums wait in the rows of O
 // behind the queries, kPrefixRows of them for a query of a chain.
-constexpr int kStage = 64;
-constexpr int kPrefixChains = 8, kPrefixRows = 3;
+constexpr int kStage = 64, kStageWide = 32;  // keys of a stage, heads of 64 and of 128 channels
+constexpr int kPrefixChains = 8, kPrefixChainsWide = 16, kPrefixRows = 3;
 constexpr bool prefix_rows_fit(int keys, int queries, int chains) { return kPrefixRows * chains * queries <= keys - queries; }
 
 // Heads of 64 channels: chains as workgroups, or (the same bits) as the wavefronts of one workgroup.  The
@@ -32,6 +32,18 @@ constexpr bool prefix_in_chains(int keys, int queries, int bh) {
     const int stages = (keys + kStage - 1) / kStage;
     const int most = queries > 32 ? (stages < 43 ? 3 * stages : 128) : stages < 64 ? 128 : 192;
     return stages >= 2 * kPrefixChains - 1 && bh <= most && prefix_rows_fit(keys, queries, kPrefixChains);
+}
+// Heads of 128 channels: chains, or one workgroup of the ring kernel that walks all keys.  A (batch, head) has a
+// wavefront per chain and block of 32 queries, which fetches the keys once more and writes the sums of its queries: the more
+// of both there are for a stage, the sooner the chip is full without chains.  The line is fitted to 313 launches of 512 to 4 096
+// tokens (0.1 % off the better of the two on average, 4 % at worst).  Ring kernel / chains, window attention included, us,
+// 5 tokens in front of 576 tokens x 64 29.8 / 25.8, x 128 37.0 / 38.8, 1 369 x 160 85.7 / 82.1, x 256 124.5 / 127.7,
+// 4 096 x 256 356 / 348, x 384 505 / 514; 32 in front of 2 304 x 160 138.5 / 137.7, x 256 201 / 224;
+// 64 in front of 4 096 x 64 140 / 117, x 80 165 / 145, x 128 219 / 251, x 512 672 / 1 069.
+constexpr bool prefix_in_chains_wide(int keys, int queries, int bh) {
+    const int stages = (keys + kStageWide - 1) / kStageWide, line = stages < 87 ? 3 * stages + 60 : 320;
+    const long long blocks = (long long)bh * ((queries + 31) / 32);
+    return stages > kPrefixChainsWide && blocks * (96 + queries) <= 96 * line && prefix_rows_fit(keys, queries, kPrefixChainsWide);
 }
 
 }  // namespace jv

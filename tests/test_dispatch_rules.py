@@ -51,3 +51,12 @@ def test_prefix_chains_of_64_channel_heads(rule):
               (33, 1369, 64), (33, 2304, 96), (64, 4096, 128), (64, 1536, 4)]
     got = rule([f"prefix_in_chains({p + n}, {p}, {bh})" for p, n, bh in one + chains])
     assert got == [0] * len(one) + [1] * len(chains)
+
+
+def test_prefix_chains_of_128_channel_heads(rule):
+    ring = [(5, 500, 4), (5, 576, 128), (5, 784, 160), (16, 784, 128), (5, 1369, 192), (5, 2304, 384), (5, 4096, 384), (16, 1024, 144),
+            (32, 2304, 256), (33, 2304, 128), (33, 4096, 128), (64, 4096, 112), (64, 4096, 512), (32, 1519, 4), (64, 1369, 4)]
+    chains = [(1, 512, 4), (5, 576, 64), (5, 1000, 144), (16, 1024, 112), (5, 1369, 160), (5, 4096, 256), (32, 2304, 160), (33, 4096, 96),
+              (64, 4096, 80), (32, 1536, 4), (64, 3100, 4)]
+    got = rule([f"prefix_in_chains_wide({p + n}, {p}, {bh})" for p, n, bh in ring + chains])
+    assert got == [0] * len(ring) + [1] * len(chains)
