@@ -7,8 +7,6 @@ namespace jv {
 
 constexpr int kStateFloats = kHeadDim * kHeadDim + kHeadDim;  // St[c2][c1] then z[c1]
 
-constexpr int kApplyRounds = 8;  // rounds of 256 tokens a workgroup of the bf16 apply pass takes at most
-
 struct LinearPlan {
     int n_split;       // token chunks per (batch, head) in the state pass
     int chunk;         // tokens per chunk (a multiple of 256, fp32 tensors: of 64)

@@ -8,6 +8,7 @@
 // and holds S transposed, St[c2][c1] (c2 = value channel, c1 = key channel), then z[c1].
 #include "jv_linear.h"
 #include "jv_mfma.h"
+#include "jv_plan.h"
 
 namespace jv {
 
@@ -42,20 +43,7 @@ LinearPlan plan_linear(int B, int heads, int N, bool bf16) {
     chunk = ((chunk + 255) / 256) * 256;
     p.chunk = (int)chunk;
     p.n_split = (int)((N + chunk - 1) / chunk);
-    // Token chunks of the apply pass.  A workgroup's time is its rounds of 256 tokens (64 per
-    // wavefront) and about one and a half more for summing the states and splitting them into
-    // operands; 512 workgroups run at a time.  Against 1 024 tokens halved until there are 512
-    // workgroups, us: 32 images of 37 x 37 with 16 heads 77.0 -> 74.2 (one chunk instead of 1 024 + 345), with
-    // 8 heads of 128 and the 3 x 3 convolution 174 -> 145, 11 of 50 x 60 with 12 heads 55.5 -> 53.0.
-    const int rounds = (N + 255) / 256;
-    long long best = -1;
-    for (int per = kApplyRounds; per > 0; --per) {
-        const long long cost = ((bh * ((rounds + per - 1) / per) + 511) / 512) * (2 * per + 3);
-        if (best < 0 || cost < best) {
-            best = cost;
-            p.apply_tokens = 256 * per;
-        }
-    }
+    p.apply_tokens = 256 * apply_rounds(bh, N);
     p.combine = p.n_split > 4;
     return p;
 }

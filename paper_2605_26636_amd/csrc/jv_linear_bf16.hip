@@ -806,16 +806,12 @@ static jv_status launch_apply(hipStream_t stream, const Problem &pr, const float
                          long long part_stride, int apply_tokens, float eps, const DwcArg &cv,
                          int focus_p) {
     const int n_chunks = (pr.N + apply_tokens - 1) / apply_tokens, n_wg = n_chunks * pr.B * pr.heads;
-    // As long as two workgroups' rings share a compute unit (grids up to 172 columns for 3 x 3, 85 for 5 x 5);
-    // at the widest of them, 64 x 128 in chunks of 256 tokens, the ring fetches every row twice and
-    // still takes 18 us instead of 19.6.
     if constexpr (KS != 0) {
-        const long long lds = conv_ring_lds(KS, pr.W);
-        if (lds <= kRingMostLds) {
+        if (conv_takes_ring(KS, cv.kappa_sb != 0, pr.W, pr.N, n_wg)) {
             static LdsLimit lds_limit;
             jv_status st = ensure_lds_limit(lds_limit, (const void *)la_apply_conv_bf16<O_BF16, KS>, kRingMostLds);
             if (st != JV_OK) return st;
-            hipLaunchKernelGGL((la_apply_conv_bf16<O_BF16, KS>), dim3(8 * ((n_wg + 7) / 8)), dim3(256), (unsigned)lds, stream,
+            hipLaunchKernelGGL((la_apply_conv_bf16<O_BF16, KS>), dim3(8 * ((n_wg + 7) / 8)), dim3(256), (unsigned)conv_ring_lds(KS, pr.W), stream,
                                pr.q, pr.o, states, n_part, part_stride, pr.heads, pr.N, apply_tokens, n_chunks,
                                n_wg, eps, pr.v, cv, focus_p);
             return launch_status("la_apply_conv_bf16");

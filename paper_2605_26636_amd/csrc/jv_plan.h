@@ -13,6 +13,37 @@ constexpr int kRingMostLds = 80 * 1024;                         // two workgroup
 constexpr long long conv_ring_lds(int ksize, long long W) {
     return kRingFixedLds + (kRingStep + 2 * (ksize / 2) * (W + 1) + kRingRepeat) * 128;
 }
+// The ring, or V loaded tap by tap (la_apply_bf16; the same bits).  Grids for which two rings do not share a compute
+// unit (above 172 columns for 3 x 3, 85 for 5 x 5) load V directly; at the widest below, 64 x 128 in chunks of 256 tokens, the ring fetches
+// every row twice and still takes 18 us instead of 19.6.  A workgroup fills its ring before the first step, which a launch of one
+// workgroup a unit waits out: up to 256 of them, of more than a step, load V directly too, unless the state pass has
+// left V in the caches (the filters come from its token sum) and there are two steps or 25 taps.  Direct / ring, us, the block with
+// static filters: 14 x 14 x 12 heads 15.4 / 16.0, 40 x 85 x 12 (168 workgroups) 20.5 / 21.6, 64 x 64 x 16 (256) 20.4 / 21.2, but
+// 10 x 10 x 12 (one step) 15.2 / 12.1, 2 of 64 x 64 x 16 (512) 30.1 / 28.4; with generated ones 3 x 3 40 x 85 x 12 27.2 / 28.0,
+// 11 x 12 x 12 22.3 / 21.8, 5 x 5 14 x 14 x 12 30.1 / 28.9.
+constexpr bool conv_takes_ring(int ksize, bool generated, int W, int N, int n_wg) {
+    return conv_ring_lds(ksize, W) <= kRingMostLds && (n_wg > 256 || N <= kRingStep || (generated && (ksize == 5 || N <= 2 * kRingStep)));
+}
+
+// Rounds of 256 tokens (64 per wavefront), 1 to kApplyRounds, that a workgroup of the apply pass of linear attention on bf16 tensors
+// takes.  Its time is its rounds and about one and a half more for summing the states and splitting them into
+// operands; 512 workgroups run at a time.  Against 1 024 tokens halved until there are 512
+// workgroups, us: 32 images of 37 x 37 with 16 heads 77.0 -> 74.2 (one chunk instead of 1 024 + 345), with
+// 8 heads of 128 and the 3 x 3 convolution 174 -> 145, 11 of 50 x 60 with 12 heads 55.5 -> 53.0.
+constexpr int kApplyRounds = 8;
+constexpr int apply_rounds(long long bh, int N) {
+    const int rounds = (N + 255) / 256;
+    long long best = -1;
+    int chosen = 1;
+    for (int per = kApplyRounds; per > 0; --per) {
+        const long long cost = ((bh * ((rounds + per - 1) / per) + 511) / 512) * (2 * per + 3);
+        if (best < 0 || cost < best) {
+            best = cost;
+            chosen = per;
+        }
+    }
+    return chosen;
+}
 
 // Prefix tokens: `queries` <= 64 queries against the `keys` tokens of a whole sequence, per (batch, head) (jv_attn_bf16.hip).
 // Keys come in stages; chains of stages run as workgroups of their own whose sums wait in the rows of O

@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+import test_gpu_linear_block
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2605_26636_amd", "csrc")
 
@@ -41,6 +43,29 @@ def test_ring_of_v_rows_at_every_width(rule):
     most, = rule(["kRingMostLds"])
     assert {(k, w) for (k, w), lds in zip(sizes, got) if lds <= most} == {
         (k, w) for k, w in sizes if w <= (172 if k == 3 else 85)}
+
+
+def test_ring_or_direct_loads_of_v(rule):
+    """(ksize, generated filters, W, N, workgroups) on either side of every line of the rule, and the launches that
+    the GPU tests of the ring count on."""
+    direct = [(3, 0, 14, 196, 12), (3, 0, 85, 3400, 168), (3, 0, 64, 4096, 256), (5, 0, 37, 1369, 96), (3, 1, 37, 1369, 96), (3, 1, 16, 257, 256),
+              (3, 0, 173, 4096, 4096), (5, 0, 86, 4096, 4096), (3, 0, 1 << 24, 1 << 24, 8192), (5, 0, 1 << 23, 1 << 23, 4096)]
+    ring = [(3, 0, 10, 100, 12), (3, 0, 16, 128, 4), (3, 1, 16, 256, 4), (3, 0, 64, 4096, 257), (5, 1, 37, 1369, 96), (3, 1, 128, 8192, 512), (3, 0, 172, 4096, 4096), (5, 0, 85, 4096, 4096)]
+    got = rule([f"conv_takes_ring({k}, {g}, {w}, {n}, {wg})" for k, g, w, n, wg in direct + ring])
+    assert got == [0] * len(direct) + [1] * len(ring)
+
+    shapes = [(k, w, p + h * w) for k, h, w, p in test_gpu_linear_block.WINDOW_OF_V]
+    rounds = rule([f"apply_rounds(512, {n})" for _, _, n in shapes])
+    many = rule([f"conv_takes_ring({k}, 0, {w}, {n}, 512 * (({n} + 256 * {r} - 1) / (256 * {r})))" for (k, w, n), r in zip(shapes, rounds)])
+    alone = rule([f"conv_takes_ring({k}, 0, {w}, {n}, 2 * (({n} + 255) / 256))" for k, w, n in shapes])
+    steps = [(min(n, 256 * r) + 127) // 128 for (_, _, n), r in zip(shapes, rounds)]
+    assert many == [w <= (172 if k == 3 else 85) for k, w, _ in shapes] and not any(alone)
+    assert min(steps) == 3 and max(steps) == 16 and sum(s >= 8 for s in steps) >= 12
+
+    for k, h, w, p in test_gpu_linear_block.RING_OR_DIRECT:
+        n = p + h * w
+        assert rule([f"conv_takes_ring({k}, 0, {w}, {n}, {wg} * (({n} + 256 * apply_rounds({wg}, {n}) - 1) / (256 * apply_rounds({wg}, {n}))))"
+                     for wg in (256, 258)]) == [0, 1]
 
 
 def test_prefix_chains_of_64_channel_heads(rule):

@@ -64,24 +64,61 @@ def test_bf16_static_and_dynamic(B, heads, H, W, ksize):
         check_bf16_pair(o32, o16, ref)
 
 
-@pytest.mark.parametrize("ksize,H,W,P", [
+# 256 copies of the image make 512 workgroups or more, on the ring of V rows up to 172 (3 x 3) and 85 (5 x 5) columns, of 3 to 16 steps
+# of 128 tokens each (checked on the host in test_dispatch_rules.py); one image alone takes the kernel that loads V directly.
+WINDOW_OF_V = [
     (3, 300, 1, 0), (3, 150, 2, 3), (3, 100, 3, 5), (3, 97, 4, 64), (3, 60, 5, 0), (3, 41, 13, 1),
     (3, 7, 172, 5), (3, 5, 173, 0),                 # the widest grid whose ring shares a unit, and one more
     (5, 300, 1, 0), (5, 70, 4, 2), (5, 40, 9, 64), (5, 33, 31, 0), (5, 11, 85, 5), (5, 9, 86, 0),
-])
+    (3, 1700, 1, 5), (3, 651, 3, 0), (3, 130, 13, 5), (3, 37, 37, 5), (3, 24, 85, 0), (3, 110, 37, 5),  # 11 to 16 steps
+    (5, 1500, 1, 5), (5, 500, 3, 5), (5, 150, 13, 0), (5, 37, 37, 5), (5, 24, 85, 5), (5, 55, 74, 0),
+]
+
+
+@pytest.mark.parametrize("ksize,H,W,P", WINDOW_OF_V)
 def test_bf16_window_of_v(ksize, H, W, P):
-    """The apply pass that moves a window of V through LDS: several steps of 128 tokens, grids whose
-    rows wrap inside a group of four tokens, prefix tokens that fill whole wavefronts' first steps,
-    and a ring that wraps at every offset."""
-    heads = 2
+    """The apply pass that moves a window of V through LDS: up to 16 steps of 128 tokens, a ring that wraps several
+    times, grids whose rows wrap inside a group of four tokens, prefix tokens that fill whole wavefronts' first
+    steps.  The same image alone goes through the kernel that loads V directly."""
+    heads, copies = 2, 256
     C = heads * 64
     q, k, v = synth.qkv(36, 1, heads, P + H * W, 64, 0.5, True)
     kern = synth.dwc_static_kernel(C, ksize, 3600 + W)
     ref = oracle.linear_block(q, k, v, H, W, 1e-6, ksize=ksize, static_kernel=kern)
-    o32 = _block(q, k, v, H, W, True, torch.float32, ksize=ksize, static_kernel=_dev(kern)[0])
-    o16 = _block(q, k, v, H, W, True, torch.bfloat16, ksize=ksize, static_kernel=_dev(kern)[0])
-    check(err_bf16(to_host(o32), ref), 2e-3)
-    check_bf16_pair(o32, o16, ref)
+    outs = []
+    for dtype in (torch.float32, torch.bfloat16):
+        dq, dk, dv = (to_device(x, True) for x in (q, k, v))
+        one = torch.full(dq.shape, float("nan"), dtype=dtype, device="cuda")
+        binding.jv_linear_block_fwd(dq, dk, dv, one, (H, W), 1e-6, ksize=ksize, static_kernel=_dev(kern)[0])
+        dq, dk, dv = (t.repeat(copies, 1, 1, 1) for t in (dq, dk, dv))
+        many = torch.full(dq.shape, float("nan"), dtype=dtype, device="cuda")
+        binding.jv_linear_block_fwd(dq, dk, dv, many, (H, W), 1e-6, ksize=ksize, static_kernel=_dev(kern)[0])
+        outs.append((one, many))
+    check(err_bf16(to_host(outs[0][0]), ref), 2e-3)
+    check_bf16_pair(outs[0][0], outs[1][0], ref)
+    check(err_bf16(to_host(outs[0][1][:1]), ref), 2e-3)
+    check_bf16_pair(outs[0][1][:1], outs[1][1][:1], ref)
+    for _, many in outs:
+        assert torch.equal(many, many[:1].expand_as(many))
+
+
+# 128 images of two heads are 256 workgroups, which load V directly, 129 take the ring; one state each.
+RING_OR_DIRECT = [(3, 16, 16, 0), (3, 50, 5, 0), (3, 2, 85, 5), (3, 10, 14, 64), (5, 16, 16, 0), (5, 250, 1, 3), (5, 3, 80, 1)]
+
+
+@pytest.mark.parametrize("ksize,H,W,P", RING_OR_DIRECT)
+def test_bf16_ring_and_direct_loads_of_v_give_the_same_bits(ksize, H, W, P):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3800 + W)
+    q, k, v = (0.5 * torch.randn((129, 2, P + H * W, 64), generator=gen, device="cuda") for _ in range(3))
+    q, k, v = (t.to(torch.bfloat16) for t in (q, k, v))
+    kern = torch.randn((128, ksize, ksize), generator=gen, device="cuda")
+    for dtype in (torch.float32, torch.bfloat16):
+        ring = torch.full(q.shape, float("nan"), dtype=dtype, device="cuda")
+        direct = torch.full_like(ring[:128], float("nan"))
+        binding.jv_linear_block_fwd(q, k, v, ring, (H, W), ksize=ksize, static_kernel=kern)
+        binding.jv_linear_block_fwd(q[:128], k[:128], v[:128], direct, (H, W), ksize=ksize, static_kernel=kern)
+        assert torch.equal(ring[:128], direct)
 
 
 @pytest.mark.parametrize("B,hidden", [(1, 4), (2, 64), (4, 68), (8, 100), (9, 128)])
