@@ -778,8 +778,8 @@ __global__ void __launch_bounds__(256, 2) attn_window8_bf16(AttnArgs a, int n_it
 // ---------------------------------------------------------------------------------------
 // Streaming kernel for windows that span whole grid rows (full attention above all), with
 // byte offsets inside one (batch, head) slice below 2^31 (checked by the launcher).
-// Same tiling as attn_stream_bf16 (a workgroup holds 256 query slots, keys pass through LDS
-// in stages of 64), but built so that the inner loop is nothing but matrix instructions,
+// Tiled as attn_stream_bf16 (a workgroup holds 128 NT query slots, 32 NT per wavefront, keys pass
+// through LDS in stages of 64; NT by ring_query_blocks), but built so that the inner loop is nothing but matrix instructions,
 // exponentials and LDS operand reads:
 //   * K/V stages go from global memory straight into a ring of three LDS stages (no register
 //     staging, no LDS stores, no per-row selects), two stages ahead of the arithmetic; a
@@ -790,7 +790,7 @@ __global__ void __launch_bounds__(256, 2) attn_window8_bf16(AttnArgs a, int n_it
 //   * every full stage runs the unmasked tile code, which is one basic block per tile apart
 //     from the (rarely taken) branch that raises the softmax reference; only the last,
 //     partial stage of a window masks keys, and it does so by key index, not through LDS.
-// grid ring_grid(a, 256): one workgroup per (block of 256 query slots, window, batch * head),
+// grid ring_grid(a, 128 * NT): one workgroup per (block of 128 NT query slots, window, batch * head),
 // dealt to the XCDs in contiguous ranges (ring_item); 256 threads.
 // ---------------------------------------------------------------------------------------
 constexpr int kRing = 3;
@@ -1975,20 +1975,7 @@ jv_status attn_bf16(const Problem &pr, const WindowGeom &g, float scale, int q_s
         return pr.o_bf16 ? launch_prefix<true, 2>(a, pr.B * pr.heads, stream)
                          : launch_prefix<false, 2>(a, pr.B * pr.heads, stream);
     }
-    // The ring kernel with two blocks of 32 queries per wavefront or with one (the same bits): two workgroups of
-    // 256 queries on a compute unit do the most per second, but three of 128 come close, and the smaller
-    // blocks leave fewer units with less than their share.  Time of a launch's last round by the workgroups
-    // a unit has in it, and of a full round, as measured at 1 374 keys, us: 256 queries 32.6 (one), 45.4 (two);
-    // 128 queries 21.6, 28.4, 38.5 (three).  Two blocks / one, us: 1 374 tokens x 16 heads 20.2 / 14.3, x 32 32.6 / 28.4,
-    // x 48 45.2 / 36.2, 5 184 x 16 151 / 130, 8 192 x 16 257 / 291, 4 096 x 64 260 / 281, x 128 515 / 550.
-    const long long lanes = (long long)g.n_win * a.n_bh;
-    const long long blocks2 = (a.q_slots + 255) / 256 * lanes, blocks1 = (a.q_slots + 127) / 128 * lanes;
-    const auto last = [](long long rest, float one, float two, float three) {
-        return rest == 0 ? 0.f : rest <= 256 ? one : rest <= 512 ? two : three;
-    };
-    const float t2 = (float)(blocks2 / 512) * 45.4f + last(blocks2 % 512, 32.6f, 45.4f, 0.f);
-    const float t1 = (float)(blocks1 / 768) * 38.5f + last(blocks1 % 768, 21.6f, 28.4f, 38.5f);
-    if (fast && NT == 2 && 1.08f * t1 < t2) {  // (rounds overlap, to the large blocks' advantage)
+    if (fast && NT == 2 && ring_query_blocks(a.q_slots, (long long)g.n_win * a.n_bh) == 1) {
         if (pr.o_bf16) hipLaunchKernelGGL((attn_ring_bf16<true, 1>), ring_grid(a, 128), dim3(256), 0, stream, a);
         else hipLaunchKernelGGL((attn_ring_bf16<false, 1>), ring_grid(a, 128), dim3(256), 0, stream, a);
         return launch_status("attn_ring_bf16");

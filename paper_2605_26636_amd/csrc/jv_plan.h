@@ -45,6 +45,22 @@ constexpr int apply_rounds(long long bh, int N) {
     return chosen;
 }
 
+// bf16 attention over whole grid rows (attn_ring_bf16): blocks of 32 queries per wavefront, two or (the same bits) one, for
+// `queries` query slots in each of `lanes` windows times (batch, head)s.  Two workgroups of 256 queries on a compute unit
+// do the most per second, but three of 128 come close, and the smaller blocks leave fewer units with less than
+// their share.  Time of a launch's last round by the workgroups a unit has in it, and of a full round, as measured at
+// 1 374 keys, us: 256 queries 32.6 (one), 45.4 (two); 128 queries 21.6, 28.4, 38.5 (three).  Two blocks / one, us: 1 374 tokens
+// x 16 heads 20.2 / 14.3, x 32 32.6 / 28.4, x 48 45.2 / 36.2, 5 184 x 16 151 / 130, 8 192 x 16 257 / 291, 4 096 x 64 260 / 281, x 128 515 / 550.
+constexpr float last_round(long long rest, float one, float two, float three) {
+    return rest == 0 ? 0.f : rest <= 256 ? one : rest <= 512 ? two : three;
+}
+constexpr int ring_query_blocks(int queries, long long lanes) {
+    const long long blocks2 = (queries + 255) / 256 * lanes, blocks1 = (queries + 127) / 128 * lanes;
+    const float t2 = (float)(blocks2 / 512) * 45.4f + last_round(blocks2 % 512, 32.6f, 45.4f, 0.f);
+    const float t1 = (float)(blocks1 / 768) * 38.5f + last_round(blocks1 % 768, 21.6f, 28.4f, 38.5f);
+    return 1.08f * t1 < t2 ? 1 : 2;  // (rounds overlap, to the large blocks' advantage)
+}
+
 // Prefix tokens: `queries` <= 64 queries against the `keys` tokens of a whole sequence, per (batch, head) (jv_attn_bf16.hip).
 // Keys come in stages; chains of stages run as workgroups of their own whose sums wait in the rows of O
 // behind the queries, kPrefixRows of them for a query of a chain.

@@ -6,6 +6,7 @@ import subprocess
 
 import pytest
 
+import test_gpu_bf16_attn
 import test_gpu_linear_block
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -66,6 +67,15 @@ def test_ring_or_direct_loads_of_v(rule):
         n = p + h * w
         assert rule([f"conv_takes_ring({k}, 0, {w}, {n}, {wg} * (({n} + 256 * apply_rounds({wg}, {n}) - 1) / (256 * apply_rounds({wg}, {n}))))"
                      for wg in (256, 258)]) == [0, 1]
+
+
+def test_query_blocks_of_full_attention(rule):
+    """(queries, lanes) on either side of the rule, as measured, and the sizes that the GPU test of equal bits counts on."""
+    one, two = [(1374, 16), (1374, 32), (1374, 48), (5184, 16), (100, 512), (200, 1)], [(8192, 16), (4096, 64), (4096, 128), (256, 400)]
+    either, same = test_gpu_bf16_attn.EITHER_SIZE, [c for c in test_gpu_bf16_attn.ONE_SIZE if c[0] > 64]
+    ask = one + two + either + [(n, 1) for n, _ in either] + same + [(n, 1) for n, _ in same]
+    got = rule([f"ring_query_blocks({n}, {lanes})" for n, lanes in ask])
+    assert got == [1] * len(one) + [2] * (len(two) + len(either)) + [1] * (len(either) + 2 * len(same))
 
 
 def test_prefix_chains_of_64_channel_heads(rule):

@@ -45,9 +45,17 @@ def test_full_attention_small_shapes(B, heads, H, W, vscale):
     check_bf16_pair(_full(q, k, v, H, W, torch.float32), _full(q, k, v, H, W), ref)
 
 
-@pytest.mark.parametrize("N", [31, 32, 33, 64, 65, 127, 128, 129, 160, 191, 193, 257])
-def test_query_blocks_of_either_size_give_the_same_bits(N):
-    """One image takes workgroups of 128 queries, 512 copies of it those of 256: the same bits, and
+# (tokens, copies of the image): one image takes workgroups of 128 queries, the copies those of 256 where EITHER_SIZE says so
+# (checked on the host in test_dispatch_rules.py).  Last blocks of 256 with 1 to 256 queries; 3 to 11 stages of 64 keys.
+EITHER_SIZE = [(129, 512), (160, 512), (191, 512), (193, 512), (255, 400), (256, 400), (385, 200), (449, 512), (509, 200), (512, 200),
+               (513, 160), (575, 160), (641, 130)]
+# ... and not here: up to 64 tokens take the window-resident kernel, the others 128 queries, in any number.
+ONE_SIZE = [(31, 512), (32, 512), (33, 512), (64, 512), (65, 512), (127, 512), (128, 512), (257, 512)]
+
+
+@pytest.mark.parametrize("N,copies", EITHER_SIZE + ONE_SIZE)
+def test_query_blocks_of_either_size_give_the_same_bits(N, copies):
+    """One image and many copies of it: the same bits, whichever block of queries each takes, and
     the oracle's values (logits that climb along the sequence, so that the reference goes up in late tiles)."""
     q, k, v = synth.qkv(38, 1, 1, N, 64, 0.5, True)
     k = synth.round_to_bf16((k * np.linspace(0.2, 8.0, N, dtype=np.float32)[None, None, :, None]).astype(np.float32))
@@ -57,7 +65,7 @@ def test_query_blocks_of_either_size_give_the_same_bits(N):
     # most rows that bound is reached, where the general bar of 2e-2 RMS assumes many.
     ref = oracle.full_attn(q, k, v)
     check(err_bf16(to_host(one), ref), 2.0 ** -9 * float(np.abs(v).max()) / float(np.sqrt(np.mean(ref * ref))) + 1e-4)
-    many = _full(*(np.repeat(x, 512, axis=0) for x in (q, k, v)), 1, N, torch.float32)
+    many = _full(*(np.repeat(x, copies, axis=0) for x in (q, k, v)), 1, N, torch.float32)
     assert torch.equal(many, one.expand_as(many))
 
 
