@@ -504,11 +504,7 @@ gemm_tile192_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W, 
             const bool inside = row < M && col < N;  // (N % 8 == 0: a piece is in or out whole)
             const u32x4 raw = *(const u32x4 *)(stage + (16 * wn + srow) * kPitch + 16 * sp);
             if (!kStageF32) {
-#ifdef T192NT
-                if (inside) st_stream((u32x4 *)((__bf16 *)Y + (size_t)row * N + col), raw);
-#else
                 if (inside) *(u32x4 *)((__bf16 *)Y + (size_t)row * N + col) = raw;
-#endif
             } else {
                 f32x4 out = __builtin_bit_cast(f32x4, raw);
                 if (OUT_BF16) {
