@@ -7,6 +7,7 @@
 
 #include "jv_common.h"
 #include "jv_mfma.h"
+#include "jv_plan.h"
 
 namespace jv {
 
@@ -28,8 +29,9 @@ __device__ inline int slot_token(const WindowGeom &g, int wy, int wx, int slot) 
 // A workgroup is four wavefronts, QW = 4 / KW blocks of 32 queries times KW groups of keys: per
 // step it stages KW tiles of K and V in LDS (fetched into registers under the arithmetic of the
 // step before) and wavefront (qw, kw) takes tile kw.  With KW > 1 the KW running softmaxes of a
-// query block are merged through LDS at the end.  KW = 4 cuts a problem of few queries into four
-// times as many wavefronts; KW = 1 stages a quarter of the bytes per flop.
+// query block are merged through LDS at the end.  KW = 2 and 4 cut a problem of few queries into two
+// and four times as many wavefronts (attn_direct_f32 takes most launches that KW = 4 could: f32_keys_staged);
+// KW = 1 stages a quarter of the bytes per flop.
 // Measured: 2 304 tokens x 64 heads 798 us = 109 TFLOP/s (a loop of these instructions alone reaches 138, at
 // the 2.1 GHz the chip holds under them).
 // Only the first q_slots query slots of every window are computed.
@@ -498,7 +500,7 @@ static jv_status attn_dispatch(const Problem &pr, const WindowGeom &g, float sca
     const int tiles = (g.slots + 31) / 32;
     if (waves < 2048 && tiles > 2) {
         const long long max_sn = pr.k.sn > pr.v.sn ? pr.k.sn : pr.v.sn;
-        if (((long long)g.H * g.W + 64) * max_sn * 4 >= (1ll << 32))  // attn_direct_f32 counts bytes in 32 bits
+        if (f32_keys_staged(tiles, g.ww == g.W, waves, ((long long)g.H * g.W + 64) * max_sn * 4))
             return launch_attn_f32<4>(pr, g, scale, q_slots, stream);
         hipLaunchKernelGGL(attn_direct_f32, dim3((unsigned)((q_slots + 31) / 32), g.n_win, pr.B * pr.heads), dim3(256), 0, stream,
                            pr.q, pr.k, pr.v, pr.o, g, pr.heads, scale * 1.4426950408889634f, q_slots);

@@ -61,6 +61,15 @@ constexpr int ring_query_blocks(int queries, long long lanes) {
     return 1.08f * t1 < t2 ? 1 : 2;  // (rounds overlap, to the large blocks' advantage)
 }
 
+// fp32 attention of few queries, the keys cut over the four wavefronts of a workgroup (`waves` blocks of 32 queries in all, windows of
+// `tiles` tiles of 32 keys): attn_direct_f32, or attn_f32<4> where that is faster or K and V span more bytes than 32-bit offsets
+// count.  With a tile per wavefront the direct kernel has nothing to fetch ahead, and only its third workgroup on a unit tells:
+// rounds of 768 against 512.  Windows of whole grid rows (the direct kernel is 2 to 10 % faster on others) of 4 tiles, staged / direct, us: 128 keys x 6 (batch, head)s 6.8 / 7.0, x 64 7.3 / 7.5, x 192 (768 blocks) 16.3 / 15.4, 112 x 256 (1 024) 19.7 / 22.0,
+// 128 x 320 25.1 / 25.9, x 384 (1 536) 28.9 / 27.3; 3 tiles 7.0 / 6.6, 7 tiles x 6 10.6 / 9.8.
+constexpr bool f32_keys_staged(int tiles, bool whole_rows, long long waves, long long kv_bytes) {
+    return kv_bytes >= (1ll << 32) || (tiles == 4 && whole_rows && (waves - 1) % 768 < 512);
+}
+
 // Prefix tokens: `queries` <= 64 queries against the `keys` tokens of a whole sequence, per (batch, head) (jv_attn_bf16.hip).
 // Keys come in stages; chains of stages run as workgroups of their own whose sums wait in the rows of O
 // behind the queries, kPrefixRows of them for a query of a chain.

@@ -78,6 +78,16 @@ def test_query_blocks_of_full_attention(rule):
     assert got == [1] * len(one) + [2] * (len(two) + len(either)) + [1] * (len(either) + 2 * len(same))
 
 
+def test_staged_or_direct_keys_of_fp32_attention(rule):
+    """(tiles, whole rows, blocks of 32 queries, bytes of a slice of K and V)"""
+    staged = [(4, 1, 24, 1 << 15), (4, 1, 512, 1 << 15), (4, 1, 1024, 1 << 15), (4, 1, 1280, 1 << 15), (4, 1, 2040, 1 << 15),
+              (10, 1, 10, (300 + 64) * 2949844 * 4), (10, 0, 10, 1 << 40)]
+    direct = [(3, 1, 24, 1 << 15), (5, 1, 24, 1 << 15), (4, 0, 24, 1 << 15), (4, 1, 513, 1 << 15), (4, 1, 768, 1 << 15), (4, 1, 1536, 1 << 15),
+              (43, 1, 516, 1 << 19), (10, 1, 10, (300 + 64) * 2949840 * 4)]
+    got = rule([f"f32_keys_staged({t}, {r}, {w}, {b}ll)" for t, r, w, b in staged + direct])
+    assert got == [1] * len(staged) + [0] * len(direct)
+
+
 def test_prefix_chains_of_64_channel_heads(rule):
     """(prefix tokens, grid tokens, batch x heads) on either side of every line of the rule, as measured."""
     one = [(5, 576, 12), (1, 784, 16), (5, 784, 64), (5, 1369, 144), (16, 1369, 192), (5, 2304, 160), (5, 4096, 256), (33, 1000, 64),

@@ -67,7 +67,8 @@ def test_attention_tile_edges(B, heads, H, W, window):
 
 
 @pytest.mark.parametrize("H,W,window,P", [
-    (1, 65, None, 0), (1, 96, None, 0), (1, 97, None, 0), (1, 128, None, 0), (1, 129, None, 0),  # 3 to 5 tiles on 4 wavefronts
+    (1, 65, None, 0), (1, 96, None, 0), (1, 97, None, 0), (1, 128, None, 0), (1, 129, None, 0),  # 3 to 5 tiles on 4 wavefronts (4: staged)
+    (20, 30, (10, 10), 0), (14, 32, (4, 32), 3),                                                 # 4 tiles: not whole rows, whole rows
     (1, 383, None, 1), (20, 21, None, 5),    # prefix tokens: key counts 384, 425
     (20, 30, (9, 11), 0), (20, 30, (12, 30), 2), (11, 13, (11, 8), 64),  # windows: ragged, of whole rows, with prefix queries
 ])
@@ -86,6 +87,20 @@ def test_keys_split_over_wavefronts(H, W, window, P):
         binding.jv_window_attn_fwd(dq, dk, dv, o, (H, W), window)
         ref = oracle.window_attn_prefix(q, k, v, P, H, W, *window)
     check(err_fp32(to_host(o), ref), FP32_TOL)
+
+
+@pytest.mark.parametrize("row", [2949840, 2949844, 1 << 22])
+def test_slices_of_four_gigabytes(row):
+    """300 tokens whose K and V rows lie `row` elements apart: the last stride at which a slice's byte offsets fit 32
+    bits, the first at which they do not, and offsets beyond 2^32 (the tiles are staged through LDS then)."""
+    q, k, v = synth.qkv(46, 1, 1, 300, 64, 1.0, False)
+    dq = to_device(q, False)
+    wide = [torch.empty(299 * row + 64, device="cuda").as_strided(dq.shape, (300 * row, 300 * row, row, 1)) for _ in range(2)]
+    for t, x in zip(wide, (k, v)):
+        t.copy_(to_device(x, False))
+    o = torch.full(dq.shape, float("nan"), device="cuda")
+    binding.jv_full_attn_fwd(dq, *wide, o, (1, 300))
+    check(err_fp32(to_host(o), oracle.full_attn(q, k, v)), FP32_TOL)
 
 
 @pytest.mark.parametrize("N", [160, 256, 1030])
