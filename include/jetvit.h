@@ -91,7 +91,9 @@ typedef struct {
  * tokens followed by the grid tokens in raster order:
  *  - full attention and linear attention take all N tokens as ordinary tokens;
  *  - window attention: a grid token attends to the grid tokens of its window (prefix tokens
- *    are in no window); a prefix token attends to all N tokens;
+ *    are in no window); a prefix token attends to all N tokens (partial sums of the prefix rows
+ *    may lie in O's grid rows until these receive their values: O is defined when the
+ *    stream has passed the call, not before);
  *  - the depth-wise convolution of the linear-attention block runs over the grid only (zero
  *    padding at its border as before): prefix tokens receive no convolution term and feed
  *    none; the token average that generates the dynamic filters runs over all N tokens.

@@ -1934,7 +1934,7 @@ jv_status attn_bf16(const Problem &pr, const WindowGeom &g, float scale, int q_s
             ((long long)pr.N + 2ll * kStageWide * g.W) * wide_sn * 2 + 512 < (1ll << 31)) {
             // a few queries against the whole sequence (prefix tokens): the keys cut into chains.  What five prefix
             // tokens add to window attention, us, ring kernel / chains: 1 369 tokens x 8 heads 30 / 8.6, 4 096 x 8
-            // 82 / 14.6, x 64 90 / 30, 16 384 x 8 324 / 36.
+            // 82 / 14.6, x 64 90 / 30, 16 384 x 8 324 / 36 (separate tensors).
             if (a.contig && a.q_slots < g.slots && a.q_slots <= 64 && g.n_win == 1 &&
                 prefix_in_chains_wide(g.slots, a.q_slots, a.n_bh))
                 return pr.o_bf16 ? launch_prefix_wide<true>(a, a.n_bh, stream)

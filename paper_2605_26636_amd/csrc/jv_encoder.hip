@@ -608,15 +608,16 @@ static jv_status launch_gemm(const void *a, const void *w, const float *bias, co
 // 64-deep block costs about 0.22, 0.33, 0.35, 0.56 and 1.15 us on 64 x 64, 64 x 128, 128 x 128, 256 x 128 and
 // 256 x 256 tiles, i.e. the larger the tile the nearer to the matrix rate.  So: the largest tile that
 // fills the chip, below that the smallest that leaves no unit with two tiles while others have one.
-// 256 x 192 tiles (fitted afterwards on 180 products of 1 374 to 20 000 rows: without them the choice was 2.8 % off the
-// best, with them 0.4 %) take launches that the large tiles would end with a round of few: QKV of width 1024
-// on 2 750 rows 26.6 -> 23.2 us, on 5 476 48.2 -> 44.2, on 8 192 58.6 -> 54.5, on 10 952 84.1 -> 76.2; fc2 on 20 000 187 -> 178.
+// 256 x 192 tiles (fitted afterwards; over 156 products of 200 to 20 000 rows the choice is 0.4 % off the best shape on average,
+// 2.2 % without them) take launches that the large tiles would end with a round of few: QKV of width 1024
+// on 2 750 rows 26.3 -> 23.7 us, on 5 476 51.5 -> 42.8, on 8 192 57.0 -> 51.9 (57.1 -> 54.9 on a slower box), on 10 952 80.8 -> 74.4;
+// fc2 on 20 000 187 -> 175.
 // Products of a block of width 1024 on the tiles chosen, us (PFLOP/s), operands not in the L2:
 //     rows      QKV          projection   fc1          fc2 (not split)
-//     1 374     18.8 (0.46)  10.3 (0.28)  22.5 (0.51)  31.5 (0.37)
-//     4 096     27.9 (0.92)  16.9 (0.51)  38.7 (0.89)  42.4 (0.81)
-//     8 192     54.5 (0.95)  26.9 (0.64)  75.5 (0.91)  66.8 (1.03)
-//     16 384    100 (1.03)   43.2 (0.80)  148 (0.93)   119 (1.16)
+//     1 374     16.0 (0.54)  9.5 (0.30)   18.3 (0.63)  31.5 (0.37)
+//     4 096     27.3 (0.95)  16.6 (0.52)  36.8 (0.93)  41.6 (0.83)
+//     8 192     52.8 (0.98)  26.9 (0.64)  70.6 (0.97)  65.5 (1.05)
+//     16 384    95.5 (1.08)  40.9 (0.84)  138 (0.99)   119 (1.16)
 struct TileModel {
     int bm, bn, slots;    // slots: workgroups that fit the chip
     float lo, hi, e;
