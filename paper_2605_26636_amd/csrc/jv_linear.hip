@@ -55,8 +55,8 @@ size_t linear_workspace_floats(const LinearPlan &p, int B, int heads) {
 // ---------------------------------------------------------------------------------------
 // fp32 path: both passes on the fp32 matrix instructions (v_mfma_f32_32x32x2_f32: operand lane
 // (half, i) holds row or column i at contraction index `half`; fp32 throughout), whose rate
-// would stream the tensors at 9.8 TB/s, so problems that fill the chip are bound by memory and small ones by
-// the two launches.
+// would stream the tensors at 9.8 TB/s, so problems that fill the chip are bound by memory and small ones,
+// where both passes are one launch, by latency.
 // ---------------------------------------------------------------------------------------
 
 // Focused feature map (Eq. 3; see focus_bf16x8 in the bf16 path) of a rectified row given the
@@ -343,12 +343,147 @@ la_apply_f32(TensorArg qt, TensorArg ot, const float *__restrict__ ws, int heads
     }
 }
 
+// Both passes in one launch, for few tokens: a workgroup forms sixteen value channels of a (batch, head)'s
+// state from all of its tokens, and applies them to a part of its queries, so that no workgroup waits for another's
+// sums.  Bound by round trips to memory and by the matrix instructions of one unit (0.9 us per pass and 256 tokens): two launches
+// make two round trips more, and here K, V and the first queries of eight wavefronts are all in flight at once.  K and V
+// are read by four workgroups for every part of the queries, which run on one XCD and share its L2.  Tiles of 16 x 16 x 4
+// (v_mfma_f32_16x16x4_f32: lane (g, i) holds row or column i at contraction index g), in two chains of sums: 256 tokens
+// x 6 heads 9.9 -> 5.5 us in two launches / here, 8.5e-8 from 64 bits (1.08e-7 before).  One part of the queries
+// instead of eight 7.1 us, sixteen wavefronts a workgroup 9.6 (registers spill).
+// grid (32 ceil(B*heads / 8), ceil(tiles of 16 tokens / apply_tiles)), 512 threads.
+constexpr int kFusedWaves = 8;
+__global__ void __launch_bounds__(64 * kFusedWaves)
+la_fused_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, int heads, int BH, int N, int apply_tiles, float eps) {
+    __shared__ __align__(16) float part[kFusedWaves][16 * kHeadDim + kHeadDim];  // 16 rows of St, then z
+    // 16-byte chunks of a row are rotated by the row: row-per-lane reads without bank conflicts
+    __shared__ __align__(16) unsigned char St[16 * 256];
+    __shared__ __align__(16) float z[kHeadDim];
+    const int bh = (int)(blockIdx.x >> 5) * 8 + (int)(blockIdx.x & 7), c0 = 16 * (int)((blockIdx.x >> 3) & 3);
+    if (bh >= BH) return;  // (the whole workgroup)
+    const int b = bh / heads, h = bh % heads;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, li = lane & 15;
+    const float *kp = (const float *)kt.ptr + b * kt.sb + h * kt.sh + 4 * li;
+    const float *vp = (const float *)vt.ptr + b * vt.sb + h * vt.sh + c0 + li;
+    const float *qp = (const float *)qt.ptr + b * qt.sb + h * qt.sh + 4 * g;
+    float *op = (float *)ot.ptr + b * ot.sb + h * ot.sh + c0 + 4 * g;
+
+    // State: wavefront w takes every eighth group of 32 tokens.  Lane (g, i) has tokens 4 u + g: channels 4 i .. + 3 of K
+    // (column i of key block e is channel 4 i + e) and channel c0 + i of V.
+    f32x4 k[8];
+    float v[8];
+    auto fetch_kv = [&](int base) __attribute__((always_inline)) {
+        const float *kr = kp + (long long)(base + g) * kt.sn, *vr = vp + (long long)(base + g) * vt.sn;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const bool real = base + 4 * u + g < N;
+            k[u] = *(const f32x4 *)(real ? kr : kp);
+            v[u] = *(real ? vr : vp);
+            kr += 4 * kt.sn;
+            vr += 4 * vt.sn;
+        }
+    };
+    // Queries: tiles of 16 tokens, lane (g, i) has channels 16 u + 4 g .. + 3 of token i
+    f32x4 q[2][4];
+    auto fetch_q = [&](f32x4 (&r)[4], int tile) __attribute__((always_inline)) {
+        const float *row = qp + (long long)min(16 * tile + li, N - 1) * qt.sn;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) r[u] = *(const f32x4 *)(row + 16 * u);
+    };
+    const int tile0 = (int)blockIdx.y * apply_tiles, n_tile = min((N + 15) / 16, tile0 + apply_tiles);
+    int base = 32 * wave;
+    if (base < N) fetch_kv(base);
+    if (tile0 + wave < n_tile) fetch_q(q[0], tile0 + wave);
+    if (tile0 + wave + kFusedWaves < n_tile) fetch_q(q[1], tile0 + wave + kFusedWaves);
+    f32x4 acc[2][4], zsum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[0][e] = acc[1][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    while (base < N) {
+        f32x4 kr[8];
+        float vr[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const bool real = base + 4 * u + g < N;
+            vr[u] = real ? v[u] : 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) kr[u][e] = real ? fmaxf(k[u][e], 0.f) : 0.f;
+        }
+        base += 32 * kFusedWaves;
+        if (base < N) fetch_kv(base);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            zsum += kr[u];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[u & 1][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[u], kr[u][e], acc[u & 1][e], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[0][e] += acc[1][e];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        *(f32x4 *)(part[wave] + (4 * g + r) * kHeadDim + 4 * li) = f32x4{acc[0][0][r], acc[0][1][r], acc[0][2][r], acc[0][3][r]};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        zsum[e] += __shfl_xor(zsum[e], 16, 64);
+        zsum[e] += __shfl_xor(zsum[e], 32, 64);
+    }
+    if (g == 0) *(f32x4 *)(part[wave] + 16 * kHeadDim + 4 * li) = zsum;
+    __syncthreads();
+    if (tid < 17 * 16) {
+        f32x4 s[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) s[w] = *(const f32x4 *)(part[w] + 4 * tid) + *(const f32x4 *)(part[w + 4] + 4 * tid);
+        const f32x4 sum = (s[0] + s[1]) + (s[2] + s[3]);
+        const int row = tid >> 4, c = tid & 15;
+        if (row < 16) *(f32x4 *)(St + row * 256 + ((c ^ row) << 4)) = sum;
+        else *(f32x4 *)(z + 4 * c) = sum;
+    }
+    __syncthreads();
+    f32x4 sreg[4], zreg[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        sreg[u] = *(const f32x4 *)(St + li * 256 + (((4 * u + g) ^ li) << 4));
+        zreg[u] = *(const f32x4 *)(z + 16 * u + 4 * g);
+    }
+    auto apply = [&](f32x4 (&r)[4], int tile) __attribute__((always_inline)) {
+        f32x4 out[2], den4 = {0.f, 0.f, 0.f, 0.f};
+        out[0] = out[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float x = fmaxf(r[u][e], 0.f);
+                den4[e] = fmaf(x, zreg[u][e], den4[e]);
+                out[e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(sreg[u][e], x, out[e & 1], 0, 0, 0);
+            }
+        if (tile + 2 * kFusedWaves < n_tile) fetch_q(r, tile + 2 * kFusedWaves);
+        float den = (den4[0] + den4[1]) + (den4[2] + den4[3]);
+        den += __shfl_xor(den, 16, 64);
+        den += __shfl_xor(den, 32, 64);
+        den += eps;
+        const float up = den < 0x1p-100f ? 0x1p60f : 1.0f;  // (as in la_apply_f32)
+        const float inv = 1.0f / (den * up);
+        const int n = 16 * tile + li;
+        if (n < N) *(f32x4 *)(op + (long long)n * ot.sn) = ((out[0] + out[1]) * up) * inv;
+    };
+    for (int tile = tile0 + wave; tile < n_tile; tile += 2 * kFusedWaves) {
+        apply(q[0], tile);
+        if (tile + kFusedWaves < n_tile) apply(q[1], tile + kFusedWaves);
+    }
+}
+
 size_t linear_workspace_bytes(int B, int heads, int N, bool bf16) {
     return linear_workspace_floats(plan_linear(B, heads, N, bf16), B, heads) * sizeof(float);
 }
 
 static jv_status linear_f32(const Problem &pr, const LinearPlan &plan, float eps, float *ws, int focus_p, hipStream_t stream) {
     const int BH = pr.B * pr.heads;
+    if (focus_p == 1 && linear_f32_in_one(BH, pr.N)) {
+        const int tiles = (pr.N + 15) / 16, parts = linear_f32_parts(BH), apply_tiles = (tiles + parts - 1) / parts;
+        hipLaunchKernelGGL(la_fused_f32, dim3(32 * ((BH + 7) / 8), (tiles + apply_tiles - 1) / apply_tiles), dim3(64 * kFusedWaves), 0, stream,
+                           pr.q, pr.k, pr.v, pr.o, pr.heads, BH, pr.N, apply_tiles, eps);
+        return launch_status("la_fused_f32");
+    }
     hipLaunchKernelGGL(la_state_f32, dim3(plan.n_split, BH), dim3(256), 0, stream, pr.k, pr.v, ws,
                        pr.heads, pr.N, plan.chunk, focus_p);
     jv_status st = launch_status("la_state_f32");

@@ -45,6 +45,16 @@ constexpr int apply_rounds(long long bh, int N) {
     return chosen;
 }
 
+// fp32 linear attention, both passes in one launch (la_fused_f32): its workgroups, four for each of `parts` parts of a (batch, head)'s
+// queries, form the state again and again, which pays while they fit the chip's 256 units once and the tokens
+// are few.  Two launches / one, us: 6 (batch, head)s of 256 tokens 9.9 / 5.5, of 1 024 13.3 / 12.7, of 1 369 14.8 / 16.2;
+// 16 of 576 13.5 / 9.7, of 784 13.8 / 12.9, of 1 024 14.6 / 14.7; 24 of 784 15.3 / 14.6, of 1 024 16.6 / 16.9; 32 of 1 369 23.0 / 21.5,
+// of 2 304 30.6 / 32.9; 48 of 1 369 34.4 / 27.7, of 2 304 47.6 / 46.3; 64 of 256 12.9 / 8.7, of 2 304 55.8 / 48.5; 80 of 576 25.2 / 25.6.
+constexpr int linear_f32_parts(int bh) { return bh > 32 ? 1 : bh > 8 ? 64 / bh : 8; }
+constexpr bool linear_f32_in_one(int bh, int N) {
+    return N <= (bh <= 8 ? 1024 : bh <= 24 ? 800 : bh <= 56 ? 1400 : bh <= 64 ? 2400 : 0);
+}
+
 // bf16 attention over whole grid rows (attn_ring_bf16): blocks of 32 queries per wavefront, two or (the same bits) one, for
 // `queries` query slots in each of `lanes` windows times (batch, head)s.  Two workgroups of 256 queries on a compute unit
 // do the most per second, but three of 128 come close, and the smaller blocks leave fewer units with less than

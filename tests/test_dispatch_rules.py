@@ -7,6 +7,7 @@ import subprocess
 import pytest
 
 import test_gpu_bf16_attn
+import test_gpu_fp32
 import test_gpu_linear_block
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -105,3 +106,15 @@ def test_prefix_chains_of_128_channel_heads(rule):
               (64, 4096, 80), (32, 1536, 4), (64, 3100, 4)]
     got = rule([f"prefix_in_chains_wide({p + n}, {p}, {bh})" for p, n, bh in ring + chains])
     assert got == [0] * len(ring) + [1] * len(chains)
+
+
+def test_linear_attention_in_one_launch(rule):
+    """One launch up to the stated token counts, its workgroups (four a part, (batch, head)s in eights) at most one a unit, and the
+    GPU test on both sides."""
+    limits = {1: 1024, 8: 1024, 9: 800, 24: 800, 25: 1400, 56: 1400, 57: 2400, 64: 2400}
+    assert rule([f"linear_f32_in_one({bh}, {n}) + 2 * linear_f32_in_one({bh}, {n} + 1)" for bh, n in limits.items()]) == [1] * len(limits)
+    assert rule([f"linear_f32_in_one({bh}, 1)" for bh in (65, 1 << 16)]) == [0, 0]
+    parts = rule([f"linear_f32_parts({bh})" for bh in range(1, 65)])
+    assert all(1 <= p <= 8 and 4 * p * bh <= 256 for bh, p in enumerate(parts, 1))
+    one = rule([f"linear_f32_in_one({b * h}, {n})" for b, h, n, _ in test_gpu_fp32.ONE_LAUNCH])
+    assert one == [0 if (b * h, n) in ((8, 1025), (24, 801), (65, 100)) else 1 for b, h, n, _ in test_gpu_fp32.ONE_LAUNCH]

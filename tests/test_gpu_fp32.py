@@ -171,6 +171,31 @@ def test_linear_chunk_edges(N):
     check(err_fp32(to_host(o), oracle.linear_attn_quadratic(q, k, v, 1e-6)), FP32_TOL)
 
 
+# (B, heads, tokens, fused projection): one launch's tiles of 16 tokens, groups of 32 and rounds of 256; parts of the queries
+# (8, 5, 2, 1, ragged last ones); either side of each limit of linear_f32_in_one
+ONE_LAUNCH = [(1, 1, 1, False), (1, 1, 15, False), (1, 3, 17, True), (2, 3, 33, False), (1, 8, 255, False), (1, 6, 256, False), (1, 6, 257, True),
+              (1, 8, 1024, False), (1, 8, 1025, False), (3, 4, 300, True), (2, 12, 800, False), (2, 12, 801, False), (1, 32, 777, True),
+              (4, 16, 600, False), (4, 14, 1400, False), (4, 16, 2400, False), (5, 13, 100, False)]
+
+
+@pytest.mark.parametrize("B,heads,N,fused", ONE_LAUNCH)
+def test_linear_attention_in_one_launch(B, heads, N, fused):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    if fused:
+        qkv = torch.randn(B, N, 3, heads, 64, generator=g, device="cuda")
+        q, k, v = (qkv[:, :, i].permute(0, 2, 1, 3) for i in range(3))
+        o = torch.full((B, N, heads, 64), float("nan"), device="cuda").permute(0, 2, 1, 3)
+    else:
+        q, k, v = (torch.randn(B, heads, N, 64, generator=g, device="cuda") for _ in range(3))
+        o = torch.full_like(q, float("nan"))
+    binding.jv_linear_attn_fwd(q, k, v, o, (1, N), 1e-6)
+    q64, k64 = q.double().clamp_min(0), k.double().clamp_min(0)
+    ref = q64 @ (k64.transpose(-1, -2).contiguous() @ v.double()) / ((q64 * k64.sum(2, keepdim=True)).sum(-1, keepdim=True) + 1e-6)
+    # 1.15e-7 is the two launches' error at these lengths (7 to 10 e-8 measured); few tokens add the rounding of a single quotient
+    check(float((o.double() - ref).norm() / ref.norm()), 1.2e-7)
+
+
 @pytest.mark.parametrize("heads,N", [(1, 4096), (1, 4097), (16, 4160), (17, 4160), (3, 10001), (1, 65536)])
 def test_linear_attention_of_long_sequences(heads, N):
     """Above 4 096 tokens of at most 16 heads the states are summed in a pass of their own."""
