@@ -19,25 +19,22 @@ __device__ inline int slot_token(const WindowGeom &g, int wy, int wx, int slot) 
 }
 
 // ---------------------------------------------------------------------------------------
-// fp32 path: tiles of 32 keys x 32 queries on the fp32 matrix instructions
-// (v_mfma_f32_32x32x2_f32: fp32 operands and accumulation, 64 cycles per instruction).
-// Bound by those instructions: 128 of them per tile against 16 exponentials per lane.  Scores
-// are formed transposed, S^T = K Q^T, so that a lane owns one query column: the maximum and the
-// sum are in-lane plus one exchange with lane ^ 32, and accumulator register v of the score tile
-// is, as it stands, the B operand of step v of O^T += V^T P^T (k-slot g of step v is the key that
-// lane half g holds in register v).
-// A workgroup is four wavefronts, QW = 4 / KW blocks of 32 queries times KW groups of keys: per
-// step it stages KW tiles of K and V in LDS (fetched into registers under the arithmetic of the
-// step before) and wavefront (qw, kw) takes tile kw.  With KW > 1 the KW running softmaxes of a
-// query block are merged through LDS at the end.  KW = 2 and 4 cut a problem of few queries into two
-// and four times as many wavefronts (attn_direct_f32 takes most launches that KW = 4 could: f32_keys_staged);
-// KW = 1 stages a quarter of the bytes per flop.
-// Measured: 2 304 tokens x 64 heads 798 us = 109 TFLOP/s (a loop of these instructions alone reaches 138, at
-// the 2.1 GHz the chip holds under them).
+// fp32 path: tiles of 32 keys x 32 queries on the fp16 matrix instructions
+// (v_mfma_f32_32x32x16_f16, fp32 accumulation; sixteen times the rate of the fp32 ones).  Every operand is the sum of
+// two fp16 numbers of 11 bits and a sign each, scaled by a power of two: hi = fp16(s x), lo = fp16(s x - hi), and
+// a b = hi hi + hi lo + lo hi; what is left out, and what lo rounds away, is below 2^-23 of the product.  The scales keep the largest
+// magnitude of a query, of K and of V between 2^12 and 2^15, so that only numbers 2^26 times smaller than that lose bits, and
+// none more than 2^-38 of it.  K and V take their scale from the tiles seen so far: it goes down, and the sums with it, when a
+// tile holds something four times as large.  Errors against 64 bits are those of the rounding of the sums: the small products are added
+// up first, and a tile's sums on their own before they join the others.  64 heads of 1 369 tokens 2.4e-7, of 2 304 2.7e-7
+// (fp32 matrix instructions 5.6e-7 and 9.2e-7).
+// Infinities and NaN turn into NaN on the way (inf - inf), and so does what overflows: a wavefront whose sums are not finite
+// goes over its keys once more with the fp32 matrix instructions (f32_again).
+// Scores are formed transposed, S^T = K Q^T, so that a lane owns one query column: the maximum and the
+// sum are in-lane plus one exchange with lane ^ 32, and accumulator registers 8 f .. + 7 of the score tile
+// are, as they stand, the B operand of step f of O^T += V^T P^T (k-slot (g, 4 r + e) of it is key 16 f + 8 r + 4 g + e).
 // Only the first q_slots query slots of every window are computed.
-// grid (ceil(q_slots / (32 QW)), n_win, B*heads), 256 threads.
 // ---------------------------------------------------------------------------------------
-constexpr int kF32Tile = 2 * 32 * kHeadDim * 4;  // K rows, then V rows, of 32 keys: 16 KB
 
 // Workgroup -> (query block, window, batch * head) with a contiguous range of the launch per XCD
 // (the hardware deals workgroups to the eight XCDs in turn): the query blocks that read one
@@ -50,6 +47,264 @@ __device__ inline void f32_item(int &qblock, int &win, int &bh) {
     qblock = (int)(item % nx);
     win = (int)((item / nx) % ny);
     bh = (int)(item / (nx * ny));
+}
+
+// A window of one (batch, head) as the kernels address it.
+struct F32Window {
+    WindowGeom g;
+    int wy, wx, first;  // first: the window's first token, always real
+    bool rows;          // windows of whole grid rows: slots are consecutive tokens
+    const float *q, *k, *v;
+    float *o;
+    long long qsn, ksn, vsn, osn;
+    __device__ int token(int slot) const {  // -1: padding, or past the window
+        if (!rows) return slot_token(g, wy, wx, slot);
+        return slot < g.slots && first + slot < g.H * g.W ? first + slot : -1;
+    }
+};
+__device__ inline F32Window f32_window(const TensorArg &q, const TensorArg &k, const TensorArg &v, const TensorArg &o, const WindowGeom &g,
+                                       int heads, int win, int bh) {
+    F32Window w;
+    const int b = bh / heads, h = bh % heads;
+    w.g = g;
+    w.wy = win / g.wins_x;
+    w.wx = win % g.wins_x;
+    w.first = w.wy * g.wh * g.W + w.wx * g.ww;
+    w.rows = g.ww == g.W;
+    w.q = (const float *)q.ptr + b * q.sb + h * q.sh;
+    w.k = (const float *)k.ptr + b * k.sb + h * k.sh;
+    w.v = (const float *)v.ptr + b * v.sb + h * v.sh;
+    w.o = (float *)o.ptr + b * o.sb + h * o.sh;
+    w.qsn = q.sn;
+    w.ksn = k.sn;
+    w.vsn = v.sn;
+    w.osn = o.sn;
+    return w;
+}
+
+struct Split {
+    f16x8 hi, lo;
+};
+// Two instructions a number (written out: the compiler rounds every odd number twice, once into each half of a register).
+__device__ inline void split_pair(float x0, float x1, float s, unsigned &hi, unsigned &lo) {
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(hi) : "v"(x0), "v"(s));
+    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(hi) : "v"(x1), "v"(s));
+    asm("v_fma_mixlo_f16 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(lo) : "v"(x0), "v"(s), "v"(hi));
+    asm("v_fma_mixhi_f16 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "+v"(lo) : "v"(x1), "v"(s), "v"(hi));
+}
+__device__ inline Split split8(const float *x, float s) {
+    u32x4 hi, lo;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        unsigned h, l;
+        split_pair(x[2 * i], x[2 * i + 1], s, h, l);
+        hi[i] = h;
+        lo[i] = l;
+    }
+    return {__builtin_bit_cast(f16x8, hi), __builtin_bit_cast(f16x8, lo)};
+}
+// Four channels of a row into its hi and lo row of 128 bytes; the lo tile lies behind the hi tile.
+constexpr int kHalfTile = 32 * kHeadDim * 2;
+__device__ inline void split_store(unsigned char *at, f32x4 x, float s) {
+    u32x2 hi, lo;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        unsigned h, l;
+        split_pair(x[2 * i], x[2 * i + 1], s, h, l);
+        hi[i] = h;
+        lo[i] = l;
+    }
+    *(u32x2 *)at = hi;
+    *(u32x2 *)(at + kHalfTile) = lo;
+}
+__device__ inline f32x16 mfma_f16(f16x8 a, f16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
+__device__ inline f32x16 mfma_small(const Split &a, const Split &b, f32x16 c) { return mfma_f16(a.hi, b.lo, mfma_f16(a.lo, b.hi, c)); }
+
+// The largest of a wavefront's 64 numbers (none negative), in every lane: rotations inside rows of 16 lanes, then across them.
+template <int ROTATE>
+__device__ inline float row_max(float x) {
+    const int r = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + ROTATE, 0xf, 0xf, false);
+    return fmaxf(x, __builtin_bit_cast(float, r));
+}
+__device__ inline float wave_max(float x) {
+    x = row_max<1>(row_max<2>(row_max<4>(row_max<8>(x))));
+    const unsigned u = __builtin_bit_cast(unsigned, x);
+    const auto s = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    x = fmaxf(__builtin_bit_cast(float, (unsigned)s[0]), __builtin_bit_cast(float, (unsigned)s[1]));
+    float lo, hi;
+    pair_values(x, &lo, &hi);
+    return fmaxf(lo, hi);
+}
+template <int N>
+__device__ inline float magnitude(const f32x4 (&x)[N]) {  // (NaN: left out)
+    float top = 0.f;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) top = fmaxf(top, fabsf(x[i][e]));
+    return top;
+}
+// A power of two for numbers of magnitude up to `top`: `scale` takes them below 2^13, and magnitudes up to `limit` below 2^15.
+struct F32Scale {
+    float limit = -1.f, scale = 0.f, inverse = 0.f;
+    __device__ void fit(float top) {
+        const int e = min(max(139 - (int)(__builtin_bit_cast(unsigned, top) >> 23), -112), 120);  // (both normal)
+        inverse = __builtin_bit_cast(float, (unsigned)(127 - e) << 23);
+        scale = __builtin_bit_cast(float, (unsigned)(127 + e) << 23);
+        limit = 4.0f * top;
+    }
+};
+
+// Queries: lane (half, i) has channels 16 t + 8 half .. + 7 of query i (t = 0 .. 3), x[8 t ..].
+__device__ inline void f32_queries(const F32Window &w, int qtok, int half, float (&x)[32]) {
+    const float *row = w.q + (long long)(qtok < 0 ? w.first : qtok) * w.qsn + 8 * half;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) *(f32x4 *)(x + 4 * c) = *(const f32x4 *)(row + 16 * (c / 2) + 4 * (c % 2));
+}
+// The scale of a lane's query; its inverse turns sums of scaled products into logits.
+__device__ inline float f32_query_scale(const float (&x)[32], float &inverse) {
+    float top = 0.f, lo, hi;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) top = fmaxf(top, fabsf(x[i]));
+    pair_values(top, &lo, &hi);
+    F32Scale s;
+    s.fit(fmaxf(lo, hi));
+    inverse = s.inverse;
+    return s.scale;
+}
+
+// 32 queries of a wavefront: acc[cb][v] is channel 32 cb + 8 (v / 4) + 4 half + v % 4 of query lane % 32.
+struct F32State {
+    f32x16 acc[2];
+    float m, l;
+    __device__ void clear() {
+        m = -1.0e30f;  // (finite stand-in for "no maximum yet")
+        l = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.f;
+    }
+    __device__ void times(float x) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            acc[0][v] *= x;
+            acc[1][v] *= x;
+        }
+    }
+    // Scores -> weights relative to the reference m, at most 2^8, summed into l.  The reference stays while no
+    // logit is more than 8 binary orders above it (numerator and denominator share it, so the result is the
+    // same), and goes up to the maximum otherwise.
+    __device__ void weights(f32x16 &s, float factor) {
+        float top = s[0];
+#pragma unroll
+        for (int v = 1; v < 16; ++v) top = fmaxf(top, s[v]);
+        if (__any(top * factor > m + 8.0f)) {
+            float lo, hi;
+            pair_values(top, &lo, &hi);
+            const float m_new = fmaxf(m, fmaxf(lo, hi) * factor), alpha = __builtin_amdgcn_exp2f(m - m_new);
+            m = m_new;
+            l *= alpha;
+            times(alpha);
+        }
+        float sum = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], factor, -m));
+            sum += s[v];
+        }
+        l += sum;
+    }
+    // The sums as those of weights of at most 1: values up to the largest floats pass as under the maximum itself.
+    // False where something is not finite.
+    __device__ bool settle(float v_inverse) {
+        times(v_inverse * 0x1p-14f);
+        float x[4] = {l, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int v = 0; v < 16; ++v) x[v % 4] = fmaf(acc[0][v], 0.f, fmaf(acc[1][v], 0.f, x[v % 4]));
+        return fabsf((x[0] + x[1]) + (x[2] + x[3])) < INFINITY;
+    }
+};
+
+// Scores of a tile whose K rows (tile_off_row) start at `ktile`.
+__device__ inline f32x16 f32_scores(const unsigned char *ktile, int li, int half, const Split (&q)[4]) {
+    Split k[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const unsigned char *at = ktile + tile_off_row(li, 2 * t + half);
+        k[t] = {*(const f16x8 *)at, *(const f16x8 *)(at + kHalfTile)};
+    }
+    f32x16 s;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) s[v] = 0.f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) s = mfma_small(k[t], q[t], s);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) s = mfma_f16(k[t].hi, q[t].hi, s);
+    return s;
+}
+// Byte offset of a lane's transposing reads in a tile of V (tile_off_tr), channel block cb.
+__device__ inline unsigned f32_value_offset(int lane, int cb) {
+    const int b = lane >> 4, j = lane & 15;
+    return tile_off_tr(4 * (lane >> 5) + (j >> 2), cb * 4 + (b & 1) * 2 + ((j & 3) >> 1)) + (j & 1) * 8;
+}
+// acc += V^T P^T 2^6 scale for the weights p of a tile.
+__device__ inline void f32_values(F32State &st, const unsigned char *vtile, const unsigned (&voff)[2], const f32x16 &p) {
+    Split w[2];
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+        float x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = p[8 * f + j];
+        w[f] = split8(x, 0x1p6f);
+    }
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) {
+        Split v[2];
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            const unsigned char *at = vtile + voff[cb] + 16 * 128 * f;
+            const u32x2 h0 = lds_read_tr16(at), h1 = lds_read_tr16(at + 1024);
+            const u32x2 l0 = lds_read_tr16(at + kHalfTile), l1 = lds_read_tr16(at + kHalfTile + 1024);
+            const u32x4 hi = {h0[0], h0[1], h1[0], h1[1]}, lo = {l0[0], l0[1], l1[0], l1[1]};
+            v[f] = {__builtin_bit_cast(f16x8, hi), __builtin_bit_cast(f16x8, lo)};
+        }
+        f32x16 sum;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sum[i] = 0.f;
+        sum = mfma_small(v[1], w[1], mfma_small(v[0], w[0], sum));
+        st.acc[cb] += mfma_f16(v[1].hi, w[1].hi, mfma_f16(v[0].hi, w[0].hi, sum));
+    }
+}
+
+// A wavefront's keys (tiles tile0, tile0 + step, ...) on the fp32 matrix instructions.
+__device__ inline void f32_again(F32State &st, const F32Window &w, int qtok, float scale_log2, int tile0, int step, int li, int half) {
+    st.clear();
+    float x[32];
+    f32_queries(w, qtok, half, x);
+    for (int k0 = 32 * tile0; k0 < w.g.slots; k0 += 32 * step) {
+        const int ktok = w.token(k0 + li);
+        const float *krow = w.k + (long long)(ktok < 0 ? w.first : ktok) * w.ksn + 8 * half;
+        f32x16 s;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[v] = 0.f;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const f32x4 k = *(const f32x4 *)(krow + 16 * (c / 2) + 4 * (c % 2));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(k[e], x[4 * c + e], s, 0, 0, 0);
+        }
+        const unsigned pad = (unsigned)__builtin_amdgcn_ballot_w64(ktok < 0) >> (4 * half);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[v] = (pad >> (8 * (v / 4) + v % 4)) & 1u ? -INFINITY : s[v];
+        st.weights(s, scale_log2);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int tok = __shfl(ktok, 8 * (v / 4) + 4 * half + v % 4, 64);
+            const float *vrow = w.v + (long long)(tok < 0 ? w.first : tok) * w.vsn + li;
+            const float p = s[v] * 0x1p-8f;
+            st.acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(tok < 0 ? 0.f : vrow[0], p, st.acc[0], 0, 0, 0);  // (0 x inf would be NaN)
+            st.acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(tok < 0 ? 0.f : vrow[32], p, st.acc[1], 0, 0, 0);
+        }
+    }
 }
 
 // Tail of the fp32 kernels.  A wavefront without partners stores its rows ...
@@ -75,17 +330,17 @@ __device__ inline void f32_park(const f32x16 (&acc)[2], unsigned char *mine, int
         }
 }
 // the merge of the KW softmaxes of each query block: O = sum_k 2^(m_k - M) acc_k / sum_k 2^(m_k - M) l_k.
-template <int KW, class Token>
-__device__ inline void f32_merge(const unsigned char *parts, const float (&ms)[4][32], const float (&ls)[4][32], int qblock, int q_slots,
-                                 Token token, float *op, long long sn, int tid) {
+template <int KW>
+__device__ inline void f32_merge(const F32Window &w, const unsigned char *parts, const float (&ms)[4][32], const float (&ls)[4][32],
+                                 int qblock, int q_slots, int tid) {
     constexpr int QW = 4 / KW;
-    const int chunk = tid & 15, srow = tid >> 4;
+    const int chunk = tid & 15;
 #pragma unroll
     for (int i = 0; i < 2 * QW; ++i) {
-        const int query = srow + 16 * i, w0 = (query >> 5) * KW, ql = query & 31;
+        const int query = (tid >> 4) + 16 * i, w0 = (query >> 5) * KW, ql = query & 31;
         const int slot = qblock * (32 * QW) + query;
-        const int tok = slot < q_slots ? token(slot) : -1;
-        if (tok < 0) continue;
+        const int to = slot < q_slots ? w.token(slot) : -1;
+        if (to < 0) continue;
         float top = ms[w0][ql];
 #pragma unroll
         for (int k = 1; k < KW; ++k) top = fmaxf(top, ms[w0 + k][ql]);
@@ -93,19 +348,26 @@ __device__ inline void f32_merge(const unsigned char *parts, const float (&ms)[4
         float den = 0.f;
 #pragma unroll
         for (int k = 0; k < KW; ++k) {
-            const float w = __builtin_amdgcn_exp2f(ms[w0 + k][ql] - top);
-            out += w * *(const f32x4 *)(parts + (w0 + k) * (32 * 256) + ql * 256 + ((chunk ^ (ql & 15)) << 4));
-            den = fmaf(w, ls[w0 + k][ql], den);
+            const float x = __builtin_amdgcn_exp2f(ms[w0 + k][ql] - top);
+            out += x * *(const f32x4 *)(parts + (w0 + k) * (32 * 256) + ql * 256 + ((chunk ^ (ql & 15)) << 4));
+            den = fmaf(x, ls[w0 + k][ql], den);
         }
-        *(f32x4 *)(op + (long long)tok * sn + 4 * chunk) = out * (1.0f / den);
+        *(f32x4 *)(w.o + (long long)to * w.osn + 4 * chunk) = out * (1.0f / den);
     }
 }
 
+// Few tiles of keys: the same tiles on the fp32 matrix instructions (v_mfma_f32_32x32x2_f32), whose operands are
+// staged in LDS as they are.  With a tile or two to a wavefront the scales and splits of the other kernels stand alone at its start.
+// A workgroup of four wavefronts takes QW = 4 / KW blocks of 32 queries times KW groups of keys: per
+// step it stages KW tiles of K and V in LDS (fetched into registers under the arithmetic of the
+// step before) and wavefront (qw, kw) takes tile kw.  With KW > 1 the KW running softmaxes of a
+// query block are merged through LDS at the end.
+// grid (ceil(q_slots / (32 QW)), n_win, B*heads), 256 threads.
 template <int KW>
 __global__ void __launch_bounds__(256, 2)
-attn_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, int heads,
+attn_short_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, int heads,
          float scale_log2, int q_slots) {
-    constexpr int QW = 4 / KW;
+    constexpr int QW = 4 / KW, kF32Tile = 2 * 32 * kHeadDim * 4;  // K rows, then V rows, of 32 keys: 16 KB
     __shared__ __align__(16) unsigned char tiles[KW * kF32Tile];
     __shared__ __align__(16) float bias[KW * 32];  // 0 for a real key, -inf for padding
     __shared__ float ms[4][32], ls[4][32];
@@ -113,26 +375,16 @@ attn_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, i
     const int kw = wave % KW, qw = wave / KW;
     int qblock, win, bh;
     f32_item(qblock, win, bh);
-    const int b = bh / heads, h = bh % heads, wy = win / g.wins_x, wx = win % g.wins_x;
-    const float *qp = (const float *)qt.ptr + b * qt.sb + h * qt.sh;
-    const float *kp = (const float *)kt.ptr + b * kt.sb + h * kt.sh;
-    const float *vp = (const float *)vt.ptr + b * vt.sb + h * vt.sh;
-    float *op = (float *)ot.ptr + b * ot.sb + h * ot.sh;
-    const int first = wy * g.wh * g.W + wx * g.ww;  // the window's first token: always real
-    const bool padded = (wy + 1) * g.wh > g.H || (wx + 1) * g.ww > g.W;
-    const bool rows = g.ww == g.W;                  // windows of whole grid rows: slots are consecutive tokens
-    auto token = [&](int slot) {
-        if (!rows) return slot_token(g, wy, wx, slot);
-        return slot < g.slots && first + slot < g.H * g.W ? first + slot : -1;
-    };
+    const F32Window w = f32_window(qt, kt, vt, ot, g, heads, win, bh);
+    const bool padded = (w.wy + 1) * g.wh > g.H || (w.wx + 1) * g.ww > g.W;
 
     // Queries: lane (half, li) holds channels 32 half .. +31 of query li.
     const int q0 = qblock * (32 * QW) + qw * 32;
     const bool live = q0 < q_slots;  // the same in the whole wavefront
     f32x4 q[8];
-    int qtok = q0 + li < q_slots ? token(q0 + li) : -1;
+    int qtok = q0 + li < q_slots ? w.token(q0 + li) : -1;
     {
-        const float *row = qp + (long long)(qtok < 0 ? first : qtok) * qt.sn + 32 * half;
+        const float *row = w.q + (long long)(qtok < 0 ? w.first : qtok) * w.qsn + 32 * half;
 #pragma unroll
         for (int i = 0; i < 8; ++i) q[i] = *(const f32x4 *)(row + 4 * i);
     }
@@ -151,11 +403,11 @@ attn_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, i
     auto fetch = [&](int step) {
 #pragma unroll
         for (int i = 0; i < 2 * KW; ++i) {
-            int tok = token(step * (32 * KW) + srow + 16 * i);
+            int tok = w.token(step * (32 * KW) + srow + 16 * i);
             breg[i] = tok < 0 ? -INFINITY : 0.f;
-            if (tok < 0) tok = first;
-            kreg[i] = *(const f32x4 *)(kp + (long long)tok * kt.sn + 4 * chunk);
-            vreg[i] = *(const f32x4 *)(vp + (long long)tok * vt.sn + 4 * chunk);
+            if (tok < 0) tok = w.first;
+            kreg[i] = *(const f32x4 *)(w.k + (long long)tok * w.ksn + 4 * chunk);
+            vreg[i] = *(const f32x4 *)(w.v + (long long)tok * w.vsn + 4 * chunk);
         }
     };
     auto stage = [&]() {
@@ -233,7 +485,7 @@ attn_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, i
         l = lo + hi;
     }
     if (KW == 1) {
-        if (qtok >= 0) f32_store_row(acc, 1.0f / l, op + (long long)qtok * ot.sn + 4 * half);
+        if (qtok >= 0) f32_store_row(acc, 1.0f / l, w.o + (long long)qtok * w.osn + 4 * half);
         return;
     }
     __syncthreads();
@@ -243,82 +495,176 @@ attn_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, i
         ls[wave][li] = l;
     }
     __syncthreads();
-    f32_merge<KW>(tiles, ms, ls, qblock, q_slots, token, op, ot.sn, tid);
+    f32_merge<KW>(w, tiles, ms, ls, qblock, q_slots, tid);
 }
 
-// attn_f32<4> with K and V fetched straight into operand registers: its wavefronts share queries and
-// no keys, so nothing is staged and the key loop has no barrier.  A contraction step takes channels
-// 8 i + 4 half + e (i = 0 .. 7, e = 0 .. 3): a lane's K and Q operands are 16-byte pieces of one row and an
-// instruction reads 32 bytes of every row; a V operand is one dword of a row, an instruction
-// two runs of 128 bytes.  Half tiles of K and V rotate through three sets of sixteen registers, each
-// fetched while the matrix instructions of two others run (1 024 cycles each); with no LDS but the merge's
-// and 168 registers three workgroups fit a compute unit.  Against attn_f32<4>, us: 1 369 tokens x 12 heads
-// 104.6 -> 87.2 (516 workgroups: four units have three and the others two; x 11 68.7 -> 60.0), 256 x 6 10.6 -> 9.7,
-// 1 025 + 5 x 36 139 -> 112, windows of 14 x 14 on 40 x 40 x 24 49.4 -> 39.7.  The matrix instructions are 44 us of the 61.
-// (Two chains of score products instead of one: the same; two workgroups per unit and more registers: the same.)
-// grid (ceil(q_slots / 32), n_win, B*heads), 256 threads.  Byte offsets inside a (batch, head) slice of K
-// and V below 2^32.
+// Many queries: a workgroup of four wavefronts takes 128 queries of a window.  Per step it splits a tile of K and V
+// (fetched under the arithmetic of the step before) into LDS, where every wavefront reads it.  Bound by the issue of matrix (24 a tile,
+// 768 cycles) and vector instructions (about 250), which overlap in part.  Measured: 2 304 tokens x 64
+// heads 791 -> 345 us (fp32 matrix instructions / here), 1 369 x 64 328 -> 128, 784 x 64 118 -> 58, windows of 16 x 16 on 48 x 48 x 64
+// 103 -> 60.  (Products added straight to the sums of the tiles before: 2 to 7 % faster, errors twice as large.)
+// grid (ceil(q_slots / 128), n_win, B*heads), 256 threads.
 __global__ void __launch_bounds__(256, 3)
-attn_direct_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, int heads,
-                float scale_log2, int q_slots) {
-    constexpr int KW = 4;
-    __shared__ __align__(16) unsigned char parts[4 * 32 * 256];
+attn_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, int heads, float scale_log2, int q_slots) {
+    __shared__ __align__(16) unsigned char tile[4 * kHalfTile];  // K hi, K lo, V hi, V lo
+    __shared__ __align__(16) float bias[32];                     // 0 for a real key, -inf for padding
+    __shared__ unsigned tops[2];                                 // largest magnitude of K and of V where it went beyond a scale's limit
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, li = lane & 31;
+    int qblock, win, bh;
+    f32_item(qblock, win, bh);
+    const F32Window w = f32_window(qt, kt, vt, ot, g, heads, win, bh);
+    const bool padded = (w.wy + 1) * g.wh > g.H || (w.wx + 1) * g.ww > g.W;
+
+    // Staging: this thread moves 16-byte chunk `chunk` of rows srow and srow + 16 of a tile.
+    const int chunk = tid & 15, srow = tid >> 4;
+    f32x4 kreg[2], vreg[2];
+    float breg[2];
+    auto fetch = [&](int step) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            int tok = w.token(32 * step + srow + 16 * i);
+            breg[i] = tok < 0 ? -INFINITY : 0.f;
+            if (tok < 0) tok = w.first;
+            kreg[i] = *(const f32x4 *)(w.k + (long long)tok * w.ksn + 4 * chunk);
+            vreg[i] = *(const f32x4 *)(w.v + (long long)tok * w.vsn + 4 * chunk);
+        }
+    };
+    fetch(0);
+    const int q0 = qblock * 128 + wave * 32;
+    const bool live = q0 < q_slots;  // the same in the whole wavefront
+    const int qtok = q0 + li < q_slots ? w.token(q0 + li) : -1;
+    Split q[4];
+    float logit;
+    {
+        float x[32];
+        f32_queries(w, qtok, half, x);
+        const float s = f32_query_scale(x, logit);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) q[t] = split8(x + 8 * t, s);
+    }
+    F32State st;
+    st.clear();
+    F32Scale ks, vs;
+    if (tid < 2) tops[tid] = 0;
+    __syncthreads();
+    const unsigned voff[2] = {f32_value_offset(lane, 0), f32_value_offset(lane, 1)};
+    const int n_step = (g.slots + 31) / 32;
+    for (int step = 0; step < n_step; ++step) {
+        const float tk = magnitude(kreg), tv = magnitude(vreg);
+        if (__any(tk > ks.limit || tv > vs.limit)) {  // (rare after the first tile)
+            const float k = wave_max(tk), v = wave_max(tv);
+            if (lane == 0) {
+                atomicMax(&tops[0], __builtin_bit_cast(unsigned, k));
+                atomicMax(&tops[1], __builtin_bit_cast(unsigned, v));
+            }
+        }
+        __syncthreads();  // the tile before has been read, and every wavefront's magnitudes are there
+        const float k_top = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(tops[0]));
+        const float v_top = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(tops[1]));
+        if (k_top > ks.limit) ks.fit(k_top);
+        if (v_top > vs.limit) {
+            const float before = vs.inverse;
+            vs.fit(v_top);
+            st.times(vs.scale * before);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int r = srow + 16 * i;
+            if (breg[i] != 0.f) kreg[i] = vreg[i] = f32x4{0.f, 0.f, 0.f, 0.f};  // 0 x inf of a padded key's row would be NaN
+            split_store(tile + tile_off_row(r, chunk >> 1) + 8 * (chunk & 1), kreg[i], ks.scale);
+            split_store(tile + 2 * kHalfTile + tile_off_tr(r, chunk >> 1) + 8 * (chunk & 1), vreg[i], vs.scale);
+            if (chunk == 0) bias[r] = breg[i];
+        }
+        __syncthreads();
+        if (step + 1 < n_step) fetch(step + 1);
+        if (!live) continue;
+        f32x16 s = f32_scores(tile, li, half, q);
+        if (padded || 32 * (step + 1) > g.slots) {  // (uniform) only here can a key be padding
+#pragma unroll
+            for (int v4 = 0; v4 < 4; ++v4) {
+                const f32x4 b = *(const f32x4 *)(bias + 8 * v4 + 4 * half);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s[4 * v4 + e] += b[e];
+            }
+        }
+        st.weights(s, (logit * ks.inverse) * scale_log2);
+        f32_values(st, tile + 2 * kHalfTile, voff, s);
+    }
+    if (!live) return;
+    if (__any(!st.settle(vs.inverse))) f32_again(st, w, qtok, scale_log2, 0, 1, li, half);
+    if (qtok < 0) return;
+    float lo, hi;
+    pair_values(st.l * 0x1p-8f, &lo, &hi);
+    f32_store_row(st.acc, 1.0f / (lo + hi), w.o + (long long)qtok * w.osn + 4 * half);
+}
+
+// Few queries: a workgroup takes 32 of them and its four wavefronts every fourth tile of keys each, whose softmaxes are merged
+// at the end.  They share queries and no keys, so K and V go straight into operand registers and the key loop has no barrier:
+// a lane's K operands are 16-byte pieces of one row, a V operand eight dwords of a channel (an instruction reads two runs of 128
+// bytes).  Half tiles of K and V rotate through three sets of sixteen registers, each
+// fetched while the matrix instructions of two others run; three workgroups fit a compute unit.  Bound by its loads (32 cache lines for an
+// instruction's K operands), the splits and the matrix instructions together.  Against the fp32 matrix
+// instructions, us: 1 369 tokens x 12 heads 87.9 -> 49.0 (516 workgroups: four units have three and the others two; x 11 60.3 -> 37.3),
+// 1 030 x 36 112 -> 65, windows of 14 x 14 on 40 x 40 x 24 39.6 -> 30.9.
+// (Tiles through LDS, a wavefront's own or shared by two: 66 and 67 us for 1 369 x 12, 99 and 75 for 1 030 x 36.  Three bf16 numbers an
+// operand and six products instead of two fp16 numbers and three: 58 us.)
+// grid (ceil(q_slots / 32), n_win, B*heads), 256 threads.  Byte offsets inside a (batch, head) slice of K and V below 2^32.
+__global__ void __launch_bounds__(256, 3)
+attn_few_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, int heads, float scale_log2, int q_slots) {
+    __shared__ __align__(16) unsigned char parts[4][32 * 256];
+    __shared__ __align__(16) unsigned char qs[2 * 4 * 1024];  // [hi, lo][step of 16 channels][lane]
     __shared__ float ms[4][32], ls[4][32];
     const int tid = threadIdx.x, kw = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, li = lane & 31;
     int qblock, win, bh;
     f32_item(qblock, win, bh);
-    const int b = bh / heads, h = bh % heads, wy = win / g.wins_x, wx = win % g.wins_x;
-    const float *qp = (const float *)qt.ptr + b * qt.sb + h * qt.sh;
-    const char *kp = (const char *)((const float *)kt.ptr + b * kt.sb + h * kt.sh);  // (uniform)
-    const char *vp = (const char *)((const float *)vt.ptr + b * vt.sb + h * vt.sh);
+    const F32Window w = f32_window(qt, kt, vt, ot, g, heads, win, bh);
+    const char *kp = (const char *)w.k, *vp = (const char *)w.v;  // (uniform)
     const unsigned ksn = 4u * (unsigned)kt.sn, vsn = 4u * (unsigned)vt.sn;
     const unsigned vlane = 4u * half * vsn + 4u * li;
-    const int first = wy * g.wh * g.W + wx * g.ww;  // the window's first token: always real
-    const bool rows = g.ww == g.W;                  // windows of whole grid rows: slots are consecutive tokens
-    auto token = [&](int slot) {
-        if (!rows) return slot_token(g, wy, wx, slot);
-        return slot < g.slots && first + slot < g.H * g.W ? first + slot : -1;
-    };
-    f32x4 q[8];
+    const int qslot = qblock * 32 + li, qtok = qslot < q_slots ? w.token(qslot) : -1;
+    float logit;
     {
-        const int slot = qblock * 32 + li, qtok = slot < q_slots ? token(slot) : -1;
-        const float *row = qp + (long long)(qtok < 0 ? first : qtok) * qt.sn + 4 * half;
+        float x[32];
+        f32_queries(w, qtok, half, x);
+        const float s = f32_query_scale(x, logit);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) q[i] = *(const f32x4 *)(row + 8 * i);
-    }
-    f32x16 acc[2];  // channels 32 cb + 8 (v / 4) + 4 half + v % 4 of query li
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[0][i] = acc[1][i] = 0.f;
-    float m = -1.0e30f, l = 0.f;  // (finite stand-in for "no maximum yet")
-    const int n_tile = (g.slots + 31) / 32;
-    float set[3][16];
-    // K operands of steps 4 hf .. + 3 of the tile whose key li is token `tok` (negative: padding)
-    auto fetch_k = [&](float (&r)[16], int tok, int hf) __attribute__((always_inline)) {
-        const unsigned at = (unsigned)(tok < 0 ? first : tok) * ksn + 16u * half;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const f32x4 x = *(const f32x4 *)(kp + at + 32 * (4 * hf + i));
-#pragma unroll
-            for (int e = 0; e < 4; ++e) r[4 * i + e] = x[e];
+        for (int t = 0; t < 4; ++t) {
+            if (t != kw) continue;  // (uniform; constant indices of x)
+            const Split q = split8(x + 8 * t, s);
+            *(f16x8 *)(qs + t * 1024 + lane * 16) = q.hi;
+            *(f16x8 *)(qs + (4 + t) * 1024 + lane * 16) = q.lo;
         }
+    }
+    F32State st;
+    st.clear();
+    F32Scale ks, vs;
+    const int n_tile = (g.slots + 31) / 32;
+    f32x4 set[3][4];
+    // K operands of steps 2 hf, 2 hf + 1 of the tile whose key li is token `tok` (negative: padding)
+    auto fetch_k = [&](f32x4 (&r)[4], int tok, int hf) __attribute__((always_inline)) {
+        const unsigned at = (unsigned)(tok < 0 ? w.first : tok) * ksn + 32u * half;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = *(const f32x4 *)(kp + at + 128 * hf + 64 * (i / 2) + 16 * (i % 2));
     };
-    // r[2 j + cb]: channel 32 cb + li of key 16 hf + 8 (j / 4) + 4 half + j % 4
-    auto fetch_v = [&](float (&r)[16], int tok, unsigned pad, int hf) __attribute__((always_inline)) {
-        if (rows && pad == 0u) {
+    // element 8 cb + j: channel 32 cb + li of key 16 hf + 8 (j / 4) + 4 half + j % 4
+    auto fetch_v = [&](f32x4 (&r)[4], int tok, unsigned pad, int hf) __attribute__((always_inline)) {
+        if (w.rows && pad == 0u) {
             const char *row = vp + (unsigned)(__builtin_amdgcn_readfirstlane(tok) + 16 * hf) * (size_t)vsn;
+            unsigned at = vlane;
+            asm volatile("" : "+v"(at));  // (a 32-bit offset to a scalar base: widened ahead of the loop it would be added in vector registers)
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                r[2 * j] = *(const float *)(row + vlane);
-                r[2 * j + 1] = *(const float *)(row + vlane + 128);
+                r[j / 4][j % 4] = *(const float *)(row + at);
+                r[2 + j / 4][j % 4] = *(const float *)(row + at + 128);
                 row += (j == 3 ? 5 : 1) * (size_t)vsn;
             }
         } else {
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const int t = __shfl(tok, 16 * hf + 8 * (j / 4) + 4 * half + j % 4, 64);
-                const unsigned at = (unsigned)(t < 0 ? first : t) * vsn + 4u * li;
-                r[2 * j] = *(const float *)(vp + at);
-                r[2 * j + 1] = *(const float *)(vp + at + 128);
+                const unsigned at = (unsigned)(t < 0 ? w.first : t) * vsn + 4u * li;
+                r[j / 4][j % 4] = *(const float *)(vp + at);
+                r[2 + j / 4][j % 4] = *(const float *)(vp + at + 128);
             }
             // (keeps the two branches' loads apart: merged into one set they would take every address
             // in a vector register of its own)
@@ -326,111 +672,103 @@ attn_direct_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGe
         }
     };
     auto real_token = [&](int tile, int &tok, unsigned &pad) __attribute__((always_inline)) {
-        tok = token(32 * tile + li);
+        tok = w.token(32 * tile + li);
         pad = (unsigned)__builtin_amdgcn_ballot_w64(tok < 0);  // bit j: key j of the tile is padding
     };
     int tok = 0;
     unsigned pad = 0u;
-    // A tile whose K operands are in (or on their way to) ka and kb; leaves those of tile + KW in kb and vc.
-    auto run_tile = [&](int tile, float (&ka)[16], float (&kb)[16], float (&vc)[16]) __attribute__((always_inline)) {
+    // A tile whose K operands are in (or on their way to) ka and kb; leaves those of the next in kb and vc.
+    auto run_tile = [&](int tile, f32x4 (&ka)[4], f32x4 (&kb)[4], f32x4 (&vc)[4]) __attribute__((always_inline)) {
         const int cur = tok;
         const unsigned cur_pad = pad, pads = half ? pad >> 4 : pad;
-        const bool more = tile + KW < n_tile;
+        f32x16 s;
+        auto scores = [&](f32x4 (&r)[4], int hf) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const unsigned char *at = qs + (2 * hf + t) * 1024 + lane * 16;
+                const Split q = {*(const f16x8 *)at, *(const f16x8 *)(at + 4096)}, k = split8((const float *)&r[2 * t], ks.scale);
+                s = mfma_f16(k.hi, q.hi, mfma_small(k, q, s));
+            }
+        };
         fetch_v(vc, cur, cur_pad, 0);
         __builtin_amdgcn_sched_barrier(0);
-        f32x16 s;
+        {
+            const float top = fmaxf(magnitude(ka), magnitude(kb));
+            if (__any(top > ks.limit)) ks.fit(wave_max(top));
+        }
 #pragma unroll
         for (int i = 0; i < 16; ++i) s[i] = 0.f;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[i], q[i / 4][i % 4], s, 0, 0, 0);
+        scores(ka, 0);
         __builtin_amdgcn_sched_barrier(0);
         fetch_v(ka, cur, cur_pad, 1);
-        if (more) real_token(tile + KW, tok, pad);
+        if (tile + 4 < n_tile) real_token(tile + 4, tok, pad);
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kb[i], q[4 + i / 4][i % 4], s, 0, 0, 0);
+        scores(kb, 1);
         __builtin_amdgcn_sched_barrier(0);
-        if (more) fetch_k(kb, tok, 0);
+        fetch_k(kb, tok, 0);  // (behind the last tile its own keys again: loads behind a branch would be waited for all at once)
         __builtin_amdgcn_sched_barrier(0);
         if (cur_pad != 0u) {  // (uniform) padded keys have no weight ...
 #pragma unroll
             for (int j = 0; j < 16; ++j) s[j] = (pads >> (8 * (j / 4) + j % 4)) & 1u ? -INFINITY : s[j];
         }
-        // The reference stays while no logit is more than 8 binary orders above it (numerator and
-        // denominator share it, so the result is the same), and goes up to the maximum otherwise.  The weights
-        // take a factor of 2^-8, exactly: none is above 1, and values up to the largest floats pass through the
-        // sums as under the maximum itself.  (The sixteen products: 1.5 % of a launch that leaves units with one
-        // workgroup.  A reference 8 orders up instead costs none, but rounds the exponents of the largest weights
-        // more coarsely: 4.7e-7 against 4.5e-7 from 64 bits at 1 369 tokens.)
-        float top = s[0];
-#pragma unroll
-        for (int j = 1; j < 16; ++j) top = fmaxf(top, s[j]);
-        if (__any(top * scale_log2 > m + 8.0f)) {
-            float lo, hi;
-            pair_values(top, &lo, &hi);
-            const float m_new = fmaxf(m, fmaxf(lo, hi) * scale_log2), alpha = __builtin_amdgcn_exp2f(m - m_new);
-            m = m_new;
-            l *= alpha;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                acc[0][j] *= alpha;
-                acc[1][j] *= alpha;
-            }
-        }
-        float sum = 0.f;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            s[j] = __builtin_amdgcn_exp2f(fmaf(s[j], scale_log2, -m)) * 0x1p-8f;
-            sum += s[j];
-        }
-        l += sum;
-        auto product = [&](float (&r)[16], int hf) __attribute__((always_inline)) {
+        st.weights(s, (logit * ks.inverse) * scale_log2);
+        auto product = [&](f32x4 (&r)[4], int hf) __attribute__((always_inline)) {
             if (cur_pad != 0u) {  // ... and zeros for the values they meet (0 x inf would be NaN)
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    const bool p = (pads >> (16 * hf + 8 * (j / 4) + j % 4)) & 1u;
-                    r[2 * j] = p ? 0.f : r[2 * j];
-                    r[2 * j + 1] = p ? 0.f : r[2 * j + 1];
+                    const bool x = (pads >> (16 * hf + 8 * (j / 4) + j % 4)) & 1u;
+                    r[j / 4][j % 4] = x ? 0.f : r[j / 4][j % 4];
+                    r[2 + j / 4][j % 4] = x ? 0.f : r[2 + j / 4][j % 4];
                 }
             }
+            const float top = magnitude(r);
+            if (__any(top > vs.limit)) {
+                const float before = vs.inverse;
+                vs.fit(wave_max(top));
+                st.times(vs.scale * before);
+            }
+            float p[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(r[2 * j], s[8 * hf + j], acc[0], 0, 0, 0);
-                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(r[2 * j + 1], s[8 * hf + j], acc[1], 0, 0, 0);
+            for (int j = 0; j < 8; ++j) p[j] = s[8 * hf + j];
+            const Split x = split8(p, 0x1p6f);
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                const Split v = split8((const float *)&r[2 * cb], vs.scale);
+                st.acc[cb] = mfma_f16(v.hi, x.hi, mfma_small(v, x, st.acc[cb]));
             }
         };
         product(vc, 0);
         __builtin_amdgcn_sched_barrier(0);
-        if (more) fetch_k(vc, tok, 1);
+        fetch_k(vc, tok, 1);
         __builtin_amdgcn_sched_barrier(0);
         product(ka, 1);
     };
+    __syncthreads();  // the queries
     if (kw < n_tile) {
         real_token(kw, tok, pad);
         fetch_k(set[0], tok, 0);
         fetch_k(set[1], tok, 1);
         for (int tile = kw;;) {
             run_tile(tile, set[0], set[1], set[2]);
-            if ((tile += KW) >= n_tile) break;
+            if ((tile += 4) >= n_tile) break;
             run_tile(tile, set[1], set[2], set[0]);
-            if ((tile += KW) >= n_tile) break;
+            if ((tile += 4) >= n_tile) break;
             run_tile(tile, set[2], set[0], set[1]);
-            if ((tile += KW) >= n_tile) break;
+            if ((tile += 4) >= n_tile) break;
         }
     }
+    if (__any(!st.settle(vs.inverse))) f32_again(st, w, qtok, scale_log2, kw, 4, li, half);
+    f32_park(st.acc, parts[kw], li, half);
     {
         float lo, hi;
-        pair_values(l, &lo, &hi);
-        l = lo + hi;
-    }
-    f32_park(acc, parts + kw * (32 * 256), li, half);
-    if (half == 0) {
-        ms[kw][li] = m;
-        ls[kw][li] = l;
+        pair_values(st.l * 0x1p-8f, &lo, &hi);
+        if (half == 0) {
+            ms[kw][li] = st.m;
+            ls[kw][li] = lo + hi;
+        }
     }
     __syncthreads();
-    float *op = (float *)ot.ptr + b * ot.sb + h * ot.sh;
-    f32_merge<KW>(parts, ms, ls, qblock, q_slots, token, op, ot.sn, tid);
+    f32_merge<4>(w, &parts[0][0], ms, ls, qblock, q_slots, tid);
 }
 
 // Windows of a few slots, of which a 32 x 32 tile would be padding but for a corner: sixteen lanes per
@@ -472,15 +810,6 @@ attn_small_window_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, Wi
 jv_status attn_bf16_check(const Problem &pr, const WindowGeom &g, int q_slots);
 jv_status attn_bf16(const Problem &pr, const WindowGeom &g, float scale, int q_slots, hipStream_t stream);
 
-template <int KW>
-static jv_status launch_attn_f32(const Problem &pr, const WindowGeom &g, float scale, int q_slots, hipStream_t stream) {
-    constexpr int kQueries = 32 * (4 / KW);
-    const dim3 grid((unsigned)((q_slots + kQueries - 1) / kQueries), g.n_win, pr.B * pr.heads);
-    hipLaunchKernelGGL(attn_f32<KW>, grid, dim3(256), 0, stream, pr.q, pr.k, pr.v, pr.o, g, pr.heads,
-                       scale * 1.4426950408889634f, q_slots);
-    return launch_status("attn_f32");
-}
-
 static jv_status attn_dispatch(const Problem &pr, const WindowGeom &g, float scale, int q_slots,
                                hipStream_t stream) {
     if (pr.bf16) return attn_bf16(pr, g, scale, q_slots, stream);
@@ -493,21 +822,15 @@ static jv_status attn_dispatch(const Problem &pr, const WindowGeom &g, float sca
                            pr.q, pr.k, pr.v, pr.o, g, pr.heads, scale);
         return launch_status("attn_small_window_f32");
     }
-    // Key groups per query block: as long as the launch has fewer than four wavefronts per SIMD
-    // (1 024 SIMDs) with every wavefront on queries of its own, the keys of a window are cut
-    // over two or four wavefronts, if it has tiles for them.
-    const long long waves = (long long)((q_slots + 31) / 32) * g.n_win * pr.B * pr.heads;
     const int tiles = (g.slots + 31) / 32;
-    if (waves < 2048 && tiles > 2) {
-        const long long max_sn = pr.k.sn > pr.v.sn ? pr.k.sn : pr.v.sn;
-        if (f32_keys_staged(tiles, g.ww == g.W, waves, ((long long)g.H * g.W + 64) * max_sn * 4))
-            return launch_attn_f32<4>(pr, g, scale, q_slots, stream);
-        hipLaunchKernelGGL(attn_direct_f32, dim3((unsigned)((q_slots + 31) / 32), g.n_win, pr.B * pr.heads), dim3(256), 0, stream,
-                           pr.q, pr.k, pr.v, pr.o, g, pr.heads, scale * 1.4426950408889634f, q_slots);
-        return launch_status("attn_direct_f32");
-    }
-    if (waves < 4096 && tiles > 1) return launch_attn_f32<2>(pr, g, scale, q_slots, stream);
-    return launch_attn_f32<1>(pr, g, scale, q_slots, stream);
+    const long long blocks = (long long)((q_slots + 31) / 32) * g.n_win * pr.B * pr.heads, max_sn = pr.k.sn > pr.v.sn ? pr.k.sn : pr.v.sn;
+    const F32Kernel kernel = f32_kernel(tiles, g.ww == g.W, blocks, ((long long)g.H * g.W + 64) * max_sn * 4);
+    const int queries = kernel == kF32Many || kernel == kF32Short1 ? 128 : kernel == kF32Short2 ? 64 : 32;
+    const auto f = kernel == kF32Many ? attn_f32 : kernel == kF32Few ? attn_few_f32 : kernel == kF32Short1 ? attn_short_f32<1> :
+                   kernel == kF32Short2 ? attn_short_f32<2> : attn_short_f32<4>;
+    hipLaunchKernelGGL(f, dim3((unsigned)((q_slots + queries - 1) / queries), g.n_win, pr.B * pr.heads), dim3(256), 0, stream,
+                       pr.q, pr.k, pr.v, pr.o, g, pr.heads, scale * 1.4426950408889634f, q_slots);
+    return launch_status("fp32 attention");
 }
 
 // All tokens of the sequence as one window of 1 x N slots (token = slot).

@@ -72,12 +72,26 @@ constexpr int ring_query_blocks(int queries, long long lanes) {
 }
 
 // fp32 attention of few queries, the keys cut over the four wavefronts of a workgroup (`waves` blocks of 32 queries in all, windows of
-// `tiles` tiles of 32 keys): attn_direct_f32, or attn_f32<4> where that is faster or K and V span more bytes than 32-bit offsets
-// count.  With a tile per wavefront the direct kernel has nothing to fetch ahead, and only its third workgroup on a unit tells:
-// rounds of 768 against 512.  Windows of whole grid rows (the direct kernel is 2 to 10 % faster on others) of 4 tiles, staged / direct, us: 128 keys x 6 (batch, head)s 6.8 / 7.0, x 64 7.3 / 7.5, x 192 (768 blocks) 16.3 / 15.4, 112 x 256 (1 024) 19.7 / 22.0,
-// 128 x 320 25.1 / 25.9, x 384 (1 536) 28.9 / 27.3; 3 tiles 7.0 / 6.6, 7 tiles x 6 10.6 / 9.8.
+// `tiles` tiles of 32 keys): attn_few_f32, or attn_short_f32<4> where that is faster or K and V span more bytes than 32-bit offsets
+// count.  With a tile per wavefront attn_few_f32 has nothing to fetch ahead and its scales and splits stand alone, and only its third
+// workgroup on a unit tells: rounds of 768 against 512.  Windows of whole grid rows of 4 tiles, staged / few, us: 128 keys x 6 (batch, head)s 6.8 / 6.9,
+// x 64 7.3 / 7.5; 7 tiles x 6 9.8 / 9.2.
 constexpr bool f32_keys_staged(int tiles, bool whole_rows, long long waves, long long kv_bytes) {
     return kv_bytes >= (1ll << 32) || (tiles == 4 && whole_rows && (waves - 1) % 768 < 512);
+}
+// fp32 attention: `blocks` blocks of 32 queries in all, windows of `tiles` tiles of 32 keys, K and V slices of up to kv_bytes.
+// attn_f32 does the most per second, but four blocks share a workgroup, and a unit with one of them waits out its barriers; attn_few_f32 gives a
+// block four wavefronts, and takes a round of 256 blocks where attn_f32 takes one of
+// 1 024.  Few / many, us: 1 369 tokens (43 tiles) of 516 blocks 49 / 71, 688 50 / 72, 1 032 80 / 87, 1 376 95 / 89; 72 tiles 864 103 / 114, 1 152 125 / 142,
+// 1 728 173 / 144; 25 tiles 600 33 / 44, 800 45 / 44; 18 tiles 576 27 / 33, 864 36 / 34; 8 tiles 512 13.5 / 18.2, 864 24 / 21; 7 tiles 756 18.0 / 18.8; 4 tiles 864 18 / 13.
+// Windows of one or two tiles leave nothing to share keys for: attn_short_f32 where its start is the shorter one.  Short / many, us: 1 tile
+// always (windows of 5 x 5, 3 072 blocks 53 / 59); 2 tiles of 108 blocks 7.1 / 7.9, of 432 8.2 / 8.8, of 864 12.6 / 11.9.
+enum F32Kernel { kF32Many, kF32Few, kF32Short1, kF32Short2, kF32Short4 };
+constexpr F32Kernel f32_kernel(int tiles, bool whole_rows, long long blocks, long long kv_bytes) {
+    if (tiles == 1) return kF32Short1;
+    if (tiles == 2) return blocks <= 640 ? kF32Short2 : kF32Many;
+    if (blocks > (tiles <= 4 ? 512 : tiles < 28 ? 768 : tiles < 40 ? 1024 : 1280)) return kF32Many;
+    return f32_keys_staged(tiles, whole_rows, blocks, kv_bytes) ? kF32Short4 : kF32Few;
 }
 
 // Prefix tokens: `queries` <= 64 queries against the `keys` tokens of a whole sequence, per (batch, head) (jv_attn_bf16.hip).

@@ -89,6 +89,20 @@ def test_staged_or_direct_keys_of_fp32_attention(rule):
     assert got == [1] * len(staged) + [0] * len(direct)
 
 
+def test_kernels_of_fp32_attention(rule):
+    """(tiles, whole rows, blocks of 32 queries, bytes of a slice) on either side of every line of the rule."""
+    want = {"kF32Short1": [(1, 1, 1, 0), (1, 0, 1 << 20, 1 << 40)], "kF32Short2": [(2, 1, 2, 0), (2, 0, 640, 1 << 40)],
+            "kF32Short4": [(4, 1, 24, 0), (4, 1, 512, 0), (10, 1, 10, 1 << 32), (57, 0, 1280, 1 << 40)],
+            "kF32Few": [(3, 1, 24, 0), (3, 0, 512, 0), (4, 0, 512, 0), (5, 1, 768, 0), (27, 0, 768, 0), (28, 1, 1024, 0), (39, 1, 1024, 0),
+                        (40, 1, 1280, 0), (43, 1, 516, (1 << 32) - 1)],
+            "kF32Many": [(2, 1, 641, 0), (3, 1, 513, 0), (4, 1, 513, 0), (5, 1, 769, 1 << 40), (27, 0, 769, 0), (28, 1, 1025, 0), (40, 1, 1281, 0),
+                         (72, 1, 1 << 30, 1 << 40)]}
+    for kernel, calls in want.items():
+        assert rule([f"f32_kernel({t}, {r}, {b}ll, {kv}ll) == {kernel}" for t, r, b, kv in calls]) == [1] * len(calls)
+    for kernel, sizes in test_gpu_fp32.SPLIT_KERNELS.items():  # (batch x heads, tokens)
+        assert rule([f"f32_kernel(({n} + 31) / 32, 1, {bh} * (({n} + 31) / 32), 1 << 20) == {kernel}" for bh, n in sizes]) == [1] * len(sizes)
+
+
 def test_prefix_chains_of_64_channel_heads(rule):
     """(prefix tokens, grid tokens, batch x heads) on either side of every line of the rule, as measured."""
     one = [(5, 576, 12), (1, 784, 16), (5, 784, 64), (5, 1369, 144), (16, 1369, 192), (5, 2304, 160), (5, 4096, 256), (33, 1000, 64),

@@ -119,6 +119,65 @@ def test_values_near_the_largest_floats(N):
     check(err_fp32(to_host(o), oracle.full_attn(q, k, v)), FP32_TOL)
 
 
+# (heads, tokens) of the two kernels whose operands are pairs of fp16 numbers
+SPLIT_KERNELS = {"kF32Few": [(2, 70), (3, 161), (2, 385), (6, 1030)], "kF32Many": [(300, 70), (160, 161), (64, 385), (40, 1030)]}
+SPLIT_SIZES = [c for sizes in SPLIT_KERNELS.values() for c in sizes]
+
+
+def _full64(q, k, v):
+    s = (q.double() @ k.double().transpose(-1, -2).contiguous()) * 0.125
+    return torch.softmax(s, -1) @ v.double()
+
+
+@pytest.mark.parametrize("heads,N", SPLIT_SIZES)
+@pytest.mark.parametrize("what", ["plain", "tiny", "large", "climb", "fall", "outlier"])
+def test_split_operands(heads, N, what):
+    """Scales: magnitudes from 1e-30 to 1e30 (products of order one), and K and V that grow or shrink by 2^24 along the sequence, so that
+    scales settled on the first tiles have to go down, or hold numbers far below them."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    q, k, v = (torch.randn(1, heads, N, 64, generator=g, device="cuda") for _ in range(3))
+    ramp = torch.exp2(torch.linspace(-12, 12, N, device="cuda"))[:, None]
+    if what == "tiny":
+        q, k, v = q * 1e-20, k * 1e20, v * 1e-30
+    elif what == "large":
+        q, k, v = q * 1e20, k * 1e-20, v * 1e30
+    elif what == "climb":
+        k, v = k * torch.exp2(torch.linspace(-24, 0, N, device="cuda"))[:, None], v * ramp
+    elif what == "fall":
+        k, v = k * torch.exp2(torch.linspace(0, -24, N, device="cuda"))[:, None], v * ramp.flip(0)
+    elif what == "outlier":  # one row of each tile 2^10 above the others
+        v[:, :, 5::32] *= 1024.0
+    o = torch.full_like(q, float("nan"))
+    binding.jv_full_attn_fwd(q, k, v, o, (1, N))
+    ref = _full64(q, k, v)
+    # sums of up to 1 030 fp32 products and logits of up to 40: 3e-7 measured with the fp32 matrix instructions at these lengths
+    check(float((o.double() - ref).norm() / ref.norm()), 5e-7)
+
+
+@pytest.mark.parametrize("heads,N", SPLIT_SIZES)
+def test_infinities_and_nan(heads, N):
+    """What is not finite ends where the formula puts it: a key's value in its channel of every query, a query's
+    in its own row, a key's score of -inf nowhere."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + 1)
+    q, k, v = (torch.randn(1, heads, N, 64, generator=g, device="cuda") for _ in range(3))
+    v[0, 0, N - 1, 7] = float("inf")
+    v[0, 0, 3, 40] = float("-inf")
+    v[0, 1, 33, 9] = float("nan")
+    q[0, 1, 5, 0] = float("nan")
+    q[..., 63] = q[..., 63].abs() + 0.1
+    k[0, 1, 40, 63] = float("-inf")  # a score of -inf: no weight
+    o = torch.full_like(q, 123.0)
+    binding.jv_full_attn_fwd(q, k, v, o, (1, N))
+    ref = _full64(q, k, v)
+    assert torch.equal(torch.isnan(o), torch.isnan(ref))
+    inf = torch.isinf(ref)
+    assert torch.equal(torch.isinf(o), inf) and torch.equal(o[inf].double(), ref[inf])
+    real = torch.isfinite(ref)
+    check(float((o.double()[real] - ref[real]).norm() / ref[real].norm()), 5e-7)  # (as above)
+
+
 @pytest.mark.parametrize("H,W,window,P", [
     (5, 7, (1, 1), 0),         # every token alone: the result is its value row
     (5, 7, (1, 2), 0), (7, 5, (3, 1), 3), (9, 11, (2, 2), 5), (6, 6, (2, 4), 0), (3, 5, (4, 2), 0),
