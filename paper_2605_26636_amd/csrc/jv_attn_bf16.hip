@@ -790,7 +790,11 @@ __global__ void __launch_bounds__(256, 2) attn_window8_bf16(AttnArgs a, int n_it
 //   * every full stage runs the unmasked tile code, which is one basic block per tile apart
 //     from the (rarely taken) branch that raises the softmax reference; only the last,
 //     partial stage of a window masks keys, and it does so by key index, not through LDS.
-// grid ring_grid(a, 128 * NT): one workgroup per (block of 128 NT query slots, window, batch * head),
+// KW = 2 (with NT = 1; ring_key_groups): for launches that leave units idle, a workgroup holds 64 query slots, and two wavefronts share
+// a block of 32 and take a tile of every stage each, with running softmaxes of their own that meet in LDS at the end.  Bound by one
+// wavefront's chain of tiles, which it halves, against twice the loads and barriers for a query: 1 374 tokens x 12
+// heads 21.5 -> 18.9 us, x 32 28.6 -> 26.0, x 6 21.0 -> 14.8, 2 304 x 6 32.9 -> 21.9; with the chip full (1 374 x 64) 40.6 -> 47.6.
+// grid ring_grid(a, 128 * NT / KW): one workgroup per (block of 128 NT / KW query slots, window, batch * head),
 // dealt to the XCDs in contiguous ranges (ring_item); 256 threads.
 // ---------------------------------------------------------------------------------------
 constexpr int kRing = 3;
@@ -858,21 +862,23 @@ __device__ __forceinline__ void ring_tile32(WaveState<NT> &w, const u32x4 (&qreg
             }
 }
 
-template <bool O_BF16, int NT>
+template <bool O_BF16, int NT, int KW = 1>
 __global__ void __launch_bounds__(256, NT == 1 ? 3 : 2) attn_ring_bf16(AttnArgs a) {
     // the logit scale, fetched (a kernel argument) and waited for here, not inside the key loop
     float c_log2 = a.c;
     asm volatile("" : "+s"(c_log2));
     __shared__ __align__(16) unsigned char smem[kRing * kStageBytes];
+    static_assert(KW == 1 || (KW == 2 && NT == 1), "key groups: one, or two with one block of queries a wavefront");
     constexpr int WAVES = 4;
     constexpr int kLoads = 8 / WAVES;  // load instructions per stage, tensor and wavefront (8 rows each)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     RingItem it;
-    if (!ring_item(a, 32 * NT * WAVES, it)) return;  // whole workgroup
+    if (!ring_item(a, 32 * NT * WAVES / KW, it)) return;  // whole workgroup
     const int bh = it.bh, b = bh / a.heads, h = bh % a.heads;
     const int win = it.win, wy = win / a.g.wins_x, wx = win % a.g.wins_x;
-    const int q0 = it.qblock * (32 * NT * WAVES) + wave * (32 * NT);
+    const int kw = wave % KW;
+    const int q0 = it.qblock * (32 * NT * WAVES / KW) + (wave / KW) * (32 * NT);
     const long long qbase = b * a.q.sb + h * a.q.sh, obase = b * a.o.sb + h * a.o.sh;
     const bool wave_live = q0 < a.q_slots;
 
@@ -942,15 +948,22 @@ __global__ void __launch_bounds__(256, NT == 1 ? 3 : 2) attn_ring_bf16(AttnArgs 
         lds_barrier();
         if (st + kRing - 1 < n_stage) issue(st + kRing - 1);
     };
-    const unsigned vaddr[2] = {vt_lane_address(smem + kStage * 128, 0, lane),
-                               vt_lane_address(smem + kStage * 128, 1, lane)};  // V rows of ring slot 0
+    const int row0 = kw * 32;  // with two key groups: the tile of a stage that is this wavefront's
+    const unsigned vaddr[2] = {vt_lane_address(smem + (kStage + row0) * 128, 0, lane),
+                               vt_lane_address(smem + (kStage + row0) * 128, 1, lane)};  // V rows of ring slot 0
     unsigned kaddr[4];
-    k_lane_addresses(kaddr, smem, lane);  // K rows of ring slot 0
+    k_lane_addresses(kaddr, smem + row0 * 128, lane);  // K rows of ring slot 0
     u32x4 ka[4];
     // A full stage in ring slot `slot` (a compile-time constant, so that every LDS offset is a
     // constant of the instruction).
     auto full_stage = [&](int st, auto slot_tag) {
         constexpr int slot = decltype(slot_tag)::value, after = (slot + 1) % kRing;
+        if constexpr (KW == 2) {  // one tile a stage: the next stage is there before its first operands are read
+            next_stage_ready(st);
+            if (wave_live)
+                ring_tile32<NT, after * kStageBytes, false, slot * kStageBytes>(w, qreg, ka, kaddr, vaddr, 0, 0, c_log2, lane);
+            return;
+        }
         if (wave_live)
             ring_tile32<NT, slot * kStageBytes + 32 * 128, false, slot * kStageBytes>(w, qreg, ka, kaddr, vaddr, 0, 0, c_log2, lane);
         next_stage_ready(st);
@@ -992,7 +1005,9 @@ __global__ void __launch_bounds__(256, NT == 1 ? 3 : 2) attn_ring_bf16(AttnArgs 
         const unsigned vlast[2] = {vaddr[0] + at, vaddr[1] + at};
         const unsigned klast[4] = {kaddr[0] + at, kaddr[1] + at, kaddr[2] + at, kaddr[3] + at};
         const int key_limit = tok_limit - st * kStage;  // 1 .. 63
-        if (key_limit > 32) {
+        if constexpr (KW == 2) {
+            if (row0 < key_limit) ring_tile32<NT, -1, true, 0>(w, qreg, ka, klast, vlast, row0, key_limit, c_log2, lane);
+        } else if (key_limit > 32) {
             ring_tile32<NT, 32 * 128, true, 0>(w, qreg, ka, klast, vlast, 0, key_limit, c_log2, lane);
             ring_tile32<NT, -1, true, 32 * 128>(w, qreg, ka, klast, vlast, 32, key_limit, c_log2, lane);
         } else {
@@ -1000,6 +1015,28 @@ __global__ void __launch_bounds__(256, NT == 1 ? 3 : 2) attn_ring_bf16(AttnArgs 
         }
     }
     __syncthreads();  // every wavefront is done with the ring: reuse it as staging
+    if constexpr (KW == 2) {
+        // The second group's sums, behind the staging rows, join the first's: O = sum_k acc_k 2^(m_k - M) / sum_k l_k 2^(m_k - M).
+        constexpr int kSums = 2 * 16 + 2;  // floats a lane
+        float *sums = (float *)(smem + 4 * 4096) + (wave >> 1) * kSums * 64 + lane;
+        if (kw == 1) {
+#pragma unroll
+            for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) sums[64 * (16 * mi + v)] = w.acc[mi][0][v];
+            sums[64 * 32] = w.m[0];
+            sums[64 * 33] = w.l[0];
+        }
+        __syncthreads();
+        if (kw == 1) return;
+        const float m1 = sums[64 * 32], top = fmaxf(w.m[0], m1);
+        const float a0 = __builtin_amdgcn_exp2f(w.m[0] - top), a1 = __builtin_amdgcn_exp2f(m1 - top);
+        w.l[0] = fmaf(a1, sums[64 * 33], a0 * w.l[0]);
+#pragma unroll
+        for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) w.acc[mi][0][v] = fmaf(a1, sums[64 * (16 * mi + v)], a0 * w.acc[mi][0][v]);
+    }
     if (wave_live) {
         AttnArgs st = a;
         st.g.slots = a.q_slots;  // query slots past the limit are not stored
@@ -1974,6 +2011,11 @@ jv_status attn_bf16(const Problem &pr, const WindowGeom &g, float scale, int q_s
                              : launch_prefix<false, 1>(a, pr.B * pr.heads, stream);
         return pr.o_bf16 ? launch_prefix<true, 2>(a, pr.B * pr.heads, stream)
                          : launch_prefix<false, 2>(a, pr.B * pr.heads, stream);
+    }
+    if (fast && ring_key_groups(a.q_slots, g.slots, (long long)g.n_win * a.n_bh) == 2) {
+        if (pr.o_bf16) hipLaunchKernelGGL((attn_ring_bf16<true, 1, 2>), ring_grid(a, 64), dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((attn_ring_bf16<false, 1, 2>), ring_grid(a, 64), dim3(256), 0, stream, a);
+        return launch_status("attn_ring_bf16");
     }
     if (fast && NT == 2 && ring_query_blocks(a.q_slots, (long long)g.n_win * a.n_bh) == 1) {
         if (pr.o_bf16) hipLaunchKernelGGL((attn_ring_bf16<true, 1>), ring_grid(a, 128), dim3(256), 0, stream, a);

@@ -71,6 +71,14 @@ constexpr int ring_query_blocks(int queries, long long lanes) {
     return 1.08f * t1 < t2 ? 1 : 2;  // (rounds overlap, to the large blocks' advantage)
 }
 
+// ... and the key groups of a workgroup: two (attn_ring_bf16<.., 1, 2>, 64 queries a workgroup) while their workgroups, twice as
+// many, fit the chip at once, three to a unit.  One group / two, us: 700 tokens x 20 heads 12.7 / 9.7, x 64 (704 workgroups) 17.5 / 16.2, 1 374 x 12 21.5 / 18.9,
+// x 32 (704) 28.6 / 26.0, x 40 (880) 29.5 / 34.1, 4 096 x 12 (768) 75 / 67, x 16 (1 024) 82 / 90, 8 192 x 6 (768) 144 / 129.  The order of summation differs,
+// so that a long sequence's last bits depend on how many there are; below 21 tiles of keys there is one group, and they do not.
+constexpr int ring_key_groups(int queries, int keys, long long lanes) {
+    return keys >= 21 * 32 && (long long)((queries + 63) / 64) * lanes <= 768 ? 2 : 1;
+}
+
 // fp32 attention of few queries, the keys cut over the four wavefronts of a workgroup (`waves` blocks of 32 queries in all, windows of
 // `tiles` tiles of 32 keys): attn_few_f32, or attn_short_f32<4> where that is faster or K and V span more bytes than 32-bit offsets
 // count.  With a tile per wavefront attn_few_f32 has nothing to fetch ahead and its scales and splits stand alone, and only its third

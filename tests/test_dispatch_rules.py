@@ -79,6 +79,15 @@ def test_query_blocks_of_full_attention(rule):
     assert got == [1] * len(one) + [2] * (len(two) + len(either)) + [1] * (len(either) + 2 * len(same))
 
 
+def test_key_groups_of_full_attention(rule):
+    """(queries, keys, lanes) on either side of the rule, and the sizes that the GPU test of key groups counts on."""
+    one, two = [(671, 671, 1), (641, 641, 1), (1374, 1374, 35), (4096, 4096, 13), (64, 672, 769), (1 << 24, 1 << 24, 65535)], [
+        (672, 672, 1), (1374, 1374, 34), (4096, 4096, 12), (64, 672, 768), (49152, 49152, 1)]
+    two += [(n, n, lanes) for n, lanes in test_gpu_bf16_attn.KEY_GROUPS]
+    got = rule([f"ring_key_groups({q}, {k}, {lanes})" for q, k, lanes in one + two])
+    assert got == [1] * len(one) + [2] * len(two)
+
+
 def test_staged_or_direct_keys_of_fp32_attention(rule):
     """(tiles, whole rows, blocks of 32 queries, bytes of a slice of K and V)"""
     staged = [(4, 1, 24, 1 << 15), (4, 1, 512, 1 << 15), (4, 1, 1024, 1 << 15), (4, 1, 1280, 1 << 15), (4, 1, 2040, 1 << 15),

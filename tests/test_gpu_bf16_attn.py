@@ -69,6 +69,24 @@ def test_query_blocks_of_either_size_give_the_same_bits(N, copies):
     assert torch.equal(many, one.expand_as(many))
 
 
+# (tokens, heads): the last stage of 64 keys with 32, 33, 64, 1 and 31 keys, the last block of 64 queries with 32, 33, 64, 1 and 31
+KEY_GROUPS = [(672, 2), (673, 3), (704, 2), (705, 4), (1055, 2)]
+
+
+@pytest.mark.parametrize("N,heads", KEY_GROUPS)
+@pytest.mark.parametrize("climb", [(0.2, 8.0), (8.0, 0.2)])
+def test_keys_in_two_groups(N, heads, climb):
+    """Few queries of a long sequence: the tiles of a stage belong to two wavefronts (logits that climb, or fall, along the sequence: references
+    far apart, and rows that one group holds almost alone)."""
+    q, k, v = synth.qkv(51, 1, heads, N, 64, 0.5, True)
+    k = synth.round_to_bf16((k * np.linspace(*climb, N, dtype=np.float32)[None, None, :, None]).astype(np.float32))
+    ref = oracle.full_attn(q, k, v)
+    o32, o16 = _full(q, k, v, 1, N, torch.float32), _full(q, k, v, 1, N)
+    # (the bound of the test above)
+    check(err_bf16(to_host(o32), ref), 2.0 ** -9 * float(np.abs(v).max()) / float(np.sqrt(np.mean(ref * ref))) + 1e-4)
+    assert torch.equal(o32.to(torch.bfloat16), o16)
+
+
 @pytest.mark.parametrize("B,heads,H,W,window,vscale", [
     (2, 2, 16, 16, (8, 8), 1.0),      # config-1 geometry in bf16
     (1, 2, 37, 37, (8, 8), 0.125),    # padded 40 x 40, windows of 64 / 40 / 25 real tokens
