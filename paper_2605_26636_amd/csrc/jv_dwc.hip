@@ -508,7 +508,7 @@ jv_status plan_dwc_wide(const jv_dwc_params *dwc, size_t base, int B, int heads,
     if (p.mode == JV_DWC_SQUEEZE_DYNAMIC) {
         const size_t C = (size_t)heads * kHeadDimWide, kk = (size_t)p.ksize * p.ksize;
         p.vsum_off = base;
-        p.hidden_off = p.vsum_off + align64f((size_t)plan_linear_wide(B, heads, N).n_split * B * C);
+        p.hidden_off = p.vsum_off + align64f((size_t)plan_linear(B, heads, N).n_split * B * C);  // (at least plan_linear_wide's)
         p.kappa_off = p.hidden_off + align64f((size_t)B * (p.hidden > 0 ? p.hidden : 1));
         p.total_floats = p.kappa_off + align64f((size_t)B * C * kk);
     }

@@ -969,7 +969,10 @@ jv_status linear_fused_projection_operands(const Problem &pr, float eps, float *
 
 // ---------------------------------------------------------------------------------------
 // head_dim 128.  la_state_wide_bf16 (below) leaves four 64 x 64 quadrant states per head,
-// la_combine sums the partial ones; this is the apply pass:
+// la_combine_wide sums the partial ones, and the one that has the whole sum leaves it as operands of the apply pass: every number as a bf16
+// high part and the bf16 rest, per quadrant kStateFloats * 4 bytes: St hi, St lo, z hi [64], z lo [64].  St[c2][c1] lies where that pass's
+// operands take it, whose loads and the stores here then cover whole lines: eight c1 of a lane, lanes, k-steps of 16 c1, blocks
+// of 32 c2 (wide_state_at).  (As rows of c1 every instruction touched 32 of them: 64 x 196 tokens x 8 heads 43.7 us.)  The apply pass:
 //   o[c2] = sum_i relu(q_i) S_ij[:, c2] / (sum_i relu(q_i) . z_i + eps),   j = c2 / 64,
 // q_i the two 64-channel halves of a query row.  A workgroup streams one token chunk of one
 // (batch, head); its four wavefronts own the four 32-channel quarters of the output, each with
@@ -982,22 +985,46 @@ jv_status linear_fused_projection_operands(const Problem &pr, float eps, float *
 // sum_taps kappa[c][tap] * V[token + tap][c] for them; the sum is rounded once.
 // grid (n_chunks * B*heads), 256 threads.
 // ---------------------------------------------------------------------------------------
+// Position of St[32 block + li][16 ks + 8 g + e] in a state.
+__device__ inline int wide_state_at(int block, int ks, int g, int li, int e) { return ((block * 4 + ks) * 64 + g * 32 + li) * 8 + e; }
+__device__ inline void store_pairs(unsigned char *hi, unsigned char *lo, f32x4 x) {
+    const u32x2 h = {pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3])};
+    *(u32x2 *)hi = h;
+    *(u32x2 *)lo = u32x2{pack_bf16x2(x[0] - bf16_lo(h[0]), x[1] - bf16_hi(h[0])), pack_bf16x2(x[2] - bf16_lo(h[1]), x[3] - bf16_hi(h[1]))};
+}
+
 template <bool O_BF16, int KS>
 __global__ void __launch_bounds__(256, 2)
 la_apply_wide_bf16(TensorArg qt, TensorArg ot, const float *__restrict__ states, int heads, int N,
                    int tokens_per_wg, int n_chunks, float eps, TensorArg vt, DwcArg cv) {
-    // query tile [64 tokens][256 B]; output tile (bf16 rows of 256 B, or fp32 rows of 512 B with
+    // ring of query tiles [64 tokens][256 B], one with the convolution; output tile (bf16 rows of 256 B, or fp32 rows of 512 B with
     // the convolution); the filters as [tap][channel]
-    constexpr int kOutBytes = KS ? 32768 : 16384;
-    __shared__ __align__(16) unsigned char smem[16384 + kOutBytes + KS * KS * kHeadDimWide * 4];
-    unsigned char *qtile = smem, *otile = smem + 16384;
-    float *kap = (float *)(smem + 16384 + kOutBytes);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, li = lane & 31;
+    constexpr int kOutBytes = KS ? 32768 : 16384, kSlots = KS ? 1 : 4, kTile = 16384;
+    __shared__ __align__(16) unsigned char smem[kSlots * kTile + kOutBytes + KS * KS * kHeadDimWide * 4];
+    unsigned char *otile = smem + kSlots * kTile;
+    float *kap = (float *)(smem + kSlots * kTile + kOutBytes);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 5, li = lane & 31;
     const int bh = blockIdx.x / n_chunks, b = bh / heads, h = bh % heads;
     const __bf16 *qp = (const __bf16 *)qt.ptr + b * qt.sb + h * qt.sh;
     const int n0 = (blockIdx.x % n_chunks) * tokens_per_wg, n1 = min(N, n0 + tokens_per_wg);
     const int frow = tid >> 4, fchunk = tid & 15;  // this thread's 16 bytes of rows frow + 16 r of a tile
+    const int n_tile = (n1 - n0 + 63) / 64;
 
+    // The next query tile.  Without the convolution tiles go from global memory straight into LDS, the first four before anything
+    // else is waited for, so that memory works under the start (8 x 4 096 tokens x 8 heads 70.1 -> 67.6 us for both passes).  A wavefront moves rows 16 r + 4 wave +
+    // lane / 16 (r < 4); the lane fetches the chunk that belongs in its slot of the row (wide_off_row).  Rows past the range
+    // are its last one again, so that all wavefronts issue the same loads.  With the convolution, whose waits for V would wait for them too (and
+    // whose output tile leaves no room), one tile passes through registers.
+    auto issue = [&](int tile) {
+        unsigned char *to = smem + (tile % kSlots) * kTile;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row0 = 16 * r + 4 * wave, row = row0 + (lane >> 4), n = min(n0 + 64 * tile + row, n1 - 1);
+            const __bf16 *from = qp + (long long)n * qt.sn + ((lane & 15) ^ (row & 15)) * 8;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)from,
+                                             (__attribute__((address_space(3))) void *)(to + row0 * 256), 16, 0, kDmaStreamAux);
+        }
+    };
     u32x4 qreg[4];
     auto fetch = [&](int t0) {
 #pragma unroll
@@ -1008,61 +1035,82 @@ la_apply_wide_bf16(TensorArg qt, TensorArg ot, const float *__restrict__ states,
             if (n < n1) qreg[r] = ld_stream((const u32x4 *)(qp + (long long)n * qt.sn + fchunk * 8));
         }
     };
-    fetch(n0);
+    if (KS) fetch(n0);
     if (KS) {  // (read after the first barrier of the token loop)
         const float *kbase = cv.kappa + b * cv.kappa_sb + (size_t)h * kHeadDimWide * KS * KS;
         for (int e = tid; e < kHeadDimWide * KS * KS; e += 256) kap[(e % (KS * KS)) * kHeadDimWide + e / (KS * KS)] = kbase[e];
     }
 
     // A operands: rows c2 of S_ij^T (this wavefront's quarter), k-slots c1 = 16 ks + 8 g + (0..7).
-    const int j = wave >> 1, c2 = 32 * (wave & 1) + li;
+    const int j = wave >> 1;
     bf16x8 s_hi[2][4], s_lo[2][4], z_op[2][4];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const float *st = states + ((size_t)bh * 4 + 2 * i + j) * kStateFloats;
+        const unsigned char *st = (const unsigned char *)(states + ((size_t)bh * 4 + 2 * i + j) * kStateFloats);
+        constexpr int kZ = kHeadDim * kHeadDim;
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
-            const float *row = st + c2 * kHeadDim + 16 * ks + 8 * g;
-            const float *zrow = st + kHeadDim * kHeadDim + 16 * ks + 8 * g;
-            const f32x4 x0 = *(const f32x4 *)row, x1 = *(const f32x4 *)(row + 4);
-            const f32x4 z0 = *(const f32x4 *)zrow, z1 = *(const f32x4 *)(zrow + 4);
-            const float x[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
-            const float zv[8] = {z0[0], z0[1], z0[2], z0[3], z1[0], z1[1], z1[2], z1[3]};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const __bf16 hi = (__bf16)x[e];
-                s_hi[i][ks][e] = hi;
-                s_lo[i][ks][e] = (__bf16)(x[e] - (float)hi);
-                // denominator block: row 0 = z high part, row 1 = z low part, other rows zero
-                const __bf16 zh = (__bf16)zv[e];
-                const __bf16 zl = (__bf16)(zv[e] - (float)zh);
-                z_op[i][ks][e] = li == 0 ? zh : (li == 1 ? zl : (__bf16)0.f);
-            }
+            const unsigned char *row = st + 2 * wide_state_at(wave & 1, ks, g, li, 0);
+            s_hi[i][ks] = as_bf16x8(*(const u32x4 *)row);
+            s_lo[i][ks] = as_bf16x8(*(const u32x4 *)(row + 2 * kZ));
+            z_op[i][ks] = as_bf16x8(*(const u32x4 *)(st + 4 * kZ + 2 * kHeadDim * (li & 1) + 2 * (16 * ks + 8 * g)));
         }
     }
+    // (behind the loads of the states, and of a number known to the compiler, so that it can wait for the states alone: tiles past
+    // the range are its last row again)
+    if (!KS) {
+#pragma unroll
+        for (int tile = 0; tile < kSlots; ++tile) issue(tile);
+    }
+    // denominator block: row 0 = z high part, row 1 = z low part, other rows zero
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+            if (li >= 2) z_op[i][ks] = as_bf16x8(u32x4{0u, 0u, 0u, 0u});
 
     const __bf16 *vp = (const __bf16 *)vt.ptr + b * vt.sb + h * vt.sh;
-    for (int t = n0; t < n1; t += 64) {
-        __syncthreads();  // the previous tile has been read, and its output rows stored
+    unsigned qaddr[8];  // this lane's operands of a tile's first 32 tokens in slot 0
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            *(u32x4 *)(qtile + wide_off_row(16 * r + frow, fchunk)) = relu_bf16x8(qreg[r]);
-        if (t + 64 < n1) fetch(t + 64);
-        __syncthreads();
+    for (int c = 0; c < 8; ++c) qaddr[c] = lds_address(smem) + wide_off_row(li, 2 * c + g);
+    for (int tile = 0; tile < n_tile; ++tile) {
+        const int t = n0 + 64 * tile;
+        if (KS) {
+            __syncthreads();  // the previous tile has been read, and its output rows stored
+#pragma unroll
+            for (int r = 0; r < 4; ++r) *(u32x4 *)(smem + wide_off_row(16 * r + frow, fchunk)) = relu_bf16x8(qreg[r]);
+            if (t + 64 < n1) fetch(t + 64);
+            __syncthreads();
+        } else {
+            // This tile has landed; at most the three issued behind it may be on their way (stores in between count too: the
+            // wait is then a little stricter).
+            const int behind = min(kSlots - 1, max(kSlots, n_tile) - 1 - tile);
+            if (behind == 3) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+            else if (behind == 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+            else if (behind == 1) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            lds_barrier();  // ... for every wavefront, and the output rows before have been read
+        }
+        const unsigned slot = (unsigned)(tile % kSlots) * kTile;
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
             if (t + 32 * nt >= n1) break;  // the same for every wavefront of the workgroup
             f32x16 acc, accz;
 #pragma unroll
             for (int v = 0; v < 16; ++v) { acc[v] = 0.f; accz[v] = 0.f; }
+            u32x4 qb[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) qb[c] = nt ? lds_read_b128_at<32 * 256>(qaddr[c] + slot) : lds_read_b128_at<0>(qaddr[c] + slot);
+            lds_reads_landed(qb[0], qb[1], qb[2], qb[3]);
+            lds_reads_landed(qb[4], qb[5], qb[6], qb[7]);
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks) {
-                    const bf16x8 qb = as_bf16x8(*(const u32x4 *)(qtile + wide_off_row(32 * nt + li, 2 * (4 * i + ks) + g)));
-                    accz = mfma32(z_op[i][ks], qb, accz);
-                    acc = mfma32(s_lo[i][ks], qb, acc);
-                    acc = mfma32(s_hi[i][ks], qb, acc);
+                    const bf16x8 q = as_bf16x8(KS ? qb[4 * i + ks] : relu_bf16x8(qb[4 * i + ks]));
+                    accz = mfma32(z_op[i][ks], q, accz);
+                    acc = mfma32(s_lo[i][ks], q, acc);
+                    acc = mfma32(s_hi[i][ks], q, acc);
                 }
             // den lives in rows 0 and 1 of the denominator block: registers 0, 1 of lanes g = 0.
             float den_lo, den_hi;
@@ -1095,7 +1143,7 @@ la_apply_wide_bf16(TensorArg qt, TensorArg ot, const float *__restrict__ states,
             }
         }
         if (KS) {
-            __syncthreads();  // the four quarters of every row are in the output tile
+            __syncthreads();  // the four quarters of every row are in the output tile, and the query tile has been read
             // This thread finishes channels 8 fchunk .. + 7 of tokens tok0 .. tok0 + 3: the taps of
             // neighbouring tokens overlap, so one tap row needs 4 + KS - 1 loads instead of 4 * KS.
             // Out-of-grid taps (and tokens past the end of the range) read a valid row with
@@ -1171,39 +1219,52 @@ la_apply_wide_bf16(TensorArg qt, TensorArg ot, const float *__restrict__ states,
                     }
                 }
             }
-        } else if (O_BF16) {
-            __syncthreads();  // the four quarters of every row are in the output tile
-            __bf16 *op = (__bf16 *)ot.ptr + b * ot.sb + h * ot.sh;
+        } else {
+            lds_barrier();  // the four quarters of every row are in the output tile, and the query tile has been read
+            if (O_BF16) {
+                __bf16 *op = (__bf16 *)ot.ptr + b * ot.sb + h * ot.sh;
+                u32x4 val[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = 16 * r + frow, n = t + row;
-                const u32x4 val = *(const u32x4 *)(otile + wide_off_row(row, fchunk));
-                if (n < n1) st_stream((u32x4 *)(op + (long long)n * ot.sn + fchunk * 8), val);
+                for (int r = 0; r < 4; ++r) val[r] = lds_read_b128_ordered(lds_address(otile) + wide_off_row(16 * r + frow, fchunk));
+                lds_reads_landed(val[0], val[1], val[2], val[3]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int n = t + 16 * r + frow;
+                    if (n < n1) st_stream((u32x4 *)(op + (long long)n * ot.sn + fchunk * 8), val[r]);
+                }
             }
         }
+        if (!KS && tile + kSlots < n_tile) issue(tile + kSlots);
     }
+    if (!KS && n_tile < kSlots) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (nothing may land in the LDS of the next workgroup)
 }
 
 // State pass for heads of 128 channels: S = relu(K)^T V (128 x 128) and z = sum relu(K) of one
-// token chunk, K and V read once.  The workgroup's four wavefronts share tiles of 64 tokens in
-// LDS -- K (rectified) and V, each as two half tiles of 64 channels in the tile_off_tr layout --
-// and wavefront 2i + j accumulates the quadrant S_ij = relu(K_i)^T V_j (channels 64i .. 64i+63
+// token chunk, K and V read once.  TEAMS (1, 2) teams of four wavefronts take tiles of 64 tokens in turn, which each
+// shares in LDS of its own -- K (rectified) and V, each as two half tiles of 64 channels in the tile_off_tr layout --
+// and wavefront 2i + j of a team accumulates the quadrant S_ij = relu(K_i)^T V_j (channels 64i .. 64i+63
 // of K against 64j .. 64j+63 of V) exactly as la_state_bf16 accumulates its one state, and z_i.
 // Two tile buffers: the next tile is fetched into registers while this one is reduced, and
-// stored after it; one barrier per tile.  The quadrants are written as four states of
+// stored after it; one barrier per tile.  At the end two teams' sums meet in LDS, each team adding up and storing
+// the half for one block of 32 K channels.  The quadrants are written as four states of
 // kStateFloats floats, quadrant 2i + j of (batch, head) bh at index 4 bh + 2i + j of `part`.
+// Bound by memory, the states among it (66 KB a workgroup, written here and read by the sum): with one team there are twice as
+// many, 34 MB beside 67 MB of K and V for 16 384 tokens x 8 heads (both passes, with the sum's and the states' present form, 46.9 -> 41.6 us, with the convolution 84 -> 68; 32 x 1 369 x 8 heads 94 -> 81).
+// Where two teams would leave as many states, two workgroups of one team overlap each other's start and end: 64 x 196
+// tokens x 8 heads 37.7 with one team, 42.0 with two (states as rows).
 // VSUM: also write the chunk's token sum of V (the input of the dynamic-filter generator of the
 // block's convolution branch) to vsum[part][bh][128]; it falls out of the V operands of the
 // wavefronts with i = 0.
-// grid (n_split, B*heads), 256 threads, kStateWideLds bytes of dynamic LDS.
-constexpr int kStateWideLds = 2 * 4 * 8192;
+// grid (n_split, B*heads), 256 TEAMS threads, TEAMS * kStateWideTeamLds bytes of dynamic LDS.
+constexpr int kStateWideTeamLds = 2 * 4 * 8192;
 
-template <bool VSUM>
-__global__ void __launch_bounds__(256, 2)
+template <bool VSUM, int TEAMS>
+__global__ void __launch_bounds__(256 * TEAMS, 2)
 la_state_wide_bf16(TensorArg kt, TensorArg vt, float *__restrict__ ws, float *__restrict__ vsum, int heads, int N,
                    int chunk) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int team = TEAMS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), tid = threadIdx.x & 255, wave = tid >> 6, lane = tid & 63;
+    unsigned char *smem = lds + team * kStateWideTeamLds;
     const int bh = blockIdx.y, b = bh / heads, h = bh % heads, part = blockIdx.x;
     const int BH = gridDim.y;
     const __bf16 *kp = (const __bf16 *)kt.ptr + b * kt.sb + h * kt.sh;
@@ -1247,11 +1308,13 @@ la_state_wide_bf16(TensorArg kt, TensorArg vt, float *__restrict__ ws, float *__
     };
 
     int buf = 0;
-    if (n0 < n1) fetch(n0);
-    for (int t = n0; t < n1; t += 64) {
-        stash(buf);
+    int t = n0 + 64 * team;
+    if (t < n1) fetch(t);
+    for (int t0 = n0; t0 < n1; t0 += 64 * TEAMS, t += 64 * TEAMS) {
+        if (t < n1) stash(buf);
         __syncthreads();
-        if (t + 64 < n1) fetch(t + 64);
+        if (t >= n1) break;  // (the second team, behind its last tile: the loop's last round)
+        if (t + 64 * TEAMS < n1) fetch(t + 64 * TEAMS);
         const unsigned char *ktile = smem + buf * 32768 + qi * 8192;
         const unsigned char *vtile = smem + buf * 32768 + 16384 + qj * 8192;
 #pragma unroll
@@ -1283,62 +1346,134 @@ la_state_wide_bf16(TensorArg kt, TensorArg vt, float *__restrict__ ws, float *__
     }
 
     // St[c2][c1] (c2: channel of V_j, c1: channel of K_i), then z_i[c1]: straight from the registers
-    // (16 KB per wavefront, once per chunk).
-    float *out = ws + ((size_t)part * BH * 4 + (size_t)bh * 4 + wave) * kStateFloats;
-    const int g = lane >> 5, li = lane & 31;
-#pragma unroll
-    for (int mi = 0; mi < 2; ++mi)
+    // (8 KB per wavefront and block of 32 K channels, once per chunk); as pairs where there is one chunk.
+    auto store = [&](auto block_tag) __attribute__((always_inline)) {
+        constexpr int mi = decltype(block_tag)::value;
+        float *out = ws + ((size_t)part * BH * 4 + (size_t)bh * 4 + wave) * kStateFloats;
+        const int g = lane >> 5, li = lane & 31;
 #pragma unroll
         for (int ni = 0; ni < 2; ++ni)
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
-                const int c2 = 32 * ni + li, c1 = 32 * mi + 8 * q4 + 4 * g;
+                const int at = wide_state_at(ni, 2 * mi + q4 / 2, q4 % 2, li, 4 * g);  // c1 = 32 mi + 8 q4 + 4 g .. + 3
                 f32x4 val = {acc[mi][ni][4 * q4], acc[mi][ni][4 * q4 + 1], acc[mi][ni][4 * q4 + 2],
                              acc[mi][ni][4 * q4 + 3]};
-                *(f32x4 *)(out + c2 * kHeadDim + c1) = val;
+                unsigned char *to = (unsigned char *)out + 2 * at;
+                if (gridDim.x == 1) store_pairs(to, to + 2 * kHeadDim * kHeadDim, val);
+                else *(f32x4 *)(out + at) = val;
             }
-#pragma unroll
-    for (int mi = 0; mi < 2; ++mi) {
         float lo, hi;
         pair_values(zacc[mi], &lo, &hi);  // the two halves of the tokens
-        if (g == 0) out[kHeadDim * kHeadDim + 32 * mi + li] = lo + hi;
-    }
-    if (VSUM && qi == 0) {
-#pragma unroll
-        for (int ni = 0; ni < 2; ++ni) {
-            float lo, hi;
-            pair_values(vacc[ni], &lo, &hi);
-            if (g == 0) vsum[((size_t)part * BH + bh) * kHeadDimWide + kHeadDim * qj + 32 * ni + li] = lo + hi;
+        const float z = lo + hi;
+        if (g == 0 && gridDim.x == 1) {
+            __bf16 *to = (__bf16 *)(out + kHeadDim * kHeadDim) + 32 * mi + li;
+            to[0] = (__bf16)z;
+            to[kHeadDim] = (__bf16)(z - (float)(__bf16)z);
+        } else if (g == 0) {
+            out[kHeadDim * kHeadDim + 32 * mi + li] = z;
         }
+        if (VSUM && qi == 0) {
+            pair_values(vacc[mi], &lo, &hi);
+            if (g == 0) vsum[((size_t)part * BH + bh) * kHeadDimWide + kHeadDim * qj + 32 * mi + li] = lo + hi;
+        }
+    };
+    if constexpr (TEAMS == 1) {
+        store(std::integral_constant<int, 0>());
+        store(std::integral_constant<int, 1>());
+    } else {
+        // The other team's sums: this team keeps block `team` of K channels and hands over the other.
+        constexpr int kHandOver = (32 + 1 + 1) * 64 * 4;  // a wavefront's: acc[.][0 .. 1], z, token sums of V
+        static_assert(4 * kHandOver <= kStateWideTeamLds, "");
+        __syncthreads();  // both teams have read their last tiles
+        float *out_sums = (float *)(lds + (team ^ 1) * kStateWideTeamLds + wave * kHandOver) + lane;
+        const float *in_sums = (const float *)(smem + wave * kHandOver) + lane;
+        auto keep = [&](auto mine_tag) __attribute__((always_inline)) {
+            constexpr int mine = decltype(mine_tag)::value, other = 1 - mine;
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) out_sums[64 * (16 * ni + v)] = acc[other][ni][v];
+            out_sums[64 * 32] = zacc[other];
+            out_sums[64 * 33] = vacc[other];
+            __syncthreads();
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[mine][ni][v] += in_sums[64 * (16 * ni + v)];
+            zacc[mine] += in_sums[64 * 32];
+            vacc[mine] += in_sums[64 * 33];
+            store(mine_tag);
+        };
+        if (team == 0) keep(std::integral_constant<int, 0>());
+        else keep(std::integral_constant<int, 1>());
     }
+}
+
+// Sum of the partial states of wide heads, as pairs.  Sixteen partials in flight: the sum of 32 is two round trips (7.7 -> 4.7 us for
+// half as many of 8 heads as with eight in flight).  grid (quadrants, ceil(kStateFloats / 256)), 64 threads.
+__global__ void __launch_bounds__(64)
+la_combine_wide(const float *__restrict__ ws, unsigned char *__restrict__ dst, int n_split, int quadrants) {
+    const int e4 = blockIdx.y * 64 + threadIdx.x;  // 16-byte piece of a state
+    constexpr int kVec = kStateFloats / 4, kZ = kHeadDim * kHeadDim;
+    if (e4 >= kVec) return;
+    const f32x4 *src = (const f32x4 *)ws + (size_t)blockIdx.x * kVec + e4;
+    const size_t stride4 = (size_t)quadrants * kVec;
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    for (int p0 = 0; p0 < n_split; p0 += 16) {
+        f32x4 part[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+            part[i] = p0 + i < n_split ? src[(size_t)(p0 + i) * stride4] : zero;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sum += part[i];
+    }
+    const int e = 4 * e4;
+    unsigned char *to = dst + (size_t)blockIdx.x * (kStateFloats * 4) + (e < kZ ? 2 * e : 4 * kZ + 2 * (e - kZ));
+    store_pairs(to, to + (e < kZ ? 2 * kZ : 2 * kHeadDim), sum);
 }
 
 LinearPlan plan_linear_wide(int B, int heads, int N) {
     LinearPlan p = plan_linear(B, heads, N);
+    // Several chunks: workgroups of two teams, one per compute unit, at least 256 tokens each, where those are fewer than
+    // plan_linear has, whose states size the workspace.
+    if (p.n_split > 1) {
+        const long long bh = (long long)B * heads;
+        long long want = (256 + bh - 1) / bh, most = (N + 255) / 256;
+        want = want < most ? want : most;
+        want = want < 64 ? want : 64;
+        p.chunk = (int)(((N + want - 1) / want + 255) / 256 * 256);
+        p.n_split = (N + p.chunk - 1) / p.chunk;
+    }
     p.combine = p.n_split > 1;  // the apply pass reads one state per quadrant
     // (the token chunks of the apply pass follow from B * heads as in plan_linear; every workgroup
     // loads its head's state once, 64 KB)
     return p;
 }
 size_t linear_wide_workspace_floats(int B, int heads, int N) {
-    return linear_workspace_floats(plan_linear_wide(B, heads, N), B, 4 * heads);
+    LinearPlan p = plan_linear(B, heads, N);
+    p.combine = p.n_split > 1;
+    return linear_workspace_floats(p, B, 4 * heads);
 }
-
 jv_status linear_wide_state(const Problem &pr, float *ws, float *vsum, hipStream_t stream) {
     if (4ll * pr.B * pr.heads > 65535) return fail(JV_ERR_UNSUPPORTED, "head_dim 128: batch * heads above 16383");
-    static LdsLimit lds_limit[2];
-    jv_status st = ensure_lds_limit(lds_limit[0], (const void *)la_state_wide_bf16<false>, kStateWideLds);
-    if (st == JV_OK) st = ensure_lds_limit(lds_limit[1], (const void *)la_state_wide_bf16<true>, kStateWideLds);
-    if (st != JV_OK) return st;
     const LinearPlan plan = plan_linear_wide(pr.B, pr.heads, pr.N);
-    const dim3 grid(plan.n_split, (unsigned)(pr.B * pr.heads));
-    if (vsum)
-        hipLaunchKernelGGL(la_state_wide_bf16<true>, grid, dim3(256), kStateWideLds, stream, pr.k, pr.v, ws, vsum,
-                           pr.heads, pr.N, plan.chunk);
-    else
-        hipLaunchKernelGGL(la_state_wide_bf16<false>, grid, dim3(256), kStateWideLds, stream, pr.k, pr.v, ws,
-                           (float *)nullptr, pr.heads, pr.N, plan.chunk);
-    return launch_status("la_state_wide_bf16");
+    auto launch = [&](auto vsum_tag, auto teams_tag) {
+        constexpr bool VSUM = decltype(vsum_tag)::value;
+        constexpr int TEAMS = decltype(teams_tag)::value;
+        static LdsLimit lds_limit;
+        const jv_status st = ensure_lds_limit(lds_limit, (const void *)la_state_wide_bf16<VSUM, TEAMS>, TEAMS * kStateWideTeamLds);
+        if (st != JV_OK) return st;
+        hipLaunchKernelGGL((la_state_wide_bf16<VSUM, TEAMS>), dim3(plan.n_split, (unsigned)(pr.B * pr.heads)), dim3(256 * TEAMS),
+                           TEAMS * kStateWideTeamLds, stream, pr.k, pr.v, ws, vsum, pr.heads, pr.N, plan.chunk);
+        return launch_status("la_state_wide_bf16");
+    };
+    const std::integral_constant<int, 1> one;
+    const std::integral_constant<int, 2> two;
+    const bool teams = plan_linear(pr.B, pr.heads, pr.N).n_split > plan.n_split;  // (where they leave fewer states)
+    if (vsum) return teams ? launch(std::true_type(), two) : launch(std::true_type(), one);
+    return teams ? launch(std::false_type(), two) : launch(std::false_type(), one);
 }
 
 jv_status linear_wide_apply(const Problem &pr, float eps, float *ws, hipStream_t stream, int ksize, const DwcArg *cv) {
@@ -1348,9 +1483,9 @@ jv_status linear_wide_apply(const Problem &pr, float eps, float *ws, hipStream_t
     const float *states = ws;
     if (plan.combine) {
         float *dst = ws + (size_t)plan.n_split * BHv * kStateFloats;
-        hipLaunchKernelGGL(la_combine, dim3((unsigned)BHv, ((kStateFloats + kHeadDim) / 4 + 255) / 256), dim3(256), 0,
-                           stream, ws, dst, (float *)nullptr, plan.n_split, (int)BHv, 0);
-        if ((st = launch_status("la_combine")) != JV_OK) return st;
+        hipLaunchKernelGGL(la_combine_wide, dim3((unsigned)BHv, (kStateFloats + 255) / 256), dim3(64), 0, stream, ws, (unsigned char *)dst,
+                           plan.n_split, (int)BHv);
+        if ((st = launch_status("la_combine_wide")) != JV_OK) return st;
         states = dst;
     }
     const int n_chunks = (pr.N + plan.apply_tokens - 1) / plan.apply_tokens;

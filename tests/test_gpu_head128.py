@@ -251,6 +251,33 @@ def test_linear_block_static_and_squeeze_dynamic(B, heads, H, W, P, ksize):
     check_bf16_pair(block(torch.float32, squeeze=dev(*sq)), block(torch.bfloat16, squeeze=dev(*sq)), ref)
 
 
+# (B, heads, tokens): one chunk of one team of wavefronts (1 to 256 tokens); one chunk of two teams, 5 and 6 tiles of 64, the last one with 1 and
+# 10 tokens; chunks of two teams, the last one with 1, 64, 65 and 76 tokens; as many chunks of one team; apply ranges of 1 to 8 tiles
+CHUNKS = [(1, 2, 1), (1, 2, 63), (1, 3, 65), (2, 2, 256), (64, 4, 257), (64, 4, 330), (64, 4, 512), (8, 8, 1025), (8, 8, 1088), (8, 8, 1089), (8, 8, 1100),
+          (1, 2, 300), (1, 3, 1000), (4, 8, 4096)]
+
+
+@pytest.mark.parametrize("B,heads,N", CHUNKS)
+@pytest.mark.parametrize("fused", [False, True])
+def test_linear_attention_chunks_of_wide_heads(B, heads, N, fused):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    if fused:
+        qkv = torch.randn(B, N, 3, heads, 128, generator=g, device="cuda").to(torch.bfloat16)
+        q, k, v = (qkv[:, :, i].permute(0, 2, 1, 3) for i in range(3))
+    else:
+        q, k, v = (torch.randn(B, heads, N, 128, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    o = torch.full((B, heads, N, 128), float("nan"), device="cuda")
+    binding.jv_linear_attn_fwd(q, k, v, o, (1, N), 1e-6)
+    q64, k64 = q.double().clamp_min(0), k.double().clamp_min(0)
+    ref = q64 @ (k64.transpose(-1, -2).contiguous() @ v.double()) / ((q64 * k64.sum(2, keepdim=True)).sum(-1, keepdim=True) + 1e-6)
+    # state and normaliser as two bf16 numbers: 2^-17 of a number, at random in sums of 128
+    check(float((o.double() - ref).norm() / ref.norm()), 2.0 ** -17)
+    o16 = torch.empty_like(o, dtype=torch.bfloat16)
+    binding.jv_linear_attn_fwd(q, k, v, o16, (1, N), 1e-6)
+    assert torch.equal(o16, o.to(torch.bfloat16))
+
+
 def test_linear_block_variants_refused_for_wide_heads():
     """The focused map and token-wise filters are built for 64-channel heads."""
     B, heads, H, W = 1, 1, 4, 4
