@@ -284,6 +284,86 @@ __device__ inline void sum_states(const float *states, int n_part, long long par
     }
 }
 
+// What the kernels that apply a state share.  A operands: S^T rows c2 = 32 mi + li, k-slots c1 = 16 ks + 8 g + (0..7), as bf16 high + low
+// parts; the denominator block: row 0 = z high part, row 1 = z low part, other rows zero.
+struct ApplyOperands {
+    bf16x8 s_hi[2][4], s_lo[2][4], z_op[4];
+};
+__device__ inline void apply_operands(ApplyOperands &o, const float *St, const float *zs, int li, int g) {
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const int c2 = 32 * mi + li, grp = 2 * ks + g;
+            const float *row = St + c2 * 64 + ((grp ^ (c2 & 7)) << 3);
+            const f32x4 x0 = *(const f32x4 *)row, x1 = *(const f32x4 *)(row + 4);
+            const float x[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const __bf16 hi = (__bf16)x[e];
+                o.s_hi[mi][ks][e] = hi;
+                o.s_lo[mi][ks][e] = (__bf16)(x[e] - (float)hi);
+            }
+        }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float zv = zs[16 * ks + 8 * g + e];
+            const __bf16 hi = (__bf16)zv;
+            const __bf16 lo = (__bf16)(zv - (float)hi);
+            o.z_op[ks][e] = li == 0 ? hi : (li == 1 ? lo : (__bf16)0.f);
+        }
+}
+// acc = S^T relu(q)^T for the query in row `row` of qtile (tile_off_row); returns 1 / (denominator + eps).
+__device__ inline float apply_products(const ApplyOperands &o, const unsigned char *qtile, int row, int g, float eps, f32x16 (&acc)[2]) {
+    f32x16 accz;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) { acc[0][v] = 0.f; acc[1][v] = 0.f; accz[v] = 0.f; }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        const bf16x8 qb = as_bf16x8(*(const u32x4 *)(qtile + tile_off_row(row, 2 * ks + g)));
+        accz = mfma32(o.z_op[ks], qb, accz);
+#pragma unroll
+        for (int mi = 0; mi < 2; ++mi) {
+            acc[mi] = mfma32(o.s_lo[mi][ks], qb, acc[mi]);
+            acc[mi] = mfma32(o.s_hi[mi][ks], qb, acc[mi]);
+        }
+    }
+    // den lives in rows 0 and 1 of the denominator block: registers 0, 1 of lanes g = 0.
+    float den_lo, den_hi;
+    pair_values(accz[0] + accz[1], &den_lo, &den_hi);
+    return __builtin_amdgcn_rcpf(den_lo + eps);
+}
+// 32 tokens from n0 on, those below n1, through 4 KB of LDS of the wavefront's own: whole rows.
+__device__ inline void apply_store_bf16(const f32x16 (&acc)[2], float inv, unsigned char *otile, __bf16 *op, long long sn, int n0, int n1, int lane) {
+    const int g = lane >> 5, li = lane & 31, lrow = lane >> 3, lchunk = lane & 7;
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const u32x2 pk = {pack_bf16x2(acc[mi][4 * q4] * inv, acc[mi][4 * q4 + 1] * inv),
+                              pack_bf16x2(acc[mi][4 * q4 + 2] * inv, acc[mi][4 * q4 + 3] * inv)};
+            *(u32x2 *)(otile + tile_off_row(li, 4 * mi + q4) + 8 * g) = pk;
+        }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int orow = r * 8 + lrow, on = n0 + orow;
+        const u32x4 val = *(const u32x4 *)(otile + tile_off_row(orow, lchunk));
+        if (on < n1) st_stream((u32x4 *)(op + (long long)on * sn + lchunk * 8), val);
+    }
+}
+__device__ inline void apply_store_f32(const f32x16 (&acc)[2], float inv, float *op, long long sn, int n, int n1, int g) {
+    if (n >= n1) return;
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const f32x4 val = {acc[mi][4 * q4] * inv, acc[mi][4 * q4 + 1] * inv, acc[mi][4 * q4 + 2] * inv, acc[mi][4 * q4 + 3] * inv};
+            *(f32x4 *)(op + (long long)n * sn + 32 * mi + 8 * q4 + 4 * g) = val;
+        }
+}
+
 // grid (8 * ceil(n_chunks * B*heads / 8)), 256 threads.  Workgroups are dealt to the eight XCDs
 // in turn; the index is remapped so that the workgroups one XCD receives walk (batch, head)
 // pairs chunk by chunk: the token chunks of a pair then share that XCD's L2 copy of the state.
@@ -336,33 +416,8 @@ la_apply_bf16(TensorArg qt, TensorArg ot, const float *__restrict__ states, int 
     sum_states(states + (size_t)bh * kStateFloats, n_part, part_stride, St, zs, tid);
     __syncthreads();
 
-    // A operands: S^T rows c2 = 32*mi + li, k-slots c1 = 16*ks + 8g + (0..7), as bf16 hi + lo.
-    bf16x8 s_hi[2][4], s_lo[2][4], z_op[4];
-#pragma unroll
-    for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const int c2 = 32 * mi + li, grp = 2 * ks + g;
-            const float *row = St + c2 * 64 + ((grp ^ (c2 & 7)) << 3);
-            f32x4 x0 = *(const f32x4 *)row, x1 = *(const f32x4 *)(row + 4);
-            float x[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                __bf16 hi = (__bf16)x[e];
-                s_hi[mi][ks][e] = hi;
-                s_lo[mi][ks][e] = (__bf16)(x[e] - (float)hi);
-            }
-        }
-    // Denominator block: row 0 = z high part, row 1 = z low part, other rows zero.
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float zv = zs[16 * ks + 8 * g + e];
-            const __bf16 hi = (__bf16)zv;
-            const __bf16 lo = (__bf16)(zv - (float)hi);
-            z_op[ks][e] = li == 0 ? hi : (li == 1 ? lo : (__bf16)0.f);
-        }
+    ApplyOperands ops;
+    apply_operands(ops, St, zs, li, g);
     __syncthreads();  // the state bytes are reused as output staging from here on
 
     unsigned char *qtile = smem + kStageBytes + wave * 8192;
@@ -377,24 +432,8 @@ la_apply_bf16(TensorArg qt, TensorArg ot, const float *__restrict__ states, int 
         for (int nt = 0; nt < 2; ++nt) {
             if (t + 32 * nt >= n1) break;  // wave-uniform
             const int row = 32 * nt + li;
-            f32x16 acc[2], accz;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) { acc[0][v] = 0.f; acc[1][v] = 0.f; accz[v] = 0.f; }
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const bf16x8 qb = as_bf16x8(*(const u32x4 *)(qtile + tile_off_row(row, 2 * ks + g)));
-                accz = mfma32(z_op[ks], qb, accz);
-#pragma unroll
-                for (int mi = 0; mi < 2; ++mi) {
-                    acc[mi] = mfma32(s_lo[mi][ks], qb, acc[mi]);
-                    acc[mi] = mfma32(s_hi[mi][ks], qb, acc[mi]);
-                }
-            }
-            // den lives in rows 0 and 1 of the denominator block: registers 0, 1 of lanes g = 0.
-            float den_lo, den_hi;
-            pair_values(accz[0] + accz[1], &den_lo, &den_hi);
-            const float inv = __builtin_amdgcn_rcpf(den_lo + eps);
-            const int n = t + row;
+            f32x16 acc[2];
+            const float inv = apply_products(ops, qtile, row, g, eps, acc);
             if (KS) {
                 // fp32 staging: 256-byte token rows, 16-byte chunk index rotated by the row
 #pragma unroll
@@ -482,35 +521,147 @@ la_apply_bf16(TensorArg qt, TensorArg ot, const float *__restrict__ states, int 
                     }
                 }
             } else if (O_BF16) {
-#pragma unroll
-                for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-                    for (int q4 = 0; q4 < 4; ++q4) {
-                        u32x2 pk = {pack_bf16x2(acc[mi][4 * q4] * inv, acc[mi][4 * q4 + 1] * inv),
-                                    pack_bf16x2(acc[mi][4 * q4 + 2] * inv, acc[mi][4 * q4 + 3] * inv)};
-                        *(u32x2 *)(otile + tile_off_row(li, 4 * mi + q4) + 8 * g) = pk;
-                    }
-                __bf16 *op = (__bf16 *)ot.ptr + b * ot.sb + h * ot.sh;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int orow = r * 8 + lrow, on = t + 32 * nt + orow;
-                    const u32x4 val = *(const u32x4 *)(otile + tile_off_row(orow, lchunk));
-                    if (on < n1) st_stream((u32x4 *)(op + (long long)on * ot.sn + lchunk * 8), val);
-                }
+                apply_store_bf16(acc, inv, otile, (__bf16 *)ot.ptr + b * ot.sb + h * ot.sh, ot.sn, t + 32 * nt, n1, lane);
             } else {
-                float *op = (float *)ot.ptr + b * ot.sb + h * ot.sh;
-                if (n < n1) {
-#pragma unroll
-                    for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-                        for (int q4 = 0; q4 < 4; ++q4) {
-                            f32x4 val = {acc[mi][4 * q4] * inv, acc[mi][4 * q4 + 1] * inv,
-                                         acc[mi][4 * q4 + 2] * inv, acc[mi][4 * q4 + 3] * inv};
-                            *(f32x4 *)(op + (long long)n * ot.sn + 32 * mi + 8 * q4 + 4 * g) = val;
-                        }
-                }
+                apply_store_f32(acc, inv, (float *)ot.ptr + b * ot.sb + h * ot.sh, ot.sn, t + row, n1, g);
             }
         }
+    }
+}
+
+// ---------------------------------------------------------------------------------------
+// Both passes in one launch, for launches whose state pass would leave the chip idle: a workgroup forms the whole state of a (batch, head), as
+// la_state_bf16 does, and applies it to a part of its queries, as la_apply_bf16 does, so that no workgroup waits for
+// another's sums.  Bound by round trips to memory (one and a half instead of the three or four of two or three launches) and by
+// what one unit takes in: K and V of a (batch, head), once for every part of its queries, whose workgroups run on one XCD and share its L2.
+// Eight wavefronts take tiles of 64 tokens in turn for the state, then units of 32 queries.
+// grid (8 * ceil(n_wg / 8)), n_wg = parts * B*heads, part fastest; 512 threads, kFusedLds bytes of dynamic LDS.
+// ---------------------------------------------------------------------------------------
+constexpr int kFusedWaves = 8;
+constexpr int kFusedZ = kFusedWaves * kWaveLds, kFusedSt = kFusedZ + 2 * kFusedWaves * kHeadDim * 4, kFusedLds = kFusedSt + kStateFloats * 4;
+
+template <bool O_BF16>
+__global__ void __launch_bounds__(64 * kFusedWaves, 1)
+la_fused_bf16(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, int heads, int N, int units_per_wg, int n_parts, int n_wg, float eps) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 5, li = lane & 31;
+    const int per_xcd = (n_wg + 7) / 8, wg = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (wg >= n_wg) return;  // whole workgroup
+    const int bh = wg / n_parts, b = bh / heads, h = bh % heads;
+    const __bf16 *qp = (const __bf16 *)qt.ptr + b * qt.sb + h * qt.sh;
+    const __bf16 *kp = (const __bf16 *)kt.ptr + b * kt.sb + h * kt.sh;
+    const __bf16 *vp = (const __bf16 *)vt.ptr + b * vt.sb + h * vt.sh;
+    const int lrow = lane >> 3, lchunk = lane & 7;
+    unsigned char *ktile = smem + wave * kWaveLds, *vtile = ktile + 8192;
+
+    u32x4 kreg[8], vreg[8], qreg[4];
+    auto fetch = [&](int t0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const int n = t0 + r * 8 + lrow;
+            u32x4 zero = {0u, 0u, 0u, 0u};
+            kreg[r] = vreg[r] = zero;
+            if (n < N) {
+                kreg[r] = *(const u32x4 *)(kp + (long long)n * kt.sn + lchunk * 8);
+                vreg[r] = *(const u32x4 *)(vp + (long long)n * vt.sn + lchunk * 8);
+            }
+        }
+    };
+    auto fetch_q = [&](int unit) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int n = 32 * unit + r * 8 + lrow;
+            u32x4 zero = {0u, 0u, 0u, 0u};
+            qreg[r] = zero;
+            if (n < N) qreg[r] = ld_stream((const u32x4 *)(qp + (long long)n * qt.sn + lchunk * 8));
+        }
+    };
+    const int unit0 = (wg % n_parts) * units_per_wg, unit1 = min((N + 31) / 32, unit0 + units_per_wg);
+    int t = wave * 64, unit = unit0 + wave;
+    if (t < N) fetch(t);
+    if (unit < unit1) fetch_q(unit);
+
+    f32x16 acc[2][2];
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
+    float zacc[2] = {0.f, 0.f};
+    for (; t < N; t += 64 * kFusedWaves) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const unsigned off = tile_off_tr(r * 8 + lrow, lchunk);
+            *(u32x4 *)(ktile + off) = relu_bf16x8(kreg[r]);
+            *(u32x4 *)(vtile + off) = vreg[r];
+        }
+        if (t + 64 * kFusedWaves < N) fetch(t + 64 * kFusedWaves);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            bf16x8 a[2], bv[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                a[i] = load_tr_operand(ktile, 16 * ks, i, lane);
+                bv[i] = load_tr_operand(vtile, 16 * ks, i, lane);
+            }
+#pragma unroll
+            for (int mi = 0; mi < 2; ++mi) {
+                const u32x4 au = as_u32x4(a[mi]);
+#pragma unroll
+                for (int w = 0; w < 4; ++w) zacc[mi] = add_bf16x2(au[w], zacc[mi]);
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = mfma32(a[mi], bv[ni], acc[mi][ni]);
+            }
+        }
+    }
+
+    // Cross-wave sum through LDS, in a fixed order, into St[c2][c1] with the 8-float group index rotated by the row, then z.
+    __syncthreads();
+    float *mine = (float *)(smem + wave * kWaveLds), *zbuf = (float *)(smem + kFusedZ), *St = (float *)(smem + kFusedSt), *zs = St + kHeadDim * kHeadDim;
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const int c2 = 32 * ni + li, c1 = 32 * mi + 8 * q4 + 4 * g;
+                const f32x4 val = {acc[mi][ni][4 * q4], acc[mi][ni][4 * q4 + 1], acc[mi][ni][4 * q4 + 2], acc[mi][ni][4 * q4 + 3]};
+                *(f32x4 *)(mine + c2 * 68 + c1) = val;
+            }
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi) zbuf[(wave * 2 + g) * kHeadDim + 32 * mi + li] = zacc[mi];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int e4 = tid + 512 * i, c2 = e4 >> 4, c1 = (e4 & 15) * 4;
+        f32x4 s[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            s[w] = *(const f32x4 *)((const float *)(smem + w * kWaveLds) + c2 * 68 + c1) + *(const f32x4 *)((const float *)(smem + (w + 4) * kWaveLds) + c2 * 68 + c1);
+        *(f32x4 *)(St + c2 * 64 + ((((c1 >> 3) ^ (c2 & 7)) << 3) | (c1 & 7))) = (s[0] + s[1]) + (s[2] + s[3]);
+    }
+    if (tid < kHeadDim) {
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < 2 * kFusedWaves; ++w) s += zbuf[w * kHeadDim + tid];
+        zs[tid] = s;
+    }
+    __syncthreads();
+    if (unit >= unit1) return;
+
+    ApplyOperands ops;
+    apply_operands(ops, St, zs, li, g);
+    unsigned char *qtile = smem + wave * kWaveLds, *otile = qtile + 4096;  // (the sums there have been read)
+    for (; unit < unit1; unit += kFusedWaves) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) *(u32x4 *)(qtile + tile_off_row(r * 8 + lrow, lchunk)) = relu_bf16x8(qreg[r]);
+        if (unit + kFusedWaves < unit1) fetch_q(unit + kFusedWaves);
+        f32x16 out[2];
+        const float inv = apply_products(ops, qtile, li, g, eps, out);
+        const int n0 = 32 * unit;
+        if (O_BF16) apply_store_bf16(out, inv, otile, (__bf16 *)ot.ptr + b * ot.sb + h * ot.sh, ot.sn, n0, N, lane);
+        else apply_store_f32(out, inv, (float *)ot.ptr + b * ot.sb + h * ot.sh, ot.sn, n0 + li, N, g);
     }
 }
 
@@ -831,6 +982,16 @@ jv_status linear_bf16(const Problem &pr, const LinearPlan &plan, float eps, floa
     if (st == JV_OK) st = ensure_lds_limit(lds_limit[2], (const void *)la_state_bf16<true, true>, kStateLds);
     if (st != JV_OK) return st;
     const int BH = pr.B * pr.heads;
+    if (dwc.mode == JV_DWC_NONE && focus_p == 1 && linear_bf16_in_one(BH, pr.N)) {
+        static LdsLimit one_limit[2];
+        st = ensure_lds_limit(one_limit[pr.o_bf16], pr.o_bf16 ? (const void *)la_fused_bf16<true> : (const void *)la_fused_bf16<false>, kFusedLds);
+        if (st != JV_OK) return st;
+        const int units = (pr.N + 31) / 32, most = linear_bf16_parts(BH), per = (units + most - 1) / most, parts = (units + per - 1) / per;
+        const auto kernel = pr.o_bf16 ? la_fused_bf16<true> : la_fused_bf16<false>;
+        hipLaunchKernelGGL(kernel, dim3(8 * ((parts * BH + 7) / 8)), dim3(64 * kFusedWaves), kFusedLds, stream, pr.q, pr.k, pr.v, pr.o, pr.heads,
+                           pr.N, per, parts, parts * BH, eps);
+        return launch_status("la_fused_bf16");
+    }
     const bool dynamic = dwc.mode == JV_DWC_SQUEEZE_DYNAMIC;
     if (dynamic)
         hipLaunchKernelGGL((la_state_bf16<true, true>), dim3(8 * ((plan.n_split * BH + 7) / 8)), dim3(256), kStateLds, stream,

@@ -55,6 +55,19 @@ constexpr bool linear_f32_in_one(int bh, int N) {
     return N <= (bh <= 8 ? 1024 : bh <= 24 ? 800 : bh <= 56 ? 1400 : bh <= 64 ? 2400 : 0);
 }
 
+// bf16 linear attention of 64-channel heads, both passes in one launch (la_fused_bf16, one workgroup a unit): its workgroups, one for each
+// of linear_bf16_parts parts of a (batch, head)'s queries, form the state again, which pays while they fit the chip once and what a unit takes in
+// stands behind two or three launches' round trips; the more (batch, head)s, the fewer parts and the longer it does.  Beyond 256 of them, where
+// the last round of workgroups is more than half full and the others neither all start nor all memory.  Two or three launches / one, us: 6 (batch, head)s of 196 tokens
+// 10.1 / 6.9, of 1 374 13.7 / 11.3, of 2 304 14.3 / 14.9; 16 of 2 304 14.6 / 16.3; 24 of 1 374 14.3 / 13.4; 40 of 3 000 27.4 / 23.9, of 3 600 27.2 / 27.8; 64 of 784 13.5 / 12.4, of 1 374
+// 20.5 / 16.0, of 4 096 33.1 / 33.2; 128 of 400 13.6 / 11.1, of 4 096 54.6 / 54.1, of 9 216 114 / 119; 256 of 784 29.3 / 22.2, of 5 184 129 / 133; 300 of 196 16.2 / 19.0;
+// 384 of 400 29.1 / 25.3, 512 of 196 19.7 / 20.6, of 600 38.3 / 34.8, 640 of 1 374 99 / 94, 1 024 of 400 52 / 56.
+constexpr int linear_bf16_parts(int bh) { return bh > 256 ? 1 : 256 / bh; }
+constexpr bool linear_bf16_in_one(int bh, int N) {
+    if (bh > 256) return bh <= 768 && 100 * bh > 62 * 256 * ((bh + 255) / 256) && N >= 300 && N <= 1400;
+    return N <= (bh < 40 ? 1900 : bh < 64 ? 3300 : 4096);
+}
+
 // bf16 attention over whole grid rows (attn_ring_bf16): blocks of 32 queries per wavefront, two or (the same bits) one, for
 // `queries` query slots in each of `lanes` windows times (batch, head)s.  Two workgroups of 256 queries on a compute unit
 // do the most per second, but three of 128 come close, and the smaller blocks leave fewer units with less than

@@ -7,6 +7,7 @@ import subprocess
 import pytest
 
 import test_gpu_bf16_attn
+import test_gpu_bf16_linear
 import test_gpu_fp32
 import test_gpu_linear_block
 
@@ -141,3 +142,15 @@ def test_linear_attention_in_one_launch(rule):
     assert all(1 <= p <= 8 and 4 * p * bh <= 256 for bh, p in enumerate(parts, 1))
     one = rule([f"linear_f32_in_one({b * h}, {n})" for b, h, n, _ in test_gpu_fp32.ONE_LAUNCH])
     assert one == [0 if (b * h, n) in ((8, 1025), (24, 801), (65, 100)) else 1 for b, h, n, _ in test_gpu_fp32.ONE_LAUNCH]
+
+
+def test_bf16_linear_attention_in_one_launch(rule):
+    """As above for bf16: limits, parts, and the GPU test on both sides."""
+    limits = {1: 1900, 39: 1900, 40: 3300, 63: 3300, 64: 4096, 256: 4096, 320: 1400, 512: 1400, 768: 1400}
+    assert rule([f"linear_bf16_in_one({bh}, {n}) + 2 * linear_bf16_in_one({bh}, {n} + 1)" for bh, n in limits.items()]) == [1] * len(limits)
+    assert rule([f"linear_bf16_in_one({bh}, {n})" for bh, n in ((257, 577), (317, 577), (318, 299), (318, 577), (520, 577), (769, 577), (65535, 400), (256, 1 << 24))]) == [0, 0, 0, 1, 1, 0, 0, 0]
+    parts = rule([f"linear_bf16_parts({bh})" for bh in (*range(1, 257), 257, 65535)])
+    assert all(p == (256 // bh if bh <= 256 else 1) for bh, p in zip((*range(1, 257), 257, 65535), parts))
+    one = rule([f"linear_bf16_in_one({b * h}, {n})" for b, h, n, _ in test_gpu_bf16_linear.ONE_LAUNCH])
+    two = ((39, 1901), (40, 3301), (128, 4097), (272, 577), (320, 299), (320, 1401))
+    assert one == [0 if (b * h, n) in two else 1 for b, h, n, _ in test_gpu_bf16_linear.ONE_LAUNCH]

@@ -84,3 +84,31 @@ def test_all_negative_queries_give_exact_zero_bf16():
     q, k, v = synth.qkv(22, B, heads, H * W, 64, 1.0, True)
     o = _run(-np.abs(q), k, v, H, W)
     assert torch.count_nonzero(o.float()).item() == 0
+
+
+# (B, heads, tokens, fused projection): tiles of 64 tokens of eight wavefronts (one tile, one round, one more), units of 32 queries and parts of them
+# (42, 256, 4, 2, 1 a (batch, head); fewer where units run out; ragged last ones); either side of each limit of linear_bf16_in_one
+ONE_LAUNCH = [(1, 1, 1, False), (1, 3, 31, False), (1, 2, 33, True), (1, 6, 64, False), (2, 3, 65, True), (1, 6, 511, False), (1, 6, 512, False),
+              (1, 12, 513, True), (1, 1, 1900, False), (3, 13, 1900, False), (3, 13, 1901, False), (4, 10, 3300, True), (4, 10, 3301, False),
+              (8, 8, 1369, True), (8, 16, 100, False), (8, 16, 4096, False), (8, 16, 4097, False), (16, 16, 577, True), (16, 17, 577, False), (20, 16, 299, False),
+              (20, 16, 300, True), (20, 16, 1400, False), (20, 16, 1401, False), (48, 16, 333, False)]
+
+
+@pytest.mark.parametrize("B,heads,N,fused", ONE_LAUNCH)
+def test_both_passes_in_one_launch(B, heads, N, fused):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    if fused:
+        qkv = torch.randn(B, N, 3, heads, 64, generator=g, device="cuda").to(torch.bfloat16)
+        q, k, v = (qkv[:, :, i].permute(0, 2, 1, 3) for i in range(3))
+        outs = [torch.full((B, N, heads, 64), float("nan"), dtype=dt, device="cuda").permute(0, 2, 1, 3) for dt in (torch.float32, torch.bfloat16)]
+    else:
+        q, k, v = (torch.randn(B, heads, N, 64, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+        outs = [torch.full((B, heads, N, 64), float("nan"), dtype=dt, device="cuda") for dt in (torch.float32, torch.bfloat16)]
+    for o in outs:
+        binding.jv_linear_attn_fwd(q, k, v, o, (1, N), 1e-6)
+    q64, k64 = q.double().clamp_min(0), k.double().clamp_min(0)
+    ref = q64 @ (k64.transpose(-1, -2).contiguous() @ v.double()) / ((q64 * k64.sum(2, keepdim=True)).sum(-1, keepdim=True) + 1e-6)
+    # state and normaliser as two bf16 numbers: 2^-17 of a number, at random in sums of 64
+    check(float((outs[0].double() - ref).norm() / ref.norm()), 2.0 ** -17)
+    assert torch.equal(outs[1], outs[0].to(torch.bfloat16))
