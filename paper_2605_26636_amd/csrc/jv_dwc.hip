@@ -75,6 +75,8 @@ jv_status plan_dwc(const jv_dwc_params *dwc, const LinearPlan &lp, int B, int he
 // Generator, first layer: u[b][j] = silu(b1[j] + sum_c w1[j][c] g[c]),  g = (token sum of V) / N.
 // grid (B, ceil(hidden / 4)), 256 threads, C floats of dynamic LDS; one wavefront per unit j.
 // vsum holds n_part partial sums per (batch, head): [n_part][B*heads][64].
+// Bound by round trips to memory: the unit's weights and bias (up to 2 048 channels in registers) are on their way while the token
+// sums are.
 // ---------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256)
 squeeze_hidden(const float *__restrict__ vsum, int n_part, const float *__restrict__ w1,
@@ -82,6 +84,17 @@ squeeze_hidden(const float *__restrict__ vsum, int n_part, const float *__restri
                float inv_n) {
     extern __shared__ __align__(16) float gmean[];
     const int b = blockIdx.x, BH = gridDim.x * heads, C = heads * kHeadDim;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int j = blockIdx.y * 4 + wave, jr = min(j, hidden - 1);
+    const float *row = w1 + (size_t)jr * C;
+    const float bias = b1[jr];
+    constexpr int kAhead = 8;
+    const bool pieces = (C & 255) == 0;  // 16-byte loads, lane-strided
+    f32x4 ahead[kAhead];
+    if (pieces) {
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) ahead[i] = *(const f32x4 *)(row + min(4 * lane + 256 * i, C - 4));
+    }
     for (int c = threadIdx.x; c < C; c += 256) {
         const float *src = vsum + (size_t)b * heads * kHeadDim + c;
         const size_t stride = (size_t)BH * kHeadDim;
@@ -96,57 +109,36 @@ squeeze_hidden(const float *__restrict__ vsum, int n_part, const float *__restri
         gmean[c] = s * inv_n;
     }
     __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int j = blockIdx.y * 4 + wave;
     if (j >= hidden) return;
-    const float *row = w1 + (size_t)j * C;
     float acc = 0.f;
-    if ((C & 255) == 0) {  // 16-byte loads, lane-strided
-        for (int c = 4 * lane; c < C; c += 256) {
-            const f32x4 wv = *(const f32x4 *)(row + c), gv = *(const f32x4 *)(gmean + c);
+    if (pieces) {
+        auto add = [&](const f32x4 &wv, int c) __attribute__((always_inline)) {
+            const f32x4 gv = *(const f32x4 *)(gmean + c);
             acc = fmaf(wv[0], gv[0], acc);
             acc = fmaf(wv[1], gv[1], acc);
             acc = fmaf(wv[2], gv[2], acc);
             acc = fmaf(wv[3], gv[3], acc);
-        }
+        };
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i)
+            if (256 * i < C) add(ahead[i], 4 * lane + 256 * i);
+        for (int c = 4 * lane + 256 * kAhead; c < C; c += 256) add(*(const f32x4 *)(row + c), c);
     } else {
         for (int c = lane; c < C; c += 64) acc = fmaf(row[c], gmean[c], acc);
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
     if (lane == 0) {
-        const float x = acc + b1[j];
+        const float x = acc + bias;
         u[(size_t)b * hidden + j] = x / (1.0f + __expf(-x));
     }
 }
 
 // Second layer: kappa[b][row] = b2[row] + sum_j w2[row][j] u[b][j], row = channel * k*k + tap.
-// One image: one thread per row.  grid (ceil(rows / 256)), 256 threads, hidden floats of dynamic LDS.
-__global__ void __launch_bounds__(256)
-squeeze_kappa(const float *__restrict__ u, const float *__restrict__ w2,
-              const float *__restrict__ b2, float *__restrict__ kappa, int hidden, int rows) {
-    extern __shared__ __align__(16) float us[];
-    for (int j = threadIdx.x; j < hidden; j += 256) us[j] = u[j];
-    __syncthreads();
-    const int row = blockIdx.x * 256 + threadIdx.x;
-    if (row >= rows) return;
-    const f32x4 *wrow = (const f32x4 *)(w2 + (size_t)row * hidden);
-    float acc = 0.f;
-    for (int j4 = 0; j4 < hidden / 4; ++j4) {
-        const f32x4 w = wrow[j4];
-        const f32x4 x = *(const f32x4 *)(us + 4 * j4);
-        acc = fmaf(w[0], x[0], acc);
-        acc = fmaf(w[1], x[1], acc);
-        acc = fmaf(w[2], x[2], acc);
-        acc = fmaf(w[3], x[3], acc);
-    }
-    kappa[row] = acc + b2[row];
-}
-
-// Several images: a workgroup takes 64 rows of w2 and kKappaImages images, so that w2 (2.4 MB at 1 024
+// A workgroup takes 64 rows of w2 and kKappaImages images, so that w2 (2.4 MB at 1 024
 // channels, 3 x 3, hidden 64) goes through the caches once per group of images instead of once
-// per image, in whole lines, and a thread (one row, two images) reads it from LDS (32 images: 12.4 -> 4.8 us).
-// The sum runs over j in one chain, as above.
+// per image, in whole lines, and a thread (one row, two images) reads it from LDS (32 images: 12.4 -> 4.8 us; one image, against a thread per row
+// that walks it for itself: 4.4 -> 3.3 us).  Bound by the round trip to memory.
 // grid (ceil(rows / 64), ceil(B / kKappaImages)), 256 threads.
 constexpr int kKappaImages = 8, kKappaSlice = 64;
 __global__ void __launch_bounds__(256)
@@ -156,6 +148,7 @@ squeeze_kappa_images(const float *__restrict__ u, const float *__restrict__ w2,
     const int row0 = blockIdx.x * 64, b0 = blockIdx.y * kKappaImages;
     const int row = threadIdx.x & 63, img = threadIdx.x >> 6;
     float acc[2] = {0.f, 0.f};
+    const float bias = b2[min(row0 + row, rows - 1)];
     for (int j0 = 0; j0 < hidden; j0 += kKappaSlice) {
         const int n4 = min(kKappaSlice, hidden - j0) / 4;
         __syncthreads();
@@ -184,7 +177,7 @@ squeeze_kappa_images(const float *__restrict__ u, const float *__restrict__ w2,
     if (row0 + row >= rows) return;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
-        if (b0 + img + 4 * i < B) kappa[(size_t)(b0 + img + 4 * i) * rows + row0 + row] = acc[i] + b2[row0 + row];
+        if (b0 + img + 4 * i < B) kappa[(size_t)(b0 + img + 4 * i) * rows + row0 + row] = acc[i] + bias;
 }
 
 jv_status squeeze_generate(const DwcPlan &dwc, float *ws, int n_part, int B, int heads, int N,
@@ -195,12 +188,8 @@ jv_status squeeze_generate(const DwcPlan &dwc, float *ws, int n_part, int B, int
                        stream, ws + dwc.vsum_off, n_part, dwc.w1, dwc.b1, ws + dwc.hidden_off, heads,
                        dwc.hidden, 1.0f / (float)N);
     if ((st = launch_status("squeeze_hidden")) != JV_OK) return st;
-    if (B == 1)
-        hipLaunchKernelGGL(squeeze_kappa, dim3((rows + 255) / 256), dim3(256), dwc.hidden * sizeof(float), stream,
-                           ws + dwc.hidden_off, dwc.w2, dwc.b2, ws + dwc.kappa_off, dwc.hidden, rows);
-    else
-        hipLaunchKernelGGL(squeeze_kappa_images, dim3((rows + 63) / 64, (B + kKappaImages - 1) / kKappaImages), dim3(256), 0, stream,
-                           ws + dwc.hidden_off, dwc.w2, dwc.b2, ws + dwc.kappa_off, dwc.hidden, rows, B);
+    hipLaunchKernelGGL(squeeze_kappa_images, dim3((rows + 63) / 64, (B + kKappaImages - 1) / kKappaImages), dim3(256), 0, stream,
+                       ws + dwc.hidden_off, dwc.w2, dwc.b2, ws + dwc.kappa_off, dwc.hidden, rows, B);
     return launch_status("squeeze_kappa");
 }
 

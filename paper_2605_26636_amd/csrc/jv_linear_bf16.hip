@@ -215,7 +215,7 @@ la_state_bf16(TensorArg kt, TensorArg vt, float *__restrict__ ws, float *__restr
 
 // grid (B*heads, or 8 * ceil(B*heads / 8) with xcd_ranges; ceil((kStateFloats + 64) / 1024)), 256
 // threads: dst[bh] = sum_p ws[p][bh], one
-// 16-byte piece per thread, the loads of eight partials in flight at a time.  With vsum (the
+// 16-byte piece per thread, the loads of sixteen partials in flight at a time.  With vsum (the
 // partial token sums of V, [n_split][B*heads][64]) the sixteen threads after the state's last
 // piece sum those too, into partial 0 (each element is read and written by one thread).
 __global__ void __launch_bounds__(256)
@@ -231,15 +231,15 @@ la_combine(const float *__restrict__ ws, float *__restrict__ dst, float *vsum, i
                              : (const f32x4 *)vsum + (size_t)bh * kSumVec + (e4 - kStateVec);
     const size_t stride4 = (size_t)BH * (state ? kStateVec : kSumVec);
     f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-    for (int p0 = 0; p0 < n_split; p0 += 8) {
-        f32x4 part[8];
+    for (int p0 = 0; p0 < n_split; p0 += 16) {
+        f32x4 part[16];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < 16; ++i) {
             f32x4 zero = {0.f, 0.f, 0.f, 0.f};
             part[i] = p0 + i < n_split ? src[(size_t)(p0 + i) * stride4] : zero;
         }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) sum += part[i];
+        for (int i = 0; i < 16; ++i) sum += part[i];
     }
     if (state) ((f32x4 *)dst)[(size_t)bh * kStateVec + e4] = sum;
     else ((f32x4 *)vsum)[(size_t)bh * kSumVec + (e4 - kStateVec)] = sum;
