@@ -126,8 +126,7 @@ squeeze_hidden(const float *__restrict__ vsum, int n_part, const float *__restri
     } else {
         for (int c = lane; c < C; c += 64) acc = fmaf(row[c], gmean[c], acc);
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    acc = wave_sum(acc);
     if (lane == 0) {
         const float x = acc + bias;
         u[(size_t)b * hidden + j] = x / (1.0f + __expf(-x));

@@ -166,6 +166,22 @@ __device__ inline void pair_values(float x, float *lo, float *hi) {
     *hi = __builtin_bit_cast(float, (unsigned)s[1]);
 }
 
+// Sum over a wavefront's 64 lanes, in every lane: exchanges with lane ^ 32 and lane ^ 16, then rotations inside rows of 16 lanes (after
+// the exchange with lane ^ 2k a rotation by k brings what lane ^ k holds), none of them through LDS.
+template <int K>
+__device__ inline float add_rotated(float x) {
+    const int r = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + K, 0xf, 0xf, false);
+    return x + __builtin_bit_cast(float, r);
+}
+__device__ inline float wave_sum(float x) {
+    float lo, hi;
+    pair_values(x, &lo, &hi);
+    const unsigned u = __builtin_bit_cast(unsigned, lo + hi);
+    const auto s = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    x = __builtin_bit_cast(float, (unsigned)s[0]) + __builtin_bit_cast(float, (unsigned)s[1]);
+    return add_rotated<1>(add_rotated<2>(add_rotated<4>(add_rotated<8>(x))));
+}
+
 // Tile of 16-bit rows in LDS, 128 bytes (64 channels) per row.  The 64-byte half a 16-byte
 // chunk lands in is flipped from row to row so that the 8 rows one transposing read touches
 // spread over all banks.
