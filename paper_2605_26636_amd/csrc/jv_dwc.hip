@@ -1,7 +1,7 @@
 // The depth-wise convolution branch of the paper's linear-attention block (Sec. 3.2.1, Eq. 4:
 // O = LA(Q, K, V) + DWC(V)) -- the parts that are not fused into the bf16 apply pass:
-//   squeeze_hidden / squeeze_kappa   the generator of the dynamic filters ("Squeeze Dynamic
-//                                    Convolution": token mean of V -> Linear -> SiLU -> Linear)
+//   squeeze_hidden,                  the generator of the dynamic filters ("Squeeze Dynamic
+//   squeeze_kappa_images             Convolution": token mean of V -> Linear -> SiLU -> Linear)
 //   v_sum_f32, dwc_add_f32           plain fp32 kernels for fp32 tensors
 //   cast_to_bf16, reorder_w2,        the token-wise dynamic variant the paper rejects for its cost
 //   pack_v_rows, dwc_token_add       (Tab. 1): the generator as two matrix products over all
@@ -189,7 +189,7 @@ jv_status squeeze_generate(const DwcPlan &dwc, float *ws, int n_part, int B, int
     if ((st = launch_status("squeeze_hidden")) != JV_OK) return st;
     hipLaunchKernelGGL(squeeze_kappa_images, dim3((rows + 63) / 64, (B + kKappaImages - 1) / kKappaImages), dim3(256), 0, stream,
                        ws + dwc.hidden_off, dwc.w2, dwc.b2, ws + dwc.kappa_off, dwc.hidden, rows, B);
-    return launch_status("squeeze_kappa");
+    return launch_status("squeeze_kappa_images");
 }
 
 // ---------------------------------------------------------------------------------------

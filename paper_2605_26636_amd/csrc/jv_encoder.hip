@@ -123,11 +123,11 @@ static void with_row_pieces(int cols, F f) {
 // Are scale and shift held in registers?  Rows of up to 768 columns: always; above 2048: never (more
 // registers than there are).  Between, they take wavefronts: seven fit a SIMD up to 1024 columns, five
 // up to 1280 and four up to 2048, where eight fit without.  fp32 rows: held (65 536 x 1280 to bf16 91 us,
-// read at the end 95; 4 096 x 1024 6.6 / 6.8).  bf16 rows need the rows in flight: held only where that
-// costs no further round of the chip (or, up to 1024 columns, where it is one of many).  Held / read
-// at the end, us: 1 374 x 1280 5.2 / 5.4, 5 120 x 1280 8.2 / 8.5, 5 200 x 1280 10.2 / 8.7, 65 536 x 1280 102 / 87,
-// 8 192 x 2048 23 / 17; 6 144 x 1024 7.7 / 8.0, 8 192 x 1024 10.4 / 9.9, 10 000 x 1024 14.1 / 14.9,
-// 16 384 x 1024 19.8 / 18.6, 32 768 x 1024 35.9 / 37.0.
+// read at the end 95; 4 096 x 1024 6.6 / 6.8, both with the sums still through LDS).  bf16 rows need the rows in flight: held only
+// where that costs no further round of the chip (or, up to 1024 columns, where it is one of many).  Held / read
+// at the end, us: 1 374 x 1280 3.8 / 3.9, 5 120 x 1280 7.7 / 7.8, 8 192 x 1280 14.2 / 11.0, 65 536 x 1280 90 / 85,
+// 8 192 x 2048 23 / 19; 6 144 x 1024 7.2 / 7.3, 8 192 x 1024 8.8 / 8.8, 10 000 x 1024 10.0 / 10.5,
+// 16 384 x 1024 18.9 / 18.5, 32 768 x 1024 34.9 / 35.9.
 static bool layernorm_holds_affine(int pieces, bool in_bf16, long long rows) {
     if (pieces <= 3) return true;
     if (pieces > 8) return false;
