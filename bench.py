@@ -255,7 +255,7 @@ def main():
                 "traffic_source": dict(TRAFFIC_SOURCE),
                 "algorithmic_flops": flops["full"], "avg_launch_ms": per["full"]["ms_avg"]}
     rooflines = {
-        "linear": hbm_roof("linear", "la_state_bf16 + la_apply_bf16"),
+        "linear": hbm_roof("linear", "la_fused_bf16"),
         "block": hbm_roof("block", "la_state_bf16 + squeeze_* + la_apply_bf16 (convolution fused)"),
         "window": hbm_roof("window", "attn_window8_bf16"),
         "full": dict(roofline),
