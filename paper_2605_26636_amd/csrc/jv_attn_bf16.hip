@@ -1967,8 +1967,7 @@ jv_status attn_bf16(const Problem &pr, const WindowGeom &g, float scale, int q_s
         // byte offsets inside a (batch, head) slice: the ring kernel
         const long long wide_sn = pr.k.sn > pr.v.sn ? pr.k.sn : pr.v.sn;
         const bool whole_windows = g.H % g.wh == 0 && g.W % g.ww == 0 && kStageWide % g.ww == 0;
-        if ((a.contig || whole_windows) &&
-            ((long long)pr.N + 2ll * kStageWide * g.W) * wide_sn * 2 + 512 < (1ll << 31)) {
+        if ((a.contig || whole_windows) && wide_offsets_fit(a.contig, pr.N, g.W, wide_sn)) {
             // a few queries against the whole sequence (prefix tokens): the keys cut into chains.  What five prefix
             // tokens add to window attention, us, ring kernel / chains: 1 369 tokens x 8 heads 30 / 8.6, 4 096 x 8
             // 82 / 14.6, x 64 90 / 30, 16 384 x 8 324 / 36 (separate tensors).

@@ -115,10 +115,20 @@ constexpr F32Kernel f32_kernel(int tiles, bool whole_rows, long long blocks, lon
     return f32_keys_staged(tiles, whole_rows, blocks, kv_bytes) ? kF32Short4 : kF32Few;
 }
 
+constexpr int kStage = 64, kStageWide = 32;  // keys of a stage, heads of 64 and of 128 channels
+
+// Wide heads: do 32-bit byte offsets inside a slice of `tokens` tokens, `sn` elements apart, reach every key of the ring kernel
+// (attn_ring_wide_bf16) and of the prefix chains?  Counted two stages past the end: 32 tokens each where windows span whole grid rows, the
+// whole sequence as one row among them; up to 32 rows of the grid of `W` columns where a stage takes a few columns of each.  Views of a
+// fused projection with prefix tokens (the sequence as one row), general kernel / here, us: window attention of 3 x 5 457 tokens
+// x 8 heads 217 / 68, 16 389 x 8 530 / 73; full attention of 5 476 x 8 231 / 135, 2 x 9 549 x 8 1 052 / 722.
+constexpr bool wide_offsets_fit(bool whole_rows, long long tokens, long long W, long long sn) {
+    return (tokens + 2ll * kStageWide * (whole_rows ? 1 : W)) * sn * 2 + 512 < (1ll << 31);
+}
+
 // Prefix tokens: `queries` <= 64 queries against the `keys` tokens of a whole sequence, per (batch, head) (jv_attn_bf16.hip).
 // Keys come in stages; chains of stages run as workgroups of their own whose sums wait in the rows of O
 // behind the queries, kPrefixRows of them for a query of a chain.
-constexpr int kStage = 64, kStageWide = 32;  // keys of a stage, heads of 64 and of 128 channels
 constexpr int kPrefixChains = 8, kPrefixChainsWide = 16, kPrefixRows = 3;
 constexpr bool prefix_rows_fit(int keys, int queries, int chains) { return kPrefixRows * chains * queries <= keys - queries; }
 

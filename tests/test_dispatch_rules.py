@@ -132,6 +132,16 @@ def test_prefix_chains_of_128_channel_heads(rule):
     assert got == [0] * len(ring) + [1] * len(chains)
 
 
+def test_32_bit_offsets_of_wide_heads(rule):
+    """Every key of a slice, and the two stages of 32 tokens (32 grid rows where stages are strided) counted past it, within 2^31 bytes; a whole
+    sequence as one row (W = tokens) counts tokens, not rows; no overflow at the largest arguments."""
+    fits = lambda whole, n, w, sn: (n + 64 * (1 if whole else w)) * sn * 2 + 512 < 1 << 31
+    cases = [(1, 5457, 5457, 3072), (1, 349461, 349461, 3072), (1, 349462, 349462, 3072), (0, 5456, 88, 3072), (0, 300000, 700, 3072),
+             (0, 300000, 800, 3072), (1, 1 << 24, 1 << 24, 63), (1, 1 << 24, 1 << 24, 64), (0, 1 << 24, 1 << 24, 1 << 24)]
+    got = rule([f"wide_offsets_fit({w}, {n}, {W}, {sn})" for w, n, W, sn in cases])
+    assert got == [int(fits(*c)) for c in cases] and got[:3] == [1, 1, 0]
+
+
 def test_linear_attention_in_one_launch(rule):
     """One launch up to the stated token counts, its workgroups (four a part, (batch, head)s in eights) at most one a unit, and the
     GPU test on both sides."""

@@ -141,6 +141,27 @@ def test_fused_projection_layout_and_rerun_bits():
         assert torch.equal(o, first)
 
 
+def test_prefix_in_views_with_wide_token_strides():
+    """Tokens 3 072 elements apart, as in the fused projection of eight heads, and so many of them that 64 times the sequence
+    (the sequence is one row of its geometry) spans more bytes than 32 bits count: the bits of separate tensors, and the
+    oracle's rows.  P = 5 takes the chains, 1 369 tokens the same rule on its other side."""
+    heads, P = 2, 5
+    for H, W in [(64, 85), (37, 37)]:
+        N = P + H * W
+        q, k, v = synth.qkv(71, 1, heads, N, D, 0.125, True)
+        fused = torch.empty(1, N, 3, 8, D, device="cuda", dtype=torch.bfloat16)
+        for i, x in enumerate((q, k, v)):
+            fused[:, :, i, :heads] = to_device(x, True).permute(0, 2, 1, 3)
+        views = [fused[:, :, i, :heads].permute(0, 2, 1, 3) for i in range(3)]
+        o = torch.empty(1, N, heads, D, device="cuda", dtype=torch.bfloat16).permute(0, 2, 1, 3)
+        binding.jv_window_attn_fwd(*views, o, (H, W), (16, 16))
+        assert torch.equal(o, _window(q, k, v, H, W, (16, 16)))
+        binding.jv_full_attn_fwd(*views, o, (H, W))
+        assert torch.equal(o, _full(q, k, v, H, W))
+        rows = synth.sample_rows(1, heads, N, 64, seed=7)
+        check_bf16_pair(_full(q, k, v, H, W, torch.float32), o, oracle.full_attn_rows(q, k, v, rows), rows)
+
+
 def test_vit_layer_size_elementwise():
     """A layer of the benchmark's size with wide heads (batch 8, 64 x 64 grid, 8 heads x 128):
     every element of window and full attention against the oracle."""
