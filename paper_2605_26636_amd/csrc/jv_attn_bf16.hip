@@ -1047,8 +1047,8 @@ __global__ void __launch_bounds__(256, NT == 1 ? 3 : 2) attn_ring_bf16(AttnArgs 
 // ---------------------------------------------------------------------------------------
 // A few queries against a whole sequence: the prefix tokens (at most 64, the first query slots
 // of a one-window geometry whose slot s is token s) attend to all N tokens.  With so few
-// queries the parallelism has to come from the keys: eight chains per (batch, head), chain w taking
-// every eighth stage of 64 keys from stage w on, one wavefront each with all the queries (NT blocks of 32)
+// queries the parallelism has to come from the keys: C chains per (batch, head), chain w taking
+// every C-th stage of 64 keys from stage w on (C = 8, or for SPLIT as prefix_chain_count says), one wavefront each with all the queries (NT blocks of 32)
 // and a running softmax of its own; the partial results are merged in the order of the chains,
 //     O = sum_w acc_w 2^(m_w - M) / sum_w l_w 2^(m_w - M),   M = max_w m_w.
 //
@@ -1057,9 +1057,9 @@ __global__ void __launch_bounds__(256, NT == 1 ? 3 : 2) attn_ring_bf16(AttnArgs 
 // which the window kernels overwrite afterwards (the caller launches them behind this one on the same
 // stream): three rows of 64 elements, 128 bytes of each, for a query of a chain: channels 0 - 31,
 // channels 32 - 63, (m, l).  prefix_combine_bf16 merges them.  Otherwise (launch_prefix) the chains are the
-// wavefronts of one workgroup (grid (1, B*heads), 512 threads) and meet in LDS.  The same bits either way.
+// wavefronts of one workgroup (grid (1, B*heads), 512 threads) and meet in LDS.  The same bits as of eight split chains.
 // The one workgroup is bound by what its compute unit takes in and by the round trips of a stage, one
-// after the other; the chains by those of an eighth of the stages, half of them hidden.
+// after the other; the chains by those of a C-th of the stages, half of them hidden.
 // Dynamic LDS: prefix_lds(SPLIT).  Requirements as attn_ring_bf16.
 // ---------------------------------------------------------------------------------------
 constexpr int prefix_lds(bool split) {
@@ -1116,12 +1116,13 @@ __global__ void __launch_bounds__(SPLIT ? 64 : 512, 1) attn_prefix_bf16(AttnArgs
     };
     int at = 0;  // byte offset of the present stage's tile
     if (SPLIT) issue(chain, 0);  // (a split launch has more stages than chains)
-    for (int st = chain; st < n_stage; st += kPrefixChains) {
+    const int chains = SPLIT ? (int)gridDim.x : kPrefixChains;
+    for (int st = chain; st < n_stage; st += chains) {
         // (the LDS reads of the previous stage have been waited for before the matrix
         // instructions that used them, so its tile may be overwritten)
         if (!SPLIT) issue(st, 0);
-        if (SPLIT && st + kPrefixChains < n_stage) {
-            issue(st + kPrefixChains, kStageBytes - at);
+        if (SPLIT && st + chains < n_stage) {
+            issue(st + chains, kStageBytes - at);
             asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
         } else {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1276,7 +1277,7 @@ __global__ void __launch_bounds__(64) prefix_combine_bf16(AttnArgs a) {
 
 // What five prefix tokens add to window attention, us, one workgroup with two blocks of queries whatever their number / as
 // chosen (prefix_in_chains): in chains 1 369 tokens x 12 heads 14.4 / 8.8, 4 096 x 16 31.8 / 16.6, x 128 37 / 28, 8 192 x 16 54 / 24,
-// 16 384 x 32 101 / 46; in one 1 369 x 512 42.7 / 33.3 (chains 44), 400 x 80 9.0 / 6.5 (8.9), 196 x 256 7.8 / 5.3 (8.9).
+// 16 384 x 32 101 / 46 (with eight chains; prefix_chain_count for more of them); in one 1 369 x 512 42.7 / 33.3 (chains 44), 400 x 80 9.0 / 6.5 (8.9), 196 x 256 7.8 / 5.3 (8.9).
 template <bool O_BF16, int NT>
 static jv_status launch_prefix(const AttnArgs &a, int BH, hipStream_t stream) {
     if (!prefix_in_chains(a.g.slots, a.q_slots, BH)) {
@@ -1286,10 +1287,13 @@ static jv_status launch_prefix(const AttnArgs &a, int BH, hipStream_t stream) {
         hipLaunchKernelGGL((attn_prefix_bf16<O_BF16, NT, false>), dim3(1, BH), dim3(512), prefix_lds(false), stream, a);
         return launch_status("attn_prefix_bf16");
     }
-    hipLaunchKernelGGL((attn_prefix_bf16<O_BF16, NT, true>), dim3(kPrefixChains, BH), dim3(64), prefix_lds(true), stream, a);
+    const int chains = prefix_chain_count(a.g.slots, a.q_slots, BH);
+    hipLaunchKernelGGL((attn_prefix_bf16<O_BF16, NT, true>), dim3(chains, BH), dim3(64), prefix_lds(true), stream, a);
     jv_status st = launch_status("attn_prefix_bf16");
     if (st != JV_OK) return st;
-    hipLaunchKernelGGL((prefix_combine_bf16<O_BF16, kHeadDim, kPrefixChains>), dim3(a.q_slots, BH), dim3(64), 0, stream, a);
+    const auto combine = chains == 32 ? prefix_combine_bf16<O_BF16, kHeadDim, 32> : chains == 16 ? prefix_combine_bf16<O_BF16, kHeadDim, 16> :
+                         prefix_combine_bf16<O_BF16, kHeadDim, kPrefixChains>;
+    hipLaunchKernelGGL(combine, dim3(a.q_slots, BH), dim3(64), 0, stream, a);
     return launch_status("prefix_combine_bf16");
 }
 

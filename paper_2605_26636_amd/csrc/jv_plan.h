@@ -132,7 +132,7 @@ constexpr bool wide_offsets_fit(bool whole_rows, long long tokens, long long W, 
 constexpr int kPrefixChains = 8, kPrefixChainsWide = 16, kPrefixRows = 3;
 constexpr bool prefix_rows_fit(int keys, int queries, int chains) { return kPrefixRows * chains * queries <= keys - queries; }
 
-// Heads of 64 channels: chains as workgroups, or (the same bits) as the wavefronts of one workgroup.  The
+// Heads of 64 channels: chains as workgroups, or (the bits of eight) as the wavefronts of one workgroup.  The
 // chains' loads and sums of a stage overlap, for a second launch and the way of the sums through memory: they pay from two
 // stages a chain on, as long as the launch's eight times as many workgroups fit the chip at once, and with two
 // blocks of queries, which write twice the sums, for fewer (batch, head)s.  One workgroup / chains, window attention included, us,
@@ -143,6 +143,16 @@ constexpr bool prefix_in_chains(int keys, int queries, int bh) {
     const int stages = (keys + kStage - 1) / kStage;
     const int most = queries > 32 ? (stages < 43 ? 3 * stages : 128) : stages < 64 ? 128 : 192;
     return stages >= 2 * kPrefixChains - 1 && bh <= most && prefix_rows_fit(keys, queries, kPrefixChains);
+}
+// How many chains: 8; 16 or 32 where that many workgroups a (batch, head) still leave few to a unit, from about two stages a chain on, since
+// a chain is bound by the round trips of its stages, one after the other, and 4 096 tokens are eight of them for each of 8 chains.  8 chains / as
+// chosen, window attention included, us: 1 token in front of 1 156 tokens x 12 16.4 / 15.6, 5 in front of 1 369 x 12 17.0 / 16.2 (x 32 with 16 chains 18.0),
+// 2 025 x 16 19.3 / 17.3, x 32 23.4 / 22.4 (x 64 30.3 / 32.0), 4 096 x 48 39.8 / 38.4 (x 64 46.4 / 48.6); with 32 4 096 x 16 26.3 / 21.5, x 32 32.4 / 31.2
+// (1 in front of 4 096 x 64 45.8 / 49.8), 1 in front of 9 207 x 12 42.4 / 27.9, 5 of 16 384 x 16 75.8 / 48.0, 64 of 16 384 x 16 99.8 / 56.5.
+constexpr int prefix_chain_count(int keys, int queries, int bh) {
+    const int stages = (keys + kStage - 1) / kStage;
+    if (stages >= 63 && bh <= 32 && prefix_rows_fit(keys, queries, 32)) return 32;
+    return stages >= 18 && bh <= (stages < 31 ? 16 : 48) && prefix_rows_fit(keys, queries, 16) ? 16 : kPrefixChains;
 }
 // Heads of 128 channels: chains, or one workgroup of the ring kernel that walks all keys.  A (batch, head) has a
 // wavefront per chain and block of 32 queries, which fetches the keys once more and writes the sums of its queries: the more

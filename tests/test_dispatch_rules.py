@@ -10,6 +10,7 @@ import test_gpu_bf16_attn
 import test_gpu_bf16_linear
 import test_gpu_fp32
 import test_gpu_linear_block
+import test_gpu_prefix
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2605_26636_amd", "csrc")
@@ -121,6 +122,16 @@ def test_prefix_chains_of_64_channel_heads(rule):
               (33, 1369, 64), (33, 2304, 96), (64, 4096, 128), (64, 1536, 4)]
     got = rule([f"prefix_in_chains({p + n}, {p}, {bh})" for p, n, bh in one + chains])
     assert got == [0] * len(one) + [1] * len(chains)
+
+
+def test_number_of_prefix_chains(rule):
+    """At least as many stages as chains, rows for all their sums, the GPU test's counts (four (batch, head)s) and both sides of every line."""
+    sizes = [(p + h * w, p, 4) for p, h, w, _ in test_gpu_prefix.CHAIN_COUNTS]
+    sizes += [(1374, 5, 16), (1374, 5, 17), (1088, 1, 4), (1985, 1, 48), (1985, 1, 49), (3969, 1, 32), (3969, 1, 33), (3968, 1, 32), (9208, 1, 512)]
+    want = [c for _, _, _, c in test_gpu_prefix.CHAIN_COUNTS] + [16, 8, 8, 16, 8, 32, 16, 16, 8]
+    assert rule([f"prefix_chain_count({k}, {q}, {bh})" for k, q, bh in sizes]) == want
+    for (keys, queries, _), chains in zip(sizes, want):
+        assert (keys + 63) // 64 >= chains and 3 * chains * queries <= keys - queries
 
 
 def test_prefix_chains_of_128_channel_heads(rule):

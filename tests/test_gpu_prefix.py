@@ -119,6 +119,22 @@ def test_prefix_rows_of_split_chains(P, H, W, fused, D):
     check_bf16_pair(outs[0], outs[1], ref)
 
 
+CHAIN_COUNTS = [  # (prefix tokens, grid, chains of a (batch, head))
+    (1, 29, 39, 16),    # 18 stages, one of four keys
+    (1, 32, 34, 16),    # 18 stages, the last of a single key
+    (40, 40, 48, 16),   # just the rows of sixteen chains of 40
+    (41, 40, 48, 8),    # a row too few for 41
+    (1, 64, 62, 32),    # 63 stages, the last of a single key
+    (41, 48, 82, 32),   # just the rows of 32 chains of 41
+    (64, 48, 82, 16),   # too few for 64
+]
+
+
+@pytest.mark.parametrize("P,H,W,chains", CHAIN_COUNTS)
+def test_prefix_rows_of_more_chains(P, H, W, chains):
+    test_prefix_rows_of_split_chains(P, H, W, True, 64)
+
+
 def test_prefix_rows_do_not_disturb_grid_rows_of_window_attention():
     """Grid rows with prefix tokens present are bit-identical to window attention on the grid
     tokens alone (the same kernels on the same rows); the prefix rows are full attention's (a
