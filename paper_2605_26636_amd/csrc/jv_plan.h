@@ -50,9 +50,11 @@ constexpr int apply_rounds(long long bh, int N) {
 // are few.  Two launches / one, us: 6 (batch, head)s of 256 tokens 9.9 / 5.5, of 1 024 13.3 / 12.7, of 1 369 14.8 / 16.2;
 // 16 of 576 13.5 / 9.7, of 784 13.8 / 12.9, of 1 024 14.6 / 14.7; 24 of 784 15.3 / 14.6, of 1 024 16.6 / 16.9; 32 of 1 369 23.0 / 21.5,
 // of 2 304 30.6 / 32.9; 48 of 1 369 34.4 / 27.7, of 2 304 47.6 / 46.3; 64 of 256 12.9 / 8.7, of 2 304 55.8 / 48.5; 80 of 576 25.2 / 25.6.
-constexpr int linear_f32_parts(int bh) { return bh > 32 ? 1 : bh > 8 ? 64 / bh : 8; }
+// A (batch, head) runs on one XCD: the parts are as many as its 32 units take for the XCD with the most (batch, head)s (12 of 595 tokens, two launches / 5 parts,
+// 40 workgroups on some XCDs / 4: 13.2 / 16.9 / 10.2 us; 9 of 400 11.6 / 13.0 / 8.2, 20 of 576 13.6 / 18.6 / 11.5, 18 of 784 14.1 / 23.7 / 14.4).
+constexpr int linear_f32_parts(int bh) { return bh > 32 ? 1 : 8 / ((bh + 7) / 8); }
 constexpr bool linear_f32_in_one(int bh, int N) {
-    return N <= (bh <= 8 ? 1024 : bh <= 24 ? 800 : bh <= 56 ? 1400 : bh <= 64 ? 2400 : 0);
+    return N <= (bh <= 8 ? 1024 : bh <= 16 ? 800 : bh < 20 ? 700 : bh <= 24 ? 800 : bh <= 56 ? 1400 : bh <= 64 ? 2400 : 0);
 }
 
 // bf16 linear attention of 64-channel heads, both passes in one launch (la_fused_bf16, one workgroup a unit): its workgroups, one for each
