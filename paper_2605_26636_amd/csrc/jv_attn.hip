@@ -176,10 +176,10 @@ __device__ inline float f32_query_scale(const float (&x)[32], float &inverse) {
 // 32 queries of a wavefront: acc[cb][v] is channel 32 cb + 8 (v / 4) + 4 half + v % 4 of query lane % 32.
 struct F32State {
     f32x16 acc[2];
-    float m, l;
+    float m, ref, l;  // m: -inf until a key has a finite score; ref: what the weights are relative to, m or 0
     __device__ void clear() {
-        m = -1.0e30f;  // (finite stand-in for "no maximum yet")
-        l = 0.f;
+        m = -INFINITY;
+        ref = l = 0.f;
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.f;
     }
@@ -190,7 +190,7 @@ struct F32State {
             acc[1][v] *= x;
         }
     }
-    // Scores -> weights relative to the reference m, at most 2^8, summed into l.  The reference stays while no
+    // Scores -> weights relative to the reference, at most 2^8, summed into l.  The reference stays while no
     // logit is more than 8 binary orders above it (numerator and denominator share it, so the result is the
     // same), and goes up to the maximum otherwise.
     __device__ void weights(f32x16 &s, float factor) {
@@ -200,7 +200,9 @@ struct F32State {
         if (__any(top * factor > m + 8.0f)) {
             float lo, hi;
             pair_values(top, &lo, &hi);
-            const float m_new = fmaxf(m, fmaxf(lo, hi) * factor), alpha = __builtin_amdgcn_exp2f(m - m_new);
+            const float m_new = fmaxf(m, fmaxf(lo, hi) * factor);
+            ref = m_new == -INFINITY ? 0.f : m_new;  // padding only so far
+            const float alpha = __builtin_amdgcn_exp2f(m - ref);
             m = m_new;
             l *= alpha;
             times(alpha);
@@ -208,7 +210,7 @@ struct F32State {
         float sum = 0.f;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], factor, -m));
+            s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], factor, -ref));
             sum += s[v];
         }
         l += sum;

@@ -156,6 +156,25 @@ def test_split_operands(heads, N, what):
 
 
 @pytest.mark.parametrize("heads,N", SPLIT_SIZES)
+def test_logits_far_below_zero(heads, N):
+    """Finite logits near -1e36: the weights are relative to the largest of them, however low that is."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + 2)
+    v = torch.randn(1, heads, N, 64, generator=g, device="cuda")
+    q, k = torch.zeros_like(v), torch.zeros_like(v)
+    q[..., 5] = 2.0 ** 60
+    k[..., 5] = -(2.0 ** 60)
+    k[:, :, N // 3, 5] = -(2.0 ** 59)  # one key far above the others ...
+    k[:, 1::2, N - 1, 5] = -(2.0 ** 59)  # ... and two of them alike in every other head
+    o = torch.full_like(q, float("nan"))
+    binding.jv_full_attn_fwd(q, k, v, o, (1, N))
+    ref = v[:, :, N // 3].clone()
+    ref[:, 1::2] = 0.5 * (v[:, 1::2, N // 3].double() + v[:, 1::2, N - 1].double()).float()
+    # weights of 0 and 1 (or 1/2) alone: the rounding of a quotient
+    assert torch.allclose(o, ref[:, :, None].expand_as(o), rtol=3e-7, atol=3e-7)
+
+
+@pytest.mark.parametrize("heads,N", SPLIT_SIZES)
 def test_infinities_and_nan(heads, N):
     """What is not finite ends where the formula puts it: a key's value in its channel of every query, a query's
     in its own row, a key's score of -inf nowhere."""
