@@ -31,8 +31,10 @@
  *    otherwise).
  *  - Inputs are never written.  O must not overlap Q, K or V: the byte range that O's
  *    strides span may not intersect the range of any input (JV_ERR_INVALID_ARG).
- *  - Arithmetic: JV_F32 tensors are processed in fp32 throughout.  JV_BF16
- *    tensors feed bf16 matrix instructions with fp32 accumulation; softmax,
+ *  - Arithmetic: JV_F32 tensors are processed in fp32 throughout, or, in softmax
+ *    attention over more than 32 keys, as sums of three bf16 numbers that together hold
+ *    all 24 bits of every operand (magnitudes below 2^-110: down to 2^-133), whatever the
+ *    magnitudes of the other operands, with fp32 accumulation.  JV_BF16 tensors feed bf16 matrix instructions with fp32 accumulation; softmax,
  *    normalisers and divisions are fp32.  O is rounded to `o_dtype` once, at the
  *    final store (round to nearest even).
  *  - Errors: every call validates its arguments on the host before any launch

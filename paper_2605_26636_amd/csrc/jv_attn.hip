@@ -19,15 +19,14 @@ __device__ inline int slot_token(const WindowGeom &g, int wy, int wx, int slot) 
 }
 
 // ---------------------------------------------------------------------------------------
-// fp32 path: tiles of 32 keys x 32 queries on the fp16 matrix instructions
-// (v_mfma_f32_32x32x16_f16, fp32 accumulation; sixteen times the rate of the fp32 ones).  Every operand is the sum of
-// two fp16 numbers of 11 bits and a sign each, scaled by a power of two: hi = fp16(s x), lo = fp16(s x - hi), and
-// a b = hi hi + hi lo + lo hi; what is left out, and what lo rounds away, is below 2^-23 of the product.  The scales keep the largest
-// magnitude of a query, of K and of V between 2^12 and 2^15, so that only numbers 2^26 times smaller than that lose bits, and
-// none more than 2^-38 of it.  K and V take their scale from the tiles seen so far: it goes down, and the sums with it, when a
-// tile holds something four times as large.  Errors against 64 bits are those of the rounding of the sums: the small products are added
-// up first, and a tile's sums on their own before they join the others.  64 heads of 1 369 tokens 2.4e-7, of 2 304 2.7e-7
-// (fp32 matrix instructions 5.6e-7 and 9.2e-7).
+// fp32 path: tiles of 32 keys x 32 queries on the bf16 matrix instructions
+// (v_mfma_f32_32x32x16_bf16, fp32 accumulation; sixteen times the rate of the fp32 ones).  Every operand is the sum of
+// three bf16 numbers, each the rounding of what the ones before leave: all 24 bits of a number, whatever the others are, down to 2^-110 in magnitude (below it
+// to 2^-133, the smallest bf16 number).  Six of the nine products are formed; what is left out is below 2^-24 of the product of two numbers (2^-28 of it
+// on average).  Errors against 64 bits are those of the rounding of the sums: the small products are added up first, and a
+// tile's sums on their own before they join the others.  64 heads of 1 369 tokens 2.0e-7, of 2 304 2.3e-7 (fp32 matrix instructions 5.6e-7 and 9.2e-7).
+// (Two fp16 numbers an operand, scaled by the largest magnitude of K, of V and of a query, and three products: 20 to 30 % faster, but what is 2^14
+// times smaller than the largest loses bits, a small channel of V beside a large one for instance.)
 // Infinities and NaN turn into NaN on the way (inf - inf), and so does what overflows: a wavefront whose sums are not finite
 // goes over its keys once more with the fp32 matrix instructions (f32_again).
 // Scores are formed transposed, S^T = K Q^T, so that a lane owns one query column: the maximum and the
@@ -82,78 +81,62 @@ __device__ inline F32Window f32_window(const TensorArg &q, const TensorArg &k, c
     return w;
 }
 
+// A number as the sum of three bf16 numbers, each the rounding of what the ones before leave: 8 + 8 + 8 bits.
 struct Split {
-    f16x8 hi, lo;
+    bf16x8 part[3];
 };
-// Two instructions a number (written out: the compiler rounds every odd number twice, once into each half of a register).
-__device__ inline void split_pair(float x0, float x1, float s, unsigned &hi, unsigned &lo) {
-    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(hi) : "v"(x0), "v"(s));
-    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(hi) : "v"(x1), "v"(s));
-    asm("v_fma_mixlo_f16 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(lo) : "v"(x0), "v"(s), "v"(hi));
-    asm("v_fma_mixhi_f16 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "+v"(lo) : "v"(x1), "v"(s), "v"(hi));
+// What the rounding of x to half `HALF` of r leaves (exact).  One instruction: the dot product of r with (-1, 0) or (0, -1) on top of x.  (The
+// constants are hidden from the compiler, which would encode them as the inline -1.0 of 32 bits: another pair of bf16 numbers.)
+template <int HALF>
+__device__ inline float split_rest(unsigned r, float x) {
+    unsigned k = HALF ? 0xbf800000u : 0x0000bf80u;
+    asm("" : "+s"(k));
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, r), __builtin_bit_cast(bf16x2, k), x, false);
 }
-__device__ inline Split split8(const float *x, float s) {
-    u32x4 hi, lo;
+// Seven instructions for two numbers.  (The first part of what lies within 2^-9 of the largest float is infinite, see f32_again.)
+__device__ inline void split_pair(float x0, float x1, unsigned (&r)[3]) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        r[i] = pack_bf16x2(x0, x1);
+        if (i == 2) break;
+        x0 = split_rest<0>(r[i], x0);
+        x1 = split_rest<1>(r[i], x1);
+    }
+}
+__device__ inline Split split8(const float *x) {
+    u32x4 part[3];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        unsigned h, l;
-        split_pair(x[2 * i], x[2 * i + 1], s, h, l);
-        hi[i] = h;
-        lo[i] = l;
-    }
-    return {__builtin_bit_cast(f16x8, hi), __builtin_bit_cast(f16x8, lo)};
-}
-// Four channels of a row into its hi and lo row of 128 bytes; the lo tile lies behind the hi tile.
-constexpr int kHalfTile = 32 * kHeadDim * 2;
-__device__ inline void split_store(unsigned char *at, f32x4 x, float s) {
-    u32x2 hi, lo;
+        unsigned r[3];
+        split_pair(x[2 * i], x[2 * i + 1], r);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        unsigned h, l;
-        split_pair(x[2 * i], x[2 * i + 1], s, h, l);
-        hi[i] = h;
-        lo[i] = l;
+        for (int j = 0; j < 3; ++j) part[j][i] = r[j];
     }
-    *(u32x2 *)at = hi;
-    *(u32x2 *)(at + kHalfTile) = lo;
+    return {as_bf16x8(part[0]), as_bf16x8(part[1]), as_bf16x8(part[2])};
 }
-__device__ inline f32x16 mfma_f16(f16x8 a, f16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
-__device__ inline f32x16 mfma_small(const Split &a, const Split &b, f32x16 c) { return mfma_f16(a.hi, b.lo, mfma_f16(a.lo, b.hi, c)); }
-
-// The largest of a wavefront's 64 numbers (none negative), in every lane: rotations inside rows of 16 lanes, then across them.
-template <int ROTATE>
-__device__ inline float row_max(float x) {
-    const int r = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + ROTATE, 0xf, 0xf, false);
-    return fmaxf(x, __builtin_bit_cast(float, r));
-}
-__device__ inline float wave_max(float x) {
-    x = row_max<1>(row_max<2>(row_max<4>(row_max<8>(x))));
-    const unsigned u = __builtin_bit_cast(unsigned, x);
-    const auto s = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    x = fmaxf(__builtin_bit_cast(float, (unsigned)s[0]), __builtin_bit_cast(float, (unsigned)s[1]));
-    float lo, hi;
-    pair_values(x, &lo, &hi);
-    return fmaxf(lo, hi);
-}
-template <int N>
-__device__ inline float magnitude(const f32x4 (&x)[N]) {  // (NaN: left out)
-    float top = 0.f;
+// Four channels of a row into its rows of 128 bytes of the three parts' tiles, one behind the other.
+constexpr int kPartTile = 32 * kHeadDim * 2;
+__device__ inline void split_store(unsigned char *at, f32x4 x) {
+    unsigned a[3], b[3];
+    split_pair(x[0], x[1], a);
+    split_pair(x[2], x[3], b);
 #pragma unroll
-    for (int i = 0; i < N; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) top = fmaxf(top, fabsf(x[i][e]));
-    return top;
+    for (int j = 0; j < 3; ++j) *(u32x2 *)(at + j * kPartTile) = u32x2{a[j], b[j]};
 }
-// A power of two for numbers of magnitude up to `top`: `scale` takes them below 2^13, and magnitudes up to `limit` below 2^15.
-struct F32Scale {
-    float limit = -1.f, scale = 0.f, inverse = 0.f;
-    __device__ void fit(float top) {
-        const int e = min(max(139 - (int)(__builtin_bit_cast(unsigned, top) >> 23), -112), 120);  // (both normal)
-        inverse = __builtin_bit_cast(float, (unsigned)(127 - e) << 23);
-        scale = __builtin_bit_cast(float, (unsigned)(127 + e) << 23);
-        limit = 4.0f * top;
-    }
-};
+__device__ inline Split split_load(const unsigned char *at, int stride) {
+    Split x;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) x.part[j] = as_bf16x8(*(const u32x4 *)(at + j * stride));
+    return x;
+}
+// a b + c but for the product of the first parts, smallest first.
+__device__ inline f32x16 mfma_small(const Split &a, const Split &b, f32x16 c) {
+    c = mfma32(a.part[0], b.part[2], c);
+    c = mfma32(a.part[2], b.part[0], c);
+    c = mfma32(a.part[1], b.part[1], c);
+    c = mfma32(a.part[0], b.part[1], c);
+    return mfma32(a.part[1], b.part[0], c);
+}
 
 // Queries: lane (half, i) has channels 16 t + 8 half .. + 7 of query i (t = 0 .. 3), x[8 t ..].
 __device__ inline void f32_queries(const F32Window &w, int qtok, int half, float (&x)[32]) {
@@ -161,27 +144,36 @@ __device__ inline void f32_queries(const F32Window &w, int qtok, int half, float
 #pragma unroll
     for (int c = 0; c < 8; ++c) *(f32x4 *)(x + 4 * c) = *(const f32x4 *)(row + 16 * (c / 2) + 4 * (c % 2));
 }
-// The scale of a lane's query; its inverse turns sums of scaled products into logits.
-__device__ inline float f32_query_scale(const float (&x)[32], float &inverse) {
-    float top = 0.f, lo, hi;
+// Many queries: of a wavefront's 32 two parts are in registers and the third in LDS, 1 KB a step of 16 channels.
+struct F32Queries {
+    bf16x8 first[4], second[4];
+    const unsigned char *third;  // this lane's
+    __device__ void split(const float (&x)[32], unsigned char *rest) {
+        third = rest;
 #pragma unroll
-    for (int i = 0; i < 32; ++i) top = fmaxf(top, fabsf(x[i]));
-    pair_values(top, &lo, &hi);
-    F32Scale s;
-    s.fit(fmaxf(lo, hi));
-    inverse = s.inverse;
-    return s.scale;
-}
+        for (int t = 0; t < 4; ++t) {
+            const Split q = split8(x + 8 * t);
+            first[t] = q.part[0];
+            second[t] = q.part[1];
+            *(u32x4 *)(rest + 1024 * t) = as_u32x4(q.part[2]);
+        }
+    }
+    __device__ Split operator[](int t) const { return {first[t], second[t], as_bf16x8(*(const u32x4 *)(third + 1024 * t))}; }
+};
 
 // 32 queries of a wavefront: acc[cb][v] is channel 32 cb + 8 (v / 4) + 4 half + v % 4 of query lane % 32.
 struct F32State {
     f32x16 acc[2];
     float m, ref, l;  // m: -inf until a key has a finite score; ref: what the weights are relative to, m or 0
+    // (Sets of 16 registers stay sets: where the compiler sees single numbers put into them it carries 32 numbers round the key loop and copies
+    // or spills them.)
+    __device__ void whole() { asm("" : "+v"(acc[0]), "+v"(acc[1])); }
     __device__ void clear() {
         m = -INFINITY;
         ref = l = 0.f;
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.f;
+        whole();
     }
     __device__ void times(float x) {
 #pragma unroll
@@ -189,6 +181,7 @@ struct F32State {
             acc[0][v] *= x;
             acc[1][v] *= x;
         }
+        whole();
     }
     // Scores -> weights relative to the reference, at most 2^8, summed into l.  The reference stays while no
     // logit is more than 8 binary orders above it (numerator and denominator share it, so the result is the
@@ -215,10 +208,8 @@ struct F32State {
         }
         l += sum;
     }
-    // The sums as those of weights of at most 1: values up to the largest floats pass as under the maximum itself.
     // False where something is not finite.
-    __device__ bool settle(float v_inverse) {
-        times(v_inverse * 0x1p-14f);
+    __device__ bool finite() const {
         float x[4] = {l, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int v = 0; v < 16; ++v) x[v % 4] = fmaf(acc[0][v], 0.f, fmaf(acc[1][v], 0.f, x[v % 4]));
@@ -227,20 +218,17 @@ struct F32State {
 };
 
 // Scores of a tile whose K rows (tile_off_row) start at `ktile`.
-__device__ inline f32x16 f32_scores(const unsigned char *ktile, int li, int half, const Split (&q)[4]) {
+__device__ inline f32x16 f32_scores(const unsigned char *ktile, int li, int half, const F32Queries &q) {
     Split k[4];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const unsigned char *at = ktile + tile_off_row(li, 2 * t + half);
-        k[t] = {*(const f16x8 *)at, *(const f16x8 *)(at + kHalfTile)};
-    }
+    for (int t = 0; t < 4; ++t) k[t] = split_load(ktile + tile_off_row(li, 2 * t + half), kPartTile);
     f32x16 s;
 #pragma unroll
     for (int v = 0; v < 16; ++v) s[v] = 0.f;
 #pragma unroll
     for (int t = 0; t < 4; ++t) s = mfma_small(k[t], q[t], s);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) s = mfma_f16(k[t].hi, q[t].hi, s);
+    for (int t = 0; t < 4; ++t) s = mfma32(k[t].part[0], q.first[t], s);
     return s;
 }
 // Byte offset of a lane's transposing reads in a tile of V (tile_off_tr), channel block cb.
@@ -248,7 +236,7 @@ __device__ inline unsigned f32_value_offset(int lane, int cb) {
     const int b = lane >> 4, j = lane & 15;
     return tile_off_tr(4 * (lane >> 5) + (j >> 2), cb * 4 + (b & 1) * 2 + ((j & 3) >> 1)) + (j & 1) * 8;
 }
-// acc += V^T P^T 2^6 scale for the weights p of a tile.
+// acc += V^T P^T for the weights p of a tile.
 __device__ inline void f32_values(F32State &st, const unsigned char *vtile, const unsigned (&voff)[2], const f32x16 &p) {
     Split w[2];
 #pragma unroll
@@ -256,57 +244,75 @@ __device__ inline void f32_values(F32State &st, const unsigned char *vtile, cons
         float x[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) x[j] = p[8 * f + j];
-        w[f] = split8(x, 0x1p6f);
+        w[f] = split8(x);
     }
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb) {
         Split v[2];
 #pragma unroll
-        for (int f = 0; f < 2; ++f) {
-            const unsigned char *at = vtile + voff[cb] + 16 * 128 * f;
-            const u32x2 h0 = lds_read_tr16(at), h1 = lds_read_tr16(at + 1024);
-            const u32x2 l0 = lds_read_tr16(at + kHalfTile), l1 = lds_read_tr16(at + kHalfTile + 1024);
-            const u32x4 hi = {h0[0], h0[1], h1[0], h1[1]}, lo = {l0[0], l0[1], l1[0], l1[1]};
-            v[f] = {__builtin_bit_cast(f16x8, hi), __builtin_bit_cast(f16x8, lo)};
-        }
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const unsigned char *at = vtile + voff[cb] + 16 * 128 * f + j * kPartTile;
+                const u32x2 r0 = lds_read_tr16(at), r1 = lds_read_tr16(at + 1024);
+                v[f].part[j] = as_bf16x8(u32x4{r0[0], r0[1], r1[0], r1[1]});
+            }
         f32x16 sum;
 #pragma unroll
         for (int i = 0; i < 16; ++i) sum[i] = 0.f;
         sum = mfma_small(v[1], w[1], mfma_small(v[0], w[0], sum));
-        st.acc[cb] += mfma_f16(v[1].hi, w[1].hi, mfma_f16(v[0].hi, w[0].hi, sum));
+        st.acc[cb] += mfma32(v[1].part[0], w[1].part[0], mfma32(v[0].part[0], w[0].part[0], sum));
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-// A wavefront's keys (tiles tile0, tile0 + step, ...) on the fp32 matrix instructions.
+// A wavefront's keys (tiles tile0, tile0 + step, ...) on the fp32 matrix instructions, straight from memory: half of the loads of a tile are in
+// flight at a time.  With an infinity in V of every head (of one head) 1 369 tokens x 12 heads take 108 (91) us instead of 69, x 64 542 (307) instead of 205; the fp32
+// instructions alone took 95 and 326.
 __device__ inline void f32_again(F32State &st, const F32Window &w, int qtok, float scale_log2, int tile0, int step, int li, int half) {
     st.clear();
     float x[32];
     f32_queries(w, qtok, half, x);
+#pragma clang loop unroll(disable)
     for (int k0 = 32 * tile0; k0 < w.g.slots; k0 += 32 * step) {
         const int ktok = w.token(k0 + li);
         const float *krow = w.k + (long long)(ktok < 0 ? w.first : ktok) * w.ksn + 8 * half;
+        f32x4 k[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) k[c] = *(const f32x4 *)(krow + 16 * (c / 2) + 4 * (c % 2));
+        float v[2][8];
+        auto fetch_v = [&](int from) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int tok = __shfl(ktok, 8 * ((from + j) / 4) + 4 * half + j % 4, 64);
+                const float *row = w.v + (long long)(tok < 0 ? w.first : tok) * w.vsn + li;
+                v[0][j] = tok < 0 ? 0.f : row[0];  // (0 x inf would be NaN)
+                v[1][j] = tok < 0 ? 0.f : row[32];
+            }
+        };
+        fetch_v(0);
         f32x16 s;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) s[v] = 0.f;
+        for (int i = 0; i < 16; ++i) s[i] = 0.f;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const f32x4 k = *(const f32x4 *)(krow + 16 * (c / 2) + 4 * (c % 2));
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(k[e], x[4 * c + e], s, 0, 0, 0);
-        }
+        for (int i = 0; i < 32; ++i) s = __builtin_amdgcn_mfma_f32_32x32x2f32(k[i / 4][i % 4], x[i], s, 0, 0, 0);
         const unsigned pad = (unsigned)__builtin_amdgcn_ballot_w64(ktok < 0) >> (4 * half);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) s[v] = (pad >> (8 * (v / 4) + v % 4)) & 1u ? -INFINITY : s[v];
+        for (int i = 0; i < 16; ++i) s[i] = (pad >> (8 * (i / 4) + i % 4)) & 1u ? -INFINITY : s[i];
         st.weights(s, scale_log2);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int tok = __shfl(ktok, 8 * (v / 4) + 4 * half + v % 4, 64);
-            const float *vrow = w.v + (long long)(tok < 0 ? w.first : tok) * w.vsn + li;
-            const float p = s[v] * 0x1p-8f;
-            st.acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(tok < 0 ? 0.f : vrow[0], p, st.acc[0], 0, 0, 0);  // (0 x inf would be NaN)
-            st.acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(tok < 0 ? 0.f : vrow[32], p, st.acc[1], 0, 0, 0);
+        for (int i = 0; i < 16; ++i) {
+            if (i == 8) {
+                __builtin_amdgcn_sched_barrier(0);
+                fetch_v(8);
+            }
+            const float p = s[i] * 0x1p-8f;  // none above 1: values up to the largest floats pass through the sums
+            st.acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[0][i % 8], p, st.acc[0], 0, 0, 0);
+            st.acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[1][i % 8], p, st.acc[1], 0, 0, 0);
         }
     }
+    st.l *= 0x1p-8f;  // all of it relative to a reference 8 orders up
+    st.m += 8.0f;
 }
 
 // Tail of the fp32 kernels.  A wavefront without partners stores its rows ...
@@ -350,7 +356,7 @@ __device__ inline void f32_merge(const F32Window &w, const unsigned char *parts,
         float den = 0.f;
 #pragma unroll
         for (int k = 0; k < KW; ++k) {
-            const float x = __builtin_amdgcn_exp2f(ms[w0 + k][ql] - top);
+            const float x = __builtin_amdgcn_exp2f(ms[w0 + k][ql] - top) * (1.0f / KW);  // (values up to the largest floats pass through the sum)
             out += x * *(const f32x4 *)(parts + (w0 + k) * (32 * 256) + ql * 256 + ((chunk ^ (ql & 15)) << 4));
             den = fmaf(x, ls[w0 + k][ql], den);
         }
@@ -359,7 +365,7 @@ __device__ inline void f32_merge(const F32Window &w, const unsigned char *parts,
 }
 
 // Few tiles of keys: the same tiles on the fp32 matrix instructions (v_mfma_f32_32x32x2_f32), whose operands are
-// staged in LDS as they are.  With a tile or two to a wavefront the scales and splits of the other kernels stand alone at its start.
+// staged in LDS as they are.  With a tile or two to a wavefront the splits of the other kernels stand alone at its start.
 // A workgroup of four wavefronts takes QW = 4 / KW blocks of 32 queries times KW groups of keys: per
 // step it stages KW tiles of K and V in LDS (fetched into registers under the arithmetic of the
 // step before) and wavefront (qw, kw) takes tile kw.  With KW > 1 the KW running softmaxes of a
@@ -501,16 +507,16 @@ attn_short_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeo
 }
 
 // Many queries: a workgroup of four wavefronts takes 128 queries of a window.  Per step it splits a tile of K and V
-// (fetched under the arithmetic of the step before) into LDS, where every wavefront reads it.  Bound by the issue of matrix (24 a tile,
-// 768 cycles) and vector instructions (about 250), which overlap in part.  Measured: 2 304 tokens x 64
-// heads 791 -> 345 us (fp32 matrix instructions / here), 1 369 x 64 328 -> 128, 784 x 64 118 -> 58, windows of 16 x 16 on 48 x 48 x 64
-// 103 -> 60.  (Products added straight to the sums of the tiles before: 2 to 7 % faster, errors twice as large.)
+// (fetched under the arithmetic of the step before) into LDS, where every wavefront reads it.  Bound by the issue of matrix (48 a tile,
+// 1 536 cycles) and vector instructions (about 250), which overlap in part.  Measured: 2 304 tokens x 64
+// heads 791 -> 512 us (fp32 matrix instructions / here), 1 369 x 64 328 -> 188, 784 x 64 118 -> 78, windows of 16 x 16 on 48 x 48 x 64
+// 103 -> 73.  (All three parts of the queries in registers, which spill: 200 us for 1 369 x 64; two workgroups a unit, whose registers do not: 207.)
 // grid (ceil(q_slots / 128), n_win, B*heads), 256 threads.
 __global__ void __launch_bounds__(256, 3)
 attn_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, int heads, float scale_log2, int q_slots) {
-    __shared__ __align__(16) unsigned char tile[4 * kHalfTile];  // K hi, K lo, V hi, V lo
+    __shared__ __align__(16) unsigned char tile[6 * kPartTile];  // the three parts of K, then of V
+    __shared__ __align__(16) unsigned char qrest[4][4 * 1024];   // the third parts of the queries
     __shared__ __align__(16) float bias[32];                     // 0 for a real key, -inf for padding
-    __shared__ unsigned tops[2];                                 // largest magnitude of K and of V where it went beyond a scale's limit
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, li = lane & 31;
     int qblock, win, bh;
     f32_item(qblock, win, bh);
@@ -535,46 +541,24 @@ attn_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, i
     const int q0 = qblock * 128 + wave * 32;
     const bool live = q0 < q_slots;  // the same in the whole wavefront
     const int qtok = q0 + li < q_slots ? w.token(q0 + li) : -1;
-    Split q[4];
-    float logit;
+    F32Queries q;
     {
         float x[32];
         f32_queries(w, qtok, half, x);
-        const float s = f32_query_scale(x, logit);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) q[t] = split8(x + 8 * t, s);
+        q.split(x, qrest[wave] + 16 * lane);
     }
     F32State st;
     st.clear();
-    F32Scale ks, vs;
-    if (tid < 2) tops[tid] = 0;
-    __syncthreads();
     const unsigned voff[2] = {f32_value_offset(lane, 0), f32_value_offset(lane, 1)};
     const int n_step = (g.slots + 31) / 32;
     for (int step = 0; step < n_step; ++step) {
-        const float tk = magnitude(kreg), tv = magnitude(vreg);
-        if (__any(tk > ks.limit || tv > vs.limit)) {  // (rare after the first tile)
-            const float k = wave_max(tk), v = wave_max(tv);
-            if (lane == 0) {
-                atomicMax(&tops[0], __builtin_bit_cast(unsigned, k));
-                atomicMax(&tops[1], __builtin_bit_cast(unsigned, v));
-            }
-        }
-        __syncthreads();  // the tile before has been read, and every wavefront's magnitudes are there
-        const float k_top = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(tops[0]));
-        const float v_top = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(tops[1]));
-        if (k_top > ks.limit) ks.fit(k_top);
-        if (v_top > vs.limit) {
-            const float before = vs.inverse;
-            vs.fit(v_top);
-            st.times(vs.scale * before);
-        }
+        __syncthreads();  // the tile before has been read
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int r = srow + 16 * i;
             if (breg[i] != 0.f) kreg[i] = vreg[i] = f32x4{0.f, 0.f, 0.f, 0.f};  // 0 x inf of a padded key's row would be NaN
-            split_store(tile + tile_off_row(r, chunk >> 1) + 8 * (chunk & 1), kreg[i], ks.scale);
-            split_store(tile + 2 * kHalfTile + tile_off_tr(r, chunk >> 1) + 8 * (chunk & 1), vreg[i], vs.scale);
+            split_store(tile + tile_off_row(r, chunk >> 1) + 8 * (chunk & 1), kreg[i]);
+            split_store(tile + 3 * kPartTile + tile_off_tr(r, chunk >> 1) + 8 * (chunk & 1), vreg[i]);
             if (chunk == 0) bias[r] = breg[i];
         }
         __syncthreads();
@@ -589,14 +573,14 @@ attn_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, i
                 for (int e = 0; e < 4; ++e) s[4 * v4 + e] += b[e];
             }
         }
-        st.weights(s, (logit * ks.inverse) * scale_log2);
-        f32_values(st, tile + 2 * kHalfTile, voff, s);
+        st.weights(s, scale_log2);
+        f32_values(st, tile + 3 * kPartTile, voff, s);
     }
     if (!live) return;
-    if (__any(!st.settle(vs.inverse))) f32_again(st, w, qtok, scale_log2, 0, 1, li, half);
+    if (__any(!st.finite())) f32_again(st, w, qtok, scale_log2, 0, 1, li, half);
     if (qtok < 0) return;
     float lo, hi;
-    pair_values(st.l * 0x1p-8f, &lo, &hi);
+    pair_values(st.l, &lo, &hi);
     f32_store_row(st.acc, 1.0f / (lo + hi), w.o + (long long)qtok * w.osn + 4 * half);
 }
 
@@ -605,16 +589,15 @@ attn_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, i
 // a lane's K operands are 16-byte pieces of one row, a V operand eight dwords of a channel (an instruction reads two runs of 128
 // bytes).  Half tiles of K and V rotate through three sets of sixteen registers, each
 // fetched while the matrix instructions of two others run; three workgroups fit a compute unit.  Bound by its loads (32 cache lines for an
-// instruction's K operands), the splits and the matrix instructions together.  Against the fp32 matrix
-// instructions, us: 1 369 tokens x 12 heads 87.9 -> 49.0 (516 workgroups: four units have three and the others two; x 11 60.3 -> 37.3),
-// 1 030 x 36 112 -> 65, windows of 14 x 14 on 40 x 40 x 24 39.6 -> 30.9.
-// (Tiles through LDS, a wavefront's own or shared by two: 66 and 67 us for 1 369 x 12, 99 and 75 for 1 030 x 36.  Three bf16 numbers an
-// operand and six products instead of two fp16 numbers and three: 58 us.)
+// instruction's K operands), the splits (280 vector instructions a tile) and the matrix instructions together.  Against the fp32 matrix
+// instructions, us: 1 369 tokens x 12 heads 88.1 -> 62.9 (516 workgroups: four units have three and the others two; x 11 60.4 -> 45.8),
+// 1 030 x 35 112 -> 82, windows of 14 x 14 on 40 x 40 x 12 22.4 -> 21.1; 2.4e-7 instead of 4.5e-7 from 64 bits at 1 369 tokens, 2.9e-7 instead of 6.5e-7 at
+// 4 096.  (Products added straight to the sums of the tiles before: 59.6 us, 3.5e-7 and 5.4e-7.)
 // grid (ceil(q_slots / 32), n_win, B*heads), 256 threads.  Byte offsets inside a (batch, head) slice of K and V below 2^32.
 __global__ void __launch_bounds__(256, 3)
 attn_few_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, int heads, float scale_log2, int q_slots) {
     __shared__ __align__(16) unsigned char parts[4][32 * 256];
-    __shared__ __align__(16) unsigned char qs[2 * 4 * 1024];  // [hi, lo][step of 16 channels][lane]
+    __shared__ __align__(16) unsigned char qs[3 * 4 * 1024];  // [part][step of 16 channels][lane]
     __shared__ float ms[4][32], ls[4][32];
     const int tid = threadIdx.x, kw = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, li = lane & 31;
     int qblock, win, bh;
@@ -624,22 +607,19 @@ attn_few_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom 
     const unsigned ksn = 4u * (unsigned)kt.sn, vsn = 4u * (unsigned)vt.sn;
     const unsigned vlane = 4u * half * vsn + 4u * li;
     const int qslot = qblock * 32 + li, qtok = qslot < q_slots ? w.token(qslot) : -1;
-    float logit;
     {
         float x[32];
         f32_queries(w, qtok, half, x);
-        const float s = f32_query_scale(x, logit);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             if (t != kw) continue;  // (uniform; constant indices of x)
-            const Split q = split8(x + 8 * t, s);
-            *(f16x8 *)(qs + t * 1024 + lane * 16) = q.hi;
-            *(f16x8 *)(qs + (4 + t) * 1024 + lane * 16) = q.lo;
+            const Split q = split8(x + 8 * t);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) *(u32x4 *)(qs + (4 * j + t) * 1024 + lane * 16) = as_u32x4(q.part[j]);
         }
     }
     F32State st;
     st.clear();
-    F32Scale ks, vs;
     const int n_tile = (g.slots + 31) / 32;
     f32x4 set[3][4];
     // K operands of steps 2 hf, 2 hf + 1 of the tile whose key li is token `tok` (negative: padding)
@@ -685,19 +665,19 @@ attn_few_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom 
         const unsigned cur_pad = pad, pads = half ? pad >> 4 : pad;
         f32x16 s;
         auto scores = [&](f32x4 (&r)[4], int hf) __attribute__((always_inline)) {
+            bf16x8 q0[2], k0[2];
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                const unsigned char *at = qs + (2 * hf + t) * 1024 + lane * 16;
-                const Split q = {*(const f16x8 *)at, *(const f16x8 *)(at + 4096)}, k = split8((const float *)&r[2 * t], ks.scale);
-                s = mfma_f16(k.hi, q.hi, mfma_small(k, q, s));
+                const Split q = split_load(qs + (2 * hf + t) * 1024 + lane * 16, 4096), k = split8((const float *)&r[2 * t]);
+                s = mfma_small(k, q, s);
+                q0[t] = q.part[0];
+                k0[t] = k.part[0];
             }
+#pragma unroll
+            for (int t = 0; t < 2; ++t) s = mfma32(k0[t], q0[t], s);
         };
         fetch_v(vc, cur, cur_pad, 0);
         __builtin_amdgcn_sched_barrier(0);
-        {
-            const float top = fmaxf(magnitude(ka), magnitude(kb));
-            if (__any(top > ks.limit)) ks.fit(wave_max(top));
-        }
 #pragma unroll
         for (int i = 0; i < 16; ++i) s[i] = 0.f;
         scores(ka, 0);
@@ -713,7 +693,7 @@ attn_few_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom 
 #pragma unroll
             for (int j = 0; j < 16; ++j) s[j] = (pads >> (8 * (j / 4) + j % 4)) & 1u ? -INFINITY : s[j];
         }
-        st.weights(s, (logit * ks.inverse) * scale_log2);
+        st.weights(s, scale_log2);
         auto product = [&](f32x4 (&r)[4], int hf) __attribute__((always_inline)) {
             if (cur_pad != 0u) {  // ... and zeros for the values they meet (0 x inf would be NaN)
 #pragma unroll
@@ -723,20 +703,17 @@ attn_few_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom 
                     r[2 + j / 4][j % 4] = x ? 0.f : r[2 + j / 4][j % 4];
                 }
             }
-            const float top = magnitude(r);
-            if (__any(top > vs.limit)) {
-                const float before = vs.inverse;
-                vs.fit(wave_max(top));
-                st.times(vs.scale * before);
-            }
             float p[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) p[j] = s[8 * hf + j];
-            const Split x = split8(p, 0x1p6f);
+            const Split x = split8(p);
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb) {
-                const Split v = split8((const float *)&r[2 * cb], vs.scale);
-                st.acc[cb] = mfma_f16(v.hi, x.hi, mfma_small(v, x, st.acc[cb]));
+                const Split v = split8((const float *)&r[2 * cb]);
+                f32x16 sum;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) sum[i] = 0.f;
+                st.acc[cb] += mfma32(v.part[0], x.part[0], mfma_small(v, x, sum));
             }
         };
         product(vc, 0);
@@ -759,11 +736,11 @@ attn_few_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom 
             if ((tile += 4) >= n_tile) break;
         }
     }
-    if (__any(!st.settle(vs.inverse))) f32_again(st, w, qtok, scale_log2, kw, 4, li, half);
+    if (__any(!st.finite())) f32_again(st, w, qtok, scale_log2, kw, 4, li, half);
     f32_park(st.acc, parts[kw], li, half);
     {
         float lo, hi;
-        pair_values(st.l * 0x1p-8f, &lo, &hi);
+        pair_values(st.l, &lo, &hi);
         if (half == 0) {
             ms[kw][li] = st.m;
             ls[kw][li] = lo + hi;
@@ -825,8 +802,8 @@ static jv_status attn_dispatch(const Problem &pr, const WindowGeom &g, float sca
         return launch_status("attn_small_window_f32");
     }
     const int tiles = (g.slots + 31) / 32;
-    const long long blocks = (long long)((q_slots + 31) / 32) * g.n_win * pr.B * pr.heads, max_sn = pr.k.sn > pr.v.sn ? pr.k.sn : pr.v.sn;
-    const F32Kernel kernel = f32_kernel(tiles, g.ww == g.W, blocks, ((long long)g.H * g.W + 64) * max_sn * 4);
+    const long long lanes = (long long)g.n_win * pr.B * pr.heads, max_sn = pr.k.sn > pr.v.sn ? pr.k.sn : pr.v.sn;
+    const F32Kernel kernel = f32_kernel(tiles, g.ww == g.W, q_slots, lanes, ((long long)g.H * g.W + 64) * max_sn * 4);
     const int queries = kernel == kF32Many || kernel == kF32Short1 ? 128 : kernel == kF32Short2 ? 64 : 32;
     const auto f = kernel == kF32Many ? attn_f32 : kernel == kF32Few ? attn_few_f32 : kernel == kF32Short1 ? attn_short_f32<1> :
                    kernel == kF32Short2 ? attn_short_f32<2> : attn_short_f32<4>;

@@ -96,24 +96,35 @@ constexpr int ring_key_groups(int queries, int keys, long long lanes) {
 
 // fp32 attention of few queries, the keys cut over the four wavefronts of a workgroup (`waves` blocks of 32 queries in all, windows of
 // `tiles` tiles of 32 keys): attn_few_f32, or attn_short_f32<4> where that is faster or K and V span more bytes than 32-bit offsets
-// count.  With a tile per wavefront attn_few_f32 has nothing to fetch ahead and its scales and splits stand alone, and only its third
-// workgroup on a unit tells: rounds of 768 against 512.  Windows of whole grid rows of 4 tiles, staged / few, us: 128 keys x 6 (batch, head)s 6.8 / 6.9,
-// x 64 7.3 / 7.5; 7 tiles x 6 9.8 / 9.2.
+// count.  With a tile per wavefront attn_few_f32 has nothing to fetch ahead and its splits stand alone, and only its third
+// workgroup on a unit tells: rounds of 768 against 512.  Windows of whole grid rows of 4 tiles, staged / few, us: 100 keys x 64 (batch, head)s 7.3 / 7.8,
+// 128 x 64 7.3 / 7.8; 7 tiles x 37 16.3 / 13.4.
 constexpr bool f32_keys_staged(int tiles, bool whole_rows, long long waves, long long kv_bytes) {
     return kv_bytes >= (1ll << 32) || (tiles == 4 && whole_rows && (waves - 1) % 768 < 512);
 }
-// fp32 attention: `blocks` blocks of 32 queries in all, windows of `tiles` tiles of 32 keys, K and V slices of up to kv_bytes.
-// attn_f32 does the most per second, but four blocks share a workgroup, and a unit with one of them waits out its barriers; attn_few_f32 gives a
-// block four wavefronts, and takes a round of 256 blocks where attn_f32 takes one of
-// 1 024.  Few / many, us: 1 369 tokens (43 tiles) of 516 blocks 49 / 71, 688 50 / 72, 1 032 80 / 87, 1 376 95 / 89; 72 tiles 864 103 / 114, 1 152 125 / 142,
-// 1 728 173 / 144; 25 tiles 600 33 / 44, 800 45 / 44; 18 tiles 576 27 / 33, 864 36 / 34; 8 tiles 512 13.5 / 18.2, 864 24 / 21; 7 tiles 756 18.0 / 18.8; 4 tiles 864 18 / 13.
-// Windows of one or two tiles leave nothing to share keys for: attn_short_f32 where its start is the shorter one.  Short / many, us: 1 tile
-// always (windows of 5 x 5, 3 072 blocks 53 / 59); 2 tiles of 108 blocks 7.1 / 7.9, of 432 8.2 / 8.8, of 864 12.6 / 11.9.
+// fp32 attention: `queries` query slots in each of `lanes` windows times (batch, head)s, windows of `tiles` tiles of 32 keys, K and V slices of up to kv_bytes.
+// attn_f32 does the most per second, but its workgroups take 128 queries, and a unit with one of them waits out its barriers; attn_few_f32's take 32, with
+// four wavefronts each.  Every unit takes workgroups in rounds: of attn_few_f32 each as long as the one before, of attn_f32 three of them at
+// once, the first as long as `round` of attn_few_f32's, two `extra` and three twice `round`.  Few / many, us: 1 369 tokens (43 tiles) of
+// 516 blocks of 32 queries (3 rounds / 1) 62 / 91, 903 (4 / 1) 84 / 92, 1 419 (6 / 2) 123 / 128, 1 591 (7 / 2) 140 / 128; 25 tiles 900 (4 / 1) 54 / 56, 1 275 (5 / 2)
+// 66 / 77, 1 600 (7 / 2) 87 / 78, 1 900 (8 / 3) 100 / 105; 13 tiles 767 (3 / 1) 26 / 32, 1 274 (5 / 2) 41 / 44, 1 404 (6 / 2) 47 / 44; 8 tiles 768 (3 / 1) 19 / 22, 896 (4 / 1) 24 / 22,
+// 1 280 (5 / 2) 29 / 30; 7 tiles 637 (3 / 1) 19.0 / 19.7, 903 (4 / 2) 23 / 26, 1 281 (6 / 2) 31 / 28; 5 tiles 400 (2 / 1) 13.1 / 15.3, 640 (3 / 1) 16.4 / 15.8; 4 tiles 516 (3 / 1) 13.8 / 13.0;
+// windows of 22 x 22 (16 tiles) 768 (3 / 1) 32 / 40, 1 024 (4 / 1) 43 / 41.
+constexpr bool f32_few(int tiles, int queries, long long lanes) {
+    const long long few = ((queries + 31) / 32 * lanes + 255) / 256, many = ((queries + 127) / 128 * lanes + 255) / 256;
+    const int round = tiles <= 5 ? 2 : tiles <= 16 ? 3 : 4, extra = round + (tiles < 8 ? 1 : 2);
+    return few <= many / 3 * 2 * round + (many % 3 == 0 ? 0 : many % 3 == 1 ? round : extra);
+}
+// Windows of one or two tiles leave nothing to share keys for, and of four the halves as long as their workgroups of 64 queries fit the units once: attn_short_f32
+// where its start is the shorter one.  Short / many, us: 1 tile always (windows of 5 x 5, 3 072 blocks 53 / 59); 2 tiles of 256 blocks 7.1 / 8.0,
+// of 1 024 12.4 / 12.8, of 1 150 17.3 / 15.2; 4 tiles, short / few: of 400 blocks 10.1 / 10.8, windows of 10 x 10 of 320 blocks 10.6 / 11.9, of 512 11.2 / 12.6.
 enum F32Kernel { kF32Many, kF32Few, kF32Short1, kF32Short2, kF32Short4 };
-constexpr F32Kernel f32_kernel(int tiles, bool whole_rows, long long blocks, long long kv_bytes) {
+constexpr F32Kernel f32_kernel(int tiles, bool whole_rows, int queries, long long lanes, long long kv_bytes) {
+    const long long blocks = (queries + 31) / 32 * lanes, pairs = (queries + 63) / 64 * lanes;  // of 32 queries, and of 64
     if (tiles == 1) return kF32Short1;
-    if (tiles == 2) return blocks <= 640 ? kF32Short2 : kF32Many;
-    if (blocks > (tiles <= 4 ? 512 : tiles < 28 ? 768 : tiles < 40 ? 1024 : 1280)) return kF32Many;
+    if (tiles == 2) return pairs <= 512 ? kF32Short2 : kF32Many;
+    if (!f32_few(tiles, queries, lanes)) return kF32Many;
+    if (tiles == 4 && blocks > 256 && pairs <= 256) return kF32Short2;
     return f32_keys_staged(tiles, whole_rows, blocks, kv_bytes) ? kF32Short4 : kF32Few;
 }
 

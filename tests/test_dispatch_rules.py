@@ -101,17 +101,17 @@ def test_staged_or_direct_keys_of_fp32_attention(rule):
 
 
 def test_kernels_of_fp32_attention(rule):
-    """(tiles, whole rows, blocks of 32 queries, bytes of a slice) on either side of every line of the rule."""
-    want = {"kF32Short1": [(1, 1, 1, 0), (1, 0, 1 << 20, 1 << 40)], "kF32Short2": [(2, 1, 2, 0), (2, 0, 640, 1 << 40)],
-            "kF32Short4": [(4, 1, 24, 0), (4, 1, 512, 0), (10, 1, 10, 1 << 32), (57, 0, 1280, 1 << 40)],
-            "kF32Few": [(3, 1, 24, 0), (3, 0, 512, 0), (4, 0, 512, 0), (5, 1, 768, 0), (27, 0, 768, 0), (28, 1, 1024, 0), (39, 1, 1024, 0),
-                        (40, 1, 1280, 0), (43, 1, 516, (1 << 32) - 1)],
-            "kF32Many": [(2, 1, 641, 0), (3, 1, 513, 0), (4, 1, 513, 0), (5, 1, 769, 1 << 40), (27, 0, 769, 0), (28, 1, 1025, 0), (40, 1, 1281, 0),
-                         (72, 1, 1 << 30, 1 << 40)]}
+    """(tiles, whole rows, queries of a window, windows times (batch, head)s, bytes of a slice) on either side of every line of the rule."""
+    want = {"kF32Short1": [(1, 1, 32, 1, 0), (1, 0, 9, 1 << 20, 1 << 40)], "kF32Short2": [(2, 1, 64, 1, 0), (2, 0, 49, 512, 1 << 40), (4, 1, 128, 65, 0), (4, 0, 100, 128, 0)],
+            "kF32Short4": [(4, 1, 128, 1, 0), (4, 1, 128, 64, 0), (10, 1, 320, 1, 1 << 32), (57, 0, 1824, 22, 1 << 40)],
+            "kF32Few": [(3, 1, 96, 170, 0), (4, 0, 128, 64, 0), (4, 0, 5, 600, 0), (5, 1, 160, 102, 0), (7, 0, 224, 109, 0), (7, 1, 224, 146, 0), (8, 1, 256, 160, 0), (16, 0, 512, 48, 0),
+                        (17, 1, 544, 60, 0), (43, 1, 1369, 12, (1 << 32) - 1), (43, 1, 1369, 35, 0), (72, 1, 2304, 21, 0), (43, 1, 5, 4096, 0), (25, 1, 800, 74, 0), (25, 1, 800, 81, 0)],
+            "kF32Many": [(2, 1, 64, 513, 0), (3, 1, 96, 171, 0), (4, 1, 128, 129, 0), (4, 0, 128, 225, 0), (5, 1, 160, 103, 0), (7, 0, 224, 110, 0), (7, 1, 224, 147, 0), (8, 1, 256, 161, 0),
+                         (16, 0, 512, 49, 0), (18, 1, 576, 86, 0), (43, 1, 1369, 36, 0), (72, 1, 2304, 22, 0), (25, 1, 800, 73, 0), (25, 1, 800, 82, 0), (43, 1, 1369, 72, 1 << 40), (72, 1, 1 << 24, 1 << 32, 0)]}
     for kernel, calls in want.items():
-        assert rule([f"f32_kernel({t}, {r}, {b}ll, {kv}ll) == {kernel}" for t, r, b, kv in calls]) == [1] * len(calls)
+        assert rule([f"f32_kernel({t}, {r}, {q}, {n}ll, {kv}ll) == {kernel}" for t, r, q, n, kv in calls]) == [1] * len(calls)
     for kernel, sizes in test_gpu_fp32.SPLIT_KERNELS.items():  # (batch x heads, tokens)
-        assert rule([f"f32_kernel(({n} + 31) / 32, 1, {bh} * (({n} + 31) / 32), 1 << 20) == {kernel}" for bh, n in sizes]) == [1] * len(sizes)
+        assert rule([f"f32_kernel(({n} + 31) / 32, 1, {n}, {bh}, 1 << 20) == {kernel}" for bh, n in sizes]) == [1] * len(sizes)
 
 
 def test_prefix_chains_of_64_channel_heads(rule):

@@ -119,8 +119,8 @@ def test_values_near_the_largest_floats(N):
     check(err_fp32(to_host(o), oracle.full_attn(q, k, v)), FP32_TOL)
 
 
-# (heads, tokens) of the two kernels whose operands are pairs of fp16 numbers
-SPLIT_KERNELS = {"kF32Few": [(2, 70), (3, 161), (2, 385), (6, 1030)], "kF32Many": [(300, 70), (160, 161), (64, 385), (40, 1030)]}
+# (heads, tokens) of the two kernels whose operands are sums of three bf16 numbers
+SPLIT_KERNELS = {"kF32Few": [(2, 70), (3, 161), (2, 385), (6, 1030)], "kF32Many": [(300, 70), (200, 161), (64, 385), (50, 1030)]}
 SPLIT_SIZES = [c for sizes in SPLIT_KERNELS.values() for c in sizes]
 
 
@@ -132,8 +132,7 @@ def _full64(q, k, v):
 @pytest.mark.parametrize("heads,N", SPLIT_SIZES)
 @pytest.mark.parametrize("what", ["plain", "tiny", "large", "climb", "fall", "outlier"])
 def test_split_operands(heads, N, what):
-    """Scales: magnitudes from 1e-30 to 1e30 (products of order one), and K and V that grow or shrink by 2^24 along the sequence, so that
-    scales settled on the first tiles have to go down, or hold numbers far below them."""
+    """Magnitudes from 1e-30 to 1e30 (products of order one), and K and V that grow or shrink by 2^24 along the sequence."""
     g = torch.Generator(device="cuda")
     g.manual_seed(N)
     q, k, v = (torch.randn(1, heads, N, 64, generator=g, device="cuda") for _ in range(3))
@@ -153,6 +152,60 @@ def test_split_operands(heads, N, what):
     ref = _full64(q, k, v)
     # sums of up to 1 030 fp32 products and logits of up to 40: 3e-7 measured with the fp32 matrix instructions at these lengths
     check(float((o.double() - ref).norm() / ref.norm()), 5e-7)
+
+
+@pytest.mark.parametrize("heads,N", SPLIT_SIZES)
+@pytest.mark.parametrize("most", [8, 24, 60])
+def test_channels_of_different_magnitude(heads, N, most):
+    """Channel by channel a power of two on V, and one on K whose inverse is on Q: every number keeps its 24 bits whatever the others
+    are, so that the result has the same bits times V's powers."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + 3)
+    q, k, v = (torch.randn(1, heads, N, 64, generator=g, device="cuda") for _ in range(3))
+    qk, on_v = (torch.exp2(torch.randint(-most, most + 1, (1, heads, 1, 64), generator=g, device="cuda").float()) for _ in range(2))
+    plain, o = torch.full_like(q, float("nan")), torch.full_like(q, float("nan"))
+    binding.jv_full_attn_fwd(q, k, v, plain, (1, N))
+    binding.jv_full_attn_fwd(q * qk, k / qk, v * on_v, o, (1, N))
+    ref = _full64(q, k, v)
+    # a channel, and a query, by its own norm: 3e-7 of the whole measured with the fp32 matrix instructions, a row of 64 numbers up to three times that
+    channel, row = ((plain.double() - ref).norm(dim=d) / ref.norm(dim=d) for d in (2, 3))
+    check(float(channel.max()), 1e-6)
+    check(float(row.max()), 1e-6)
+    assert torch.equal(o, plain * on_v)
+
+
+@pytest.mark.parametrize("heads,N", SPLIT_SIZES)
+def test_rows_of_different_magnitude(heads, N):
+    """Every query attends almost to its own key, and values grow by 2^24 along the sequence: a row of small values next to large ones of
+    weights near 1e-8, by its own norm."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + 4)
+    k, v = (torch.randn(1, heads, N, 64, generator=g, device="cuda") for _ in range(2))
+    k = 12.0 * k / k.norm(dim=-1, keepdim=True)
+    v = v * torch.exp2(torch.linspace(-12, 12, N, device="cuda"))[:, None]
+    o = torch.full_like(k, float("nan"))
+    binding.jv_full_attn_fwd(k, k, v, o, (1, N))
+    ref = _full64(k, k, v)
+    # exponents of up to 26 binary orders, each rounded to 2^-20, from scores of up to 144, rounded to 2^-17: 2^-17 of a weight
+    check(float(((o.double() - ref).norm(dim=-1) / ref.norm(dim=-1)).max()), 2.0 ** -17)
+
+
+@pytest.mark.parametrize("heads,N", SPLIT_SIZES)
+def test_many_small_weights(heads, N):
+    """One key of weight 1 and a value of 2^-32, all others of weights near 2^-32 and values near 1: half of the result comes from weights that far
+    below the largest."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + 5)
+    q, k = torch.zeros(1, heads, N, 64, device="cuda"), torch.zeros(1, heads, N, 64, device="cuda")
+    v = torch.rand(1, heads, N, 64, generator=g, device="cuda") + 0.5
+    q[..., 9] = 8.0
+    k[:, :, N // 2, 9] = 22.0
+    v[:, :, N // 2] *= 2.0 ** -32 * N
+    o = torch.full_like(q, float("nan"))
+    binding.jv_full_attn_fwd(q, k, v, o, (1, N))
+    ref = _full64(q, k, v)
+    # an exponent of 32 binary orders rounded to 2^-19, and sums of up to 1 030 numbers of one sign
+    check(float(((o.double() - ref).norm(dim=-1) / ref.norm(dim=-1)).max()), 2.0 ** -18)
 
 
 @pytest.mark.parametrize("heads,N", SPLIT_SIZES)
