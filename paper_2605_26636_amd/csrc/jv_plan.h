@@ -47,27 +47,34 @@ constexpr int apply_rounds(long long bh, int N) {
 
 // fp32 linear attention, both passes in one launch (la_fused_f32): its workgroups, four for each of `parts` parts of a (batch, head)'s
 // queries, form the state again and again, which pays while they fit the chip's 256 units once and the tokens
-// are few.  Two launches / one, us: 6 (batch, head)s of 256 tokens 9.9 / 5.5, of 1 024 13.3 / 12.7, of 1 369 14.8 / 16.2;
-// 16 of 576 13.5 / 9.7, of 784 13.8 / 12.9, of 1 024 14.6 / 14.7; 24 of 784 15.3 / 14.6, of 1 024 16.6 / 16.9; 32 of 1 369 23.0 / 21.5,
-// of 2 304 30.6 / 32.9; 48 of 1 369 34.4 / 27.7, of 2 304 47.6 / 46.3; 64 of 256 12.9 / 8.7, of 2 304 55.8 / 48.5; 80 of 576 25.2 / 25.6.
+// are few.  Two launches / one, us, on three tensors in turn (and on ones read for the first time, of which several workgroups read the same
+// bytes): 6 (batch, head)s of 256 tokens 9.9 / 5.5 (11.4 / 6.6), 8 of 900 14.0 / 12.3 (14.1 / 14.0), 6 of 1 024 13.5 / 12.6 (14.0 / 14.3);
+// 16 of 576 13.5 / 9.8 (14.2 / 11.6), 12 of 800 13.4 / 12.8 (14.4 / 14.3); 17 of 700 13.7 / 13.2 (15.2 / 15.0), 20 of 800 14.6 / 14.5 (15.6 / 16.2); 25 of 1 400
+// 21.7 / 21.4 (23.3 / 23.4), 48 of 1 369 34.4 / 27.7 (37.2 / 31.2), of 2 304 47.6 / 46.3; 64 of 256 12.9 / 8.7 (14.1 / 10.1), of 2 400 56.6 / 50.8 (61.1 / 57.6); 80 of 576 25.2 / 25.6.
 // A (batch, head) runs on one XCD: the parts are as many as its 32 units take for the XCD with the most (batch, head)s (12 of 595 tokens, two launches / 5 parts,
 // 40 workgroups on some XCDs / 4: 13.2 / 16.9 / 10.2 us; 9 of 400 11.6 / 13.0 / 8.2, 20 of 576 13.6 / 18.6 / 11.5, 18 of 784 14.1 / 23.7 / 14.4).
 constexpr int linear_f32_parts(int bh) { return bh > 32 ? 1 : 8 / ((bh + 7) / 8); }
 constexpr bool linear_f32_in_one(int bh, int N) {
-    return N <= (bh <= 8 ? 1024 : bh <= 16 ? 800 : bh < 20 ? 700 : bh <= 24 ? 800 : bh <= 56 ? 1400 : bh <= 64 ? 2400 : 0);
+    return N <= (bh <= 8 ? 900 : bh <= 16 ? 800 : bh <= 24 ? 700 : bh <= 56 ? 1400 : bh <= 64 ? 2400 : 0);
 }
 
 // bf16 linear attention of 64-channel heads, both passes in one launch (la_fused_bf16, one workgroup a unit): its workgroups, one for each
 // of linear_bf16_parts parts of a (batch, head)'s queries, form the state again, which pays while they fit the chip once and what a unit takes in
 // stands behind two or three launches' round trips; the more (batch, head)s, the fewer parts and the longer it does.  Beyond 256 of them, where
-// the last round of workgroups is more than half full and the others neither all start nor all memory.  Two or three launches / one, us: 6 (batch, head)s of 196 tokens
-// 10.1 / 6.9, of 1 374 13.7 / 11.3, of 2 304 14.3 / 14.9; 16 of 2 304 14.6 / 16.3; 24 of 1 374 14.3 / 13.4; 40 of 3 000 27.4 / 23.9, of 3 600 27.2 / 27.8; 64 of 784 13.5 / 12.4, of 1 374
-// 20.5 / 16.0, of 4 096 33.1 / 33.2; 128 of 400 13.6 / 11.1, of 4 096 54.6 / 54.1, of 9 216 114 / 119; 256 of 784 29.3 / 22.2, of 5 184 129 / 133; 300 of 196 16.2 / 19.0;
-// 384 of 400 29.1 / 25.3, 512 of 196 19.7 / 20.6, of 600 38.3 / 34.8, 640 of 1 374 99 / 94, 1 024 of 400 52 / 56.
+// the last round of workgroups is well filled and the others neither all start nor all memory.  Two or three launches / one, us (in brackets tensors
+// read for the first time, as above): 6 (batch, head)s of 196 tokens 10.1 / 6.9 (12.2 / 7.7), 12 of 1 374 14.5 / 11.9 (15.5 / 13.8), of 1 700 15.1 / 12.9 (15.7 / 14.9), 24 of
+// 1 900 15.2 / 15.8 (17.1 / 17.7); 40 of 2 304 21.1 / 18.2 (22.5 / 20.9), of 2 900 22.6 / 22.4 (23.9 / 25.2); 48 of 3 100 27.8 / 24.6 (29.8 / 28.0), 64 of 784 14.0 / 12.6 (15.4 / 14.7), of 3 100
+// 30.1 / 26.8 (32.4 / 30.9), of 3 500 31.0 / 29.9 (33.5 / 34.2), 72 of 4 300 41.3 / 36.6 (43.9 / 45.0); 80 of 4 300 43.8 / 40.1 (45.3 / 45.0), of 4 600 44.2 / 42.1 (47.2 / 49.9);
+// 128 of 400 13.6 / 11.2 (15.4 / 12.1), of 4 600 62.5 / 59.8 (66.2 / 63.6), of 5 200 70 / 72 (74 / 75), 256 of 784 30.2 / 22.7 (31.3 / 25.4), of 4 300 109 / 102 (113 / 107), of
+// 4 600 113 / 113 (118 / 118), of 4 800 118 / 122 (125 / 126); 300 of 196 16.2 / 19.1, 320 of 784 39.5 / 34.2 (40.6 / 38.4), of 1 400 55.4 / 56.4 (58.9 / 59.8), 384 of
+// 1 374 62 / 59 (66 / 63), 512 of 300 25.6 / 24.3 (26.6 / 27.1), 640 of 1 374 96 / 92 (101 / 97), 1 024 of 400 52 / 56.
 constexpr int linear_bf16_parts(int bh) { return bh > 256 ? 1 : 256 / bh; }
 constexpr bool linear_bf16_in_one(int bh, int N) {
-    if (bh > 256) return bh <= 768 && 100 * bh > 62 * 256 * ((bh + 255) / 256) && N >= 300 && N <= 1400;
-    return N <= (bh < 40 ? 1900 : bh < 64 ? 3300 : 4096);
+    if (bh > 256) {
+        const int rounds = (bh + 255) / 256;
+        return bh <= 768 && 100 * bh > 62 * 256 * rounds && N >= 300 && N <= (100 * bh > 72 * 256 * rounds ? 1400 : 1000);
+    }
+    return N <= (bh < 40 ? 1700 : bh < 48 ? 2400 : bh < 80 ? 3100 : bh < 96 ? 4300 : 4600);
 }
 
 // bf16 attention over whole grid rows (attn_ring_bf16): blocks of 32 queries per wavefront, two or (the same bits) one, for

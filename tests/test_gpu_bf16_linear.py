@@ -89,9 +89,9 @@ def test_all_negative_queries_give_exact_zero_bf16():
 # (B, heads, tokens, fused projection): tiles of 64 tokens of eight wavefronts (one tile, one round, one more), units of 32 queries and parts of them
 # (42, 256, 4, 2, 1 a (batch, head); fewer where units run out; ragged last ones); either side of each limit of linear_bf16_in_one
 ONE_LAUNCH = [(1, 1, 1, False), (1, 3, 31, False), (1, 2, 33, True), (1, 6, 64, False), (2, 3, 65, True), (1, 6, 511, False), (1, 6, 512, False),
-              (1, 12, 513, True), (1, 1, 1900, False), (3, 13, 1900, False), (3, 13, 1901, False), (4, 10, 3300, True), (4, 10, 3301, False),
-              (8, 8, 1369, True), (8, 16, 100, False), (8, 16, 4096, False), (8, 16, 4097, False), (16, 16, 577, True), (16, 17, 577, False), (20, 16, 299, False),
-              (20, 16, 300, True), (20, 16, 1400, False), (20, 16, 1401, False), (48, 16, 333, False)]
+              (1, 12, 513, True), (1, 1, 1700, False), (3, 13, 1700, False), (3, 13, 1701, False), (4, 10, 2400, True), (4, 10, 2401, False), (3, 16, 3100, False), (3, 16, 3101, False),
+              (8, 8, 1369, True), (8, 16, 100, False), (8, 10, 4300, False), (8, 10, 4301, True), (8, 16, 4096, False), (8, 16, 4600, False), (8, 16, 4601, False), (16, 16, 577, True), (16, 17, 577, False), (20, 16, 299, False),
+              (20, 16, 300, True), (20, 16, 1000, False), (20, 16, 1001, False), (24, 16, 1400, False), (24, 16, 1401, False), (48, 16, 333, False)]
 
 
 @pytest.mark.parametrize("B,heads,N,fused", ONE_LAUNCH)

@@ -305,7 +305,7 @@ def test_linear_chunk_edges(N):
 # (B, heads, tokens, fused projection): one launch's tiles of 16 tokens, groups of 32 and rounds of 256; parts of the queries
 # (8, 5, 2, 1, ragged last ones); either side of each limit of linear_f32_in_one
 ONE_LAUNCH = [(1, 1, 1, False), (1, 1, 15, False), (1, 3, 17, True), (2, 3, 33, False), (1, 8, 255, False), (1, 6, 256, False), (1, 6, 257, True),
-              (1, 8, 1024, False), (1, 8, 1025, False), (3, 4, 300, True), (2, 12, 800, False), (2, 12, 801, False), (1, 32, 777, True),
+              (1, 8, 900, False), (1, 8, 901, False), (3, 4, 300, True), (2, 12, 700, False), (2, 12, 701, False), (1, 32, 777, True),
               (4, 16, 600, False), (4, 14, 1400, False), (4, 16, 2400, False), (5, 13, 100, False)]
 
 
