@@ -213,15 +213,15 @@ la_state_bf16(TensorArg kt, TensorArg vt, float *__restrict__ ws, float *__restr
     }
 }
 
-// grid (B*heads, or 8 * ceil(B*heads / 8) with xcd_ranges; ceil((kStateFloats + 64) / 1024)), 256
+// grid (8 * ceil(B*heads / 8), ceil((kStateFloats + 64) / 1024)), 256
 // threads: dst[bh] = sum_p ws[p][bh], one
-// 16-byte piece per thread, the loads of sixteen partials in flight at a time.  With vsum (the
+// 16-byte piece per thread, the loads of sixteen partials in flight at a time, and states in contiguous ranges per XCD, as
+// la_state_bf16 and la_apply_bf16 take them.  With vsum (the
 // partial token sums of V, [n_split][B*heads][64]) the sixteen threads after the state's last
 // piece sum those too, into partial 0 (each element is read and written by one thread).
 __global__ void __launch_bounds__(256)
-la_combine(const float *__restrict__ ws, float *__restrict__ dst, float *vsum, int n_split, int BH, int xcd_ranges) {
-    // xcd_ranges: states in contiguous ranges per XCD, as la_state_bf16 and la_apply_bf16 take them
-    const int bh = xcd_ranges ? (blockIdx.x & 7) * ((BH + 7) >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+la_combine(const float *__restrict__ ws, float *__restrict__ dst, float *vsum, int n_split, int BH) {
+    const int bh = (blockIdx.x & 7) * ((BH + 7) >> 3) + (blockIdx.x >> 3);
     if (bh >= BH) return;  // whole workgroup
     const int e4 = blockIdx.y * 256 + threadIdx.x;
     constexpr int kStateVec = kStateFloats / 4, kSumVec = kHeadDim / 4;
@@ -247,7 +247,7 @@ la_combine(const float *__restrict__ ws, float *__restrict__ dst, float *vsum, i
 
 jv_status combine_states(const float *ws, float *dst, float *vsum, int n_split, int BH, hipStream_t stream) {
     hipLaunchKernelGGL(la_combine, dim3(8 * ((BH + 7) / 8), ((kStateFloats + kHeadDim) / 4 + 255) / 256), dim3(256), 0,
-                       stream, ws, dst, vsum, n_split, BH, 1);
+                       stream, ws, dst, vsum, n_split, BH);
     return launch_status("la_combine");
 }
 
@@ -1116,9 +1116,7 @@ jv_status linear_fused_projection_operands(const Problem &pr, float eps, float *
     hipLaunchKernelGGL((la_state_bf16<false, false>), dim3(8 * ((plan.n_split * BH + 7) / 8)), dim3(256), kStateLds, stream,
                        pr.k, pr.v, ws, (float *)nullptr, pr.heads, pr.N, plan.chunk, 1, plan.n_split, BH);
     if ((st = launch_status("la_state_bf16")) != JV_OK) return st;
-    hipLaunchKernelGGL(la_combine, dim3(8 * ((BH + 7) / 8), ((kStateFloats + kHeadDim) / 4 + 255) / 256), dim3(256), 0,
-                       stream, ws, states, (float *)nullptr, plan.n_split, BH, 1);
-    if ((st = launch_status("la_combine")) != JV_OK) return st;
+    if ((st = combine_states(ws, states, nullptr, plan.n_split, BH, stream)) != JV_OK) return st;
     hipLaunchKernelGGL(la_fold_projection, dim3(C / 64, BH), dim3(256), 0, stream, states, (const __bf16 *)w_o,
                        (__bf16 *)w_fold, pr.heads, C);
     if ((st = launch_status("la_fold_projection")) != JV_OK) return st;
