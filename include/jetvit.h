@@ -34,9 +34,15 @@
  *  - Arithmetic: JV_F32 tensors are processed in fp32 throughout, or, in softmax
  *    attention over more than 32 keys, as sums of three bf16 numbers that together hold
  *    all 24 bits of every operand (magnitudes below 2^-110: down to 2^-133), whatever the
- *    magnitudes of the other operands, with fp32 accumulation.  JV_BF16 tensors feed bf16 matrix instructions with fp32 accumulation; softmax,
+ *    magnitudes of the other operands, with fp32 accumulation.  JV_BF16 tensors
+ *    feed bf16 matrix instructions with fp32 accumulation; softmax,
  *    normalisers and divisions are fp32.  O is rounded to `o_dtype` once, at the
  *    final store (round to nearest even).
+ *  - Same bits: a call repeated on the same tensors gives the same bits.  The order of
+ *    summation follows from the sizes of the whole call, batch included (kernels and the
+ *    parts that keys, tokens or a product's inner dimension are cut into are chosen by how
+ *    full the device gets), so an image alone and the same image in a batch may differ by
+ *    the rounding of the formats above: of a bf16 softmax weight, say, in full attention.
  *  - Errors: every call validates its arguments on the host before any launch
  *    and returns a jv_status.  On any status other than JV_OK nothing was
  *    launched and no buffer was touched (JV_ERR_HIP excepted: a launch was
