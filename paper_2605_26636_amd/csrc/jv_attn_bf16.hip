@@ -1072,7 +1072,8 @@ __device__ inline char *prefix_scratch(const AttnArgs &a, long long obase, int r
     return (char *)a.o.ptr + (O_BF16 ? 2 : 4) * (obase + (long long)(a.q_slots + row) * a.o.sn);
 }
 
-template <bool O_BF16, int NT, bool SPLIT>
+// CHAINS: C, known to the compiler (as a number of the launch it costs 0.3 of 17.5 us, window attention included).
+template <bool O_BF16, int NT, bool SPLIT, int CHAINS = kPrefixChains>
 __global__ void __launch_bounds__(SPLIT ? 64 : 512, 1) attn_prefix_bf16(AttnArgs a) {
     // the logit scale, fetched (a kernel argument) and waited for here, not inside the key loop
     float c_log2 = a.c;
@@ -1116,13 +1117,13 @@ __global__ void __launch_bounds__(SPLIT ? 64 : 512, 1) attn_prefix_bf16(AttnArgs
     };
     int at = 0;  // byte offset of the present stage's tile
     if (SPLIT) issue(chain, 0);  // (a split launch has more stages than chains)
-    const int chains = SPLIT ? (int)gridDim.x : kPrefixChains;
-    for (int st = chain; st < n_stage; st += chains) {
+    static_assert(SPLIT || CHAINS == kPrefixChains, "the one workgroup has eight wavefronts");
+    for (int st = chain; st < n_stage; st += CHAINS) {
         // (the LDS reads of the previous stage have been waited for before the matrix
         // instructions that used them, so its tile may be overwritten)
         if (!SPLIT) issue(st, 0);
-        if (SPLIT && st + chains < n_stage) {
-            issue(st + chains, kStageBytes - at);
+        if (SPLIT && st + CHAINS < n_stage) {
+            issue(st + CHAINS, kStageBytes - at);
             asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
         } else {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1287,14 +1288,19 @@ static jv_status launch_prefix(const AttnArgs &a, int BH, hipStream_t stream) {
         hipLaunchKernelGGL((attn_prefix_bf16<O_BF16, NT, false>), dim3(1, BH), dim3(512), prefix_lds(false), stream, a);
         return launch_status("attn_prefix_bf16");
     }
-    const int chains = prefix_chain_count(a.g.slots, a.q_slots, BH);
-    hipLaunchKernelGGL((attn_prefix_bf16<O_BF16, NT, true>), dim3(chains, BH), dim3(64), prefix_lds(true), stream, a);
-    jv_status st = launch_status("attn_prefix_bf16");
-    if (st != JV_OK) return st;
-    const auto combine = chains == 32 ? prefix_combine_bf16<O_BF16, kHeadDim, 32> : chains == 16 ? prefix_combine_bf16<O_BF16, kHeadDim, 16> :
-                         prefix_combine_bf16<O_BF16, kHeadDim, kPrefixChains>;
-    hipLaunchKernelGGL(combine, dim3(a.q_slots, BH), dim3(64), 0, stream, a);
-    return launch_status("prefix_combine_bf16");
+    const auto launch = [&](auto chains_tag) {
+        constexpr int chains = decltype(chains_tag)::value;
+        hipLaunchKernelGGL((attn_prefix_bf16<O_BF16, NT, true, chains>), dim3(chains, BH), dim3(64), prefix_lds(true), stream, a);
+        const jv_status st = launch_status("attn_prefix_bf16");
+        if (st != JV_OK) return st;
+        hipLaunchKernelGGL((prefix_combine_bf16<O_BF16, kHeadDim, chains>), dim3(a.q_slots, BH), dim3(64), 0, stream, a);
+        return launch_status("prefix_combine_bf16");
+    };
+    switch (prefix_chain_count(a.g.slots, a.q_slots, BH)) {
+        case 32: return launch(std::integral_constant<int, 32>());
+        case 16: return launch(std::integral_constant<int, 16>());
+        default: return launch(std::integral_constant<int, kPrefixChains>());
+    }
 }
 
 template <bool O_BF16, int WPW>
