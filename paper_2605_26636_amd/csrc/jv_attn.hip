@@ -23,8 +23,9 @@ __device__ inline int slot_token(const WindowGeom &g, int wy, int wx, int slot) 
 // (v_mfma_f32_32x32x16_bf16, fp32 accumulation; sixteen times the rate of the fp32 ones).  Every operand is the sum of
 // three bf16 numbers, each the rounding of what the ones before leave: all 24 bits of a number, whatever the others are, down to 2^-110 in magnitude (below it
 // to 2^-133, the smallest bf16 number).  Six of the nine products are formed; what is left out is below 2^-24 of the product of two numbers (2^-28 of it
-// on average).  Errors against 64 bits are those of the rounding of the sums: the small products are added up first, and a
-// tile's sums on their own before they join the others.  64 heads of 1 369 tokens 2.0e-7, of 2 304 2.3e-7 (fp32 matrix instructions 5.6e-7 and 9.2e-7).
+// on average).  Errors against 64 bits are those of the rounding of the sums: the small products are added up first, and the
+// sums of a tile (attn_f32) or of half a tile (attn_few_f32) on their own before they join the others.  attn_f32: 64 heads of 1 369 tokens 2.0e-7, of
+// 2 304 2.3e-7 (fp32 matrix instructions 5.6e-7 and 9.2e-7); attn_few_f32: 12 heads of 1 369 2.4e-7, 8 of 4 096 2.9e-7 (4.5e-7 and 6.5e-7).
 // (Two fp16 numbers an operand, scaled by the largest magnitude of K, of V and of a query, and three products: 20 to 30 % faster, but what is 2^14
 // times smaller than the largest loses bits, a small channel of V beside a large one for instance.)
 // Infinities and NaN turn into NaN on the way (inf - inf), and so does what overflows: a wavefront whose sums are not finite
@@ -591,8 +592,8 @@ attn_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, i
 // fetched while the matrix instructions of two others run; three workgroups fit a compute unit.  Bound by its loads (32 cache lines for an
 // instruction's K operands), the splits (280 vector instructions a tile) and the matrix instructions together.  Against the fp32 matrix
 // instructions, us: 1 369 tokens x 12 heads 88.1 -> 62.9 (516 workgroups: four units have three and the others two; x 11 60.4 -> 45.8),
-// 1 030 x 35 112 -> 82, windows of 14 x 14 on 40 x 40 x 12 22.4 -> 21.1; 2.4e-7 instead of 4.5e-7 from 64 bits at 1 369 tokens, 2.9e-7 instead of 6.5e-7 at
-// 4 096.  (Products added straight to the sums of the tiles before: 59.6 us, 3.5e-7 and 5.4e-7.)
+// 1 030 x 35 112 -> 82, windows of 14 x 14 on 40 x 40 x 12 22.4 -> 21.1.
+// (Products added straight to the sums of the tiles before: 59.6 us for 1 369 x 12, but 3.5e-7 from 64 bits, and 5.4e-7 at 4 096 tokens.)
 // grid (ceil(q_slots / 32), n_win, B*heads), 256 threads.  Byte offsets inside a (batch, head) slice of K and V below 2^32.
 __global__ void __launch_bounds__(256, 3)
 attn_few_f32(TensorArg qt, TensorArg kt, TensorArg vt, TensorArg ot, WindowGeom g, int heads, float scale_log2, int q_slots) {
