@@ -122,16 +122,16 @@ constexpr bool f32_few(int tiles, int queries, long long lanes) {
     const int round = tiles <= 5 ? 2 : tiles <= 16 ? 3 : 4, extra = round + (tiles < 8 ? 1 : 2);
     return few <= many / 3 * 2 * round + (many % 3 == 0 ? 0 : many % 3 == 1 ? round : extra);
 }
-// Windows of one or two tiles leave nothing to share keys for, and of four the halves as long as their workgroups of 64 queries fit the units once: attn_short_f32
-// where its start is the shorter one.  Short / many, us: 1 tile always (windows of 5 x 5, 3 072 blocks 53 / 59); 2 tiles of 256 blocks 7.1 / 8.0,
-// of 1 024 12.4 / 12.8, of 1 150 17.3 / 15.2; 4 tiles, short / few: of 400 blocks 10.1 / 10.8, windows of 10 x 10 of 320 blocks 10.6 / 11.9, of 512 11.2 / 12.6.
+// Windows of one or two tiles leave nothing to share keys for: attn_short_f32 where its start is the shorter one.  Short / many, us: 1 tile
+// always (windows of 5 x 5, 3 072 blocks 53 / 59); 2 tiles of 256 blocks 7.1 / 8.0, of 640 11.2 / 11.9; from there to 1 024 it would be 3 to 6 % shorter still, but
+// is further from 64 bits (2.0e-7 / 1.4e-7).  The same of 257 to 512 blocks of four tiles, two key groups of attn_short_f32 against attn_few_f32: 4 to 10 %, and
+// 2.7e-7 / 1.9e-7.
 enum F32Kernel { kF32Many, kF32Few, kF32Short1, kF32Short2, kF32Short4 };
 constexpr F32Kernel f32_kernel(int tiles, bool whole_rows, int queries, long long lanes, long long kv_bytes) {
-    const long long blocks = (queries + 31) / 32 * lanes, pairs = (queries + 63) / 64 * lanes;  // of 32 queries, and of 64
+    const long long blocks = (queries + 31) / 32 * lanes;  // of 32 queries
     if (tiles == 1) return kF32Short1;
-    if (tiles == 2) return pairs <= 512 ? kF32Short2 : kF32Many;
+    if (tiles == 2) return blocks <= 640 ? kF32Short2 : kF32Many;
     if (!f32_few(tiles, queries, lanes)) return kF32Many;
-    if (tiles == 4 && blocks > 256 && pairs <= 256) return kF32Short2;
     return f32_keys_staged(tiles, whole_rows, blocks, kv_bytes) ? kF32Short4 : kF32Few;
 }
 

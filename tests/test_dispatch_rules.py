@@ -102,11 +102,11 @@ def test_staged_or_direct_keys_of_fp32_attention(rule):
 
 def test_kernels_of_fp32_attention(rule):
     """(tiles, whole rows, queries of a window, windows times (batch, head)s, bytes of a slice) on either side of every line of the rule."""
-    want = {"kF32Short1": [(1, 1, 32, 1, 0), (1, 0, 9, 1 << 20, 1 << 40)], "kF32Short2": [(2, 1, 64, 1, 0), (2, 0, 49, 512, 1 << 40), (4, 1, 128, 65, 0), (4, 0, 100, 128, 0)],
-            "kF32Short4": [(4, 1, 128, 1, 0), (4, 1, 128, 64, 0), (10, 1, 320, 1, 1 << 32), (57, 0, 1824, 22, 1 << 40)],
-            "kF32Few": [(3, 1, 96, 170, 0), (4, 0, 128, 64, 0), (4, 0, 5, 600, 0), (5, 1, 160, 102, 0), (7, 0, 224, 109, 0), (7, 1, 224, 146, 0), (8, 1, 256, 160, 0), (16, 0, 512, 48, 0),
+    want = {"kF32Short1": [(1, 1, 32, 1, 0), (1, 0, 9, 1 << 20, 1 << 40)], "kF32Short2": [(2, 1, 64, 1, 0), (2, 0, 49, 320, 1 << 40)],
+            "kF32Short4": [(4, 1, 128, 1, 0), (4, 1, 128, 128, 0), (10, 1, 320, 1, 1 << 32), (57, 0, 1824, 22, 1 << 40)],
+            "kF32Few": [(3, 1, 96, 170, 0), (4, 0, 128, 128, 0), (4, 0, 5, 600, 0), (5, 1, 160, 102, 0), (7, 0, 224, 109, 0), (7, 1, 224, 146, 0), (8, 1, 256, 160, 0), (16, 0, 512, 48, 0),
                         (17, 1, 544, 60, 0), (43, 1, 1369, 12, (1 << 32) - 1), (43, 1, 1369, 35, 0), (72, 1, 2304, 21, 0), (43, 1, 5, 4096, 0), (25, 1, 800, 74, 0), (25, 1, 800, 81, 0)],
-            "kF32Many": [(2, 1, 64, 513, 0), (3, 1, 96, 171, 0), (4, 1, 128, 129, 0), (4, 0, 128, 225, 0), (5, 1, 160, 103, 0), (7, 0, 224, 110, 0), (7, 1, 224, 147, 0), (8, 1, 256, 161, 0),
+            "kF32Many": [(2, 1, 64, 321, 0), (3, 1, 96, 171, 0), (4, 1, 128, 129, 0), (4, 0, 128, 225, 0), (5, 1, 160, 103, 0), (7, 0, 224, 110, 0), (7, 1, 224, 147, 0), (8, 1, 256, 161, 0),
                          (16, 0, 512, 49, 0), (18, 1, 576, 86, 0), (43, 1, 1369, 36, 0), (72, 1, 2304, 22, 0), (25, 1, 800, 73, 0), (25, 1, 800, 82, 0), (43, 1, 1369, 72, 1 << 40), (72, 1, 1 << 24, 1 << 32, 0)]}
     for kernel, calls in want.items():
         assert rule([f"f32_kernel({t}, {r}, {q}, {n}ll, {kv}ll) == {kernel}" for t, r, q, n, kv in calls]) == [1] * len(calls)
